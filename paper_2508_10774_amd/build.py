@@ -18,8 +18,11 @@ LIB = os.path.join(HERE, "libasa.so")
 SOURCES = ["asa_api.hip", "asa_fwd.hip", "asa_mask.hip", "asa_bwd.hip", "asa_reorder.hip", "asa_order.hip"]
 
 HIPCC_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
+    "--offload-arch=gfx950", "-O3", "-std=c++20", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # results of matrix instructions go to ordinary registers, where the vector ALU can use them
+    # (a kernel that wants accumulation registers says so itself)
+    "-mllvm", "-amdgpu-mfma-vgpr-form=1",
     "-Wall", "-Wno-unused-function",
     "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
 ]

@@ -18,13 +18,12 @@
 #include <stdlib.h>
 
 #include <type_traits>
+#include <utility>
 
 #include "asa_common.hpp"
 #include "asa_tiles.hpp"
 
 namespace asa {
-
-__device__ __forceinline__ int kappa_b(int r) { return kappa(r); }
 
 constexpr float kLog2e = 1.44269504088896340736f;
 
@@ -40,7 +39,7 @@ template <int D>
 __global__ __launch_bounds__(256) void delta_kernel(const void *o, const void *o_lo,
                                                     const void *d_o, TensorView to, int H, int L,
                                                     int Lpad, const float *lse, float bias_log2,
-                                                    float *delta, float *lse2, float *lse2g) {
+                                                    float *ndelta, float *lse2, float *lse2g) {
   const int slab = blockIdx.y;
   const int row = blockIdx.x * 16 + (threadIdx.x >> 4);
   const int sub = threadIdx.x & 15;
@@ -70,7 +69,7 @@ __global__ __launch_bounds__(256) void delta_kernel(const void *o, const void *o
   if (row < Lpad && sub == 0) {
     const int64_t at = (int64_t)slab * Lpad + row;
     const float l2 = row < L ? lse[(int64_t)slab * L + row] * kLog2e : INFINITY;
-    delta[at] = acc;
+    ndelta[at] = -acc;
     lse2[at] = l2;
     if (lse2g) lse2g[at] = l2 - bias_log2;
   }
@@ -78,8 +77,8 @@ __global__ __launch_bounds__(256) void delta_kernel(const void *o, const void *o
 
 struct BwdArgs {
   const void *q, *k, *v, *d_o;
-  const float *lse2, *delta;  // [slab][Lpad]: LSE * log2(e) (minus this launch's key bias), Delta; padded with +inf, 0
-  float *delta_out;           // where the Delta-only walk of dq_kernel writes (the same array as delta)
+  const float *lse2, *ndelta; // [slab][Lpad]: LSE * log2(e) (minus this launch's key bias), -Delta; padded with +inf, 0
+  float *ndelta_out;          // where the Delta-only walk of dq_kernel writes (the same array as ndelta)
   const int32_t *row_ptr, *col_idx, *col_ptr, *row_idx;
   void *dq, *dk, *dv;
   TensorView tq, tk, tv, to;
@@ -104,22 +103,52 @@ template <int BLK, int D>
 struct BwdCfg {
   static constexpr int kWaves = BLK / 32;
   static constexpr int kThreads = kWaves * 64;
-  static constexpr int kST = 64;                 // rows (keys or queries) per step
-  static constexpr int kSub = BLK / kST;         // steps per block
-  static constexpr int kRowTile = kST * D;       // [64][D]  elements, swizzled, unpadded
-  // LDS stages: two where the second does not cost a resident workgroup (block 128), else one
-  static constexpr int kStages = BLK == 128 ? 2 : 1;
-  static constexpr int kDqStage = 2 * kRowTile * 2;                  // K rows, V rows
+  static constexpr int kST = 32;                       // rows (keys or queries) per tile
+  static constexpr int kSub = BLK / kST;               // tiles per block
+  static constexpr int kStages = 4;                    // LDS stages
+  static constexpr int kTile = kST * D * 2;            // bytes of one row tile
+  static constexpr int kDqStage = 2 * kTile;                   // K rows, V rows
+  static constexpr int kDkvStage = 2 * kTile + 2 * kST * 4;    // Q rows, dO rows, LSE, -Delta
   static constexpr int kDqLds = kStages * kDqStage;
-  static constexpr int kDkvStage = 2 * kRowTile * 2 + 2 * kST * 4;   // Q rows, dO rows, LSE, Delta
   static constexpr int kDkvLds = kStages * kDkvStage;
+  static constexpr int kWavesPerSimd = D == 128 ? 1 : 2;
 };
 
 // ---------------------------------------------------------------------------------------
+// The tile loop of dq_kernel and dkv_kernel: a software pipeline inside ONE wavefront.
+//
+// Two wavefronts of a SIMD that each run "matrix products, then vector work, then products" hardly
+// overlap on this chip: the cycles of a step were the SUM of its matrix, vector and copy cycles
+// (dQ at block 128 / d 128: 2640 of them for 1536 matrix cycles).  But one wavefront hides two
+// exponentials and three multiply-adds under every 32-cycle MFMA it issues itself (33..38 cycles
+// measured).  So a tile is 32 rows, and an iteration has two phases:
+//   A: the S and dP products of tile t + 1; between them, two instructions here and there, the
+//      exponentials, products and packs that turn S and dP of tile t into P and dS;
+//   B: the products that add tile t to the gradients; between them the copies of tile t + 3.
+// Everything is pinned slot by slot (one MFMA, its share of the other work, a scheduling barrier),
+// LDS operands are read 5..6 products ahead through a ring that runs on across iterations, and
+// there is one workgroup barrier per tile.  A wavefront issues one instruction every ~5 cycles, so
+// the number of instructions matters as much as the MFMAs: four LDS stages with the loop unrolled
+// by four make every LDS address a register plus an immediate; -Delta is the initial value of the
+// dP accumulator; a tile that reaches past the last row uses a second set of copy offsets instead
+// of a branch.
+// Registers: at d = 128 one wavefront per SIMD with the gradients in accumulation registers (the
+// instruction is written out for that: the compiler would move S and P there as well, at a
+// vector instruction per register and tile), at d = 64 two.
+// Bound: the matrix cores at the power limit (1.15 PFLOP/s executed at a clock of 1.68 GHz, matrix
+// pipe busy 65 % of the cycles at the Wan2.1 shape; with neither copies nor vector work the same
+// loop runs at 1.4).  Against two unpipelined wavefronts per SIMD, 25 % density, MI355X:
+//   block 128 / d 128, 12 heads of 32 760:  dK+dV 3.19 -> 2.75 ms, dQ 2.40 -> 2.05 ms
+//   block 64 / d 64, 48 heads of 17 776:    dK+dV 1.93 -> 1.67 ms, dQ 1.52 -> 1.33 ms
+//   block 64 / d 128, 12 slabs of 4 332:    dK+dV 235 -> 118 us, dQ 177 -> 98 us, Delta 144 -> 75 us
+// Eight stages instead of four are 1.5 % slower (longer start of a workgroup), 4 or 7 operands ahead
+// instead of 6 change nothing.
+// ---------------------------------------------------------------------------------------
+
+// ---------------------------------------------------------------------------------------
 // dQ: one workgroup per query block, one wavefront per 32 query rows (its Q and dO rows stay
-// in registers as B operands).  Per step of 64 keys the workgroup copies K rows and V rows
-// straight into one of two LDS stages while it works on the other; the "channels x keys"
-// operand of dQ^T = K^T dS^T is gathered from the K row tile by the transposing LDS read.
+// in registers as B operands).  The "channels x keys" operand of dQ^T = K^T dS^T is gathered from
+// the K row tile by the transposing LDS read.
 // ---------------------------------------------------------------------------------------
 // GT: with the pooled (global) tokens of ASA_G appended to every query block's list
 // DELTA_ONLY: no gradient; the same walk forms Delta_q = sum_c P_qc dP_qc (= rowsum(dO * O) with
@@ -128,12 +157,12 @@ struct BwdCfg {
 // is off by up to 0.05 in rows whose soft-max is spread over keys with similar values, and that
 // error goes into dQ and dK times the size of the keys / queries.
 template <int BLK, int D, bool GT, bool DELTA_ONLY = false>
-__global__ __launch_bounds__(BLK * 2, 2) void dq_kernel(BwdArgs a) {
+__global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dq_kernel(BwdArgs a) {
   using C = BwdCfg<BLK, D>;
   extern __shared__ __align__(1024) unsigned char smem[];
   __shared__ int cols[kMaxNb];
-  constexpr int kStage = C::kDqStage;          // K rows [64][D], V rows [64][D] (t_swz images)
-  constexpr int kVOff = C::kRowTile * 2;
+  constexpr int kVOff = C::kTile, kStage = C::kDqStage;
+  constexpr int kPooled = 1 << 30;             // flag of an entry of cols[]: a block of pooled tokens
 
   const int slot = xcd_contiguous_work(blockIdx.x, a.n_slabs * a.Nb);
   if (slot < 0) return;
@@ -150,12 +179,12 @@ __global__ __launch_bounds__(BLK * 2, 2) void dq_kernel(BwdArgs a) {
   const bf16 *gs = slab_ptr(a.d_o, a.to, slab, a.H);
   const bool dense = a.row_ptr == nullptr;   // no index lists: every key block
   const int t_begin = dense ? 0 : a.row_ptr[slab * (a.Nb + 1) + qb];
-  const int n_own_tiles = dense ? a.Nb : a.row_ptr[slab * (a.Nb + 1) + qb + 1] - t_begin;
-  const int n_tiles = n_own_tiles + (GT ? a.Nbg : 0);   // pooled blocks come after the row's own list
+  const int n_own_blocks = dense ? a.Nb : a.row_ptr[slab * (a.Nb + 1) + qb + 1] - t_begin;
+  const int n_blocks = n_own_blocks + (GT ? a.Nbg : 0);   // pooled blocks come after the row's own list
   {
     const int32_t *g = a.col_idx + (int64_t)slab * a.Nb * a.Nb + t_begin;
-    for (int t = tid; t < n_tiles; t += C::kThreads)
-      cols[t] = t >= n_own_tiles ? t - n_own_tiles : (dense ? t : g[t]);
+    for (int t = tid; t < n_blocks; t += C::kThreads)
+      cols[t] = t >= n_own_blocks ? (t - n_own_blocks) | kPooled : (dense ? t : g[t]);
   }
   // pooled keys / values of this slab: rows of D elements, padded to whole blocks
   const bf16 *kgs = reinterpret_cast<const bf16 *>(a.kg) + (int64_t)slab * a.Nbg * BLK * D;
@@ -172,7 +201,11 @@ __global__ __launch_bounds__(BLK * 2, 2) void dq_kernel(BwdArgs a) {
   }
   // rows past L have LSE = +inf there, so that every probability is exactly zero
   const float lse2 = a.lse2[(int64_t)slab * a.Lpad + qrow];
-  const float delta = DELTA_ONLY ? 0.f : a.delta[(int64_t)slab * a.Lpad + qrow];
+  // dP starts from -Delta instead of zero: the subtraction costs nothing
+  const float ndelta = DELTA_ONLY ? 0.f : a.ndelta[(int64_t)slab * a.Lpad + qrow];
+  f32x16 nd16;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) nd16[i] = ndelta;
   float dsum = 0.f;   // DELTA_ONLY: sum of P * dP over my keys
 
   f32x16 acc[D / 32];
@@ -181,106 +214,268 @@ __global__ __launch_bounds__(BLK * 2, 2) void dq_kernel(BwdArgs a) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[dm][i] = 0.f;
 
-  // row-wise A fragments (S^T = K Q^T, dP^T = V dO^T): row kappa(n) of a 32-key group
-  const int kr = kappa_b(n);
-  const int kx = (hl ^ t_swz<D>(kr)) * 8;
-  // transposed A fragments "32 channels x 16 keys" of dQ^T += K^T dS^T (see dkv_kernel)
-  const lds_char *smem_lds = (const lds_char *)smem;
-  const uint32_t smem_addr = ASA_LDS_ADDR_OF(smem);
-  const int tr_i = lane & 15, tr_w = tr_i & 3, tr_j = tr_i >> 2, tr_b = (lane >> 4) & 1;
-  const uint32_t tr_lane = tr_piece<D>(8 * hl + tr_j, 16 * (tr_w & 1) + 8 * tr_b + 4 * (tr_w >> 1));
-  const float c = a.scale_log2e;
-  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
-                         0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  using Copy = TrTileCopy<C::kST, D, C::kWaves>;
+  Copy copy_k, copy_v;
+  copy_k.init(wave, lane, a.tk.sL, a.L);
+  copy_v.init(wave, lane, a.tv.sL, a.L);
+  constexpr int kI = Copy::kInstr;
+  constexpr int kBatch = 2 * kI;                // copy instructions per tile and wavefront
+  const int last_row0 = Copy::last_row0(a.L);
+  Copy copy_p;                                  // pooled rows: D elements apart, never ragged
+  if (GT) copy_p.init(wave, lane, D, C::kST);
 
-  const int n_steps = n_tiles * C::kSub;
-  auto issue = [&](int step, int stage) {
-    const int key0 = cols[step / C::kSub] * BLK + (step % C::kSub) * C::kST;
-    int lane_o = lane;
-    asm volatile("" : "+v"(lane_o));   // offsets are rebuilt here, not hoisted into registers
-    using RowCopy = LeanRowTileCopy<C::kST, D, C::kWaves>;
-    const uint32_t st = smem_addr + stage * kStage;
-    if (GT && step >= n_own_tiles * C::kSub) {
-      RowCopy::issue(st, kgs, key0, a.Nbg * BLK, D, wave, lane_o);   // never ragged
-      RowCopy::issue(st + kVOff, vgs, key0, a.Nbg * BLK, D, wave, lane_o);
+  // (stages are absolute LDS addresses, multiples of 256: the XORs below touch lower bits only)
+  const uint32_t smem_addr = ASA_LDS_ADDR_OF(smem);
+  // row-wise A fragments (S^T = K Q^T, dP^T = V dO^T): row kappa(n) of the 32 keys
+  const int kr = kappa(n);
+  uint32_t row_at[D / 16];
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s)
+    row_at[s] = (smem_addr + (uint32_t)(kr * D * 2 + (hl ^ t_swz<D>(kr)) * 16)) ^ (uint32_t)(32 * s);
+  // transposed A fragments "32 channels x 16 keys" of dQ^T += K^T dS^T (see dkv_kernel)
+  const int tr_i = lane & 15, tr_w = tr_i & 3, tr_j = tr_i >> 2, tr_b = (lane >> 4) & 1;
+  const uint32_t tr_lane = smem_addr + tr_piece<D>(8 * hl + tr_j, 16 * (tr_w & 1) + 8 * tr_b + 4 * (tr_w >> 1));
+  uint32_t tr_at[2 * (D / 32)];
+#pragma unroll
+  for (int dm = 0; dm < D / 32; ++dm) {
+    tr_at[2 * dm] = tr_lane ^ (uint32_t)(((4 * dm) ^ t_swz<D>(0)) * 16);
+    tr_at[2 * dm + 1] = tr_lane ^ (uint32_t)(((4 * dm) ^ t_swz<D>(4)) * 16);
+  }
+  const float c = a.scale_log2e;
+  const int n_it = n_blocks * C::kSub;
+
+  // The tile whose copies come next (see dkv_kernel)
+  int entry_v = 0, entry_at = 0, key_c = 0;
+  bool last_tile = false, pooled_c = false;
+  const char *base_k = nullptr, *base_v = nullptr;
+  auto fetch_entry = [&]() __attribute__((always_inline)) {
+    entry_v = cols[entry_at < n_blocks ? entry_at : n_blocks - 1];
+    ++entry_at;
+  };
+  auto next_tile = [&](auto part_tag, auto new_block_tag) __attribute__((always_inline)) {
+    constexpr int part = decltype(part_tag)::value;
+    constexpr bool new_block = decltype(new_block_tag)::value;
+    if constexpr (part == 0) {
+      if constexpr (new_block) {
+        const int e = __builtin_amdgcn_readfirstlane(entry_v);
+        if (GT) pooled_c = (e & kPooled) != 0;
+        key_c = (GT ? e & (kPooled - 1) : e) * BLK;
+      } else {
+        key_c += C::kST;
+      }
+    } else if constexpr (part == 1) {
+      base_k = reinterpret_cast<const char *>(ks) + (int64_t)min(key_c, last_row0) * (a.tk.sL * 2);
+      last_tile = key_c >= last_row0;
+      if (GT) base_k = pooled_c ? reinterpret_cast<const char *>(kgs) + (int64_t)key_c * (D * 2) : base_k;
     } else {
-      RowCopy::issue(st, ks, key0, a.L, a.tk.sL, wave, lane_o);
-      RowCopy::issue(st + kVOff, vs, key0, a.L, a.tv.sL, wave, lane_o);
+      base_v = reinterpret_cast<const char *>(vs) + (int64_t)min(key_c, last_row0) * (a.tv.sL * 2);
+      if (GT) base_v = pooled_c ? reinterpret_cast<const char *>(vgs) + (int64_t)key_c * (D * 2) : base_v;
     }
   };
-  if (C::kStages == 2) {
-    __syncthreads();   // cols[] is written
-    if (n_steps > 0) issue(0, 0);
-  }
-  for (int step = 0; step < n_steps; ++step) {
-    __builtin_amdgcn_s_setprio(3);
-    if (C::kStages == 1) {
-      __syncthreads();                    // cols[] is written; everyone is done with the stage
-      issue(step, 0);
+  auto copy_one = [&](int i, uint32_t st) __attribute__((always_inline)) {
+    if (GT) {
+      const int x = i < kI ? i : i - kI;
+      const Copy &own = i < kI ? copy_k : copy_v;
+      const uint32_t off = pooled_c ? copy_p.off[x] : (last_tile ? own.off_last[x] : own.off[x]);
+      lds_dma16_sv(i < kI ? base_k : base_v, off, st + (i < kI ? 0 : kVOff) + own.lds0 + x * 1024);
+    } else if (i < kI) {
+      copy_k.issue_one(i, st, base_k, last_tile);
+    } else {
+      copy_v.issue_one(i - kI, st + kVOff, base_v, last_tile);
     }
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): my copies of this step have landed
-    __syncthreads();                      // everyone's have; everyone is done with the other stage
-    const int stage = C::kStages == 2 ? (step & 1) : 0;
-    if (C::kStages == 2 && step + 1 < n_steps) issue(step + 1, stage ^ 1);
-    const bf16 *Ks = reinterpret_cast<const bf16 *>(smem + stage * kStage);
-    const bf16 *Vs = Ks + C::kRowTile;
-    const uint32_t tr_base = tr_lane + (uint32_t)(stage * kStage);   // kStage % 512 == 0
-    const int key0 = cols[step / C::kSub] * BLK + (step % C::kSub) * C::kST;
-    const bool pooled = GT && step >= n_own_tiles * C::kSub;
-    const int key_end = pooled ? a.Lg : a.L;   // keys at or past it do not exist
-    const bool tail = key0 + C::kST > key_end;
-    const float lse_b = pooled ? lse2 - a.pooled_bias_log2 : lse2;
-#pragma unroll
-    for (int mt = 0; mt < C::kST / 32; ++mt) {
-      __builtin_amdgcn_s_setprio(0);
-      const bf16 *krow = Ks + (mt * 32 + kr) * D;
-      const bf16 *vrow = Vs + (mt * 32 + kr) * D;
-      f32x16 sacc = zero16, pacc = zero16;
-#pragma unroll
-      for (int s = 0; s < D / 16; ++s) {
-        bf16x8 ka = *reinterpret_cast<const bf16x8 *>(krow + ((16 * s) ^ kx));
-        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qreg[s], sacc, 0, 0, 0);
-        bf16x8 va = *reinterpret_cast<const bf16x8 *>(vrow + ((16 * s) ^ kx));
-        pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, greg[s], pacc, 0, 0, 0);
-      }
-      // accumulator register i of lane half hl is key 32mt + 16(i/8) + 8hl + (i%8)
-      uint32_t dsb[8];
-      __builtin_amdgcn_s_setprio(3);   // vector work goes ahead of the other workgroup's MFMA stream
-#pragma unroll
-      for (int i = 0; i < 16; i += 2) {
-        float p0 = fast_exp2(fmaf(sacc[i], c, -lse_b));
-        float p1 = fast_exp2(fmaf(sacc[i + 1], c, -lse_b));
-        if (tail) {
-          int key = key0 + mt * 32 + 16 * (i >> 3) + 8 * hl + (i & 7);
-          if (key >= key_end) p0 = 0.f;
-          if (key + 1 >= key_end) p1 = 0.f;
-        }
-        if (DELTA_ONLY) dsum += fmaf(p0, pacc[i], p1 * pacc[i + 1]);
-        else dsb[i >> 1] = pack_bf16x2(p0 * (pacc[i] - delta), p1 * (pacc[i + 1] - delta));
-      }
-      __builtin_amdgcn_s_setprio(0);
-      if (DELTA_ONLY) continue;
-#pragma unroll
-      for (int tt = 0; tt < 2; ++tt) {
-        uint4 raw = make_uint4(dsb[4 * tt], dsb[4 * tt + 1], dsb[4 * tt + 2], dsb[4 * tt + 3]);
-        bf16x8 dsf = *reinterpret_cast<bf16x8 *>(&raw);
-#pragma unroll
-        for (int dm = 0; dm < D / 32; ++dm) {
-          // keys 32 mt + 16 tt + 8 hl + (0..7) of channels 32 dm + rho(lane % 32)
-          const uint32_t x0 = (uint32_t)(((4 * dm) ^ t_swz<D>(0)) * 16), x1 = (uint32_t)(((4 * dm) ^ t_swz<D>(4)) * 16);
-          const bf16x4 lo = lds_read_tr16(smem_lds + ((tr_base ^ x0) + (uint32_t)((32 * mt + 16 * tt) * D * 2)));
-          const bf16x4 hi = lds_read_tr16(smem_lds + ((tr_base ^ x1) + (uint32_t)((32 * mt + 16 * tt + 4) * D * 2)));
-          const bf16x8 ta = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-          acc[dm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ta, dsf, acc[dm], 0, 0, 0);
-        }
-      }
+  };
+  auto wait_copies = [&](auto n_tag) __attribute__((always_inline)) {
+    constexpr int N = decltype(n_tag)::value;    // at most N instructions still in flight
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+  };
+  // The block of the tile in work, for the masks of the last block and the bias of pooled keys
+  int cur_v = 0, cur_at = 0, key_t = 0, key_end = 0;
+  float lse_t = lse2;
+  auto fetch_current = [&]() __attribute__((always_inline)) {
+    cur_v = cols[cur_at < n_blocks ? cur_at : n_blocks - 1];
+    ++cur_at;
+  };
+  auto next_current = [&](auto new_block_tag) __attribute__((always_inline)) {
+    if constexpr (decltype(new_block_tag)::value) {
+      const int e = __builtin_amdgcn_readfirstlane(cur_v);
+      key_t = (GT ? e & (kPooled - 1) : e) * BLK;
+      const bool pooled = GT && (e & kPooled) != 0;
+      key_end = pooled ? a.Lg : a.L;             // keys at or past it do not exist
+      if (GT) lse_t = pooled ? lse2 - a.pooled_bias_log2 : lse2;
+    } else {
+      key_t += C::kST;
     }
+  };
+
+  // One iteration handles tile t of 32 keys: phase A computes S^T and dP^T of tile t + 1 while the
+  // vector ALU turns those of tile t into dS^T, phase B adds tile t's product to dQ^T (see
+  // dkv_kernel for the ring of operands, the stages and the unrolling by four tiles).
+  constexpr int kNA = 2 * (D / 16), kNB = DELTA_ONLY ? 0 : 2 * (D / 32), kN = kNA + kNB;
+  constexpr int kRing = kN % 8 == 0 ? 8 : 6, kDepth = kRing == 8 ? 6 : 5;
+  static_assert(kN % kRing == 0, "the ring continues across iterations");
+  constexpr int kBar = kNA < kN - kDepth ? kNA : kN - kDepth;   // the barrier comes before this product
+  bf16x8 ring[kRing];
+  auto read_row = [&](auto e_tag, auto stage_tag) __attribute__((always_inline)) {   // operand e of phase A
+    constexpr int e = decltype(e_tag)::value, st = decltype(stage_tag)::value * kStage;
+    ring[e % kRing] = lds_read<bf16x8>(row_at[e / 2] + (uint32_t)(st + (e & 1) * kVOff));
+  };
+  auto read_tr = [&](auto f_tag, auto stage_tag) __attribute__((always_inline)) {    // operand f of phase B
+    constexpr int f = decltype(f_tag)::value, dm = f % (D / 32), tt = f / (D / 32);
+    constexpr int at = decltype(stage_tag)::value * kStage + 16 * tt * D * 2;
+    const bf16x4 lo = lds_read_tr16((const lds_char *)(uintptr_t)(tr_at[2 * dm] + (uint32_t)at));
+    const bf16x4 hi = lds_read_tr16((const lds_char *)(uintptr_t)(tr_at[2 * dm + 1] + (uint32_t)(at + 4 * D * 2)));
+    ring[(kNA + f) % kRing] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
+  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
+                         0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  auto accumulate = [](f32x16 &d, bf16x8 x, bf16x8 y) __attribute__((always_inline)) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    if constexpr (C::kWavesPerSimd == 1)
+      asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(x), "v"(y));
+    else
+      d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, d, 0, 0, 0);
+#endif
+  };
+
+  f32x16 s0, p0, s1, p1;
+  auto body = [&](auto u_tag, f32x16 &sc, f32x16 &pc, f32x16 &sn, f32x16 &pn) __attribute__((always_inline)) {
+    constexpr int U = decltype(u_tag)::value;        // tile index mod 4
+    using St = std::integral_constant<int, U>;
+    using St1 = std::integral_constant<int, (U + 1) & 3>;
+    using St2 = std::integral_constant<int, (U + 2) & 3>;
+    constexpr bool kNewBlock = (U + C::kStages - 1) % C::kSub == 0;   // of the tile copied here
+    constexpr bool kNextNewBlock = (U + C::kStages) % C::kSub == 0;
+    if (key_t + C::kST > key_end) {                  // (uniform, rare) keys past the end
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (key_t + 16 * (i >> 3) + 8 * hl + (i & 7) >= key_end) sc[i] = -INFINITY;
+    }
+    uint32_t db[8];
+    // (accumulator register i of lane half hl is key 16 (i / 8) + 8 hl + i % 8)
+    auto finish = [&](int i) __attribute__((always_inline)) {
+      if (DELTA_ONLY) {
+        dsum = fmaf(sc[i], pc[i], dsum);
+      } else {
+        pc[i] *= sc[i];
+        if (i & 1) db[i >> 1] = pack_bf16x2(pc[i - 1], pc[i]);
+      }
+    };
+    __builtin_amdgcn_sched_barrier(0);
+    [&]<int... X>(std::integer_sequence<int, X...>) __attribute__((always_inline)) {
+      ([&]() __attribute__((always_inline)) {
+        constexpr int x = X;
+        if constexpr (x == kBar) {
+          // tile t + 2 has landed (everyone's copies) and nobody reads tile t - 1 any more
+          wait_copies(std::integral_constant<int, (C::kStages - 4) * kBatch>{});
+          asm volatile("s_barrier" ::: "memory");
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (x + kDepth < kNA) read_row(std::integral_constant<int, x + kDepth>{}, St1{});
+        else if constexpr (x + kDepth < kN) read_tr(std::integral_constant<int, x + kDepth - kNA>{}, St{});
+        else read_row(std::integral_constant<int, x + kDepth - kN>{}, St2{});
+        if constexpr (x < kNA) {
+          constexpr int s = x / 2;
+          if constexpr ((x & 1) == 0)
+            sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[x % kRing], qreg[s], s == 0 ? zero16 : sn, 0, 0, 0);
+          else
+            pn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[x % kRing], greg[s], s == 0 ? nd16 : pn, 0, 0, 0);
+          constexpr int per = 16 / kNA;                // elements of tile t that belong to this slot
+#pragma unroll
+          for (int u = 0; u < per; ++u) {
+            const int i = x * per + u;
+            sc[i] = fast_exp2(fmaf(sc[i], c, -lse_t));
+          }
+          if constexpr (x > 0) {
+#pragma unroll
+            for (int u = 0; u < per; ++u) finish((x - 1) * per + u);
+          }
+          if constexpr (x == kNA - 1) {
+#pragma unroll
+            for (int u = 0; u < per; ++u) finish(x * per + u);
+          }
+        } else {
+          constexpr int f = x - kNA, dm = f % (D / 32), tt = f / (D / 32);
+          const u32x4 raw = {db[4 * tt], db[4 * tt + 1], db[4 * tt + 2], db[4 * tt + 3]};
+          accumulate(acc[dm], ring[x % kRing], __builtin_bit_cast(bf16x8, raw));
+        }
+        if constexpr (x == 1) next_tile(std::integral_constant<int, 0>{}, std::bool_constant<kNewBlock>{});
+        if constexpr (x == 3) next_tile(std::integral_constant<int, 1>{}, std::bool_constant<kNewBlock>{});
+        if constexpr (x == 5) next_tile(std::integral_constant<int, 2>{}, std::bool_constant<kNewBlock>{});
+        if constexpr (x == 2 && (U + 1) % C::kSub == 0) fetch_current();
+        if constexpr (x == kN - 2 && kNextNewBlock) fetch_entry();
+        // copies of tile t + kStages - 1, spread over the slots behind the barrier
+        if constexpr (x >= kBar) {
+          constexpr int i0 = (x - kBar) * kBatch / (kN - kBar), i1 = (x - kBar + 1) * kBatch / (kN - kBar);
+#pragma unroll
+          for (int i = i0; i < i1; ++i)
+            copy_one(i, smem_addr + ((U + 3) & 3) * kStage);
+        }
+        if constexpr (x == kN - 1) next_current(std::bool_constant<(U + 1) % C::kSub == 0>{});
+        __builtin_amdgcn_sched_barrier(0);
+      }(), ...);
+    }(std::make_integer_sequence<int, kN>{});
+  };
+
+  __syncthreads();   // cols[] is written
+  if (n_it > 0) {
+    // The loop takes four tiles at a time, one per stage.  Blocks of 64 rows are two tiles: with an
+    // odd number of them tile 0 goes to stage 2 and the first two tiles come before the loop.
+    const bool odd = C::kSub == 2 && (n_blocks & 1);
+    const uint32_t first_stage = odd ? 2u : 0u, first_off = first_stage * kStage;
+    // tiles 0 .. kStages - 2
+    for (int t = 0; t < C::kStages - 1; ++t) {
+      if (t % C::kSub == 0) {
+        fetch_entry();
+        next_tile(std::integral_constant<int, 0>{}, std::true_type{});
+      } else {
+        next_tile(std::integral_constant<int, 0>{}, std::false_type{});
+      }
+      next_tile(std::integral_constant<int, 1>{}, std::false_type{});
+      next_tile(std::integral_constant<int, 2>{}, std::false_type{});
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) copy_one(i, smem_addr + ((t + first_stage) & 3u) * kStage);
+    }
+    if ((C::kStages - 1) % C::kSub == 0) fetch_entry();
+    fetch_current();
+    next_current(std::true_type{});
+    wait_copies(std::integral_constant<int, (C::kStages - 3) * kBatch>{});   // tiles 0 and 1
+    __syncthreads();
+    // S^T and dP^T of tile 0, first operands of tile 1
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) row_at[s] += first_off;
+    s0 = zero16;
+    p0 = nd16;
+    [&]<int... E>(std::integer_sequence<int, E...>) __attribute__((always_inline)) {
+      ([&]() __attribute__((always_inline)) {
+        constexpr int e = E;
+        read_row(std::integral_constant<int, e>{}, std::integral_constant<int, 0>{});
+        if constexpr ((e & 1) == 0) s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[e % kRing], qreg[e / 2], s0, 0, 0, 0);
+        else p0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[e % kRing], greg[e / 2], p0, 0, 0, 0);
+      }(), ...);
+    }(std::make_integer_sequence<int, kNA>{});
+    [&]<int... E>(std::integer_sequence<int, E...>) __attribute__((always_inline)) {
+      (read_row(std::integral_constant<int, E>{}, std::integral_constant<int, 1>{}), ...);
+    }(std::make_integer_sequence<int, kDepth>{});
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) row_at[s] -= first_off;
+    if (odd) {
+      body(std::integral_constant<int, 2>{}, s0, p0, s1, p1);
+      body(std::integral_constant<int, 3>{}, s1, p1, s0, p0);
+    }
+    for (int t = odd ? 2 : 0; t < n_it; t += 4) {
+      body(std::integral_constant<int, 0>{}, s0, p0, s1, p1);
+      body(std::integral_constant<int, 1>{}, s1, p1, s0, p0);
+      body(std::integral_constant<int, 2>{}, s0, p0, s1, p1);
+      body(std::integral_constant<int, 3>{}, s1, p1, s0, p0);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);          // stray copies must land before the LDS is given up
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
   }
 
   if (DELTA_ONLY) {
     // the two lane halves hold different keys of the same query; rows past L get 0 (their P is 0)
     const float total = dsum + swap_halves(dsum);
-    if (hl == 0) a.delta_out[(int64_t)slab * a.Lpad + qrow] = total;
+    if (hl == 0) a.ndelta_out[(int64_t)slab * a.Lpad + qrow] = -total;
     return;
   }
   if (qvalid) {
@@ -301,21 +496,17 @@ __global__ __launch_bounds__(BLK * 2, 2) void dq_kernel(BwdArgs a) {
 // ---------------------------------------------------------------------------------------
 // dK, dV: one workgroup per key block, one wavefront per 32 keys; its K and V rows stay in
 // registers as B operands and both 32 x d fp32 accumulators live in registers, so S and P are
-// computed once per tile for both gradients.  Per step of 64 queries the workgroup copies Q rows
-// and dO rows (and the 64 LSE and Delta values) into one of two LDS stages while it works on
-// the other.  The products with P^T and dS^T need "channels x queries" operands: they are
-// gathered from the same row tiles by the transposing LDS read, so no transposed copy of Q or
-// dO exists, in LDS or in memory.  The register file is full (2 wavefronts per SIMD at 256
-// registers): per-lane copy offsets are rebuilt at each use instead of kept.
+// computed once per tile for both gradients.  A tile is the Q rows and dO rows of 32 queries and
+// their LSE and -Delta values.  The products with P^T and dS^T need "channels x queries" operands:
+// they are gathered from the same row tiles by the transposing LDS read, so no transposed copy of
+// Q or dO exists, in LDS or in memory.
 // ---------------------------------------------------------------------------------------
 template <int BLK, int D>
-__global__ __launch_bounds__(BLK * 2, 2) void dkv_kernel(BwdArgs a) {
+__global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dkv_kernel(BwdArgs a) {
   using C = BwdCfg<BLK, D>;
   extern __shared__ __align__(1024) unsigned char smem[];
   __shared__ int rows[kMaxNb];
-  // a stage: Q rows [64][D], dO rows [64][D] (t_swz images), LSE [64], Delta [64]
-  constexpr int kStage = C::kDkvStage;
-  constexpr int kGOff = C::kRowTile * 2, kLseOff = 2 * C::kRowTile * 2, kDeltaOff = kLseOff + C::kST * 4;
+  constexpr int kGOff = C::kTile, kStatOff = 2 * C::kTile, kStage = C::kDkvStage;
 
   const int work_c = xcd_contiguous_work(blockIdx.x, a.n_slabs * a.Nbk * a.q_chunks);
   if (work_c < 0) return;
@@ -331,19 +522,20 @@ __global__ __launch_bounds__(BLK * 2, 2) void dkv_kernel(BwdArgs a) {
   const bf16 *ks = slab_ptr(a.k, a.tk, slab, a.H);
   const bf16 *vs = slab_ptr(a.v, a.tv, slab, a.H);
   const bf16 *gs = slab_ptr(a.d_o, a.to, slab, a.H);
-  const float *lse_s = a.lse2 + (int64_t)slab * a.Lpad;      // padded: every copy is 64 whole values
-  const float *delta_s = a.delta + (int64_t)slab * a.Lpad;
+  // lanes 0..31 fetch the 32 LSE values of a tile, lanes 32..63 its 32 negated Deltas (both arrays
+  // are padded to whole blocks: no bounds test; the host puts lse2 behind ndelta, less than 4 GiB away)
+  const float *stat_s = a.ndelta + (int64_t)slab * a.Lpad;
+  const uint32_t stat_off = (uint32_t)(n * 4) + (hl ? 0u : (uint32_t)((a.lse2 - a.ndelta) * 4));
   const bool dense = a.col_ptr == nullptr;   // no index lists: every query block
   const int t_begin = dense ? 0 : a.col_ptr[slab * (a.Nb + 1) + kb];
   const int per_chunk = (a.Nb + a.q_chunks - 1) / a.q_chunks;
   const int first = chunk * per_chunk;          // dense: my range of query blocks
-  const int n_tiles = dense ? max(0, min(per_chunk, a.Nb - first))
-                            : a.col_ptr[slab * (a.Nb + 1) + kb + 1] - t_begin;
+  const int n_blocks = dense ? max(0, min(per_chunk, a.Nb - first))
+                             : a.col_ptr[slab * (a.Nb + 1) + kb + 1] - t_begin;
   {
     const int32_t *g = a.row_idx + (int64_t)slab * a.Nb * a.Nb + t_begin;
-    for (int t = tid; t < n_tiles; t += C::kThreads) rows[t] = dense ? first + t : g[t];
+    for (int t = tid; t < n_blocks; t += C::kThreads) rows[t] = dense ? first + t : g[t];
   }
-
   const int krow = kb * BLK + wave * 32 + n;
   const bool kvalid = krow < a.Lk;
   const int krow_c = kvalid ? krow : a.Lk - 1;
@@ -359,126 +551,252 @@ __global__ __launch_bounds__(BLK * 2, 2) void dkv_kernel(BwdArgs a) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) kacc[dm][i] = vacc[dm][i] = 0.f;
 
-  // row-wise A fragments (S = Q K^T, dP = dO V^T): row kappa(n) of a 32-query group
-  const int kr = kappa_b(n);
-  const int kx = (hl ^ t_swz<D>(kr)) * 8;
+  TrTileCopy<C::kST, D, C::kWaves> copy_q, copy_g;
+  copy_q.init(wave, lane, a.tq.sL, a.L);
+  copy_g.init(wave, lane, a.to.sL, a.L);
+  constexpr int kI = TrTileCopy<C::kST, D, C::kWaves>::kInstr;
+  constexpr int kBatch = 2 * kI + 1;            // copy instructions per tile and wavefront
+  const int last_row0 = TrTileCopy<C::kST, D, C::kWaves>::last_row0(a.L);
+
+  // (stages are absolute LDS addresses, multiples of 256: the XORs below touch lower bits only)
+  const uint32_t smem_addr = ASA_LDS_ADDR_OF(smem);
+  // row-wise A fragments (S = Q K^T, dP = dO V^T): row kappa(n) of the 32 queries, 16-byte chunk
+  // (2 s + hl) ^ t_swz(row)
+  const int kr = kappa(n);
+  uint32_t row_at[D / 16];
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s)
+    row_at[s] = (smem_addr + (uint32_t)(kr * D * 2 + (hl ^ t_swz<D>(kr)) * 16)) ^ (uint32_t)(32 * s);
   // transposed A fragments "32 channels x 16 queries" (dV^T += dO^T P, dK^T += Q^T dS): lane i of
   // a 16-lane group addresses query i / 4 of 4 consecutive ones and 4 of the channels that
   // the MFMA rows of its group stand for (row order rho); two reads make the 8 queries of a lane
-  const lds_char *smem_lds = (const lds_char *)smem;
-  const uint32_t smem_addr = ASA_LDS_ADDR_OF(smem);
   const int tr_i = lane & 15, tr_w = tr_i & 3, tr_j = tr_i >> 2, tr_b = (lane >> 4) & 1;
-  const uint32_t tr_lane = tr_piece<D>(8 * hl + tr_j, 16 * (tr_w & 1) + 8 * tr_b + 4 * (tr_w >> 1));
+  const uint32_t tr_lane = smem_addr + tr_piece<D>(8 * hl + tr_j, 16 * (tr_w & 1) + 8 * tr_b + 4 * (tr_w >> 1));
+  uint32_t tr_at[2 * (D / 32)];
+#pragma unroll
+  for (int dm = 0; dm < D / 32; ++dm) {
+    tr_at[2 * dm] = tr_lane ^ (uint32_t)(((4 * dm) ^ t_swz<D>(0)) * 16);
+    tr_at[2 * dm + 1] = tr_lane ^ (uint32_t)(((4 * dm) ^ t_swz<D>(4)) * 16);
+  }
   const float c = a.scale_log2e;
+  const int n_it = n_blocks * C::kSub;
+
+  // The tile whose copies come next: query block `cb` (entry of the list) and its first row, base
+  // addresses.  Tiles past the end repeat the last block: the number of copies in flight stays the
+  // same and their data is not used.
+  int entry_v = 0, entry_at = 0, q0 = 0;
+  bool last_tile = false;
+  const char *base_q = nullptr, *base_g = nullptr, *base_st = nullptr;
+  const int64_t tile_q = (int64_t)C::kST * a.tq.sL * 2, tile_g = (int64_t)C::kST * a.to.sL * 2;
+  auto fetch_entry = [&]() __attribute__((always_inline)) {      // (read well before it is used)
+    entry_v = rows[entry_at < n_blocks ? entry_at : n_blocks - 1];
+    ++entry_at;
+  };
+  // three parts, so that a kernel slot holds a few scalar instructions only
+  auto next_tile = [&](auto part_tag, auto new_block_tag) __attribute__((always_inline)) {
+    constexpr int part = decltype(part_tag)::value;
+    constexpr bool new_block = decltype(new_block_tag)::value;
+    if constexpr (part == 0) {
+      q0 = new_block ? __builtin_amdgcn_readfirstlane(entry_v) * BLK : q0 + C::kST;
+      base_st = reinterpret_cast<const char *>(stat_s + q0);
+    } else if constexpr (part == 1) {
+      base_q = reinterpret_cast<const char *>(qs) + (int64_t)min(q0, last_row0) * (a.tq.sL * 2);
+      last_tile = q0 >= last_row0;
+    } else {
+      base_g = reinterpret_cast<const char *>(gs) + (int64_t)min(q0, last_row0) * (a.to.sL * 2);
+    }
+  };
+  auto copy_one = [&](int i, uint32_t st) __attribute__((always_inline)) {
+    if (i < kI) copy_q.issue_one(i, st, base_q, last_tile);
+    else if (i < 2 * kI) copy_g.issue_one(i - kI, st + kGOff, base_g, last_tile);
+    else lds_dma4_sv(base_st, stat_off, st + kStatOff);
+  };
+  auto wait_copies = [&](auto n_tag) __attribute__((always_inline)) {
+    constexpr int N = decltype(n_tag)::value;    // at most N instructions still in flight
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+  };
+
+  // One iteration handles tile t: phase A computes S and dP of tile t + 1 (matrix pipe) while the
+  // vector ALU turns S and dP of tile t into P and dS; phase B adds tile t's products to dV and dK.
+  // The A operands are read kDepth products ahead through a ring that runs on from iteration to
+  // iteration.  The loop is unrolled by four tiles, one per stage: every LDS address is a
+  // register plus an immediate.
+  constexpr int kNA = 2 * (D / 16), kNB = 4 * (D / 32), kN = kNA + kNB;
+  constexpr int kRing = 8, kDepth = 6;
+  static_assert(kN % kRing == 0, "the ring continues across iterations");
+  bf16x8 ring[kRing];
+  auto read_row = [&](auto e_tag, auto stage_tag) __attribute__((always_inline)) {   // operand e of phase A
+    constexpr int e = decltype(e_tag)::value, st = decltype(stage_tag)::value * kStage;
+    ring[e % kRing] = lds_read<bf16x8>(row_at[e / 2] + (uint32_t)(st + (e & 1) * kGOff));
+  };
+  auto read_tr = [&](auto f_tag, auto stage_tag) __attribute__((always_inline)) {    // operand f of phase B
+    constexpr int f = decltype(f_tag)::value, st = decltype(stage_tag)::value * kStage;
+    constexpr int dm = (f / 2) % (D / 32), tt = f / (2 * (D / 32));
+    constexpr int at = st + ((f & 1) == 0 ? kGOff : 0) + 16 * tt * D * 2;
+    const bf16x4 lo = lds_read_tr16((const lds_char *)(uintptr_t)(tr_at[2 * dm] + (uint32_t)at));
+    const bf16x4 hi = lds_read_tr16((const lds_char *)(uintptr_t)(tr_at[2 * dm + 1] + (uint32_t)(at + 4 * D * 2)));
+    ring[(kNA + f) % kRing] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
+  // LSE and -Delta of the 8 + 8 queries of my lane half, from stage `st`
+  f32x4 lse_v[4];
+  uint32_t stat_at = smem_addr + kStatOff + 32 * hl;
+  auto read_lse = [&](int q, int st) __attribute__((always_inline)) {
+    lse_v[q] = lds_read<f32x4>(stat_at + (uint32_t)(st * kStage + ((q >> 1) * 16 + (q & 1) * 4) * 4));
+  };
+  auto read_ndelta = [&](int q, int st, f32x16 &p) __attribute__((always_inline)) {
+    const f32x4 v = lds_read<f32x4>(stat_at + (uint32_t)(st * kStage + C::kST * 4 + ((q >> 1) * 16 + (q & 1) * 4) * 4));
+#pragma unroll
+    for (int x = 0; x < 4; ++x) p[4 * q + x] = v[x];
+  };
   const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
                          0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-
-  const int n_steps = n_tiles * C::kSub;
-  auto issue = [&](int step, int stage) {
-    const int q0 = rows[step / C::kSub] * BLK + (step % C::kSub) * C::kST;
-    int lane_o = lane;
-    asm volatile("" : "+v"(lane_o));   // offsets are rebuilt here, not hoisted into registers
-    using RowCopy = LeanRowTileCopy<C::kST, D, C::kWaves>;
-    const uint32_t st = smem_addr + stage * kStage;
-    RowCopy::issue(st, qs, q0, a.L, a.tq.sL, wave, lane_o);
-    RowCopy::issue(st + kGOff, gs, q0, a.L, a.to.sL, wave, lane_o);
-    if (wave == 0) lds_dma4_v(lse_s + q0 + lane_o, st + kLseOff);
-    if (wave == 1) lds_dma4_v(delta_s + q0 + lane_o, st + kDeltaOff);
+  auto accumulate = [](f32x16 &acc, bf16x8 x, bf16x8 y) __attribute__((always_inline)) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    if constexpr (C::kWavesPerSimd == 1)
+      asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(x), "v"(y));
+    else
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, acc, 0, 0, 0);
+#endif
   };
-  if (C::kStages == 2) {
-    __syncthreads();   // rows[] is written
-    if (n_steps > 0) issue(0, 0);
-  }
-  for (int step = 0; step < n_steps; ++step) {
-    __builtin_amdgcn_s_setprio(3);
-    if (C::kStages == 1) {
-      __syncthreads();                    // rows[] is written; everyone is done with the stage
-      issue(step, 0);
-    }
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): my copies of this step have landed
-    __syncthreads();                      // everyone's have; everyone is done with the other stage
-    const int stage = C::kStages == 2 ? (step & 1) : 0;
-    if (C::kStages == 2 && step + 1 < n_steps) issue(step + 1, stage ^ 1);
-    const bf16 *Qs = reinterpret_cast<const bf16 *>(smem + stage * kStage);
-    const bf16 *Gs = Qs + C::kRowTile;
-    const float *sLse = reinterpret_cast<const float *>(smem + stage * kStage + kLseOff);
-    const float *sDelta = sLse + C::kST;
-    const uint32_t tr_base = tr_lane + (uint32_t)(stage * kStage);   // kStage % 512 == 0
-    auto tr_operand = [&](int tile_bytes, int mt, int tt, int dm) -> bf16x8 {
-      // queries 32 mt + 16 tt + 8 hl + (0..7) of channels 32 dm + rho(lane % 32)
-      const uint32_t x0 = (uint32_t)(((4 * dm) ^ t_swz<D>(0)) * 16), x1 = (uint32_t)(((4 * dm) ^ t_swz<D>(4)) * 16);
-      const bf16x4 lo = lds_read_tr16(smem_lds + ((tr_base ^ x0) + (uint32_t)(tile_bytes + (32 * mt + 16 * tt) * D * 2)));
-      const bf16x4 hi = lds_read_tr16(smem_lds + ((tr_base ^ x1) + (uint32_t)(tile_bytes + (32 * mt + 16 * tt + 4) * D * 2)));
-      return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+
+  f32x16 s0, p0, s1, p1;
+  auto body = [&](auto u_tag, f32x16 &sc, f32x16 &pc, f32x16 &sn, f32x16 &pn) __attribute__((always_inline)) {
+    constexpr int U = decltype(u_tag)::value;        // tile index mod 4
+    using St = std::integral_constant<int, U>;
+    using St1 = std::integral_constant<int, (U + 1) & 3>;
+    using St2 = std::integral_constant<int, (U + 2) & 3>;
+    // the tile copied in this iteration, t + kStages - 1, starts a new query block?
+    constexpr bool kNewBlock = (U + C::kStages - 1) % C::kSub == 0;
+    constexpr bool kNextNewBlock = (U + C::kStages) % C::kSub == 0;
+    uint32_t pb[8], db[8];
+    auto pack = [&](int i) __attribute__((always_inline)) {
+      pc[i] *= sc[i];
+      if (i & 1) {
+        pb[i >> 1] = pack_bf16x2(sc[i - 1], sc[i]);
+        db[i >> 1] = pack_bf16x2(pc[i - 1], pc[i]);
+      }
     };
-    // S -> P -> dV first, then dP -> dS -> dK, so that fewer registers are live at once
+    __builtin_amdgcn_sched_barrier(0);
+    [&]<int... E>(std::integer_sequence<int, E...>) __attribute__((always_inline)) {
+      ([&]() __attribute__((always_inline)) {
+        constexpr int e = E;
+        if constexpr (e + kDepth < kNA) read_row(std::integral_constant<int, e + kDepth>{}, St1{});
+        else read_tr(std::integral_constant<int, e + kDepth - kNA>{}, St{});
+        constexpr int s = e / 2;
+        if constexpr ((e & 1) == 0)
+          sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[e % kRing], kreg[s], s == 0 ? zero16 : sn, 0, 0, 0);
+        else
+          pn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[e % kRing], vreg[s], pn, 0, 0, 0);
+        constexpr int per = 16 / kNA;                // elements of tile t that belong to this slot
 #pragma unroll
-    for (int mt = 0; mt < C::kST / 32; ++mt) {
-      __builtin_amdgcn_s_setprio(0);
-      const bf16 *qrow = Qs + (mt * 32 + kr) * D;
-      const bf16 *grow = Gs + (mt * 32 + kr) * D;
-      f32x16 sacc = zero16;
-#pragma unroll
-      for (int s = 0; s < D / 16; ++s) {
-        bf16x8 qa = *reinterpret_cast<const bf16x8 *>(qrow + ((16 * s) ^ kx));
-        sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, kreg[s], sacc, 0, 0, 0);
-      }
-      // accumulator register i of lane half hl is query 32mt + 16(i/8) + 8hl + (i%8)
-      __builtin_amdgcn_s_setprio(3);   // vector work goes ahead of the other workgroup's MFMA stream
-      uint32_t pb[8];
-#pragma unroll
-      for (int t8 = 0; t8 < 2; ++t8) {
-        const int qq = mt * 32 + 16 * t8 + 8 * hl;
-        f32x4 l0 = *reinterpret_cast<const f32x4 *>(sLse + qq);
-        f32x4 l1 = *reinterpret_cast<const f32x4 *>(sLse + qq + 4);
-        float lv[8] = {l0[0], l0[1], l0[2], l0[3], l1[0], l1[1], l1[2], l1[3]};
-#pragma unroll
-        for (int e = 0; e < 8; e += 2) {
-          const int i = 8 * t8 + e;
-          sacc[i] = kvalid ? fast_exp2(fmaf(sacc[i], c, -lv[e])) : 0.f;
-          sacc[i + 1] = kvalid ? fast_exp2(fmaf(sacc[i + 1], c, -lv[e + 1])) : 0.f;
-          pb[i >> 1] = pack_bf16x2(sacc[i], sacc[i + 1]);
+        for (int u = 0; u < per; ++u) {
+          const int i = e * per + u;
+          sc[i] = fast_exp2(fmaf(sc[i], c, -lse_v[i >> 2][i & 3]));
         }
-      }
-      __builtin_amdgcn_s_setprio(0);
+        if constexpr (e > 0) {
 #pragma unroll
-      for (int tt = 0; tt < 2; ++tt) {
-        uint4 raw = make_uint4(pb[4 * tt], pb[4 * tt + 1], pb[4 * tt + 2], pb[4 * tt + 3]);
-        bf16x8 bp = *reinterpret_cast<bf16x8 *>(&raw);
-#pragma unroll
-        for (int dm = 0; dm < D / 32; ++dm)
-          vacc[dm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_operand(kGOff, mt, tt, dm), bp, vacc[dm], 0, 0, 0);
-      }
-      f32x16 pacc = zero16;
-#pragma unroll
-      for (int s = 0; s < D / 16; ++s) {
-        bf16x8 ga = *reinterpret_cast<const bf16x8 *>(grow + ((16 * s) ^ kx));
-        pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ga, vreg[s], pacc, 0, 0, 0);
-      }
-      __builtin_amdgcn_s_setprio(3);
-      uint32_t dsb[8];
-#pragma unroll
-      for (int t8 = 0; t8 < 2; ++t8) {
-        const int qq = mt * 32 + 16 * t8 + 8 * hl;
-        f32x4 d0 = *reinterpret_cast<const f32x4 *>(sDelta + qq);
-        f32x4 d1 = *reinterpret_cast<const f32x4 *>(sDelta + qq + 4);
-        float dv[8] = {d0[0], d0[1], d0[2], d0[3], d1[0], d1[1], d1[2], d1[3]};
-#pragma unroll
-        for (int e = 0; e < 8; e += 2) {
-          const int i = 8 * t8 + e;
-          dsb[i >> 1] = pack_bf16x2(sacc[i] * (pacc[i] - dv[e]), sacc[i + 1] * (pacc[i + 1] - dv[e + 1]));
+          for (int u = 0; u < per; ++u) pack((e - 1) * per + u);
         }
-      }
-      __builtin_amdgcn_s_setprio(0);
+        if constexpr (e == kNA - 1) {
 #pragma unroll
-      for (int tt = 0; tt < 2; ++tt) {
-        uint4 raw = make_uint4(dsb[4 * tt], dsb[4 * tt + 1], dsb[4 * tt + 2], dsb[4 * tt + 3]);
-        bf16x8 bd = *reinterpret_cast<bf16x8 *>(&raw);
+          for (int u = 0; u < per; ++u) pack(e * per + u);
+        }
+        if constexpr (e == 1) next_tile(std::integral_constant<int, 0>{}, std::bool_constant<kNewBlock>{});
+        if constexpr (e == 3) next_tile(std::integral_constant<int, 1>{}, std::bool_constant<kNewBlock>{});
+        if constexpr (e == 5) next_tile(std::integral_constant<int, 2>{}, std::bool_constant<kNewBlock>{});
+        __builtin_amdgcn_sched_barrier(0);
+      }(), ...);
+    }(std::make_integer_sequence<int, kNA>{});
+
+    // tile t + 2 has landed (everyone's copies) and nobody reads tile t - 1 any more
+    wait_copies(std::integral_constant<int, (C::kStages - 4) * kBatch>{});
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    [&]<int... F>(std::integer_sequence<int, F...>) __attribute__((always_inline)) {
+      ([&]() __attribute__((always_inline)) {
+        constexpr int f = F, e = kNA + f;
+        if constexpr (f + kDepth < kNB) read_tr(std::integral_constant<int, f + kDepth>{}, St{});
+        else read_row(std::integral_constant<int, f + kDepth - kNB>{}, St2{});
+        constexpr int dm = (f / 2) % (D / 32), tt = f / (2 * (D / 32));
+        if constexpr ((f & 1) == 0) {
+          const u32x4 raw = {pb[4 * tt], pb[4 * tt + 1], pb[4 * tt + 2], pb[4 * tt + 3]};
+          accumulate(vacc[dm], ring[e % kRing], __builtin_bit_cast(bf16x8, raw));
+        } else {
+          const u32x4 raw = {db[4 * tt], db[4 * tt + 1], db[4 * tt + 2], db[4 * tt + 3]};
+          accumulate(kacc[dm], ring[e % kRing], __builtin_bit_cast(bf16x8, raw));
+        }
+        if constexpr (f < 4) read_lse(f, (U + 1) & 3);
+        else if constexpr (f < 8) read_ndelta(f - 4, (U + 2) & 3, pc);
+        if constexpr (f == 0 && kNextNewBlock) fetch_entry();
+        // copies of tile t + kStages - 1, spread over the slots
+        constexpr int i0 = f * kBatch / kNB, i1 = (f + 1) * kBatch / kNB;
 #pragma unroll
-        for (int dm = 0; dm < D / 32; ++dm)
-          kacc[dm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_operand(0, mt, tt, dm), bd, kacc[dm], 0, 0, 0);
+        for (int i = i0; i < i1; ++i)
+          copy_one(i, smem_addr + ((U + 3) & 3) * kStage);
+        __builtin_amdgcn_sched_barrier(0);
+      }(), ...);
+    }(std::make_integer_sequence<int, kNB>{});
+  };
+
+  __syncthreads();   // rows[] is written
+  if (n_it > 0) {
+    // The loop takes four tiles at a time, one per stage.  Blocks of 64 rows are two tiles: with an
+    // odd number of them tile 0 goes to stage 2 and the first two tiles come before the loop.
+    const bool odd = C::kSub == 2 && (n_blocks & 1);
+    const uint32_t first_stage = odd ? 2u : 0u, first_off = first_stage * kStage;
+    // tiles 0 .. kStages - 2
+    for (int t = 0; t < C::kStages - 1; ++t) {
+      if (t % C::kSub == 0) {
+        fetch_entry();
+        next_tile(std::integral_constant<int, 0>{}, std::true_type{});
+      } else {
+        next_tile(std::integral_constant<int, 0>{}, std::false_type{});
       }
+      next_tile(std::integral_constant<int, 1>{}, std::false_type{});
+      next_tile(std::integral_constant<int, 2>{}, std::false_type{});
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) copy_one(i, smem_addr + ((t + first_stage) & 3u) * kStage);
     }
+    if ((C::kStages - 1) % C::kSub == 0) fetch_entry();
+    wait_copies(std::integral_constant<int, (C::kStages - 3) * kBatch>{});   // tiles 0 and 1
+    __syncthreads();
+    // S and dP of tile 0, first operands of tile 1
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) row_at[s] += first_off;
+    stat_at += first_off;
+    s0 = zero16;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      read_lse(q, 0);
+      read_ndelta(q, 0, p0);
+      read_ndelta(q, 1, p1);
+    }
+    [&]<int... E>(std::integer_sequence<int, E...>) __attribute__((always_inline)) {
+      ([&]() __attribute__((always_inline)) {
+        constexpr int e = E;
+        read_row(std::integral_constant<int, e>{}, std::integral_constant<int, 0>{});
+        if constexpr ((e & 1) == 0) s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[e % kRing], kreg[e / 2], s0, 0, 0, 0);
+        else p0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[e % kRing], vreg[e / 2], p0, 0, 0, 0);
+      }(), ...);
+    }(std::make_integer_sequence<int, kNA>{});
+    [&]<int... E>(std::integer_sequence<int, E...>) __attribute__((always_inline)) {
+      (read_row(std::integral_constant<int, E>{}, std::integral_constant<int, 1>{}), ...);
+    }(std::make_integer_sequence<int, kDepth>{});
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) row_at[s] -= first_off;
+    stat_at -= first_off;
+    if (odd) {
+      body(std::integral_constant<int, 2>{}, s0, p0, s1, p1);
+      body(std::integral_constant<int, 3>{}, s1, p1, s0, p0);
+    }
+    for (int t = odd ? 2 : 0; t < n_it; t += 4) {
+      body(std::integral_constant<int, 0>{}, s0, p0, s1, p1);
+      body(std::integral_constant<int, 1>{}, s1, p1, s0, p0);
+      body(std::integral_constant<int, 2>{}, s0, p0, s1, p1);
+      body(std::integral_constant<int, 3>{}, s1, p1, s0, p0);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);          // stray copies must land before the LDS is given up
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
   }
 
   // epilogue of one gradient: acc holds its transpose for my 32 keys
@@ -592,7 +910,7 @@ static hipError_t launch_bwd_t(const BwdArgs &a, const BwdArgs *pooled_launch, h
   }
   const int grid = xcd_grid(a.n_slabs * a.Nb);
   hipError_t e = hipSuccess;
-  if (a.delta_out) {
+  if (a.ndelta_out) {
     // no low half of O from the caller: Delta from the tiles themselves, before anything uses it
     if (pooled_launch)
       hipLaunchKernelGGL((dq_kernel<BLK, D, true, true>), dim3(grid), dim3(C::kThreads), C::kDqLds, st, a);
@@ -639,7 +957,7 @@ hipError_t launch_bwd(const Problem &pb, const void *q, const void *k, const voi
                       hipStream_t st, const GlobalTokens *gt) {
   unsigned char *ws = reinterpret_cast<unsigned char *>(workspace);
   const size_t rb = rowstat_bytes(pb);
-  float *delta = reinterpret_cast<float *>(ws);
+  float *ndelta = reinterpret_cast<float *>(ws);
   float *lse2 = reinterpret_cast<float *>(ws + rb);
   float *lse2g = reinterpret_cast<float *>(ws + 2 * rb);
   int32_t *order = reinterpret_cast<int32_t *>(ws + 3 * rb);
@@ -649,17 +967,17 @@ hipError_t launch_bwd(const Problem &pb, const void *q, const void *k, const voi
   dim3 dgrid((pb.Lpad + 15) / 16, pb.n_slabs);
   if (pb.d == 128)
     hipLaunchKernelGGL(delta_kernel<128>, dgrid, dim3(256), 0, st, o, o_lo, d_o, pb.o, pb.H, pb.L,
-                       pb.Lpad, lse, pooled_bias, delta, lse2, gt ? lse2g : nullptr);
+                       pb.Lpad, lse, pooled_bias, ndelta, lse2, gt ? lse2g : nullptr);
   else
     hipLaunchKernelGGL(delta_kernel<64>, dgrid, dim3(256), 0, st, o, o_lo, d_o, pb.o, pb.H, pb.L,
-                       pb.Lpad, lse, pooled_bias, delta, lse2, gt ? lse2g : nullptr);
+                       pb.Lpad, lse, pooled_bias, ndelta, lse2, gt ? lse2g : nullptr);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
 
   BwdArgs a;
   a.q = q; a.k = k; a.v = v; a.d_o = d_o;
-  a.lse2 = lse2; a.delta = delta;
-  a.delta_out = o_lo ? nullptr : delta;
+  a.lse2 = lse2; a.ndelta = ndelta;
+  a.ndelta_out = o_lo ? nullptr : ndelta;
   a.row_ptr = row_ptr; a.col_idx = col_idx; a.col_ptr = col_ptr; a.row_idx = row_idx;
   a.dq = dq; a.dk = dk; a.dv = dv;
   a.tq = pb.q; a.tk = pb.k; a.tv = pb.v; a.to = pb.o;

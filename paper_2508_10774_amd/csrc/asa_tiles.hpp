@@ -55,6 +55,11 @@ template <int D>
 __device__ __forceinline__ uint32_t tr_piece(int r, int d4) {
   return (uint32_t)((r * D + (((d4 >> 3) ^ t_swz<D>(r)) << 3) + (d4 & 4)) * 2);
 }
+// read of a T at an absolute LDS byte address
+template <typename T>
+__device__ __forceinline__ T lds_read(uint32_t addr) {
+  return *reinterpret_cast<const __attribute__((address_space(3))) T *>((uintptr_t)addr);
+}
 // ds_read_b64_tr_b16: inside each group of 16 lanes, lane i receives as element j (j = 0..3) the
 // 16-bit element i % 4 of the 8 bytes that lane 4 j + i / 4 of the group addressed.
 __device__ __forceinline__ bf16x4 lds_read_tr16(const lds_char *p) {
@@ -102,17 +107,14 @@ __device__ __forceinline__ void lds_dma16_sv(const void *uniform_base, uint32_t 
                :: "v"(lane_off), "s"(bu), "s"((uint32_t)__builtin_amdgcn_readfirstlane(lds_byte_addr)) : "memory");
 #endif
 }
-// The same (compiler-invisible) load with a full per-lane 64-bit address, and its 4-byte form.
-__device__ __forceinline__ void lds_dma16_v(const void *lane_ptr, uint32_t lds_byte_addr) {
+// The same with 4 bytes per lane.
+__device__ __forceinline__ void lds_dma4_sv(const void *uniform_base, uint32_t lane_off, uint32_t lds_byte_addr) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-               :: "v"(lane_ptr), "s"((uint32_t)__builtin_amdgcn_readfirstlane(lds_byte_addr)) : "memory");
-#endif
-}
-__device__ __forceinline__ void lds_dma4_v(const void *lane_ptr, uint32_t lds_byte_addr) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
-               :: "v"(lane_ptr), "s"((uint32_t)__builtin_amdgcn_readfirstlane(lds_byte_addr)) : "memory");
+  const uint64_t b = reinterpret_cast<uint64_t>(uniform_base);
+  const uint64_t bu = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b) |
+                      ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32)) << 32);
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
+               :: "v"(lane_off), "s"(bu), "s"((uint32_t)__builtin_amdgcn_readfirstlane(lds_byte_addr)) : "memory");
 #endif
 }
 // LDS byte address of an object that the compiler knows to live in LDS (apply it to the
@@ -232,44 +234,35 @@ struct ColTileCopy {
   }
 };
 
-// The same two copies (the row tile with the t_swz swizzle) for a kernel that cannot spare registers for the offset tables: nothing
-// is kept per lane, each offset is rebuilt from the lane number where it is used (a few integer
-// instructions per load).  The caller passes the lane number through an empty asm statement
-// inside its loop, so that the compiler does not hoist the offsets back into registers.
+// ROWS x D row tile with the t_swz swizzle, copied by WAVES wavefronts one instruction at a time, so
+// that a kernel can place the copies between other work.  Tiles start at multiples of ROWS; the one
+// that holds the last row L - 1 re-reads that row where it reaches past it (a second set of
+// per-lane offsets, chosen without a branch).  A tile wholly past L - 1 is replaced by
+// the one that holds it: the caller masks such rows anyway.
 template <int ROWS, int D, int WAVES>
-struct LeanRowTileCopy {
+struct TrTileCopy {
   static constexpr int kChunks = D / 8;                       // 16-byte chunks per row
-  static constexpr int kRowsPer = 64 / kChunks;               // rows per wave instruction
   static constexpr int kInstr = ROWS * kChunks / 64 / WAVES;  // wave instructions per copy
-  static_assert((kInstr * kRowsPer) % 16 == 0, "a wave's first row must be a multiple of 16");
+  static_assert(kInstr * 64 * WAVES == ROWS * kChunks, "whole instructions per wavefront");
+  uint32_t off[kInstr], off_last[kInstr];
+  uint32_t lds0;                                              // LDS distance of my first instruction
 
-  // copy rows [row0, row0 + ROWS) of `tensor` (slab base, row pitch sL elements) to the LDS
-  // byte address `stage`; rows past L - 1 re-read row L - 1.  The loads are of the kind the
-  // compiler does not see: the caller waits with an explicit vmcnt before reading the tile.
-  static __device__ __forceinline__ void issue(uint32_t stage, const bf16 *tensor, int row0, int L,
-                                               int64_t sL, int wave, int lane) {
-    const int64_t pitch = sL * 2;
-    const int lane_row = lane / kChunks, pos = lane % kChunks;
-    const char *base = reinterpret_cast<const char *>(tensor) + (int64_t)row0 * pitch;
-    const int lim = L - 1 - row0;   // last valid row of the tile
-    if (lim >= ROWS - 1) {
-      const uint32_t lane_row_off = (uint32_t)lane_row * (uint32_t)pitch;
+  static __device__ __forceinline__ int last_row0(int L) { return (L - 1) / ROWS * ROWS; }
+  __device__ __forceinline__ void init(int wave, int lane, int64_t sL, int L) {
+    const uint32_t pitch = (uint32_t)(sL * 2);
+    lds0 = (uint32_t)(wave * kInstr * 1024);
 #pragma unroll
-      for (int i = 0; i < kInstr; ++i) {
-        const int r0 = (wave * kInstr + i) * kRowsPer;                    // wave-uniform
-        const int sw = t_swz<D>(((i * kRowsPer) & 15) + lane_row);        // = t_swz(r0 + lane_row)
-        const uint32_t lo = lane_row_off + (uint32_t)((pos ^ sw) * 16);
-        lds_dma16_sv(base + (int64_t)r0 * pitch, lo, stage + (wave * kInstr + i) * 1024);
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < kInstr; ++i) {
-        const int row = (wave * kInstr + i) * kRowsPer + lane_row;
-        const int sw = t_swz<D>(row);
-        const int src_row = row > lim ? lim : row;                        // may be negative
-        lds_dma16_v(base + (int64_t)src_row * pitch + (pos ^ sw) * 16, stage + (wave * kInstr + i) * 1024);
-      }
+    for (int i = 0; i < kInstr; ++i) {
+      const int row = (wave * kInstr + i) * (64 / kChunks) + lane / kChunks;
+      const int row_c = min(row, L - 1 - last_row0(L));
+      const uint32_t chunk = (uint32_t)(((lane % kChunks) ^ t_swz<D>(row)) * 16);
+      off[i] = (uint32_t)row * pitch + chunk;
+      off_last[i] = (uint32_t)row_c * pitch + chunk;
     }
+  }
+  // last (wave-uniform): this is the tile that holds row L - 1
+  __device__ __forceinline__ void issue_one(int i, uint32_t stage, const char *base, bool last) const {
+    lds_dma16_sv(base, last ? off_last[i] : off[i], stage + lds0 + i * 1024);
   }
 };
 

@@ -156,3 +156,26 @@ def test_bwd_packed_qkv_layout_with_different_strides_per_tensor(L, d, block):
         want = oracle.attn_bwd(qf[0, h], kf[0, h], vf[0, h], gf[0, h], mask[h], block, None)
         for name, a, w in zip(("dQ", "dK", "dV"), got, want):
             util.assert_close_bf16(a[0, h], w, f"packed {name}[{h}]")
+
+
+@pytest.mark.parametrize("block", [64, 128])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("tail", [1, 20, 32, 33, 64])
+def test_bwd_list_lengths_and_tails(block, d, tail):
+    """Row and column lists of 0, 1, 2, 3, ... blocks (the tile loop takes four tiles of 32 rows at a
+    time, blocks of 64 rows are two of them) with a last block that ends inside its first tile, at
+    the end of it, inside the second one, or at a block's end; with and without the low half of O.
+    A last block of a single key gathers dV values of 16 and more, whose rounding to bf16 alone is
+    up to 2^-8 |want| = 0.06: the element-wise allowance of util.assert_close_bf16, not the plain one."""
+    Nb = 6
+    L = (Nb - 1) * block + tail
+    print(f"case L={L} d={d} block={block}", flush=True)
+    p = binding.Params(B=1, H=2, L=L, d=d, block=block)
+    shape = (1, 2, L, d)
+    qb, kb, vb, gb = (synth.make_iid(shape, L + d, 80 + s) for s in range(4))
+    mask = np.zeros((2, Nb, Nb), np.uint8)
+    for i in range(Nb):
+        mask[0, i, Nb - i:] = 1      # rows of 0 .. 5 blocks, every one of them with the ragged block
+        mask[1, i, :i + 1] = 1       # rows of 1 .. 6, columns of 6 .. 1
+    _check_bwd(p, qb, kb, vb, gb, mask, use_mag=True)
+    _check_bwd(p, qb, kb, vb, gb, mask, with_lo=False, use_mag=True)
