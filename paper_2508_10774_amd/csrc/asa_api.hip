@@ -384,10 +384,7 @@ int asa_global_tokens(const asa_params *p, int n, const void *k, const void *v, 
   if (rc != ASA_OK) return rc;
   if (!k || !v || !kg || !vg) return ASA_ERR_INVALID_ARG;
   if (!aligned16(k) || !aligned16(v) || !aligned16(kg) || !aligned16(vg)) return ASA_ERR_INVALID_ARG;
-  hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
-  hipError_t e = launch_pool(pb, n, k, pb.k, kg, st);
-  if (e != hipSuccess) return finish(e);
-  return finish(launch_pool(pb, n, v, pb.v, vg, st));
+  return finish(launch_pool(pb, n, k, v, kg, vg, reinterpret_cast<hipStream_t>(hip_stream)));
 }
 
 size_t asa_fwd_g_workspace_bytes(const asa_params *p, int n) {

@@ -69,7 +69,7 @@ struct GlobalTokens {
   const void *vg;     // [slab][Nbg * block][d] bf16
   const void *vgt;    // [slab][Nbg][d][block] bf16, transposed tiles of vg (workspace)
 };
-hipError_t launch_pool(const Problem &pb, int n, const void *src, const TensorView &tv, void *dst,
+hipError_t launch_pool(const Problem &pb, int n, const void *k, const void *v, void *kg, void *vg,
                        hipStream_t st);
 hipError_t launch_fwd(const Problem &pb, const void *q, const void *k, const void *vt,
                       const int32_t *row_ptr, const int32_t *col_idx, void *o, void *o_lo,

@@ -52,6 +52,29 @@ def test_pooled_tokens_are_the_rounded_window_means(L, d, block, n):
             assert (diff > 0).mean() < 2e-3
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n", [1, 2, 3, 8, 15, 16, 17, 31, 32, 33, 100, 403])
+def test_pooled_tokens_at_the_edges_of_the_window_shares(n, d):
+    """A window's tokens are shared by 1 .. 16 (d = 128) or 1 .. 32 (d = 64) groups of lanes: windows
+    just below, at and just above those counts, K and V with different strides, a short last window.
+    Sums in fp32 against fp64: one bf16 step at most (2^-7 of the value), and rarely."""
+    L, H = 403, 3
+    qkv = torch.empty((1, L, 3, H, d), dtype=torch.bfloat16, device="cuda")
+    kb, vb = (synth.make_iid((1, H, L, d), 22 + n, s) for s in range(2))
+    qkv[:, :, 1] = util.dev_bf16(kb).permute(0, 2, 1, 3)
+    k, v = qkv[:, :, 1].permute(0, 2, 1, 3), util.dev_bf16(vb)
+    p = binding.Params(B=1, H=H, L=L, d=d, block=64, k_stride=tuple(k.stride()[:3]))
+    for got, src in zip(_pooled(p, n, k, v), (kb, vb)):
+        Lg = og.n_windows(L, n)
+        g = util.host_f32(got)
+        assert (g[:, :, Lg:] == 0).all()
+        for h in range(H):
+            want, _ = og.pool(synth.bf16_bits_to_f32(src[0, h]), n)
+            diff = np.abs(g[0, h, :Lg] - want)
+            assert (diff <= np.abs(want) * 2.0 ** -7 + 1e-30).all()
+            assert (diff > 0).mean() < 5e-3
+
+
 @pytest.mark.parametrize("B,H,L,d,block,n,dens", [
     (1, 2, 1024, 64, 64, 64, 0.4),       # window = block, exact multiples
     (1, 2, 1000, 128, 128, 128, 0.5),    # ragged last block and last window (104 tokens)
