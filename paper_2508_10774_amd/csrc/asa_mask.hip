@@ -731,49 +731,77 @@ __global__ __launch_bounds__(128) void csr_fill_kernel(const uint8_t *mask, int 
   }
 }
 
-// The same in ONE kernel where a slab's mask fits in LDS (Nb <= 384).  kCsrParts workgroups per
-// slab; each holds the whole mask (rows padded by 4 bytes, so that a walk down a column meets
-// every bank once), counts every row and column (one thread each), scans the counts in a single
-// wavefront and then fills its share of the lists (one wavefront per row or column, ballot
-// compaction, so the lists come out ascending and the stores are coalesced).  The counting is
-// repeated by every part of a slab: cheaper than a second launch and a trip through memory.
-constexpr int kCsrLdsMaxNb = 384;
-constexpr int kCsrParts = 16;
-__global__ __launch_bounds__(1024) void csr_slab_kernel(const uint8_t *mask, int Nb, int32_t *row_ptr,
+// The same in ONE kernel where a slab's mask fits in LDS: several workgroups per slab and direction.
+// Each copies the whole mask into LDS, turns it into bits (pieces of 16 rows x 64 columns:
+// lane r keeps the ballot of row r, or lane c gathers column c by shifts), counts with
+// popcounts, scans the counts and fills its share of the lists, a wavefront per row or column,
+// ascending, with coalesced stores.  Reading the mask again in every part costs less than a second
+// launch and a trip through memory.  Bound: the latency of the copy and of the four steps behind it.
+// Nb = 256, 12 slabs: 15 -> 13 us; Nb = 278, 48 slabs: 65 -> 24 us, against one thread per row or column that
+// counts byte by byte out of LDS.  (Bytes straight from global memory instead of the copy: 22 and
+// 48 us, bound by the address unit.)
+constexpr int kCsrBitsMaxNb = 352;               // mask, bits and counts in 160 KB of LDS
+constexpr int kCsrWords = (kCsrBitsMaxNb + 63) / 64;
+__global__ __launch_bounds__(1024) void csr_bits_kernel(const uint8_t *mask, int Nb, int32_t *row_ptr,
                                                         int32_t *col_idx, int32_t *col_ptr,
                                                         int32_t *row_idx) {
-  extern __shared__ __align__(16) unsigned char csr_smem[];
-  __shared__ int cnt[2][kCsrLdsMaxNb + 1];        // row counts, column counts -> exclusive offsets
-  const int part = blockIdx.x, slab = blockIdx.y, tid = threadIdx.x;
-  const int wave = tid >> 6, lane = tid & 63;
-  const int pitch = Nb + 4;
+  extern __shared__ __align__(16) unsigned char csr_smem[];        // the slab's mask, rows of Nb bytes
+  __shared__ unsigned long long bits[kCsrBitsMaxNb * kCsrWords];   // [row or column][word]
+  __shared__ int start[kCsrBitsMaxNb + 1];                         // counts, then exclusive offsets
+  const int part = blockIdx.x, dir = blockIdx.y, slab = blockIdx.z, n_parts = gridDim.x;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int W = (Nb + 63) / 64;
+  for (int x = tid; x < Nb; x += 1024) bits[x * W + W - 1] = 0;   // (its last quarters may have no rows)
   const uint8_t *m = mask + (int64_t)slab * Nb * Nb;
-  if ((Nb & 3) == 0 && (reinterpret_cast<uintptr_t>(mask) & 3) == 0) {   // four entries at a time
+  if ((reinterpret_cast<uintptr_t>(m) & 3) == 0) {                 // four entries at a time
     const uint32_t *m4 = reinterpret_cast<const uint32_t *>(m);
-    for (int t = tid; t < Nb * Nb / 4; t += 1024) {
-      const int e = 4 * t;
-      *reinterpret_cast<uint32_t *>(csr_smem + (e / Nb) * pitch + (e % Nb)) = m4[t];
-    }
+    uint32_t *l4 = reinterpret_cast<uint32_t *>(csr_smem);
+    const int n4 = Nb * Nb / 4;
+#pragma unroll 8
+    for (int t = tid; t < n4; t += 1024) l4[t] = m4[t];
+    for (int t = 4 * n4 + tid; t < Nb * Nb; t += 1024) csr_smem[t] = m[t];
   } else {
-    for (int t = tid; t < Nb * Nb; t += 1024) csr_smem[(t / Nb) * pitch + (t % Nb)] = m[t];
+#pragma unroll 8
+    for (int t = tid; t < Nb * Nb; t += 1024) csr_smem[t] = m[t];
   }
   __syncthreads();
-  const int n_dir = col_ptr ? 2 : 1;
-  if (tid < n_dir * Nb) {                          // thread = one row (dir 0) or one column (dir 1)
-    const int dir = tid / Nb, i = tid - dir * Nb;
-    const unsigned char *src = csr_smem + (dir == 0 ? i * pitch : i);
-    const int step = dir == 0 ? 1 : pitch;
+  // pieces of 16 rows x 64 columns
+  for (int piece = wave; piece < W * ((Nb + 15) / 16); piece += 16) {
+    const int r0 = (piece / W) * 16, c0 = (piece % W) * 64;
+    const int n_rows = min(16, Nb - r0);
+    const bool c_ok = c0 + lane < Nb;
+    const unsigned char *src = csr_smem + r0 * Nb + c0 + (c_ok ? lane : 0);
+    uint8_t b[16];
+#pragma unroll
+    for (int x = 0; x < 16; ++x) b[x] = src[min(x, n_rows - 1) * Nb];
+    if (dir == 0) {                              // lane x < 16: row r0 + x, columns c0 ..
+      unsigned long long word = 0;
+#pragma unroll
+      for (int x = 0; x < 16; ++x) {
+        const unsigned long long row = __ballot(c_ok && b[x] != 0);
+        if (lane == x) word = row;
+      }
+      if (lane < n_rows) bits[(r0 + lane) * W + c0 / 64] = word;
+    } else {                                     // lane: column c0 + lane, a quarter of its word of rows
+      uint32_t quarter = 0;
+#pragma unroll
+      for (int x = 0; x < 16; ++x) quarter |= (uint32_t)(x < n_rows && b[x] != 0) << x;
+      if (c_ok) reinterpret_cast<uint16_t *>(bits)[(c0 + lane) * W * 4 + r0 / 16] = (uint16_t)quarter;
+    }
+  }
+  __syncthreads();
+  for (int x = tid; x < Nb; x += 1024) {
     int n = 0;
-    for (int x = 0; x < Nb; ++x) n += src[x * step] != 0;
-    cnt[dir][i] = n;
+    for (int w = 0; w < W; ++w) n += __popcll(bits[x * W + w]);
+    start[x] = n;
   }
   __syncthreads();
-  if (wave < n_dir) {                              // one wavefront per direction: exclusive scan
-    int32_t *ptr = (wave == 0 ? row_ptr : col_ptr) + (int64_t)slab * (Nb + 1);
+  int32_t *ptr = (dir == 0 ? row_ptr : col_ptr) + (int64_t)slab * (Nb + 1);
+  if (wave == 0) {                                 // exclusive scan of the counts
     int run = 0;
     for (int x0 = 0; x0 < Nb; x0 += 64) {
       const int x = x0 + lane;
-      const int v = x < Nb ? cnt[wave][x] : 0;
+      const int v = x < Nb ? start[x] : 0;
       int inc = v;
 #pragma unroll
       for (int off = 1; off < 64; off <<= 1) {
@@ -781,7 +809,7 @@ __global__ __launch_bounds__(1024) void csr_slab_kernel(const uint8_t *mask, int
         if (lane >= off) inc += o;
       }
       if (x < Nb) {
-        cnt[wave][x] = run + inc - v;
+        start[x] = run + inc - v;
         if (part == 0) ptr[x] = run + inc - v;
       }
       run += __shfl(inc, 63, 64);
@@ -789,15 +817,12 @@ __global__ __launch_bounds__(1024) void csr_slab_kernel(const uint8_t *mask, int
     if (part == 0 && lane == 0) ptr[Nb] = run;
   }
   __syncthreads();
-  for (int item = part * 16 + wave; item < n_dir * Nb; item += 16 * kCsrParts) {
-    const int dir = item / Nb, i = item - dir * Nb;
-    int32_t *idx = (dir == 0 ? col_idx : row_idx) + (int64_t)slab * Nb * Nb;
-    int o = cnt[dir][i];
-    for (int x0 = 0; x0 < Nb; x0 += 64) {
-      const int x = x0 + lane;
-      const bool f = x < Nb && csr_smem[dir == 0 ? i * pitch + x : x * pitch + i] != 0;
-      const unsigned long long b = __ballot(f);
-      if (f) idx[o + __popcll(b & ((1ull << lane) - 1ull))] = x;
+  int32_t *idx = (dir == 0 ? col_idx : row_idx) + (int64_t)slab * Nb * Nb;
+  for (int i = part * 16 + wave; i < Nb; i += 16 * n_parts) {
+    int o = start[i];
+    for (int w = 0; w < W; ++w) {
+      const unsigned long long b = bits[i * W + w];
+      if ((b >> lane) & 1) idx[o + __popcll(b & ((1ull << lane) - 1ull))] = 64 * w + lane;
       o += __popcll(b);
     }
   }
@@ -805,13 +830,17 @@ __global__ __launch_bounds__(1024) void csr_slab_kernel(const uint8_t *mask, int
 
 hipError_t launch_csr(const Problem &pb, const uint8_t *mask, int32_t *row_ptr, int32_t *col_idx,
                       int32_t *col_ptr, int32_t *row_idx, hipStream_t st) {
-  if (pb.Nb <= kCsrLdsMaxNb) {
-    const int lds = pb.Nb * (pb.Nb + 4);
-    hipError_t e0 = set_dynamic_lds_once(reinterpret_cast<const void *>(&csr_slab_kernel),
-                                         kCsrLdsMaxNb * (kCsrLdsMaxNb + 4));
+  if (pb.Nb <= kCsrBitsMaxNb) {
+    // as many parts as keep one workgroup per compute unit, at most one per 16 rows
+    const int n_dir = col_ptr ? 2 : 1;
+    const int most = (pb.Nb + 15) / 16;
+    int parts = 256 / (n_dir * pb.n_slabs);
+    parts = parts < 1 ? 1 : (parts > most ? most : parts);
+    hipError_t e0 = set_dynamic_lds_once(reinterpret_cast<const void *>(&csr_bits_kernel),
+                                         kCsrBitsMaxNb * kCsrBitsMaxNb);
     if (e0 != hipSuccess) return e0;
-    hipLaunchKernelGGL(csr_slab_kernel, dim3(kCsrParts, pb.n_slabs), dim3(1024), lds, st, mask, pb.Nb, row_ptr,
-                       col_idx, col_ptr, row_idx);
+    hipLaunchKernelGGL(csr_bits_kernel, dim3(parts, n_dir, pb.n_slabs), dim3(1024), pb.Nb * pb.Nb, st, mask,
+                       pb.Nb, row_ptr, col_idx, col_ptr, row_idx);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(csr_count_kernel, dim3(pb.Nb, pb.n_slabs), dim3(128), 0, st, mask, pb.Nb,

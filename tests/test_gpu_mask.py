@@ -94,6 +94,63 @@ def test_index_lists_match_the_mask(Nb, dens):
         assert np.array_equal(gci[s, :n], ci[s, :n]) and np.array_equal(gri[s, :n], ri[s, :n])
 
 
+@pytest.mark.parametrize("Nb", [2, 63, 64, 65, 127, 129, 320, 351, 352, 353])
+@pytest.mark.parametrize("with_csc", [True, False])
+def test_index_lists_at_the_edges_of_the_64_block_pieces(Nb, with_csc):
+    """The lists are cut out of 64 x 64 pieces of the mask, up to Nb = 352 in one kernel; whole numbers,
+    compared exactly.  Mask values other than 1 count as kept."""
+    slabs = 3
+    p = binding.Params(B=1, H=slabs, L=Nb * 64 - 7, d=64, block=64)
+    mask = synth.random_block_mask(Nb, 0.3, seed=Nb, slabs=slabs)
+    mask[0, Nb // 2, :] = 0
+    mask[1, :, Nb - 1] = 0
+    mask[2] *= 255
+    bufs = util.lists_from_mask(p, mask, with_csc=with_csc)
+    torch.cuda.synchronize()
+    todo = [(oracle.csr_from_mask, "row_ptr", "col_idx")]
+    if with_csc:
+        todo.append((oracle.csc_from_mask, "col_ptr", "row_idx"))
+    for fn, ptr, idx in todo:
+        want_p, want_i = fn((mask != 0).astype(np.uint8))
+        assert np.array_equal(bufs[ptr].cpu().numpy(), want_p)
+        got_i = bufs[idx].cpu().numpy()
+        for s in range(slabs):
+            n = want_p[s, -1]
+            assert np.array_equal(got_i[s, :n], want_i[s, :n])
+
+
+@pytest.mark.parametrize("H,Nb", [(1, 1), (3, 5), (8, 100), (16, 128), (33, 500)])
+def test_every_work_item_runs_once_whatever_the_list_lengths(H, Nb):
+    """The attention kernels take their (slab, block) items longest list first, sorted inside each of
+    eight shares (up to 2048 items; the last size takes the natural order).  Lists of 0 .. Nb blocks,
+    many of one length: every row of O, dQ, dK, dV is written, none is left at its fill value, and a
+    permuted mask row gives the permuted result bit for bit."""
+    rng = np.random.default_rng(Nb)
+    block, d = 64, 64
+    L = Nb * block - (3 if Nb > 1 else 0)
+    p = binding.Params(B=1, H=H, L=L, d=d, block=block)
+    keep = np.minimum(rng.integers(0, 7, size=(H, Nb)) ** 2, Nb)
+    mask = (rng.random((H, Nb, Nb)).argsort(axis=2) < keep[:, :, None]).astype(np.uint8)
+    g = torch.Generator(device="cuda").manual_seed(Nb)
+    q, k, v, do = (torch.randn(1, H, L, d, device="cuda", generator=g).bfloat16() for _ in range(4))
+    bufs = util.lists_from_mask(p, mask)
+    o = torch.full_like(q, float("nan"))
+    lse = torch.full((H, L), float("nan"), device="cuda")
+    ws = binding.alloc_workspace(binding.asa_fwd_workspace_bytes(p))
+    binding.asa_attn_fwd(p, q, k, v, bufs["row_ptr"], bufs["col_idx"], o, lse, ws)
+    grads = util.run_bwd(p, q, k, v, o, lse, do, bufs)
+    assert not torch.isnan(lse).any()
+    for x in (o, *grads):
+        assert torch.isfinite(x.float()).all()
+    # the heads in another order: other shares, other neighbours, the same numbers
+    perm = torch.from_numpy(rng.permutation(H)).cuda()
+    bufs2 = util.lists_from_mask(p, mask[perm.cpu().numpy()])
+    q2, k2, v2 = (x[:, perm].contiguous() for x in (q, k, v))
+    o2, lse2 = util.run_fwd(p, q2, k2, v2, bufs2)
+    assert torch.equal(o2.view(torch.int16), o[:, perm].contiguous().view(torch.int16))
+    assert torch.equal(lse2, lse[perm])
+
+
 def _build(p, qb, kb, want_csc=True):
     bufs = binding.alloc_index_lists(p, with_csc=want_csc)
     pimp = torch.empty((p.B * p.H, p.Nb, p.Nb), dtype=torch.float32, device="cuda")
