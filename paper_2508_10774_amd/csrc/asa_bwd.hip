@@ -587,7 +587,6 @@ __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dkv_
   int entry_v = 0, entry_at = 0, q0 = 0;
   bool last_tile = false;
   const char *base_q = nullptr, *base_g = nullptr, *base_st = nullptr;
-  const int64_t tile_q = (int64_t)C::kST * a.tq.sL * 2, tile_g = (int64_t)C::kST * a.to.sL * 2;
   auto fetch_entry = [&]() __attribute__((always_inline)) {      // (read well before it is used)
     entry_v = rows[entry_at < n_blocks ? entry_at : n_blocks - 1];
     ++entry_at;
@@ -989,12 +988,10 @@ hipError_t launch_bwd(const Problem &pb, const void *q, const void *k, const voi
   {
     const int total = pb.n_slabs * pb.Nb;
     if (col_ptr && length_order_fits(total)) {
-      e = launch_length_order(col_ptr, pb.Nb, total, order, st);
+      int32_t *order_q = reinterpret_cast<int32_t *>(ws + 3 * rb + order_bytes(pb));
+      e = launch_length_order(col_ptr, pb.Nb, total, order, st, row_ptr, order_q);
       if (e != hipSuccess) return e;
       a.order = order;
-      int32_t *order_q = reinterpret_cast<int32_t *>(ws + 3 * rb + order_bytes(pb));
-      e = launch_length_order(row_ptr, pb.Nb, total, order_q, st);
-      if (e != hipSuccess) return e;
       a.order_q = order_q;
     }
   }

@@ -106,7 +106,9 @@ size_t bwd_workspace_bytes(const Problem &pb);
 // total = n_slabs * Nb (slab, block) items, longest list first (ptr = row_ptr or col_ptr of all
 // slabs).  Only where a share holds at most as many items as the sort takes (length_order_fits).
 bool length_order_fits(int total);
-hipError_t launch_length_order(const int32_t *ptr, int Nb, int total, int32_t *order, hipStream_t st);
+// ptr2 / order2: a second list (the other direction of the same mask) in the same launch, or null.
+hipError_t launch_length_order(const int32_t *ptr, int Nb, int total, int32_t *order, hipStream_t st,
+                               const int32_t *ptr2 = nullptr, int32_t *order2 = nullptr);
 size_t bwd_g_workspace_bytes(const Problem &pb, int Nbg);
 
 #ifdef __HIPCC__
