@@ -12,7 +12,7 @@ namespace asa {
 // soft-max (over ALL sampled keys of the slab) of scale * Qs Ks^T.
 //
 // Alg. 1 of the paper, reorganised for 64-wide wavefronts.  A workgroup of 8 wavefronts owns 8
-// query blocks and sweeps one of kProbeKeySplits ranges of the key blocks of its slab:
+// query blocks and sweeps one range of the key blocks of its slab:
 // wavefronts w and w + 4 share two query blocks and split every chunk of key blocks between them.  The sampled key rows (Alg. 2
 // steps 1-3) are gathered from K by direct global->LDS loads, 8 key blocks (128 rows) per
 // chunk, double-buffered and shared by all wavefronts.  One chain of 32x32x16
@@ -42,10 +42,12 @@ struct ProbeArgs {
 };
 
 constexpr int kProbeQBlocks = 8;   // query blocks per workgroup
-constexpr int kProbeKBlocks = 8;   // key blocks per LDS chunk
+constexpr int kProbeKBlocks = 8;   // key blocks per LDS chunk (a wavefront takes two pairs of them)
 // The key blocks of a slab are cut into this many ranges, one workgroup each: at the Wan2.1 shape
 // 12 heads x 32 query groups x 2 = 768 workgroups, three per compute unit (one range per group
-// gave 384 workgroups for 512 resident slots: half of the compute units carried twice the load).
+// gave 384 workgroups for 512 resident slots: half of the compute units carried twice the load;
+// four ranges, whole rounds of 512, are slower by 11 %: a workgroup's start costs more than the
+// half-empty round).
 constexpr int kProbeKeySplits = 2;
 
 typedef __attribute__((address_space(3))) void lds_void_m;
@@ -187,56 +189,66 @@ __global__ __launch_bounds__(512, 4) void probe_kernel(ProbeArgs a) {   // (4 wa
   const int rt_off = (2 * half * (kProbeKBlocks / 4) + hl) * 32 + n;
 
   float rt_pend[kProbeKBlocks / 4];   // block-row maxima of the chunk just swept
-  float Mt = -INFINITY;  // running maximum of my query over the key blocks of parity hl
-  double lt = 0.0;       // running denominator over the same keys
+  float Mr = -INFINITY;  // running maximum of my query's raw logits over the key blocks of parity hl
+  float br = INFINITY;   // -Mr in the exponent of 2, as rounded for the exponentials
+  double lt = 0.0;       // running denominator over the same keys, relative to 2^-br
   const float c2 = a.scale * 1.44269504088896340736f;
 
-  // one chunk out of LDS buffer BUF (a compile-time constant: every LDS address of the sweep is
-  // a per-lane register plus an immediate)
+  // One chunk out of LDS buffer BUF (a compile-time constant: every LDS address of the sweep is
+  // a per-lane register plus an immediate): both pairs of key blocks of my half at once.  The
+  // exponentials are taken relative to the running maximum, brought up to date first (with 64
+  // rows per tile some row's maximum grows in most tiles, so there is no branch for it): one
+  // fp64 update per 32 keys.  At d = 64, 48 heads, Nb = 278: 270 -> 252 us (vector instructions
+  // 86 -> 75 million), at d = 128, 12 heads, Nb = 256: 80 -> 75 us, against exponentials relative to
+  // each pair's own maximum.
   auto sweep_chunk = [&](int chunk, auto buf_tag) __attribute__((always_inline)) {
-    constexpr int BUF = decltype(buf_tag)::value;
+    constexpr int BUF = decltype(buf_tag)::value, NT = kProbeKBlocks / 4;
     const bf16 *Kb = Kc[BUF];
+    f32x16 acc[NT];
 #pragma unroll
-    for (int sb = 0; sb < kProbeKBlocks / 4; ++sb) {
-      const int j0 = chunk * kProbeKBlocks + 2 * (half * (kProbeKBlocks / 4) + sb);
-      f32x16 acc;
+    for (int sb = 0; sb < NT; ++sb)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+      for (int i = 0; i < 16; ++i) acc[sb][i] = 0.f;
+#pragma unroll
+    for (int sb = 0; sb < NT; ++sb)
 #pragma unroll
       for (int s = 0; s < D / 16; ++s) {
         bf16x8 ka = *reinterpret_cast<const bf16x8 *>(Kb + sb * 32 * D + a_off[s]);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qreg[s], acc, 0, 0, 0);
+        acc[sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qreg[s], acc[sb], 0, 0, 0);
       }
+    float mnew = Mr;
+#pragma unroll
+    for (int sb = 0; sb < NT; ++sb) {
+      const int j0 = chunk * kProbeKBlocks + 2 * (half * NT + sb);
       // register i of lane half hl is sample i of key block j0 + hl; samples past L (only in
       // the last block), past the last block, or in sample slots >= k are masked out
       if (a.ks < kMaxSamples || j0 + 2 >= a.Nb) {
         const int nv = valid_in_block(j0 + hl);
 #pragma unroll
         for (int i = 0; i < 16; ++i)
-          if (i >= nv) acc[i] = -INFINITY;
+          if (i >= nv) acc[sb][i] = -INFINITY;
       }
       float mraw = -INFINITY;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) mraw = fmaxf(mraw, acc[i]);
-      const float mij = mraw * a.scale;                  // block-row maximum, Alg. 1 step 12
-      rt_pend[sb] = mij;
-      // Alg. 1 steps 12-15: tile-local exponentials exp(scale * (s - max)) as one fused
-      // multiply-add and one exp2 each, then fold into the running pair
-      const float bias = (mraw == -INFINITY) ? 0.f : -mraw * c2;
-      float lij = 0.f;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) lij += fast_exp2(fmaf(acc[i], c2, bias));
-      if (__any(mij > Mt)) {
-        const float mnew = fmaxf(Mt, mij);
-        const float mnew_s = (mnew == -INFINITY) ? 0.f : mnew;
-        lt = (double)__expf(Mt - mnew_s) * lt + (double)__expf(mij - mnew_s) * (double)lij;
-        Mt = mnew;
-      } else {
-        // no row's maximum grew (the usual case once the sweep has passed the query's own
-        // neighbourhood): the general update with a factor of exactly 1 on the old sum
-        lt += (double)__expf(mij - ((Mt == -INFINITY) ? 0.f : Mt)) * (double)lij;
-      }
+      for (int i = 0; i < 16; ++i) mraw = fmaxf(mraw, acc[sb][i]);
+      rt_pend[sb] = mraw * a.scale;                      // block-row maximum, Alg. 1 step 12
+      mnew = fmaxf(mnew, mraw);
     }
+    // Alg. 1 steps 12-15 with the exponentials exp(scale * (s - max)) as one fused multiply-add
+    // and one exp2 each
+    const float b_new = -mnew * c2;                      // (+inf while no key has been seen)
+    const float bias = (mnew == -INFINITY) ? 0.f : b_new;
+    const float keep = fast_exp2(bias - br);             // the old sum was relative to 2^-br
+    br = b_new;
+    float sum[NT];
+#pragma unroll
+    for (int sb = 0; sb < NT; ++sb) {
+      sum[sb] = 0.f;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) sum[sb] += fast_exp2(fmaf(acc[sb][i], c2, bias));
+    }
+    lt = fma(lt, (double)keep, (double)(sum[0] + sum[1]));
+    Mr = mnew;
   };
 
   // The block-row maxima of a chunk are stored at the start of the NEXT chunk's turn, just before
@@ -269,6 +281,7 @@ __global__ __launch_bounds__(512, 4) void probe_kernel(ProbeArgs a) {   // (4 wa
   // merge the two parities of each query; the pair (maximum, denominator) of this wavefront's
   // share of the keys goes to the workspace (the kernel that follows merges the shares)
   {
+    const float Mt = Mr * a.scale;
     const float Mo = __shfl_xor(Mt, 32, 64);
     const double lo = __shfl_xor(lt, 32, 64);
     const float Mall = fmaxf(Mt, Mo);
