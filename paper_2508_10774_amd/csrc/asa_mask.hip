@@ -282,6 +282,8 @@ __global__ __launch_bounds__(512, 4) void probe_kernel(ProbeArgs a) {   // (4 wa
   // share of the keys goes to the workspace (the kernel that follows merges the shares)
   {
     const float Mt = Mr * a.scale;
+    // what the rounding of br dropped, put right here, once: lt relative to the row's maximum itself
+    if (Mr != -INFINITY) lt *= (double)fast_exp2(fmaf(-Mr, c2, -br));
     const float Mo = __shfl_xor(Mt, 32, 64);
     const double lo = __shfl_xor(lt, 32, 64);
     const float Mall = fmaxf(Mt, Mo);
