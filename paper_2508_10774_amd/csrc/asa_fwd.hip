@@ -471,8 +471,8 @@ __global__ __launch_bounds__(BLK * 4, (BLK == 64 && D == 64) ? 2 : 1) void fwd_p
   {
     const int32_t *g = a.col_idx + (int64_t)slab * a.Nb * a.Nb + t_begin;
     for (int t = tid; t < n_tiles + C::kTabPad; t += C::kThreads) {
-      const int tc = t < n_tiles ? t : n_tiles - 1;
-      if (tc < n_own_tiles) {
+      const int tc = t < n_tiles ? t : n_tiles - 1;      // (-1 where the list is empty: no entry to read)
+      if (tc >= 0 && tc < n_own_tiles) {
         const uint32_t j = dense ? (uint32_t)tc : (uint32_t)g[tc];
         tabK[t] = j * k_tile_bytes;
         tabV[t] = j * v_tile_bytes;

@@ -194,3 +194,22 @@ def test_fwd_is_deterministic():
     o1, l1 = util.run_fwd(p, *args, bufs)
     o2, l2 = util.run_fwd(p, *args, bufs)
     assert torch.equal(o1.view(torch.int16), o2.view(torch.int16)) and torch.equal(l1, l2)
+
+
+@pytest.mark.parametrize("block", [64, 128])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("tail", [1, 31, 32, 33, 64])
+def test_fwd_list_lengths_and_tails(block, d, tail, kernel_choice):
+    """Rows of 0, 1, 2, 3, ... blocks (the pipelined kernel takes four tiles of 32 keys at a time,
+    blocks of 64 keys are two of them) with a last block that ends inside its first tile, at the
+    end of it, inside the second one, or at a block's end."""
+    Nb = 6
+    L = (Nb - 1) * block + tail
+    print(f"case L={L} d={d} block={block} {kernel_choice}", flush=True)
+    p = binding.Params(B=1, H=2, L=L, d=d, block=block)
+    qb, kb, vb = _case(1, 2, L, d, block, seed=L + d)
+    mask = np.zeros((2, Nb, Nb), np.uint8)
+    for i in range(Nb):
+        mask[0, i, Nb - i:] = 1      # rows of 0 .. 5 blocks, every one of them with the ragged block
+        mask[1, i, :i + 1] = 1       # rows of 1 .. 6
+    _check_fwd(p, qb, kb, vb, mask)
