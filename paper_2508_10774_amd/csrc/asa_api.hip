@@ -327,8 +327,7 @@ int asa_attn_fwd(const asa_params *p, const void *q, const void *k, const void *
   if (!workspace || workspace_bytes < transposed_bytes(pb) + fwd_order_bytes(pb) || !aligned16(workspace))
     return ASA_ERR_WORKSPACE;
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
-  hipError_t e = launch_transpose(pb, v, pb.v, workspace, st);
-  if (e != hipSuccess) return finish(e);
+  hipError_t e;
   // rows of uneven length (the rule's own m per row): longest first inside each XCD's share
   int32_t *order = nullptr;
   if (row_ptr && length_order_fits(pb.n_slabs * pb.Nb)) {
@@ -336,8 +335,7 @@ int asa_attn_fwd(const asa_params *p, const void *q, const void *k, const void *
     e = launch_length_order(row_ptr, pb.Nb, pb.n_slabs * pb.Nb, order, st);
     if (e != hipSuccess) return finish(e);
   }
-  timing_begin(st);
-  e = launch_fwd(pb, q, k, workspace, row_ptr, col_idx, o, o_lo, lse, order, st);
+  e = launch_fwd(pb, q, k, v, workspace, row_ptr, col_idx, o, o_lo, lse, order, st);
   timing_end(st);
   return finish(e);
 }
@@ -353,20 +351,6 @@ static int global_dims(const Problem &pb, int n, int *Lg, int *Nbg) {
 static size_t pooled_tile_bytes(const Problem &pb, int Nbg) {
   return round256((size_t)pb.n_slabs * Nbg * pb.block * pb.d * sizeof(uint16_t));
 }
-// the pooled tensors seen as a problem of their own (contiguous [B, H, Nbg * block, d])
-static Problem pooled_problem(const Problem &pb, int Lg, int Nbg) {
-  Problem g = pb;
-  g.L = Lg;
-  g.Nb = Nbg;
-  g.Lpad = Nbg * pb.block;
-  TensorView tv;
-  tv.sL = pb.d;
-  tv.sH = (int64_t)g.Lpad * pb.d;
-  tv.sB = tv.sH * pb.H;
-  g.q = g.k = g.v = g.o = tv;
-  return g;
-}
-
 size_t asa_global_token_count(const asa_params *p, int n) {
   Problem pb;
   int Lg, Nbg;
@@ -417,11 +401,7 @@ int asa_attn_fwd_g(const asa_params *p, int n, const void *q, const void *k, con
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
   char *ws = reinterpret_cast<char *>(workspace);
   void *vgt = ws + transposed_bytes(pb);
-  hipError_t e = launch_transpose(pb, v, pb.v, ws, st);
-  if (e != hipSuccess) return finish(e);
-  const Problem g = pooled_problem(pb, Lg, Nbg);
-  e = launch_transpose(g, vg, g.v, vgt, st);
-  if (e != hipSuccess) return finish(e);
+  hipError_t e = hipSuccess;
   GlobalTokens gt;
   gt.n = n; gt.Lg = Lg; gt.Nbg = Nbg; gt.kg = kg; gt.vg = vg; gt.vgt = vgt;
   int32_t *order = nullptr;
@@ -430,8 +410,7 @@ int asa_attn_fwd_g(const asa_params *p, int n, const void *q, const void *k, con
     e = launch_length_order(row_ptr, pb.Nb, pb.n_slabs * pb.Nb, order, st);
     if (e != hipSuccess) return finish(e);
   }
-  timing_begin(st);
-  e = launch_fwd(pb, q, k, ws, row_ptr, col_idx, o, o_lo, lse, order, st, &gt);
+  e = launch_fwd(pb, q, k, v, ws, row_ptr, col_idx, o, o_lo, lse, order, st, &gt);
   timing_end(st);
   return finish(e);
 }

@@ -346,9 +346,10 @@ __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dq_k
     constexpr bool kNewBlock = (U + C::kStages - 1) % C::kSub == 0;   // of the tile copied here
     constexpr bool kNextNewBlock = (U + C::kStages) % C::kSub == 0;
     if (key_t + C::kST > key_end) {                  // (uniform, rare) keys past the end
+      const int left = key_end - key_t - 8 * hl;     // (compared with constants: nothing to keep in registers)
 #pragma unroll
       for (int i = 0; i < 16; ++i)
-        if (key_t + 16 * (i >> 3) + 8 * hl + (i & 7) >= key_end) sc[i] = -INFINITY;
+        if (16 * (i >> 3) + (i & 7) >= left) sc[i] = -INFINITY;
     }
     uint32_t db[8];
     // (accumulator register i of lane half hl is key 16 (i / 8) + 8 hl + i % 8)

@@ -59,8 +59,6 @@ hipError_t set_dynamic_lds_once(const void *fn, int bytes);
 int forced_fwd_kernel();
 
 // launchers (each returns a hipError_t from the launch)
-hipError_t launch_transpose(const Problem &pb, const void *src, const TensorView &tv, void *dst,
-                            hipStream_t st);
 // Global tokens of ASA_G as the attention kernels see them (all device pointers).
 struct GlobalTokens {
   int n;              // pooling window
@@ -71,7 +69,9 @@ struct GlobalTokens {
 };
 hipError_t launch_pool(const Problem &pb, int n, const void *k, const void *v, void *kg, void *vg,
                        hipStream_t st);
-hipError_t launch_fwd(const Problem &pb, const void *q, const void *k, const void *vt,
+// vt, gt->vgt: room for the transposed copies of V and of the pooled values (written where the kernel
+// that runs wants them)
+hipError_t launch_fwd(const Problem &pb, const void *q, const void *k, const void *v, const void *vt,
                       const int32_t *row_ptr, const int32_t *col_idx, void *o, void *o_lo,
                       float *lse, const int32_t *order, hipStream_t st, const GlobalTokens *gt = nullptr);
 hipError_t launch_csr(const Problem &pb, const uint8_t *mask, int32_t *row_ptr, int32_t *col_idx,

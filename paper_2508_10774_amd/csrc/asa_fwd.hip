@@ -16,6 +16,7 @@
 #include <stdlib.h>
 
 #include <type_traits>
+#include <utility>
 
 #include "asa_common.hpp"
 #include "asa_tiles.hpp"
@@ -30,10 +31,13 @@ namespace asa {
 // ---------------------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(256) void transpose_kernel(const void *src, TensorView tv, int H,
-                                                        int L, int Lpad, int block, bf16 *dst) {
+                                                        int L, int Lpad, int block, bf16 *dst,
+                                                        const int32_t *row_ptr, int Nb, int min_tiles) {
   constexpr int TL = 64;  // positions per workgroup
   __shared__ uint16_t tile[TL][D + 2];
   const int slab = blockIdx.y;
+  // (with lists: slabs of fewer tiles go to a kernel that reads the rows of V themselves)
+  if (row_ptr && row_ptr[slab * (Nb + 1) + Nb] < min_tiles) return;
   const int l0 = blockIdx.x * TL;
   const uint16_t *s = reinterpret_cast<const uint16_t *>(slab_ptr(src, tv, slab, H));
   const int tid = threadIdx.x;
@@ -60,15 +64,16 @@ __global__ __launch_bounds__(256) void transpose_kernel(const void *src, TensorV
   }
 }
 
-hipError_t launch_transpose(const Problem &pb, const void *src, const TensorView &tv, void *dst,
-                            hipStream_t st) {
-  dim3 grid(pb.Lpad / 64, pb.n_slabs);
-  if (pb.d == 128)
-    hipLaunchKernelGGL(transpose_kernel<128>, grid, dim3(256), 0, st, src, tv, pb.H, pb.L, pb.Lpad,
-                       pb.block, reinterpret_cast<bf16 *>(dst));
+static hipError_t launch_transpose(const void *src, const TensorView &tv, int H, int L, int Lpad, int block,
+                                   int d, int n_slabs, const bf16 *dst, hipStream_t st,
+                                   const int32_t *row_ptr = nullptr, int Nb = 0, int min_tiles = 0) {
+  dim3 grid(Lpad / 64, n_slabs);
+  if (d == 128)
+    hipLaunchKernelGGL(transpose_kernel<128>, grid, dim3(256), 0, st, src, tv, H, L, Lpad, block,
+                       const_cast<bf16 *>(dst), row_ptr, Nb, min_tiles);
   else
-    hipLaunchKernelGGL(transpose_kernel<64>, grid, dim3(256), 0, st, src, tv, pb.H, pb.L, pb.Lpad,
-                       pb.block, reinterpret_cast<bf16 *>(dst));
+    hipLaunchKernelGGL(transpose_kernel<64>, grid, dim3(256), 0, st, src, tv, H, L, Lpad, block,
+                       const_cast<bf16 *>(dst), row_ptr, Nb, min_tiles);
   return hipGetLastError();
 }
 
@@ -157,17 +162,18 @@ hipError_t launch_pool(const Problem &pb, int n, const void *k, const void *v, v
 // forward kernel
 // ---------------------------------------------------------------------------------------
 struct FwdArgs {
-  const void *q, *k;
+  const void *q, *k, *v;
   const bf16 *vt;  // [slab][Nb][d][block]: V, one transposed tile per key block
   const int32_t *row_ptr, *col_idx;
   void *o, *o_lo;
   float *lse;
-  TensorView tq, tk, to;
+  TensorView tq, tk, tv, to;
   int H, L, Lpad, Nb, n_slabs;
   float scale_log2e;  // scale * log2(e)
   // global tokens (ASA_G); Nbg = 0 switches them off
   const void *kg;     // [slab][Nbg * block][d] bf16 pooled keys, zero rows past Lg
   const bf16 *vgt;    // [slab][Nbg][d][block]: pooled values, transposed tiles
+  const void *vg;     // [slab][Nbg * block][d] bf16 pooled values
   int Lg, Nbg;        // pooled tokens per slab, key blocks they fill
   float bias_log2;    // log2(n): the additive ln(n) of the pooled scores, in the exp2 domain
   // Choice between the two kernels per (batch, head) slab, made on the device from the slab's
@@ -209,7 +215,9 @@ struct FwdCfg {
 // that opens step s; with one, the copies of a step are waited for right away and the other
 // workgroups on the CU compute meanwhile.  It serves the tile shapes other than block 128 / d 128 and tensors that the
 // ping-pong kernel below does not take (slabs of 4 GiB and more).
-template <int BLK, int D>
+// VT: the operand of the second product comes from the transposed copy of V (one 16-byte read)
+// instead of the rows of V (two transposing reads).
+template <int BLK, int D, bool VT>
 // (block 64 / d 64 fits 128 registers: four wavefronts per SIMD, 2 % faster than three)
 __global__ __launch_bounds__(BLK * 2, (BLK == 64 && D == 64) ? 4 : 2) void fwd_kernel(FwdArgs a) {
   using C = FwdCfg<BLK, D>;
@@ -229,6 +237,7 @@ __global__ __launch_bounds__(BLK * 2, (BLK == 64 && D == 64) ? 4 : 2) void fwd_k
 
   const bf16 *qs = slab_ptr(a.q, a.tq, slab, a.H);
   const bf16 *ks = slab_ptr(a.k, a.tk, slab, a.H);
+  const bf16 *vs = slab_ptr(a.v, a.tv, slab, a.H);
   const bf16 *vts = a.vt + (int64_t)slab * D * a.Lpad;
   // no index lists: dense attention, every key block in order
   const bool dense = a.row_ptr == nullptr;
@@ -254,11 +263,18 @@ __global__ __launch_bounds__(BLK * 2, (BLK == 64 && D == 64) ? 4 : 2) void fwd_k
   const float c = a.scale_log2e;
 
   RowTileCopy<C::kKT, D, C::kWaves> copy_k;
-  ColTileCopy<BLK, D, C::kWaves> copy_v;
+  TrTileCopy<C::kKT, D, C::kWaves> copy_v;
+  ColTileCopy<BLK, D, C::kWaves> copy_vt;
   copy_k.init(wave, lane, a.tk.sL);
-  copy_v.init(wave, lane);
+  if (VT) copy_vt.init(wave, lane);
+  else copy_v.init(wave, lane, a.tv.sL, a.L);
+  const int last_row0 = copy_v.last_row0(a.L);
   const int kr = kappa(n), cr = rho(n);
   const int kx = (hl ^ k_swz<D>(kr)) * 8, cx = (hl ^ v_swz(cr)) * 8;
+  // transposed A fragments "32 channels x 16 keys" of O^T += V^T P^T, gathered from the rows of V by
+  // the transposing LDS read (see asa_bwd.hip)
+  const int tr_i = lane & 15, tr_w = tr_i & 3, tr_j = tr_i >> 2, tr_b = (lane >> 4) & 1;
+  const uint32_t tr_lane = tr_piece<D>(8 * hl + tr_j, 16 * (tr_w & 1) + 8 * tr_b + 4 * (tr_w >> 1));
   const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
                          0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
@@ -276,8 +292,13 @@ __global__ __launch_bounds__(BLK * 2, (BLK == 64 && D == 64) ? 4 : 2) void fwd_k
     const int lim = a.L - 1 - row0;
     if (lim >= C::kKT - 1) copy_k.issue_at(st, kbase);
     else copy_k.issue_at_ragged(st, kbase, lim);
-    copy_v.issue_at(st + C::kKElems * 2,
-                    reinterpret_cast<const char *>(vts + (int64_t)j * D * BLK + sub * C::kKT));
+    if (VT) {
+      copy_vt.issue_at(st + C::kKElems * 2, reinterpret_cast<const char *>(vts + (int64_t)j * D * BLK + sub * C::kKT));
+      return;
+    }
+    const char *vbase = reinterpret_cast<const char *>(vs) + (int64_t)min(row0, last_row0) * a.tv.sL * 2;
+#pragma unroll
+    for (int i = 0; i < copy_v.kInstr; ++i) copy_v.issue_one(i, st + C::kKElems * 2, vbase, row0 >= last_row0);
   };
   if (C::kStages == 2) {
     __syncthreads();                      // cols[] is complete
@@ -292,8 +313,15 @@ __global__ __launch_bounds__(BLK * 2, (BLK == 64 && D == 64) ? 4 : 2) void fwd_k
     __syncthreads();                      // everyone's have; everyone is done with the other stage
     if (C::kStages == 2 && step + 1 < n_steps) fetch(step + 1, (step + 1) & 1);
     const bf16 *Ks = lds + (C::kStages == 2 ? (step & 1) : 0) * kStageElems;
-    const bf16 *Vs = Ks + C::kKElems;
+    const uint32_t v_at = lds_addr + ((C::kStages == 2 ? (step & 1) : 0) * kStageElems + C::kKElems) * 2;
     const int key0 = cols[step / C::kSub] * BLK + (step % C::kSub) * C::kKT;
+    if (!VT && key0 + C::kKT > a.L) {
+      // (uniform, once at most) keys past the end have P = 0: their V rows must be finite
+      const int first = max(0, a.L - key0);
+      for (int x = first * (D / 8) + tid; x < C::kKT * (D / 8); x += C::kThreads)
+        reinterpret_cast<u32x4 *>(const_cast<bf16 *>(Ks) + C::kKElems)[x] = u32x4{0, 0, 0, 0};
+      __syncthreads();
+    }
     f32x16 sacc[C::kKT / 32];
 #pragma unroll
     for (int mt = 0; mt < C::kKT / 32; ++mt) {
@@ -348,8 +376,16 @@ __global__ __launch_bounds__(BLK * 2, (BLK == 64 && D == 64) ? 4 : 2) void fwd_k
         bf16x8 pf = *reinterpret_cast<bf16x8 *>(&praw);
 #pragma unroll
         for (int dm = 0; dm < D / 32; ++dm) {
-          bf16x8 va = *reinterpret_cast<const bf16x8 *>(Vs + (dm * 32 + cr) * C::kKT +
-                                                        ((16 * (2 * mt + tt)) ^ cx));
+          const uint32_t x0 = (uint32_t)(((4 * dm) ^ t_swz<D>(0)) * 16), x1 = (uint32_t)(((4 * dm) ^ t_swz<D>(4)) * 16);
+          const uint32_t at = v_at + (uint32_t)((32 * mt + 16 * tt) * D * 2);
+          bf16x8 va;
+          if (VT) {
+            va = *reinterpret_cast<const bf16x8 *>(Ks + C::kKElems + (dm * 32 + cr) * C::kKT + ((16 * (2 * mt + tt)) ^ cx));
+          } else {
+            const bf16x4 lo = lds_read_tr16((const lds_char *)(uintptr_t)((tr_lane ^ x0) + at));
+            const bf16x4 hi = lds_read_tr16((const lds_char *)(uintptr_t)((tr_lane ^ x1) + at + 4 * D * 2));
+            va = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+          }
           oacc[dm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pf, oacc[dm], 0, 0, 0);
         }
       }
@@ -906,40 +942,464 @@ __global__ __launch_bounds__(BLK * 4, (BLK == 64 && D == 64) ? 2 : 1) void fwd_p
   }
 }
 
+// ---------------------------------------------------------------------------------------
+// Pipelined forward: the software pipeline of the backward kernels (see asa_bwd.hip).  One workgroup per
+// query block, one wavefront per 32 query rows, tiles of 32 keys.  In iteration t a wavefront
+// computes S^T of tile t + 1 and adds P V of tile t - 1, and between those MFMAs turns S^T of tile t
+// into P; O is rescaled at the end of an iteration whose rows found a larger logit (the maximum is
+// never allowed to lag behind, as in the other kernels).  The V operand is gathered from V's rows by the
+// transposing LDS read: no transposed copy of V.  K and V have four LDS stages each.
+//
+// Bound: at large sizes the direct-to-LDS copies (every wavefront of a workgroup requests its share
+// at the same point, ~75 cycles each, twice as many per product as in the backward: without them
+// the block 128 / d 128 loop runs 24 % faster) and, at d = 64, vector issue.  Its place is where a
+// wavefront's own speed counts: few workgroups, or shapes whose lock-step workgroup leaves the SIMDs
+// idle (launch_fwd_t has the figures).
+// ---------------------------------------------------------------------------------------
+template <int BLK, int D>
+struct PipeCfg {
+  static constexpr int kWaves = BLK / 32;
+  static constexpr int kThreads = kWaves * 64;
+  static constexpr int kST = 32;                       // keys per tile
+  static constexpr int kSub = BLK / kST;
+  static constexpr int kStages = 4;
+  static constexpr int kTile = kST * D * 2;            // bytes of one row tile
+  static constexpr int kLds = 2 * kStages * kTile;     // K stages, then V stages
+  static constexpr int kWavesPerSimd = (BLK == 64 && D == 128) ? 1 : 2;
+};
+
+// GT: with the pooled (global) tokens of ASA_G appended to every query block's list
+template <int BLK, int D, bool GT>
+__global__ __launch_bounds__(BLK * 2, (PipeCfg<BLK, D>::kWavesPerSimd)) void fwd_pipe_kernel(FwdArgs a) {
+  using C = PipeCfg<BLK, D>;
+  extern __shared__ __align__(1024) unsigned char smem[];
+  __shared__ int cols[kMaxNb];
+  constexpr int kStage = C::kTile, kVBase = C::kStages * C::kTile;
+  constexpr int kPooled = 1 << 30;             // flag of an entry of cols[]: a block of pooled tokens
+
+  const int slot = xcd_contiguous_work(blockIdx.x, a.n_slabs * a.Nb);
+  if (slot < 0) return;
+  const int work = a.order ? a.order[slot] : slot;
+  const int slab = work / a.Nb;
+  const int qb = work - slab * a.Nb;
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63, hl = lane >> 5, n = lane & 31;
+
+  const bf16 *qs = slab_ptr(a.q, a.tq, slab, a.H);
+  const bf16 *ks = slab_ptr(a.k, a.tk, slab, a.H);
+  const bf16 *vs = slab_ptr(a.v, a.tv, slab, a.H);
+  const bool dense = a.row_ptr == nullptr;   // no index lists: dense attention, every key block in order
+  const int t_begin = dense ? 0 : a.row_ptr[slab * (a.Nb + 1) + qb];
+  const int n_own_blocks = dense ? a.Nb : a.row_ptr[slab * (a.Nb + 1) + qb + 1] - t_begin;
+  const int n_blocks = n_own_blocks + (GT ? a.Nbg : 0);   // pooled blocks come after the row's own list
+  {
+    const int32_t *g = a.col_idx + (int64_t)slab * a.Nb * a.Nb + t_begin;
+    for (int t = tid; t < n_blocks; t += C::kThreads)
+      cols[t] = t >= n_own_blocks ? (t - n_own_blocks) | kPooled : (dense ? t : g[t]);
+  }
+  const bf16 *kgs = reinterpret_cast<const bf16 *>(a.kg) + (int64_t)slab * a.Nbg * BLK * D;
+  const bf16 *vgs = reinterpret_cast<const bf16 *>(a.vg) + (int64_t)slab * a.Nbg * BLK * D;
+
+  const int qrow = qb * BLK + wave * 32 + n;
+  const bool qvalid = qrow < a.L;
+  const int qrow_c = qvalid ? qrow : a.L - 1;
+  bf16x8 qreg[D / 16];
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s)
+    qreg[s] = *reinterpret_cast<const bf16x8 *>(qs + (int64_t)qrow_c * a.tq.sL + 16 * s + 8 * hl);
+  f32x16 oacc[D / 32];
+#pragma unroll
+  for (int dm = 0; dm < D / 32; ++dm)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) oacc[dm][i] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;
+  const float c = a.scale_log2e;
+
+  using Copy = TrTileCopy<C::kST, D, C::kWaves>;
+  Copy copy_k, copy_v, copy_p;
+  copy_k.init(wave, lane, a.tk.sL, a.L);
+  copy_v.init(wave, lane, a.tv.sL, a.L);
+  constexpr int kI = Copy::kInstr;
+  const int last_row0 = Copy::last_row0(a.L);
+  if (GT) copy_p.init(wave, lane, D, C::kST);   // pooled rows: D elements apart, never ragged
+
+  const uint32_t smem_addr = ASA_LDS_ADDR_OF(smem);
+  // A fragments of S^T = K Q^T: row kappa(n) of the 32 keys (see asa_bwd.hip)
+  const int kr = kappa(n);
+  uint32_t row_at[D / 16];
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s)
+    row_at[s] = (smem_addr + (uint32_t)(kr * D * 2 + (hl ^ t_swz<D>(kr)) * 16)) ^ (uint32_t)(32 * s);
+  // transposed A fragments "32 channels x 16 keys" of O^T += V^T P^T
+  const int tr_i = lane & 15, tr_w = tr_i & 3, tr_j = tr_i >> 2, tr_b = (lane >> 4) & 1;
+  const uint32_t tr_lane = smem_addr + kVBase + tr_piece<D>(8 * hl + tr_j, 16 * (tr_w & 1) + 8 * tr_b + 4 * (tr_w >> 1));
+  uint32_t tr_at[2 * (D / 32)];
+#pragma unroll
+  for (int dm = 0; dm < D / 32; ++dm) {
+    tr_at[2 * dm] = tr_lane ^ (uint32_t)(((4 * dm) ^ t_swz<D>(0)) * 16);
+    tr_at[2 * dm + 1] = tr_lane ^ (uint32_t)(((4 * dm) ^ t_swz<D>(4)) * 16);
+  }
+  const int n_it = n_blocks * C::kSub;
+
+  // The tile whose K rows are copied next, and the tile before it, whose V rows are
+  int entry_v = 0, entry_at = 0, key_c = 0;
+  bool last_k = false, last_v = false, pooled_k = false, pooled_v = false;
+  const char *base_k = nullptr, *base_v = nullptr, *base_v_next = nullptr;
+  auto fetch_entry = [&]() __attribute__((always_inline)) {
+    entry_v = cols[entry_at < n_blocks ? entry_at : n_blocks - 1];
+    ++entry_at;
+  };
+  auto next_tile = [&](auto part_tag, auto new_block_tag) __attribute__((always_inline)) {
+    constexpr int part = decltype(part_tag)::value;
+    constexpr bool new_block = decltype(new_block_tag)::value;
+    if constexpr (part == 0) {
+      last_v = last_k;
+      pooled_v = pooled_k;
+      base_v = base_v_next;
+      if constexpr (new_block) {
+        const int e = __builtin_amdgcn_readfirstlane(entry_v);
+        if (GT) pooled_k = (e & kPooled) != 0;
+        key_c = (GT ? e & (kPooled - 1) : e) * BLK;
+      } else {
+        key_c += C::kST;
+      }
+      last_k = key_c >= last_row0;
+    } else if constexpr (part == 1) {
+      base_k = reinterpret_cast<const char *>(ks) + (int64_t)min(key_c, last_row0) * (a.tk.sL * 2);
+      if (GT) base_k = pooled_k ? reinterpret_cast<const char *>(kgs) + (int64_t)key_c * (D * 2) : base_k;
+    } else {
+      base_v_next = reinterpret_cast<const char *>(vs) + (int64_t)min(key_c, last_row0) * (a.tv.sL * 2);
+      if (GT) base_v_next = pooled_k ? reinterpret_cast<const char *>(vgs) + (int64_t)key_c * (D * 2) : base_v_next;
+    }
+  };
+  auto copy_k_one = [&](int i, uint32_t st) __attribute__((always_inline)) {
+    if (GT) lds_dma16_sv(base_k, pooled_k ? copy_p.off[i] : (last_k ? copy_k.off_last[i] : copy_k.off[i]), st + copy_k.lds0 + i * 1024);
+    else copy_k.issue_one(i, st, base_k, last_k);
+  };
+  auto copy_v_one = [&](int i, uint32_t st) __attribute__((always_inline)) {
+    if (GT) lds_dma16_sv(base_v, pooled_v ? copy_p.off[i] : (last_v ? copy_v.off_last[i] : copy_v.off[i]), st + kVBase + copy_v.lds0 + i * 1024);
+    else copy_v.issue_one(i, st + kVBase, base_v, last_v);
+  };
+  // The block of the tile in work, for the masks of the last block and the bias of pooled keys
+  int cur_v = 0, cur_at = 0, key_t = 0, key_end = 0;
+  float bias = 0.f;
+  auto fetch_current = [&]() __attribute__((always_inline)) {
+    cur_v = cols[cur_at < n_blocks ? cur_at : n_blocks - 1];
+    ++cur_at;
+  };
+  auto next_current = [&](auto new_block_tag) __attribute__((always_inline)) {
+    if constexpr (decltype(new_block_tag)::value) {
+      const int e = __builtin_amdgcn_readfirstlane(cur_v);
+      key_t = (GT ? e & (kPooled - 1) : e) * BLK;
+      const bool pooled = GT && (e & kPooled) != 0;
+      key_end = pooled ? a.Lg : a.L;             // keys at or past it do not exist
+      if (GT) bias = pooled ? a.bias_log2 : 0.f;
+    } else {
+      key_t += C::kST;
+    }
+  };
+
+  constexpr int kNS = D / 16, kNV = 2 * (D / 32), kN = kNS + kNV;
+  constexpr int kRing = 8, kDepth = 6;
+  static_assert(kN % kRing == 0, "the ring continues across iterations");
+  constexpr int kBar = kNS < kN - kDepth ? kNS : kN - kDepth;   // the barrier comes before this product
+  bf16x8 ring[kRing];
+  auto read_row = [&](auto e_tag, auto stage_tag) __attribute__((always_inline)) {
+    constexpr int e = decltype(e_tag)::value;
+    ring[e % kRing] = lds_read<bf16x8>(row_at[e] + (uint32_t)(decltype(stage_tag)::value * kStage));
+  };
+  auto read_tr = [&](auto f_tag, auto stage_tag) __attribute__((always_inline)) {
+    constexpr int f = decltype(f_tag)::value, dm = f % (D / 32), tt = f / (D / 32);
+    constexpr int at = decltype(stage_tag)::value * kStage + 16 * tt * D * 2;
+    const bf16x4 lo = lds_read_tr16((const lds_char *)(uintptr_t)(tr_at[2 * dm] + (uint32_t)at));
+    const bf16x4 hi = lds_read_tr16((const lds_char *)(uintptr_t)(tr_at[2 * dm + 1] + (uint32_t)(at + 4 * D * 2)));
+    ring[(kNS + f) % kRing] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
+  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
+                         0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  f32x16 s0, s1;
+  uint32_t pb[8];                        // bf16 P of the tile before the one in work
+#pragma unroll
+  for (int i = 0; i < 8; ++i) pb[i] = 0;
+  auto pv = [&](auto f_tag) __attribute__((always_inline)) {
+    constexpr int f = decltype(f_tag)::value, dm = f % (D / 32), tt = f / (D / 32);
+    const u32x4 raw = {pb[4 * tt], pb[4 * tt + 1], pb[4 * tt + 2], pb[4 * tt + 3]};
+    oacc[dm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[(kNS + f) % kRing], __builtin_bit_cast(bf16x8, raw), oacc[dm], 0, 0, 0);
+  };
+
+  auto body = [&](auto u_tag, f32x16 &sc, f32x16 &sn) __attribute__((always_inline)) {
+    constexpr int U = decltype(u_tag)::value;        // tile index mod 4
+    using StK1 = std::integral_constant<int, (U + 1) & 3>;
+    using StK2 = std::integral_constant<int, (U + 2) & 3>;
+    using StVp = std::integral_constant<int, (U + 3) & 3>;   // V rows of tile t - 1
+    constexpr bool kNewBlock = (U + C::kStages - 1) % C::kSub == 0;   // of the K tile copied here
+    constexpr bool kNextNewBlock = (U + C::kStages) % C::kSub == 0;
+    if (key_t + C::kST > key_end) {                  // (uniform, rare) keys past the end
+      const int left = key_end - key_t - 8 * hl;     // (compared with constants: nothing to keep in registers)
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (16 * (i >> 3) + (i & 7) >= left) sc[i] = -INFINITY;
+      // their V rows (in LDS since the last barrier, read after the next one) must be finite
+      u32x4 *z = reinterpret_cast<u32x4 *>(smem + kVBase + U * kStage);
+      for (int x = max(0, key_end - key_t) * (D / 8) + tid; x < kStage / 16; x += C::kThreads) z[x] = u32x4{0, 0, 0, 0};
+      __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+    }
+    uint32_t pn[8];
+    float mx = -INFINITY, m_use = 0.f, alpha = 1.f, sum0 = 0.f, sum1 = 0.f;
+    bool grew = false;
+    constexpr int kFirst = kN == 16 ? 5 : 2;         // slot of the first exponentials
+    __builtin_amdgcn_sched_barrier(0);
+    [&]<int... X>(std::integer_sequence<int, X...>) __attribute__((always_inline)) {
+      ([&]() __attribute__((always_inline)) {
+        constexpr int x = X;
+        if constexpr (x == kBar) {
+          // K of tile t + 2 and V of tile t have landed (everyone's copies)
+          __builtin_amdgcn_s_waitcnt(0x0F70);
+          asm volatile("s_barrier" ::: "memory");
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (x + kDepth < kNS) read_row(std::integral_constant<int, x + kDepth>{}, StK1{});
+        else if constexpr (x + kDepth < kN) read_tr(std::integral_constant<int, x + kDepth - kNS>{}, StVp{});
+        else if constexpr (x + kDepth - kN < kNS) read_row(std::integral_constant<int, x + kDepth - kN>{}, StK2{});
+        else read_tr(std::integral_constant<int, x + kDepth - kN - kNS>{}, std::integral_constant<int, U>{});
+        if constexpr (x < kNS)
+          sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[x % kRing], qreg[x], x == 0 ? zero16 : sn, 0, 0, 0);
+        else
+          pv(std::integral_constant<int, x - kNS>{});
+        // row maximum of tile t
+        if constexpr (x < kFirst - 1) {
+          constexpr int nm = kFirst >= 5 ? kFirst - 2 : 1;     // slots that take part
+          constexpr int i0 = x < nm ? x * 16 / nm : 16, i1 = x < nm ? (x + 1) * 16 / nm : 16;
+#pragma unroll
+          for (int i = i0; i < i1; ++i) mx = fmaxf(mx, sc[i]);
+        }
+        if constexpr (x == (kFirst >= 5 ? kFirst - 2 : 1)) mx = max_of_halves(mx) * c + bias;
+        if constexpr (x == kFirst - 1) {
+          grew = mx > m_run;
+          const float m_new = fmaxf(m_run, mx);
+          const float m_fin = (m_new == -INFINITY) ? 0.f : m_new;
+          alpha = fast_exp2(m_run - m_fin);
+          m_use = m_fin - bias;
+          m_run = m_new;
+        }
+        if constexpr (x >= kFirst) {
+          constexpr int i0 = (x - kFirst) * 16 / (kN - kFirst), i1 = (x - kFirst + 1) * 16 / (kN - kFirst);
+#pragma unroll
+          for (int i = i0; i < i1; ++i) {
+            sc[i] = fast_exp2(fmaf(sc[i], c, -m_use));
+            if (i & 1) {
+              sum1 += sc[i];
+              pn[i >> 1] = pack_bf16x2(sc[i - 1], sc[i]);
+            } else {
+              sum0 += sc[i];
+            }
+          }
+        }
+        if constexpr (x == 1) next_tile(std::integral_constant<int, 0>{}, std::bool_constant<kNewBlock>{});
+        if constexpr (x == 2) next_tile(std::integral_constant<int, 1>{}, std::bool_constant<kNewBlock>{});
+        if constexpr (x == 3) next_tile(std::integral_constant<int, 2>{}, std::bool_constant<kNewBlock>{});
+        if constexpr (x == 2 && (U + 1) % C::kSub == 0) fetch_current();
+        if constexpr (x == kN - 2 && kNextNewBlock) fetch_entry();
+        // copies of K of tile t + 3 and V of tile t + 2, spread over the slots behind the barrier
+        // (their stages were last read in iteration t - 1)
+        if constexpr (x >= kBar) {
+          constexpr int i0 = (x - kBar) * 2 * kI / (kN - kBar), i1 = (x - kBar + 1) * 2 * kI / (kN - kBar);
+#pragma unroll
+          for (int i = i0; i < i1; ++i) {
+            if (i < kI) copy_k_one(i, smem_addr + ((U + 3) & 3) * kStage);
+            else copy_v_one(i - kI, smem_addr + ((U + 2) & 3) * kStage);
+          }
+        }
+        if constexpr (x == kN - 1) next_current(std::bool_constant<(U + 1) % C::kSub == 0>{});
+        __builtin_amdgcn_sched_barrier(0);
+      }(), ...);
+    }(std::make_integer_sequence<int, kN>{});
+    l_run = fmaf(l_run, alpha, sum0 + sum1);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) pb[i] = pn[i];
+    if (__any(grew)) {
+#pragma unroll
+      for (int dm = 0; dm < D / 32; ++dm)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) oacc[dm][i] *= alpha;
+    }
+  };
+
+  if (n_it > 0) {
+    const bool odd = C::kSub == 2 && (n_blocks & 1);
+    const uint32_t first_stage = odd ? 2u : 0u, first_off = first_stage * kStage;
+    {
+      // the products of tile -1 have P = 0: their V operand only has to be finite
+      u32x4 *z = reinterpret_cast<u32x4 *>(smem + kVBase + ((first_stage + 3) & 3) * kStage);
+      for (int x = tid; x < kStage / 16; x += C::kThreads) z[x] = u32x4{0, 0, 0, 0};
+    }
+    __syncthreads();   // cols[] is written
+    // K of tiles 0, 1, 2 and V of tiles 0, 1
+    for (int t = 0; t < 3; ++t) {
+      if (t % C::kSub == 0) {
+        fetch_entry();
+        next_tile(std::integral_constant<int, 0>{}, std::true_type{});
+      } else {
+        next_tile(std::integral_constant<int, 0>{}, std::false_type{});
+      }
+      next_tile(std::integral_constant<int, 1>{}, std::false_type{});
+      next_tile(std::integral_constant<int, 2>{}, std::false_type{});
+#pragma unroll
+      for (int i = 0; i < kI; ++i) copy_k_one(i, smem_addr + ((t + first_stage) & 3u) * kStage);
+      if (t > 0) {
+#pragma unroll
+        for (int i = 0; i < kI; ++i) copy_v_one(i, smem_addr + ((t - 1 + first_stage) & 3u) * kStage);
+      }
+    }
+    if (3 % C::kSub == 0) fetch_entry();
+    fetch_current();
+    next_current(std::true_type{});
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * kI));   // K of tiles 0 and 1
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) row_at[s] += first_off;
+    s0 = zero16;
+    [&]<int... E>(std::integer_sequence<int, E...>) __attribute__((always_inline)) {
+      ([&]() __attribute__((always_inline)) {
+        read_row(std::integral_constant<int, E>{}, std::integral_constant<int, 0>{});
+        s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[E % kRing], qreg[E], s0, 0, 0, 0);
+      }(), ...);
+    }(std::make_integer_sequence<int, kNS>{});
+    // first operands of iteration 0 (all of them where it has fewer rows than the ring is deep)
+    [&]<int... E>(std::integer_sequence<int, E...>) __attribute__((always_inline)) {
+      (read_row(std::integral_constant<int, E>{}, std::integral_constant<int, 1>{}), ...);
+    }(std::make_integer_sequence<int, (kNS < kDepth ? kNS : kDepth)>{});
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) row_at[s] -= first_off;
+    if constexpr (kNS < kDepth) {
+#pragma unroll
+      for (int x = 0; x < 2 * (D / 32); ++x) tr_at[x] -= first_off;      // stage 3, or 1
+      [&]<int... F>(std::integer_sequence<int, F...>) __attribute__((always_inline)) {
+        (read_tr(std::integral_constant<int, F>{}, std::integral_constant<int, 3>{}), ...);
+      }(std::make_integer_sequence<int, kDepth - kNS>{});
+#pragma unroll
+      for (int x = 0; x < 2 * (D / 32); ++x) tr_at[x] += first_off;
+    }
+    if (odd) {
+      body(std::integral_constant<int, 2>{}, s0, s1);
+      body(std::integral_constant<int, 3>{}, s1, s0);
+    }
+    for (int t = odd ? 2 : 0; t < n_it; t += 4) {
+      body(std::integral_constant<int, 0>{}, s0, s1);
+      body(std::integral_constant<int, 1>{}, s1, s0);
+      body(std::integral_constant<int, 2>{}, s0, s1);
+      body(std::integral_constant<int, 3>{}, s1, s0);
+    }
+    // the last tile's P V (stage 3: the loop ends on a multiple of four)
+    __builtin_amdgcn_s_waitcnt(0x0F70);          // stray copies must land before the LDS is given up
+    [&]<int... F>(std::integer_sequence<int, F...>) __attribute__((always_inline)) {
+      ([&]() __attribute__((always_inline)) {
+        read_tr(std::integral_constant<int, F>{}, std::integral_constant<int, 3>{});
+        pv(std::integral_constant<int, F>{});
+      }(), ...);
+    }(std::make_integer_sequence<int, kNV>{});
+  }
+
+  const float l_tot = l_run + swap_halves(l_run);
+  const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+  if (qvalid) {
+    bf16 *os = slab_ptr(a.o, a.to, slab, a.H) + (int64_t)qrow * a.to.sL;
+    bf16 *ls = a.o_lo ? slab_ptr(a.o_lo, a.to, slab, a.H) + (int64_t)qrow * a.to.sL : nullptr;
+#pragma unroll
+    for (int dm = 0; dm < D / 32; ++dm) {
+      uint32_t w[8], r[8];
+#pragma unroll
+      for (int i = 0; i < 16; i += 2) {
+        const float v0 = oacc[dm][i] * inv, v1 = oacc[dm][i + 1] * inv;
+        const uint32_t pk = pack_bf16x2(v0, v1);
+        w[i >> 1] = pk;
+        r[i >> 1] = pack_bf16x2(v0 - bf16_bits_to_float(pk & 0xffffu),
+                                v1 - bf16_bits_to_float(pk >> 16));
+      }
+      uint4 *dst = reinterpret_cast<uint4 *>(os + dm * 32 + 16 * hl);
+      dst[0] = make_uint4(w[0], w[1], w[2], w[3]);
+      dst[1] = make_uint4(w[4], w[5], w[6], w[7]);
+      if (ls) {
+        uint4 *dl = reinterpret_cast<uint4 *>(ls + dm * 32 + 16 * hl);
+        dl[0] = make_uint4(r[0], r[1], r[2], r[3]);
+        dl[1] = make_uint4(r[4], r[5], r[6], r[7]);
+      }
+    }
+    if (hl == 0)
+      a.lse[(int64_t)slab * a.L + qrow] =
+          l_tot > 0.f ? m_run * 0.69314718055994530942f + __logf(l_tot) : -INFINITY;
+  }
+}
+
 template <int BLK, int D>
 static hipError_t launch_fwd_t(const FwdArgs &a, hipStream_t st) {
   using C = FwdCfg<BLK, D>;
   using P = PpCfg<BLK, D>;
+  using X = PipeCfg<BLK, D>;
   constexpr int lds = C::kStages * (C::kKElems + C::kVElems) * 2;
-  const int grid = xcd_grid(a.n_slabs * a.Nb);
-  // The ping-pong kernel is the faster one at block = 128, d = 128 (998 vs 914 TFLOP/s at the Wan
-  // shape); with smaller blocks or heads its workgroup has too few wavefronts per SIMD or too
-  // little work per phase and the lock-step kernel wins (e.g. 761 vs 511 TFLOP/s at block 64,
-  // d 128).  It addresses K tiles by 32-bit byte offsets inside a slab, so slabs of 4 GiB and
-  // more also take the lock-step kernel.  Global tokens exist in the ping-pong kernel only.
-  // The tests can force one or the other (asa_test_force_fwd_kernel).
+  const int total = a.n_slabs * a.Nb, grid = xcd_grid(total);
+  // Which kernel.  Measured on MI355X, the transposition of V included where a kernel needs it:
+  //   block 128 / d 128, long rows: ping-pong 1.56 ms, pipelined 1.84 ms (12 heads of 32 760 tokens, a
+  //     quarter of the tiles); short rows: see below.
+  //   block 128 / d 64: pipelined 34 us, lock-step 41 us (16 slabs of 3 510 tokens);
+  //   block 64 / d 128: pipelined 98 us, lock-step 128 us (12 slabs of 4 332 tokens).
+  //   block 64 / d 64: 48 heads of 17 776 tokens, 13 344 workgroups: lock-step 1.24 ms, pipelined 1.31 ms
+  //     (four wavefronts per SIMD against two: vector throughput decides); 2 heads of 1 024 tokens,
+  //     32 workgroups: pipelined 12 us, lock-step 17 us (one wavefront's own speed decides).  The
+  //     line is drawn where the pipelined kernel's workgroups (four per compute unit) stop being all
+  //     resident at once.
+  // The ping-pong kernel addresses K tiles by 32-bit byte offsets inside a slab: slabs of 4 GiB and
+  // more take one of the others.  The tests can force the ping-pong or the lock-step kernel
+  // (asa_test_force_fwd_kernel).
   const bool fits32 = (uint64_t)a.Nb * BLK * (uint64_t)a.tk.sL * 2u < 0xFFFFFFFFull;
   if (a.Nbg > 0 && (!fits32 || a.Nb + a.Nbg > kMaxNb || a.tk.sL != D)) return hipErrorNotSupported;
   const int forced = forced_fwd_kernel();
-  const bool prefer_pp = forced == 2 || (forced == 0 && BLK == 128 && D == 128);
+  constexpr bool kPingPongShape = BLK == 128 && D == 128, kLockStepShape = BLK == 64 && D == 64;
+  const bool pipe = forced == 0 ? !kPingPongShape && (!kLockStepShape || a.Nbg > 0 || total <= 1024)
+                                : forced == 1 && a.Nbg > 0 && !kPingPongShape;
   FwdArgs b = a;
   b.select = 0;
   hipError_t e = hipSuccess;
-  // Short lists: the ping-pong kernel costs ~8 us per workgroup around its steady state, the
-  // lock-step kernel ~3 us; they cross at 16-20 tiles per row.  The host cannot see the lists, so
-  // with lists BOTH kernels are launched and each workgroup leaves at once if its (batch, head)
-  // slab's tile count belongs to the other kernel (the launch that finds nothing to do costs
-  // 4-10 us).  Without lists (dense) every row holds Nb tiles and the choice is made here.
+  if (pipe) {
+    const void *fn = a.Nbg > 0 ? reinterpret_cast<const void *>(&fwd_pipe_kernel<BLK, D, true>)
+                               : reinterpret_cast<const void *>(&fwd_pipe_kernel<BLK, D, false>);
+    e = set_dynamic_lds_once(fn, X::kLds);
+    if (e != hipSuccess) return e;
+    timing_begin(st);
+    if (a.Nbg > 0)
+      hipLaunchKernelGGL((fwd_pipe_kernel<BLK, D, true>), dim3(grid), dim3(X::kThreads), X::kLds, st, b);
+    else
+      hipLaunchKernelGGL((fwd_pipe_kernel<BLK, D, false>), dim3(grid), dim3(X::kThreads), X::kLds, st, b);
+    return hipGetLastError();
+  }
+  // Short lists at block 128 / d 128: the ping-pong kernel costs ~8 us per workgroup around its steady
+  // state, the lock-step kernel ~3 us; they cross at 16-20 tiles per row.  The host cannot see the
+  // lists, so with lists BOTH kernels are launched and each workgroup leaves at once if its (batch,
+  // head) slab's tile count belongs to the other kernel (the launch that finds nothing to do costs
+  // 4-10 us); the transposition of V leaves out the slabs of the lock-step kernel, which reads the
+  // rows of V themselves there.  Without lists (dense) every row holds Nb tiles and the choice is
+  // made here.
   constexpr int kPingPongMinTiles = 18;
   b.select_min_tiles = kPingPongMinTiles;
   const bool dense_short = !a.row_ptr && a.Nbg == 0 && a.Nb < kPingPongMinTiles && forced == 0;
-  if (fits32 && (a.Nbg > 0 || prefer_pp) && !dense_short) {
+  if (fits32 && (a.Nbg > 0 || forced == 2 || (forced == 0 && kPingPongShape)) && !dense_short) {
     const bool both = a.Nbg == 0 && a.row_ptr && forced == 0;
     if (both) b.select = 1;
+    e = launch_transpose(a.v, a.tv, a.H, a.L, a.Lpad, BLK, D, a.n_slabs, a.vt, st, both ? a.row_ptr : nullptr,
+                         a.Nb, kPingPongMinTiles * a.Nb);
+    if (e == hipSuccess && a.Nbg > 0) {
+      // the pooled values: contiguous [slab][Nbg * block][d]
+      TensorView tvg;
+      tvg.sL = D; tvg.sH = (int64_t)a.Nbg * BLK * D; tvg.sB = tvg.sH * a.H;
+      e = launch_transpose(a.vg, tvg, a.H, a.Lg, a.Nbg * BLK, BLK, D, a.n_slabs, a.vgt, st);
+    }
+    if (e != hipSuccess) return e;
     const void *fn = a.Nbg > 0 ? reinterpret_cast<const void *>(&fwd_pp_kernel<BLK, D, true>)
                                : reinterpret_cast<const void *>(&fwd_pp_kernel<BLK, D, false>);
     e = set_dynamic_lds_once(fn, P::kLdsBytes);
     if (e != hipSuccess) return e;
+    timing_begin(st);
     if (a.Nbg > 0)
       hipLaunchKernelGGL((fwd_pp_kernel<BLK, D, true>), dim3(grid), dim3(P::kThreads), P::kLdsBytes, st, b);
     else
@@ -947,14 +1407,21 @@ static hipError_t launch_fwd_t(const FwdArgs &a, hipStream_t st) {
     e = hipGetLastError();
     if (e != hipSuccess || !both) return e;
     b.select = -1;
+  } else if (kLockStepShape) {
+    // (from V's rows 1.25 ms + 0, from the transposed copy 1.20 ms + 0.035 at 48 heads of 17 776 tokens)
+    e = launch_transpose(a.v, a.tv, a.H, a.L, a.Lpad, BLK, D, a.n_slabs, a.vt, st);
+    if (e != hipSuccess) return e;
+    timing_begin(st);
+  } else {
+    timing_begin(st);
   }
-  e = set_dynamic_lds_once(reinterpret_cast<const void *>(&fwd_kernel<BLK, D>), lds);
+  e = set_dynamic_lds_once(reinterpret_cast<const void *>(&fwd_kernel<BLK, D, kLockStepShape>), lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((fwd_kernel<BLK, D>), dim3(grid), dim3(C::kThreads), lds, st, b);
+  hipLaunchKernelGGL((fwd_kernel<BLK, D, kLockStepShape>), dim3(grid), dim3(C::kThreads), lds, st, b);
   return hipGetLastError();
 }
 
-hipError_t launch_fwd(const Problem &pb, const void *q, const void *k, const void *vt,
+hipError_t launch_fwd(const Problem &pb, const void *q, const void *k, const void *v, const void *vt,
                       const int32_t *row_ptr, const int32_t *col_idx, void *o, void *o_lo,
                       float *lse, const int32_t *order, hipStream_t st, const GlobalTokens *gt) {
   FwdArgs a;
@@ -964,9 +1431,9 @@ hipError_t launch_fwd(const Problem &pb, const void *q, const void *k, const voi
   a.Lg = gt ? gt->Lg : 0;
   a.Nbg = gt ? gt->Nbg : 0;
   a.bias_log2 = gt ? log2f((float)gt->n) : 0.f;
-  a.q = q; a.k = k; a.vt = reinterpret_cast<const bf16 *>(vt);
+  a.q = q; a.k = k; a.v = v; a.vg = gt ? gt->vg : nullptr; a.vt = reinterpret_cast<const bf16 *>(vt);
   a.row_ptr = row_ptr; a.col_idx = col_idx; a.o = o; a.o_lo = o_lo; a.lse = lse;
-  a.tq = pb.q; a.tk = pb.k; a.to = pb.o;
+  a.tq = pb.q; a.tk = pb.k; a.tv = pb.v; a.to = pb.o;
   a.H = pb.H; a.L = pb.L; a.Lpad = pb.Lpad; a.Nb = pb.Nb; a.n_slabs = pb.n_slabs;
   a.scale_log2e = pb.scale * 1.44269504088896340736f;
   a.select = 0;

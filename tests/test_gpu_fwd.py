@@ -213,3 +213,32 @@ def test_fwd_list_lengths_and_tails(block, d, tail, kernel_choice):
         mask[0, i, Nb - i:] = 1      # rows of 0 .. 5 blocks, every one of them with the ragged block
         mask[1, i, :i + 1] = 1       # rows of 1 .. 6
     _check_fwd(p, qb, kb, vb, mask)
+
+
+@pytest.mark.parametrize("H,Nb", [(16, 64), (17, 64)])
+def test_fwd_block_64_d_64_on_both_sides_of_the_kernel_choice(H, Nb):
+    """Up to 1024 query blocks the pipelined kernel runs, beyond that the lock-step kernel."""
+    L = Nb * 64 - 9
+    print(f"case H={H} L={L}", flush=True)
+    p = binding.Params(B=1, H=H, L=L, d=64, block=64)
+    qb, kb, vb = _case(1, H, L, 64, 64, seed=H)
+    _check_fwd(p, qb, kb, vb, synth.random_block_mask(Nb, 0.2, seed=H, slabs=H), heads=[0, H - 1])
+
+
+@pytest.mark.parametrize("which", [0, 1, 2])
+@pytest.mark.parametrize("block,d", [(64, 64), (64, 128), (128, 64), (128, 128)])
+def test_fwd_infinite_value_in_the_last_row_stays_infinite(block, d, which, kernel_choice):
+    """Keys past the end have probability zero and must not turn an infinite value of a real key into
+    NaN (0 * inf), whatever stands in for their rows."""
+    if kernel_choice != "auto":
+        pytest.skip("this test picks the kernel itself")
+    L = 2 * block + 5
+    p = binding.Params(B=1, H=1, L=L, d=d, block=block)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    q, k, v = (torch.randn(1, 1, L, d, device="cuda", generator=g).mul(0.3).bfloat16() for _ in range(3))
+    v[0, 0, L - 1] = float("inf")
+    bufs = util.lists_from_mask(p, np.ones((1, p.Nb, p.Nb), np.uint8), with_csc=False)
+    binding.asa_test_force_fwd_kernel(which)
+    o, lse = util.run_fwd(p, q, k, v, bufs)
+    assert torch.isposinf(o.float()).all()
+    assert torch.isfinite(lse).all()
