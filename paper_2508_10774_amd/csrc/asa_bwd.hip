@@ -111,7 +111,11 @@ struct BwdCfg {
   static constexpr int kDkvStage = 2 * kTile + 2 * kST * 4;    // Q rows, dO rows, LSE, -Delta
   static constexpr int kDqLds = kStages * kDqStage;
   static constexpr int kDkvLds = kStages * kDkvStage;
-  static constexpr int kWavesPerSimd = D == 128 ? 1 : 2;
+  static constexpr int kWavesPerSimd = D == 128 ? 1 : 2;              // dK / dV
+  // dQ at block 128 / d 128 just fits 256 registers: two workgroups per compute unit hide each other's
+  // starts and barriers (2.12 -> 2.00 ms at 12 heads of 32 760 tokens).  At block 64 / d 128 the copy
+  // offsets of two wavefronts do not fit (spills: 98 -> 130 us at 12 slabs of 4 332).
+  static constexpr int kDqWavesPerSimd = D == 128 && BLK == 64 ? 1 : 2;
 };
 
 // ---------------------------------------------------------------------------------------
@@ -132,13 +136,13 @@ struct BwdCfg {
 // by four make every LDS address a register plus an immediate; -Delta is the initial value of the
 // dP accumulator; a tile that reaches past the last row uses a second set of copy offsets instead
 // of a branch.
-// Registers: at d = 128 one wavefront per SIMD with the gradients in accumulation registers (the
-// instruction is written out for that: the compiler would move S and P there as well, at a
-// vector instruction per register and tile), at d = 64 two.
+// Registers: dK / dV at d = 128 (and dQ at block 64 / d 128) run one wavefront per SIMD with the
+// gradients in accumulation registers (the instruction is written out for that: the compiler would
+// move S and P there as well, at a vector instruction per register and tile), the others two.
 // Bound: the matrix cores at the power limit (1.15 PFLOP/s executed at a clock of 1.68 GHz, matrix
 // pipe busy 65 % of the cycles at the Wan2.1 shape; with neither copies nor vector work the same
 // loop runs at 1.4).  Against two unpipelined wavefronts per SIMD, 25 % density, MI355X:
-//   block 128 / d 128, 12 heads of 32 760:  dK+dV 3.19 -> 2.75 ms, dQ 2.40 -> 2.05 ms
+//   block 128 / d 128, 12 heads of 32 760:  dK+dV 3.19 -> 2.75 ms, dQ 2.40 -> 2.00 ms
 //   block 64 / d 64, 48 heads of 17 776:    dK+dV 1.93 -> 1.67 ms, dQ 1.52 -> 1.33 ms
 //   block 64 / d 128, 12 slabs of 4 332:    dK+dV 235 -> 118 us, dQ 177 -> 98 us, Delta 144 -> 75 us
 // Eight stages instead of four are 1.5 % slower (longer start of a workgroup), 4 or 7 operands ahead
@@ -157,7 +161,7 @@ struct BwdCfg {
 // is off by up to 0.05 in rows whose soft-max is spread over keys with similar values, and that
 // error goes into dQ and dK times the size of the keys / queries.
 template <int BLK, int D, bool GT, bool DELTA_ONLY = false>
-__global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dq_kernel(BwdArgs a) {
+__global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kDqWavesPerSimd)) void dq_kernel(BwdArgs a) {
   using C = BwdCfg<BLK, D>;
   extern __shared__ __align__(1024) unsigned char smem[];
   __shared__ int cols[kMaxNb];
@@ -201,11 +205,13 @@ __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dq_k
   }
   // rows past L have LSE = +inf there, so that every probability is exactly zero
   const float lse2 = a.lse2[(int64_t)slab * a.Lpad + qrow];
-  // dP starts from -Delta instead of zero: the subtraction costs nothing
+  // dP starts from -Delta instead of zero (the subtraction then costs nothing) where 16 registers for
+  // it do not cost a wavefront
   const float ndelta = DELTA_ONLY ? 0.f : a.ndelta[(int64_t)slab * a.Lpad + qrow];
+  constexpr bool kInitDelta = !(BLK == 128 && D == 128) || DELTA_ONLY;
   f32x16 nd16;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) nd16[i] = ndelta;
+  for (int i = 0; i < 16; ++i) nd16[i] = kInitDelta ? ndelta : 0.f;
   float dsum = 0.f;   // DELTA_ONLY: sum of P * dP over my keys
 
   f32x16 acc[D / 32];
@@ -311,7 +317,7 @@ __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dq_k
   // vector ALU turns those of tile t into dS^T, phase B adds tile t's product to dQ^T (see
   // dkv_kernel for the ring of operands, the stages and the unrolling by four tiles).
   constexpr int kNA = 2 * (D / 16), kNB = DELTA_ONLY ? 0 : 2 * (D / 32), kN = kNA + kNB;
-  constexpr int kRing = kN % 8 == 0 ? 8 : 6, kDepth = kRing == 8 ? 6 : 5;
+  constexpr int kRing = kN % 8 == 0 && (kInitDelta || kN % 6) ? 8 : 6, kDepth = kRing == 8 ? 6 : 5;
   static_assert(kN % kRing == 0, "the ring continues across iterations");
   constexpr int kBar = kNA < kN - kDepth ? kNA : kN - kDepth;   // the barrier comes before this product
   bf16x8 ring[kRing];
@@ -330,7 +336,7 @@ __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dq_k
                          0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   auto accumulate = [](f32x16 &d, bf16x8 x, bf16x8 y) __attribute__((always_inline)) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    if constexpr (C::kWavesPerSimd == 1)
+    if constexpr (C::kDqWavesPerSimd == 1)
       asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(x), "v"(y));
     else
       d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, d, 0, 0, 0);
@@ -357,7 +363,7 @@ __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dq_k
       if (DELTA_ONLY) {
         dsum = fmaf(sc[i], pc[i], dsum);
       } else {
-        pc[i] *= sc[i];
+        pc[i] = kInitDelta ? pc[i] * sc[i] : (pc[i] + ndelta) * sc[i];
         if (i & 1) db[i >> 1] = pack_bf16x2(pc[i - 1], pc[i]);
       }
     };
