@@ -330,7 +330,7 @@ int asa_attn_fwd(const asa_params *p, const void *q, const void *k, const void *
   hipError_t e;
   // rows of uneven length (the rule's own m per row): longest first inside each XCD's share
   int32_t *order = nullptr;
-  if (row_ptr && length_order_fits(pb.n_slabs * pb.Nb)) {
+  if (row_ptr && length_order_wanted(pb.n_slabs * pb.Nb)) {
     order = reinterpret_cast<int32_t *>(reinterpret_cast<char *>(workspace) + transposed_bytes(pb));
     e = launch_length_order(row_ptr, pb.Nb, pb.n_slabs * pb.Nb, order, st);
     if (e != hipSuccess) return finish(e);
@@ -405,7 +405,7 @@ int asa_attn_fwd_g(const asa_params *p, int n, const void *q, const void *k, con
   GlobalTokens gt;
   gt.n = n; gt.Lg = Lg; gt.Nbg = Nbg; gt.kg = kg; gt.vg = vg; gt.vgt = vgt;
   int32_t *order = nullptr;
-  if (row_ptr && length_order_fits(pb.n_slabs * pb.Nb)) {
+  if (row_ptr && length_order_wanted(pb.n_slabs * pb.Nb)) {
     order = reinterpret_cast<int32_t *>(ws + transposed_bytes(pb) + pooled_tile_bytes(pb, Nbg));
     e = launch_length_order(row_ptr, pb.Nb, pb.n_slabs * pb.Nb, order, st);
     if (e != hipSuccess) return finish(e);

@@ -990,7 +990,7 @@ hipError_t launch_bwd(const Problem &pb, const void *q, const void *k, const voi
   a.order_q = nullptr;
   {
     const int total = pb.n_slabs * pb.Nb;
-    if (col_ptr && length_order_fits(total)) {
+    if (col_ptr && length_order_wanted(total)) {
       int32_t *order_q = reinterpret_cast<int32_t *>(ws + 3 * rb + order_bytes(pb));
       e = launch_length_order(col_ptr, pb.Nb, total, order, st, row_ptr, order_q);
       if (e != hipSuccess) return e;

@@ -104,8 +104,9 @@ hipError_t launch_bwd(const Problem &pb, const void *q, const void *k, const voi
 size_t bwd_workspace_bytes(const Problem &pb);
 // order[w] = work item of workgroup slot w: inside each XCD's contiguous share of the
 // total = n_slabs * Nb (slab, block) items, longest list first (ptr = row_ptr or col_ptr of all
-// slabs).  Only where a share holds at most as many items as the sort takes (length_order_fits).
-bool length_order_fits(int total);
+// slabs).  Only where a share holds at most as many items as the sort takes and there are more items than
+// compute units (length_order_wanted).
+bool length_order_wanted(int total);
 // ptr2 / order2: a second list (the other direction of the same mask) in the same launch, or null.
 hipError_t launch_length_order(const int32_t *ptr, int Nb, int total, int32_t *order, hipStream_t st,
                                const int32_t *ptr2 = nullptr, int32_t *order2 = nullptr);

@@ -127,7 +127,9 @@ __global__ __launch_bounds__(64) void length_order_small_kernel(OrderArgs a) {
   if (lane < count) order[first + rank] = first + lane;
 }
 
-bool length_order_fits(int total) { return (total + kNumXcd - 1) / kNumXcd <= kOrderMax; }
+// Up to one workgroup per compute unit all of them start at once, in whatever order: the launch
+// would cost its 3-5 us for nothing.
+bool length_order_wanted(int total) { return total > 256 && (total + kNumXcd - 1) / kNumXcd <= kOrderMax; }
 
 hipError_t launch_length_order(const int32_t *ptr, int Nb, int total, int32_t *order, hipStream_t st,
                                const int32_t *ptr2, int32_t *order2) {
