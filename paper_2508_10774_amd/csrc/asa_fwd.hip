@@ -8,9 +8,11 @@
 //                    online soft-max need a single cross-lane exchange;
 //   O^T += V^T P^T   the accumulator of S^T, rounded to bf16, already IS the B operand of
 //                    this product, provided the rows of K are read in the permuted order
-//                    kappa; V is consumed from a per-block transposed copy so that both
-//                    LDS operand reads are 16-byte loads.
-// A key block is walked in steps of 64 keys.  The K rows and the V^T slice of a step are copied
+//                    kappa; the V^T operand comes from a per-block transposed copy of V (both
+//                    LDS operand reads are then 16-byte loads) or, where making the copy costs
+//                    more than it gains, from V's rows by the transposing LDS read.
+// Three kernels (launch_fwd_t says which runs where): lock-step, ping-pong, pipelined.  A key block is
+// walked in steps of 64 (pipelined: 32) keys.  The K rows and the V^T slice (or V rows) of a step are copied
 // straight from global memory into LDS (no register staging) with an XOR swizzle of 16-byte
 // chunks instead of row padding, which keeps the 16-byte fragment reads conflict-free.
 #include <stdlib.h>
@@ -213,8 +215,8 @@ struct FwdCfg {
 // Lock-step kernel: one workgroup per query block, all wavefronts in lock step.  With two LDS
 // stages (2 x 32 KB at d = 128) the copies of step s + 1 are requested right after the barrier
 // that opens step s; with one, the copies of a step are waited for right away and the other
-// workgroups on the CU compute meanwhile.  It serves the tile shapes other than block 128 / d 128 and tensors that the
-// ping-pong kernel below does not take (slabs of 4 GiB and more).
+// workgroups on the CU compute meanwhile.  It serves large block 64 / d 64 calls and, at block 128 /
+// d 128, short rows and tensors that the ping-pong kernel below does not take (slabs of 4 GiB and more).
 // VT: the operand of the second product comes from the transposed copy of V (one 16-byte read)
 // instead of the rows of V (two transposing reads).
 template <int BLK, int D, bool VT>

@@ -407,7 +407,8 @@ hipError_t launch_sample_offsets(const Problem &pb, uint64_t seed, uint8_t *tabl
 // keys in LDS the kernel was bound by LDS bandwidth).  One lane then forms the fp64 running sums
 // c_r in rank order -- the additions happen in exactly the sequence the algorithm states, so the
 // decision is bit-identical to a sequential implementation -- then m* = #{r : c_r < tau * T},
-// m = clamp(m*, m_min, m_max), keep rank < m.  A NaN score counts as 0.
+// m = clamp(m*, m_min, m_max), keep rank < m.  A NaN score counts as 0.  Where m_min == m_max the m
+// best keys are selected without sorting or summing.
 // ---------------------------------------------------------------------------------------
 struct RuleArgs {
   const float *scores;
