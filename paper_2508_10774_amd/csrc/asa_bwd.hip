@@ -134,9 +134,9 @@ struct BwdCfg {
 // Registers: dK / dV at d = 128 (and dQ at block 64 / d 128) run one wavefront per SIMD with the
 // gradients in accumulation registers (the instruction is written out for that: the compiler would
 // move S and P there as well, at a vector instruction per register and tile), the others two.
-// Bound: the matrix cores at the power limit (1.15 PFLOP/s executed at a clock of 1.68 GHz, matrix
-// pipe busy 65 % of the cycles at the Wan2.1 shape; with neither copies nor vector work the same
-// loop runs at 1.4).  Against two unpipelined wavefronts per SIMD, 25 % density, MI355X:
+// Bound: the matrix cores at the power limit (Wan2.1 shape: dK / dV 1.18 PFLOP/s executed, matrix pipe
+// busy 73 % of the cycles at 1.53 GHz, dQ 1.23 PFLOP/s, 86 % at 1.37 GHz; with neither copies nor
+// vector work the same loop runs at 1.4).  Against two unpipelined wavefronts per SIMD, 25 % density, MI355X:
 //   block 128 / d 128, 12 heads of 32 760:  dK+dV 3.19 -> 2.75 ms, dQ 2.40 -> 2.00 ms
 //   block 64 / d 64, 48 heads of 17 776:    dK+dV 1.93 -> 1.67 ms, dQ 1.52 -> 1.33 ms
 //   block 64 / d 128, 12 slabs of 4 332:    dK+dV 235 -> 118 us, dQ 177 -> 98 us, Delta 144 -> 75 us
