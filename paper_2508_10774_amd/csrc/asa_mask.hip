@@ -19,11 +19,10 @@ namespace asa {
 // bf16 MFMAs gives a 32 x 32 logit tile: 2 key blocks x 16 samples on the M axis, 2 query
 // blocks x 16 samples on the N axis.  The rows of the A operand are ordered so that lane half h
 // holds, for ONE sampled query, all 16 samples of key block j0 + h: the block-row maximum
-// Rt[query][j] of Alg. 1 is then a lane-local maximum, and the running maximum / denominator of
+// Rt[query][j] of Alg. 1 is then a lane-local maximum, and the running reference / denominator of
 // the row is kept lane-locally over the key blocks of that parity and merged across the two
 // halves (and the two wavefronts of a pair) once, at the end.  No cross-lane traffic inside the
-// sweep; the exponentials of a tile depend only on that tile's own maximum (Alg. 1 steps 12-14),
-// so consecutive tiles overlap.  Rt and each wavefront's (maximum, denominator) pair go to a
+// sweep.  Rt (unscaled logits) and each wavefront's (reference, denominator) pair go to a
 // workspace in global memory; finish_rule_kernel merges the pairs of a sampled row, turns Rt
 // into probabilities, max-pools over the sampled rows and applies the rule to the row.
 // ---------------------------------------------------------------------------------------
@@ -31,12 +30,14 @@ struct ProbeArgs {
   const void *q, *k;
   float *p_imp;
   float *rt;         // workspace [query group][pair][Nb rounded up to 8][32]: block-row maxima
-  float *stat_m;     // workspace [work item][wave][32]: running maximum of the wavefront's keys
-  double *stat_l;    //           and the matching denominator
+  float *stat_r;     // workspace [work item][wave][32]: reference exponent of the wavefront's keys
+  double *stat_l;    //           and the denominator relative to 2^reference
   TensorView tq, tk;
   int H, L, Nb, n_slabs, block, ks;
   int n_valid_last;  // sampled tokens of the last block that lie below L
-  float scale;
+  float c2;          // scale * log2(e)
+  float rest;        // ln(2) * what the rounding of c2 left out
+  float s_bound;     // bound of the logits in the factor 1 + s * rest
   int offs[kMaxSamples];
   const uint8_t *table;   // per-block sample positions [slab][Nb][ks] (TAB kernels), else null
 };
@@ -49,6 +50,13 @@ constexpr int kProbeKBlocks = 8;   // key blocks per LDS chunk (a wavefront take
 // four ranges, whole rounds of 512, are slower by 11 %: a workgroup's start costs more than the
 // half-empty round).
 constexpr int kProbeKeySplits = 2;
+
+// The exponent of 2 of a raw logit s is s * c2 with c2 = scale * log2(e), rounded to fp32.  What the
+// rounding leaves out multiplies exp2(s * c2) by 1 + s * rest; s is bounded so that the factor stays
+// next to 1 (logits beyond the bound are themselves rounded by more than that).
+__device__ __forceinline__ float bounded_logit(const ProbeArgs &a, float s) {
+  return __builtin_amdgcn_fmed3f(s, -a.s_bound, a.s_bound);
+}
 
 typedef __attribute__((address_space(3))) void lds_void_m;
 __device__ __forceinline__ void probe_dma16(const void *src, void *lds_dst) {
@@ -189,18 +197,19 @@ __global__ __launch_bounds__(512, 4) void probe_kernel(ProbeArgs a) {   // (4 wa
   const int rt_off = (2 * half * (kProbeKBlocks / 4) + hl) * 32 + n;
 
   float rt_pend[kProbeKBlocks / 4];   // block-row maxima of the chunk just swept
-  float Mr = -INFINITY;  // running maximum of my query's raw logits over the key blocks of parity hl
-  float br = INFINITY;   // -Mr in the exponent of 2, as rounded for the exponentials
-  double lt = 0.0;       // running denominator over the same keys, relative to 2^-br
-  const float c2 = a.scale * 1.44269504088896340736f;
+  float Rr = -INFINITY;  // reference exponent of my query over the key blocks of parity hl (an integer)
+  double lt = 0.0;       // running denominator over the same keys, relative to 2^Rr
+  const float c2 = a.c2;
 
   // One chunk out of LDS buffer BUF (a compile-time constant: every LDS address of the sweep is
   // a per-lane register plus an immediate): both pairs of key blocks of my half at once.  The
-  // exponentials are taken relative to the running maximum, brought up to date first (with 64
-  // rows per tile some row's maximum grows in most tiles, so there is no branch for it): one
-  // fp64 update per 32 keys.  At d = 64, 48 heads, Nb = 278: 270 -> 252 us (vector instructions
-  // 86 -> 75 million), at d = 128, 12 heads, Nb = 256: 80 -> 75 us, against exponentials relative to
-  // each pair's own maximum.
+  // exponentials are taken relative to the power of two at or below the running maximum's, brought up
+  // to date first (no branch for it): one fp64 update per 32 keys, and neither the reference nor a
+  // change of it is rounded (at or below: no numerator underflows that would not underflow relative
+  // to the maximum).  finish_rule_kernel forms the numerators from the same product s * c2; the rest of
+  // the rounded c2 is put right there per entry and here per chunk.  Against exponentials relative to each
+  // pair's own maximum: at d = 64, 48 heads, Nb = 278: 270 -> 252 us (vector instructions
+  // 86 -> 75 million), at d = 128, 12 heads, Nb = 256: 80 -> 75 us.
   auto sweep_chunk = [&](int chunk, auto buf_tag) __attribute__((always_inline)) {
     constexpr int BUF = decltype(buf_tag)::value, NT = kProbeKBlocks / 4;
     const bf16 *Kb = Kc[BUF];
@@ -216,7 +225,7 @@ __global__ __launch_bounds__(512, 4) void probe_kernel(ProbeArgs a) {   // (4 wa
         bf16x8 ka = *reinterpret_cast<const bf16x8 *>(Kb + sb * 32 * D + a_off[s]);
         acc[sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qreg[s], acc[sb], 0, 0, 0);
       }
-    float mnew = Mr;
+    float mnew = -INFINITY;
 #pragma unroll
     for (int sb = 0; sb < NT; ++sb) {
       const int j0 = chunk * kProbeKBlocks + 2 * (half * NT + sb);
@@ -231,15 +240,14 @@ __global__ __launch_bounds__(512, 4) void probe_kernel(ProbeArgs a) {   // (4 wa
       float mraw = -INFINITY;
 #pragma unroll
       for (int i = 0; i < 16; ++i) mraw = fmaxf(mraw, acc[sb][i]);
-      rt_pend[sb] = mraw * a.scale;                      // block-row maximum, Alg. 1 step 12
+      rt_pend[sb] = mraw;                                // block-row maximum, Alg. 1 step 12 (unscaled)
       mnew = fmaxf(mnew, mraw);
     }
-    // Alg. 1 steps 12-15 with the exponentials exp(scale * (s - max)) as one fused multiply-add
+    // Alg. 1 steps 12-15 with the exponentials exp(scale * (s - reference)) as one fused multiply-add
     // and one exp2 each
-    const float b_new = -mnew * c2;                      // (+inf while no key has been seen)
-    const float bias = (mnew == -INFINITY) ? 0.f : b_new;
-    const float keep = fast_exp2(bias - br);             // the old sum was relative to 2^-br
-    br = b_new;
+    const float r_new = fmaxf(Rr, floorf(mnew * c2));
+    const float bias = (r_new == -INFINITY) ? 0.f : -r_new;   // (no key has been seen yet: all sums stay 0)
+    const int shift = (int)fmaxf(Rr - r_new, -2000.f);        // (-inf - x and -inf - -inf: the old sum is 0)
     float sum[NT];
 #pragma unroll
     for (int sb = 0; sb < NT; ++sb) {
@@ -247,8 +255,9 @@ __global__ __launch_bounds__(512, 4) void probe_kernel(ProbeArgs a) {   // (4 wa
 #pragma unroll
       for (int i = 0; i < 16; ++i) sum[sb] += fast_exp2(fmaf(acc[sb][i], c2, bias));
     }
-    lt = fma(lt, (double)keep, (double)(sum[0] + sum[1]));
-    Mr = mnew;
+    lt = fma((double)(sum[0] + sum[1]), fma((double)bounded_logit(a, mnew), (double)a.rest, 1.0),
+             __builtin_amdgcn_ldexp(lt, shift));
+    Rr = r_new;
   };
 
   // The block-row maxima of a chunk are stored at the start of the NEXT chunk's turn, just before
@@ -278,19 +287,16 @@ __global__ __launch_bounds__(512, 4) void probe_kernel(ProbeArgs a) {   // (4 wa
     sweep_chunk(chunk + 1, std::integral_constant<int, 1>{});
   }
   if (c0 < c1) store_rt(c1 - 1);
-  // merge the two parities of each query; the pair (maximum, denominator) of this wavefront's
+  // merge the two parities of each query; the pair (reference, denominator) of this wavefront's
   // share of the keys goes to the workspace (the kernel that follows merges the shares)
   {
-    const float Mt = Mr * a.scale;
-    // what the rounding of br dropped, put right here, once: lt relative to the row's maximum itself
-    if (Mr != -INFINITY) lt *= (double)fast_exp2(fmaf(-Mr, c2, -br));
-    const float Mo = __shfl_xor(Mt, 32, 64);
+    const float Ro = __shfl_xor(Rr, 32, 64);
     const double lo = __shfl_xor(lt, 32, 64);
-    const float Mall = fmaxf(Mt, Mo);
-    const float Ms = (Mall == -INFINITY) ? 0.f : Mall;
-    const double lall = (double)__expf(Mt - Ms) * lt + (double)__expf(Mo - Ms) * lo;
+    const float Rall = fmaxf(Rr, Ro);
+    const double lall = __builtin_amdgcn_ldexp(lt, (int)fmaxf(Rr - Rall, -2000.f)) +
+                        __builtin_amdgcn_ldexp(lo, (int)fmaxf(Ro - Rall, -2000.f));
     if (hl == 0) {
-      a.stat_m[((int64_t)item * 8 + wave) * 32 + n] = Mall;
+      a.stat_r[((int64_t)item * 8 + wave) * 32 + n] = Rall;
       a.stat_l[((int64_t)item * 8 + wave) * 32 + n] = lall;
     }
   }
@@ -316,10 +322,12 @@ static void fill_probe_args(const Problem &pb, const void *q, const void *k, flo
   unsigned char *ws = reinterpret_cast<unsigned char *>(workspace);
   a->rt = reinterpret_cast<float *>(ws);
   a->stat_l = reinterpret_cast<double *>(ws + probe_rt_bytes(pb));
-  a->stat_m = reinterpret_cast<float *>(ws + probe_rt_bytes(pb) + probe_items(pb) * 8 * 32 * sizeof(double));
+  a->stat_r = reinterpret_cast<float *>(ws + probe_rt_bytes(pb) + probe_items(pb) * 8 * 32 * sizeof(double));
   a->tq = pb.q; a->tk = pb.k;
   a->H = pb.H; a->L = pb.L; a->Nb = pb.Nb; a->n_slabs = pb.n_slabs; a->block = pb.block; a->ks = pb.ks;
-  a->scale = pb.scale;
+  a->c2 = pb.scale * 1.44269504088896340736f;
+  a->rest = (float)(((double)pb.scale * 1.44269504088896340736 - (double)a->c2) * 0.69314718055994530942);
+  a->s_bound = fminf(1.0e5f / a->c2, 3.0e38f);   // (finite: the -inf of a tile without keys is bounded too)
   for (int u = 0; u < kMaxSamples; ++u) a->offs[u] = pb.offs[u];
   a->n_valid_last = 0;
   for (int u = 0; u < pb.ks; ++u)
@@ -604,35 +612,36 @@ __global__ __launch_bounds__(256) void finish_rule_kernel(ProbeArgs a, RuleArgs 
   const int w = i % kProbeQBlocks, pr_ = w >> 1, qb = w & 1;  // its pair and position in the pair
   const float *rtq = a.rt + ((int64_t)work * 4 + pr_) * nb_pad * 32 + qb * 16;
   // merge the shares: wavefronts pr_ and pr_ + 4 of every key range
-  // (the denominator is summed in fp64; its reciprocal is rounded to fp32 once per sampled
-  // row: the exponentials below are fp32 anyway)
+  // (the denominator is summed in fp64; its reciprocal is kept in two fp32 halves)
   // Lane u < 16 merges the shares of sampled row u; the 16 results are then handed to every
   // lane through scalar registers (all lanes doing all 16 rows cost 16 fp64 divisions a lane).
-  float my_m = -INFINITY, my_inv = 0.f;
+  float my_r = -INFINITY, my_inv = 0.f, my_inv_lo = 0.f;
   {
     const int u = lane & 15;
-    float pm[2 * kProbeKeySplits];
+    float pr[2 * kProbeKeySplits];
     double pl[2 * kProbeKeySplits];
 #pragma unroll
     for (int sp = 0; sp < kProbeKeySplits; ++sp)
 #pragma unroll
       for (int hf = 0; hf < 2; ++hf) {
         const int64_t at = (((int64_t)work * kProbeKeySplits + sp) * 8 + pr_ + 4 * hf) * 32 + qb * 16 + u;
-        pm[2 * sp + hf] = a.stat_m[at];
+        pr[2 * sp + hf] = a.stat_r[at];
         pl[2 * sp + hf] = a.stat_l[at];
-        my_m = fmaxf(my_m, pm[2 * sp + hf]);
+        my_r = fmaxf(my_r, pr[2 * sp + hf]);
       }
-    const float ms = (my_m == -INFINITY) ? 0.f : my_m;
     double l = 0.0;
 #pragma unroll
-    for (int x = 0; x < 2 * kProbeKeySplits; ++x) l += (double)__expf(pm[x] - ms) * pl[x];
-    my_inv = (float)(1.0 / l);
+    for (int x = 0; x < 2 * kProbeKeySplits; ++x) l += __builtin_amdgcn_ldexp(pl[x], (int)fmaxf(pr[x] - my_r, -2000.f));
+    const double inv = 1.0 / l;
+    my_inv = (float)inv;
+    my_inv_lo = (float)(inv - (double)my_inv);
   }
-  float Mrow[16], Linv[16];
+  float Rrow[16], Linv[16], Linv_lo[16];
 #pragma unroll
   for (int u = 0; u < 16; ++u) {
-    Mrow[u] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, my_m), u));
+    Rrow[u] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, my_r), u));
     Linv[u] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, my_inv), u));
+    Linv_lo[u] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, my_inv_lo), u));
   }
   int rows_ok = a.ks;                       // sampled rows of this block that lie below L
   if (i == a.Nb - 1) {
@@ -658,7 +667,11 @@ __global__ __launch_bounds__(256) void finish_rule_kernel(ProbeArgs a, RuleArgs 
       float best = 0.f;
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
-        if (u < rows_ok && rv[u] != -INFINITY) best = fmaxf(best, __expf(rv[u] - Mrow[u]) * Linv[u]);
+        if (u < rows_ok && rv[u] != -INFINITY) {
+          // exp2 / denominator with one rounding of its own: the low parts enter the sum before it
+          const float e = fast_exp2(fmaf(rv[u], a.c2, -Rrow[u]));
+          best = fmaxf(best, fmaf(e, Linv[u], e * fmaf(bounded_logit(a, rv[u]) * a.rest, Linv[u], Linv_lo[u])));
+        }
       }
       if (out) out[j] = best;
       key[r] = ((unsigned long long)desc_key(best) << 32) | (unsigned)j;

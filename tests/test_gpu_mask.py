@@ -1,5 +1,7 @@
 """GPU parity: mask generation (importance map, threshold rule, index lists) vs the oracle."""
 
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -302,6 +304,40 @@ def test_every_token_sampled_gives_the_exact_importance_map(B, H, L, d, block):
     torch.cuda.synchronize()
     assert torch.equal(bufs["mask"], bufs2["mask"])
     del heads
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("L,gain", [(32760, 1.0), (8000, 1.0), (32760, 2.0)])
+def test_importance_map_error_does_not_grow_with_the_distance_to_the_maximum(d, L, gain):
+    """P_imp against 64 bits, scale as given (fp32), flat rows.  The mean relative error over all entries
+    shows what all entries of a row share, above all the rounding of the exponent factor
+    scale * log2(e), relative size eps: it may count for the distance between a chunk's largest logit and
+    the keys of that chunk (32 keys, N(0, gain^2): 1.5 nats at most), not for the distance to the
+    row's maximum (4 nats and more).  2^-25 for the exponentials of the hardware, good to 1 ulp = 2^-23,
+    whose errors hardly share a sign.  Exponentials relative to the rounded row maximum:
+    9.1e-8 and 9.9e-8 at d = 128, L = 32760, against a bound of 6.9e-8."""
+    H = 4
+    g = torch.Generator(device="cuda").manual_seed(L + d)
+    q, k = (torch.randn(1, H, L, d, device="cuda", generator=g).mul(gain ** 0.5).bfloat16() for _ in range(2))
+    scale = float(np.float32(1) / np.sqrt(np.float32(d)))
+    p = binding.Params(B=1, H=H, L=L, d=d, block=128, tau=0.9, scale=scale)
+    bufs = binding.alloc_index_lists(p, with_csc=False)
+    got = torch.empty((H, p.Nb, p.Nb), dtype=torch.float32, device="cuda")
+    ws = binding.alloc_workspace(binding.asa_mask_workspace_bytes(p))
+    binding.asa_build_mask(p, q, k, bufs["mask"], bufs["row_ptr"], bufs["col_idx"], None, None, got, ws)
+    at = (torch.arange(p.Nb, device="cuda")[:, None] * 128 + torch.arange(16, device="cuda") * 8).reshape(-1)
+    valid = at < L
+    err, n = 0.0, 0
+    for h in range(H):
+        s = (q[0, h, at.clamp(max=L - 1)].double() @ k[0, h, at.clamp(max=L - 1)].double().t()) * scale
+        s.masked_fill_(~valid, -math.inf)
+        want = torch.softmax(s, dim=1).masked_fill_(~valid[:, None], 0.0).view(p.Nb, 16, p.Nb, 16).amax(dim=(1, 3))
+        ok = want > 1e-30
+        err += float((got[h].double()[ok] / want[ok] - 1).sum())
+        n += int(ok.sum())
+    print(f"d={d} L={L} gain={gain}: mean relative error {err / n:+.2e}", flush=True)
+    eps = abs(float(np.float32(scale) * np.float32(math.log2(math.e))) / (scale * math.log2(math.e)) - 1)
+    assert abs(err / n) <= 1.5 * eps + 2.0 ** -25
 
 
 def test_every_token_sampled_is_refused_beyond_its_length_limit():
