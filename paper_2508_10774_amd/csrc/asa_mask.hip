@@ -37,7 +37,7 @@ struct ProbeArgs {
   int n_valid_last;  // sampled tokens of the last block that lie below L
   float c2;          // scale * log2(e)
   float rest;        // ln(2) * what the rounding of c2 left out
-  float s_bound;     // bound of the logits in the factor 1 + s * rest
+  float s_bound;     // kMaxExactExponent / c2
   int offs[kMaxSamples];
   const uint8_t *table;   // per-block sample positions [slab][Nb][ks] (TAB kernels), else null
 };
@@ -52,11 +52,9 @@ constexpr int kProbeKBlocks = 8;   // key blocks per LDS chunk (a wavefront take
 constexpr int kProbeKeySplits = 2;
 
 // The exponent of 2 of a raw logit s is s * c2 with c2 = scale * log2(e), rounded to fp32.  What the
-// rounding leaves out multiplies exp2(s * c2) by 1 + s * rest; s is bounded so that the factor stays
-// next to 1 (logits beyond the bound are themselves rounded by more than that).
-__device__ __forceinline__ float bounded_logit(const ProbeArgs &a, float s) {
-  return __builtin_amdgcn_fmed3f(s, -a.s_bound, a.s_bound);
-}
+// rounding leaves out multiplies exp2(s * c2) by 1 + s * rest.  That is used up to this exponent (logits
+// beyond it are themselves rounded by more than that).
+constexpr float kMaxExactExponent = 8192.f;
 
 typedef __attribute__((address_space(3))) void lds_void_m;
 __device__ __forceinline__ void probe_dma16(const void *src, void *lds_dst) {
@@ -255,7 +253,7 @@ __global__ __launch_bounds__(512, 4) void probe_kernel(ProbeArgs a) {   // (4 wa
 #pragma unroll
       for (int i = 0; i < 16; ++i) sum[sb] += fast_exp2(fmaf(acc[sb][i], c2, bias));
     }
-    lt = fma((double)(sum[0] + sum[1]), fma((double)bounded_logit(a, mnew), (double)a.rest, 1.0),
+    lt = fma((double)(sum[0] + sum[1]), fma((double)__builtin_amdgcn_fmed3f(mnew, -a.s_bound, a.s_bound), (double)a.rest, 1.0),
              __builtin_amdgcn_ldexp(lt, shift));
     Rr = r_new;
   };
@@ -327,7 +325,7 @@ static void fill_probe_args(const Problem &pb, const void *q, const void *k, flo
   a->H = pb.H; a->L = pb.L; a->Nb = pb.Nb; a->n_slabs = pb.n_slabs; a->block = pb.block; a->ks = pb.ks;
   a->c2 = pb.scale * 1.44269504088896340736f;
   a->rest = (float)(((double)pb.scale * 1.44269504088896340736 - (double)a->c2) * 0.69314718055994530942);
-  a->s_bound = fminf(1.0e5f / a->c2, 3.0e38f);   // (finite: the -inf of a tile without keys is bounded too)
+  a->s_bound = fminf(kMaxExactExponent / a->c2, 3.0e38f);   // (finite: the -inf of a tile without keys is bounded too)
   for (int u = 0; u < kMaxSamples; ++u) a->offs[u] = pb.offs[u];
   a->n_valid_last = 0;
   for (int u = 0; u < pb.ks; ++u)
@@ -615,7 +613,7 @@ __global__ __launch_bounds__(256) void finish_rule_kernel(ProbeArgs a, RuleArgs 
   // (the denominator is summed in fp64; its reciprocal is kept in two fp32 halves)
   // Lane u < 16 merges the shares of sampled row u; the 16 results are then handed to every
   // lane through scalar registers (all lanes doing all 16 rows cost 16 fp64 divisions a lane).
-  float my_r = -INFINITY, my_inv = 0.f, my_inv_lo = 0.f;
+  float my_r = -INFINITY, my_inv = 0.f, my_inv_lo = 0.f, my_inv_rest = 0.f;
   {
     const int u = lane & 15;
     float pr[2 * kProbeKeySplits];
@@ -635,13 +633,15 @@ __global__ __launch_bounds__(256) void finish_rule_kernel(ProbeArgs a, RuleArgs 
     const double inv = 1.0 / l;
     my_inv = (float)inv;
     my_inv_lo = (float)(inv - (double)my_inv);
+    my_inv_rest = fabsf(my_r) < kMaxExactExponent ? my_inv * a.rest : 0.f;
   }
-  float Rrow[16], Linv[16], Linv_lo[16];
+  float Rrow[16], Linv[16], Linv_lo[16], Linv_rest[16];
 #pragma unroll
   for (int u = 0; u < 16; ++u) {
     Rrow[u] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, my_r), u));
     Linv[u] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, my_inv), u));
     Linv_lo[u] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, my_inv_lo), u));
+    Linv_rest[u] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, my_inv_rest), u));
   }
   int rows_ok = a.ks;                       // sampled rows of this block that lie below L
   if (i == a.Nb - 1) {
@@ -668,9 +668,10 @@ __global__ __launch_bounds__(256) void finish_rule_kernel(ProbeArgs a, RuleArgs 
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
         if (u < rows_ok && rv[u] != -INFINITY) {
-          // exp2 / denominator with one rounding of its own: the low parts enter the sum before it
+          // exp2(s * c2 - R) * (1 + s * rest) / denominator with one rounding of its own: the low parts enter
+          // the sum before it
           const float e = fast_exp2(fmaf(rv[u], a.c2, -Rrow[u]));
-          best = fmaxf(best, fmaf(e, Linv[u], e * fmaf(bounded_logit(a, rv[u]) * a.rest, Linv[u], Linv_lo[u])));
+          best = fmaxf(best, fmaf(e, Linv[u], e * fmaf(rv[u], Linv_rest[u], Linv_lo[u])));
         }
       }
       if (out) out[j] = best;
