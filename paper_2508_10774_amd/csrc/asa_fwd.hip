@@ -1334,32 +1334,54 @@ __global__ __launch_bounds__(BLK * 2, (PipeCfg<BLK, D>::kWavesPerSimd)) void fwd
   }
 }
 
+template <int BLK, int D, bool VT>
+static hipError_t launch_lock_step(const FwdArgs &a, int grid, hipStream_t st) {
+  using C = FwdCfg<BLK, D>;
+  constexpr int lds = C::kStages * (C::kKElems + C::kVElems) * 2;
+  const hipError_t e = set_dynamic_lds_once(reinterpret_cast<const void *>(&fwd_kernel<BLK, D, VT>), lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((fwd_kernel<BLK, D, VT>), dim3(grid), dim3(C::kThreads), lds, st, a);
+  return hipGetLastError();
+}
+
 template <int BLK, int D>
 static hipError_t launch_fwd_t(const FwdArgs &a, hipStream_t st) {
-  using C = FwdCfg<BLK, D>;
   using P = PpCfg<BLK, D>;
   using X = PipeCfg<BLK, D>;
-  constexpr int lds = C::kStages * (C::kKElems + C::kVElems) * 2;
   const int total = a.n_slabs * a.Nb, grid = xcd_grid(total);
   // Which kernel.  Measured on MI355X, the transposition of V included where a kernel needs it:
   //   block 128 / d 128, long rows: ping-pong 1.56 ms, pipelined 1.84 ms (12 heads of 32 760 tokens, a
   //     quarter of the tiles); short rows: see below.
-  //   block 128 / d 64: pipelined 34 us, lock-step 41 us (16 slabs of 3 510 tokens);
-  //   block 64 / d 128: pipelined 98 us, lock-step 128 us (12 slabs of 4 332 tokens).
   //   block 64 / d 64: 48 heads of 17 776 tokens, 13 344 workgroups: lock-step 1.24 ms, pipelined 1.31 ms
   //     (four wavefronts per SIMD against two: vector throughput decides); 2 heads of 1 024 tokens,
   //     32 workgroups: pipelined 12 us, lock-step 17 us (one wavefront's own speed decides).  The
   //     line is drawn where the pipelined kernel's workgroups (four per compute unit) stop being all
   //     resident at once.
+  //   block 128 / d 64 and block 64 / d 128: the pipelined kernel has two workgroups per compute unit and
+  //     is the faster one as long as they all start at once (512; block 64 / d 128, 16 .. 512 workgroups:
+  //     1.25-1.5x) and where a few long rows decide (lists with always-kept prefix blocks or uneven rows:
+  //     up to 1.5x).  With more workgroups and rows of one length the lock-step kernel shares a compute
+  //     unit between more of them.  Without lists, 632 workgroups of 79 tiles: 303 us against 325 at
+  //     block 128 / d 64, 166 us against 197 at block 64 / d 128.  There full rounds of 512 are an
+  //     exception (three of 128 tiles: 565 against 500) and so are 1025 .. 1536 workgroups, three rounds
+  //     that the lock-step kernel's 1024 at a time do not fill either (1264: 302 and 292).  Lists hide their
+  //     lengths from the host and stay pipelined: rows of one length are then 2-6 % slower than
+  //     lock-step beyond 1000 workgroups (11 % at 1600 of 10 tiles, block 64 / d 128), uneven ones up to
+  //     1.5x faster.
   // The ping-pong kernel addresses K tiles by 32-bit byte offsets inside a slab: slabs of 4 GiB and
   // more take one of the others.  The tests can force the ping-pong or the lock-step kernel
   // (asa_test_force_fwd_kernel).
   const bool fits32 = (uint64_t)a.Nb * BLK * (uint64_t)a.tk.sL * 2u < 0xFFFFFFFFull;
   if (a.Nbg > 0 && (!fits32 || a.Nb + a.Nbg > kMaxNb || a.tk.sL != D)) return hipErrorNotSupported;
   const int forced = forced_fwd_kernel();
-  constexpr bool kPingPongShape = BLK == 128 && D == 128, kLockStepShape = BLK == 64 && D == 64;
-  const bool pipe = forced == 0 ? !kPingPongShape && (!kLockStepShape || a.Nbg > 0 || total <= 1024)
-                                : forced == 1 && a.Nbg > 0 && !kPingPongShape;
+  constexpr bool kPingPongShape = BLK == 128 && D == 128, kSmallTile = BLK == 64 && D == 64;
+  const bool dense = a.row_ptr == nullptr;
+  const int resident = kSmallTile ? 1024 : 512;      // pipelined workgroups on the chip
+  bool fits_pipe = total <= resident || (!kSmallTile && !dense);
+  if (BLK == 64 && D == 128)
+    fits_pipe |= (total + resident - 1) / resident * resident - total <= total / 20 ||
+                 (total > 2 * resident && total <= 3 * resident);
+  const bool pipe = !kPingPongShape && (forced == 0 ? a.Nbg > 0 || fits_pipe : forced == 1 && a.Nbg > 0);
   FwdArgs b = a;
   b.select = 0;
   hipError_t e = hipSuccess;
@@ -1409,18 +1431,21 @@ static hipError_t launch_fwd_t(const FwdArgs &a, hipStream_t st) {
     e = hipGetLastError();
     if (e != hipSuccess || !both) return e;
     b.select = -1;
-  } else if (kLockStepShape) {
-    // (from V's rows 1.25 ms + 0, from the transposed copy 1.20 ms + 0.035 at 48 heads of 17 776 tokens)
+    if constexpr (kPingPongShape) return launch_lock_step<BLK, D, false>(b, grid, st);
+  }
+  // The lock-step kernel reads V's rows or their transposed copy.  Block 64 / d 64: 1.25 ms, or 1.20 ms +
+  // 0.035 for the copy (48 heads of 17 776 tokens).  Mixed shapes: the rows cost more per tile, the copy costs
+  // the same whatever the length of the rows; equal at about 3 500 keys per row (block 64 / d 128: 16 tiles
+  // 43 and 48 us, 79 tiles 170 and 166; block 128 / d 64: 20 tiles 109 and 118, 79 tiles 311 and 303).
+  const bool copy_v = kSmallTile || (!kPingPongShape && a.L >= 3584);
+  if (copy_v) {
     e = launch_transpose(a.v, a.tv, a.H, a.L, a.Lpad, BLK, D, a.n_slabs, a.vt, st);
     if (e != hipSuccess) return e;
-    timing_begin(st);
-  } else {
-    timing_begin(st);
   }
-  e = set_dynamic_lds_once(reinterpret_cast<const void *>(&fwd_kernel<BLK, D, kLockStepShape>), lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((fwd_kernel<BLK, D, kLockStepShape>), dim3(grid), dim3(C::kThreads), lds, st, b);
-  return hipGetLastError();
+  timing_begin(st);
+  if constexpr (kSmallTile) return launch_lock_step<BLK, D, true>(b, grid, st);
+  else if constexpr (kPingPongShape) return launch_lock_step<BLK, D, false>(b, grid, st);
+  else return copy_v ? launch_lock_step<BLK, D, true>(b, grid, st) : launch_lock_step<BLK, D, false>(b, grid, st);
 }
 
 hipError_t launch_fwd(const Problem &pb, const void *q, const void *k, const void *v, const void *vt,

@@ -225,6 +225,45 @@ def test_fwd_block_64_d_64_on_both_sides_of_the_kernel_choice(H, Nb):
     _check_fwd(p, qb, kb, vb, synth.random_block_mask(Nb, 0.2, seed=H, slabs=H), heads=[0, H - 1])
 
 
+@pytest.mark.parametrize("block,d,H,Nb,lists,lock_step", [
+    (128, 64, 12, 42, False, False),    # 504 query blocks: pipelined workgroups all start at once
+    (128, 64, 52, 10, False, True),     # 520, 1 271 keys per row: lock-step from V's rows
+    (128, 64, 13, 40, False, True),     # 520, 5 111 keys: lock-step from the transposed copy
+    (64, 128, 8, 64, False, False),     # 512
+    (64, 128, 19, 27, False, True),     # 513, 1 719 keys
+    (64, 128, 9, 57, False, True),      # 513, 3 639 keys
+    (64, 128, 16, 63, False, False),    # 1008: two rounds, the second one nearly full
+    (64, 128, 41, 25, False, False),    # 1025: a second round of lock-step workgroups
+    (64, 128, 53, 29, False, True),     # 1537: a fourth round of pipelined ones
+    (128, 64, 16, 60, True, False),     # lists: pipelined whatever the number (960, 600)
+    (64, 128, 20, 30, True, False),
+])
+def test_fwd_mixed_shapes_on_both_sides_of_the_kernel_choice(block, d, H, Nb, lists, lock_step, kernel_choice):
+    """Which kernel ran shows in the last bits (tiles of 64 keys or of 32): auto equals the forced lock-step
+    kernel exactly where the choice falls on it.  One head against the oracle."""
+    if kernel_choice != "auto":
+        pytest.skip("the choice is what is tested")
+    L = Nb * block - 9
+    print(f"case H={H} L={L} d={d} block={block} lists={lists}", flush=True)
+    p = binding.Params(B=1, H=H, L=L, d=d, block=block)
+    qb, kb, vb = _case(1, H, L, d, block, seed=H)
+    q, k, v = (util.dev_bf16(x) for x in (qb, kb, vb))
+    mask = np.ones((H, Nb, Nb), np.uint8)
+    bufs = {"row_ptr": None, "col_idx": None}
+    if lists:
+        mask = synth.random_block_mask(Nb, 0.2, seed=H, slabs=H)
+        bufs = util.lists_from_mask(p, mask, with_csc=False)
+    o, lse = util.run_fwd(p, q, k, v, bufs)
+    binding.asa_test_force_fwd_kernel(1)
+    o1, lse1 = util.run_fwd(p, q, k, v, bufs)
+    same = torch.equal(o.view(torch.int16), o1.view(torch.int16)) and torch.equal(lse, lse1)
+    assert same == lock_step
+    qf, kf, vf = (synth.bf16_bits_to_f32(x[0, H - 1]) for x in (qb, kb, vb))
+    want, wl = oracle.attn_fwd(qf, kf, vf, mask[H - 1], block)
+    util.assert_close_bf16(util.host_f32(o[0, H - 1]), want, "O")
+    assert np.abs(lse[H - 1].cpu().numpy() - wl).max() <= util.LSE_ABS
+
+
 @pytest.mark.parametrize("which", [0, 1, 2])
 @pytest.mark.parametrize("block,d", [(64, 64), (64, 128), (128, 64), (128, 128)])
 def test_fwd_infinite_value_in_the_last_row_stays_infinite(block, d, which, kernel_choice):
