@@ -1381,7 +1381,16 @@ static hipError_t launch_fwd_t(const FwdArgs &a, hipStream_t st) {
   if (BLK == 64 && D == 128)
     fits_pipe |= (total + resident - 1) / resident * resident - total <= total / 20 ||
                  (total > 2 * resident && total <= 3 * resident);
-  const bool pipe = !kPingPongShape && (forced == 0 ? a.Nbg > 0 || fits_pipe : forced == 1 && a.Nbg > 0);
+  bool pipe = !kPingPongShape && (forced == 0 ? a.Nbg > 0 || fits_pipe : forced == 1 && a.Nbg > 0);
+  // Pooled tokens at d 64: the ping-pong kernel has two groups of wavefronts per query block and wins where
+  // all of its workgroups start at once and their rows are long: from 16 tiles at block 128 (144 workgroups:
+  // 14 tiles 37 us against 35 pipelined, 36 tiles 65 against 76, 144 tiles 199 against 269) and 24 at
+  // block 64 (512 workgroups: 8 tiles 30 against 25, 26 tiles 45 and 48, 128 tiles 130 against 177).
+  // Lists hide their lengths: an eighth of the blocks is assumed (fixed budgets keep a quarter, the
+  // threshold alone a few per cent).
+  const int tiles = dense ? a.Nb : a.Nb / 8;
+  if (D == 64 && a.Nbg > 0 && forced == 0 && total <= (BLK == 128 ? 256 : 512) && tiles >= (BLK == 128 ? 16 : 24))
+    pipe = false;
   FwdArgs b = a;
   b.select = 0;
   hipError_t e = hipSuccess;

@@ -101,6 +101,39 @@ def test_fwd_global_tokens(B, H, L, d, block, n, dens):
             assert dl <= util.LSE_ABS
 
 
+@pytest.mark.parametrize("block,H,Nb,lists,ping_pong", [
+    (128, 1, 15, False, False), (128, 1, 16, False, True),       # 16 tiles per row
+    (128, 15, 17, False, True), (128, 16, 17, False, False),     # 256 workgroups
+    (128, 1, 127, True, False), (128, 2, 128, True, True),       # lists: an eighth of the blocks is assumed
+    (64, 1, 23, False, False), (64, 1, 24, False, True),         # 24 tiles per row
+    (64, 21, 24, False, True), (64, 22, 24, False, False),       # 512 workgroups
+    (64, 1, 191, True, False), (64, 2, 192, True, True),
+])
+def test_fwd_global_tokens_on_both_sides_of_the_kernel_choice(block, H, Nb, lists, ping_pong):
+    """d = 64.  Which kernel ran shows in the last bits: auto equals the forced ping-pong kernel exactly where
+    the choice falls on it, and agrees with the other one up to the rounding of P and O (bf16)."""
+    L, n = Nb * block - 9, 100
+    print(f"case H={H} L={L} block={block} lists={lists}", flush=True)
+    p = binding.Params(B=1, H=H, L=L, d=64, block=block)
+    q, k, v = (util.dev_bf16(synth.make_iid((1, H, L, 64), Nb, s)) for s in range(3))
+    bufs = {"row_ptr": None, "col_idx": None}
+    if lists:
+        bufs = util.lists_from_mask(p, synth.random_block_mask(Nb, 0.1, seed=H, slabs=H), with_csc=False)
+    o, lse, _, _, _ = _run_fwd_g(p, n, q, k, v, bufs)
+    other = {}
+    for which in (1, 2):
+        binding.asa_test_force_fwd_kernel(which)
+        try:
+            other[which] = _run_fwd_g(p, n, q, k, v, bufs)[:2]
+        finally:
+            binding.asa_test_force_fwd_kernel(0)
+        util.assert_close_bf16(util.host_f32(o), util.host_f32(other[which][0]), f"O, kernel {which}")
+        assert float((lse - other[which][1]).abs().max()) <= util.LSE_ABS
+    same = {w: torch.equal(o.view(torch.int16), x[0].view(torch.int16)) and torch.equal(lse, x[1])
+            for w, x in other.items()}
+    assert same == {1: not ping_pong, 2: ping_pong}
+
+
 def test_fwd_global_tokens_dense_lists_and_residual():
     p = binding.Params(B=1, H=1, L=640, d=128, block=128)
     n = 32
