@@ -812,7 +812,13 @@ __global__ __launch_bounds__(128) void csr_fill_kernel(const uint8_t *mask, int 
 // Nb = 256, 12 slabs: 15 -> 13 us; Nb = 278, 48 slabs: 65 -> 24 us, against one thread per row or column that
 // counts byte by byte out of LDS.  (Bytes straight from global memory instead of the copy: 22 and
 // 48 us, bound by the address unit.)
-constexpr int kCsrBitsMaxNb = 352;               // mask, bits and counts in 160 KB of LDS
+// Up to 352 blocks (mask, bits and counts: 142 of 160 KB of LDS).  From 320 blocks on, with few slabs, the
+// three launches above are faster than one copy of the whole mask per workgroup: 352 blocks, 1 .. 8 slabs, both
+// directions 16.4 us against 20.3 .. 21.5, 12 slabs 20.9 and 22.0, 24 slabs 33 and 24; rows only, up to
+// 32 slabs 16 .. 19 against 20 .. 23; 320 blocks, 8 slabs 16.5 and 17.3, rows only 16.0 and 16.2
+constexpr int kCsrBitsMaxNb = 352;
+// (48 slabs 21.2 and 18.7).
+constexpr int kCsrThreeNb = 320, kCsrThreeSlabs = 12, kCsrThreeSlabsRows = 32;
 constexpr int kCsrWords = (kCsrBitsMaxNb + 63) / 64;
 __global__ __launch_bounds__(1024) void csr_bits_kernel(const uint8_t *mask, int Nb, int32_t *row_ptr,
                                                         int32_t *col_idx, int32_t *col_ptr,
@@ -902,7 +908,8 @@ __global__ __launch_bounds__(1024) void csr_bits_kernel(const uint8_t *mask, int
 
 hipError_t launch_csr(const Problem &pb, const uint8_t *mask, int32_t *row_ptr, int32_t *col_idx,
                       int32_t *col_ptr, int32_t *row_idx, hipStream_t st) {
-  if (pb.Nb <= kCsrBitsMaxNb) {
+  const int few = col_ptr ? kCsrThreeSlabs : kCsrThreeSlabsRows;
+  if (pb.Nb < kCsrThreeNb || (pb.Nb <= kCsrBitsMaxNb && pb.n_slabs > few)) {
     // as many parts as keep one workgroup per compute unit, at most one per 16 rows
     const int n_dir = col_ptr ? 2 : 1;
     const int most = (pb.Nb + 15) / 16;

@@ -96,12 +96,13 @@ def test_index_lists_match_the_mask(Nb, dens):
         assert np.array_equal(gci[s, :n], ci[s, :n]) and np.array_equal(gri[s, :n], ri[s, :n])
 
 
-@pytest.mark.parametrize("Nb", [2, 63, 64, 65, 127, 129, 320, 351, 352, 353])
+@pytest.mark.parametrize("Nb,slabs", [(Nb, 3) for Nb in (2, 63, 64, 65, 127, 129, 319, 320, 351, 352, 353, 384)] +
+                         [(Nb, s) for s in (12, 13, 32, 33) for Nb in (320, 352)])
 @pytest.mark.parametrize("with_csc", [True, False])
-def test_index_lists_at_the_edges_of_the_64_block_pieces(Nb, with_csc):
-    """The lists are cut out of 64 x 64 pieces of the mask, up to Nb = 352 in one kernel; whole numbers,
-    compared exactly.  Mask values other than 1 count as kept."""
-    slabs = 3
+def test_index_lists_at_the_edges_of_the_64_block_pieces(Nb, slabs, with_csc):
+    """The lists are cut out of 16 x 64 pieces of the mask, up to Nb = 352 in one kernel (from 320 on with
+    more than 12 slabs, rows only 32); whole numbers, compared exactly.  Mask values other
+    than 1 count as kept."""
     p = binding.Params(B=1, H=slabs, L=Nb * 64 - 7, d=64, block=64)
     mask = synth.random_block_mask(Nb, 0.3, seed=Nb, slabs=slabs)
     mask[0, Nb // 2, :] = 0
