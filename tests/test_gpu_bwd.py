@@ -179,3 +179,17 @@ def test_bwd_list_lengths_and_tails(block, d, tail):
         mask[1, i, :i + 1] = 1       # rows of 1 .. 6, columns of 6 .. 1
     _check_bwd(p, qb, kb, vb, gb, mask, use_mag=True)
     _check_bwd(p, qb, kb, vb, gb, mask, with_lo=False, use_mag=True)
+
+
+@pytest.mark.parametrize("d,block", [(128, 64), (64, 128)])
+def test_bwd_without_the_low_half_does_not_depend_on_o(d, block):
+    """Delta then comes from the tiles: an O of NaN gives the same gradients bit for bit."""
+    L = 5 * block + 7
+    p = binding.Params(B=1, H=2, L=L, d=d, block=block)
+    q, k, v, g = (util.dev_bf16(synth.make_iid((1, 2, L, d), 5, s)) for s in range(4))
+    bufs = util.lists_from_mask(p, synth.random_block_mask(p.Nb, 0.5, seed=3, slabs=2))
+    o, lse = util.run_fwd(p, q, k, v, bufs)
+    want = util.run_bwd(p, q, k, v, o, lse, g, bufs)
+    got = util.run_bwd(p, q, k, v, torch.full_like(o, float("nan")), lse, g, bufs)
+    for a, b in zip(got, want):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
