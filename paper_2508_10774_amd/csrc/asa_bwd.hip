@@ -28,9 +28,9 @@ namespace asa {
 constexpr float kLog2e = 1.44269504088896340736f;
 
 // ---------------------------------------------------------------------------------------
-// Row statistics of the backward, padded to whole blocks (pitch Lpad) so that the kernels can
-// fetch 64 of them without a bounds test:
-//   delta[slab][row] = sum_x dO[row][x] * (O[row][x] + O_lo[row][x])  (fp32), 0 past L
+// Row statistics of the backward, three rows of Lpad values per slab, padded to whole blocks so that the
+// kernels can fetch 64 of them without a bounds test:
+//   ndelta[slab][row] = - sum_x dO[row][x] * (O[row][x] + O_lo[row][x])  (fp32), 0 past L
 //   lse2[slab][row]  = LSE[row] * log2(e), +inf past L (every probability of such a row is 0)
 //   lse2g            = lse2 - bias (for keys whose scores carry an additive bias), if asked for
 // D / 8 lanes per row, 16 bytes each (bound: HBM; with 16 lanes per row at d = 64, half of them idle,
@@ -57,7 +57,7 @@ __global__ __launch_bounds__(256) void delta_kernel(const void *o, const void *o
 #pragma unroll
   for (int off = kLanes / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
   if (row < Lpad && sub == 0) {
-    const int64_t at = (int64_t)slab * Lpad + row;
+    const int64_t at = 3 * (int64_t)slab * Lpad + row;
     const float l2 = row < L ? lse[(int64_t)slab * L + row] * kLog2e : INFINITY;
     ndelta[at] = -acc;
     lse2[at] = l2;
@@ -72,7 +72,7 @@ __global__ __launch_bounds__(256) void lse2_kernel(int L, int Lpad, const float 
                                                    float *lse2, float *lse2g) {
   const int slab = blockIdx.y, row = blockIdx.x * 256 + threadIdx.x;
   if (row >= Lpad) return;
-  const int64_t at = (int64_t)slab * Lpad + row;
+  const int64_t at = 3 * (int64_t)slab * Lpad + row;
   const float l2 = row < L ? lse[(int64_t)slab * L + row] * kLog2e : INFINITY;
   lse2[at] = l2;
   if (lse2g) lse2g[at] = l2 - bias_log2;
@@ -80,7 +80,7 @@ __global__ __launch_bounds__(256) void lse2_kernel(int L, int Lpad, const float 
 
 struct BwdArgs {
   const void *q, *k, *v, *d_o;
-  const float *lse2, *ndelta; // [slab][Lpad]: LSE * log2(e) (minus this launch's key bias), -Delta; padded with +inf, 0
+  const float *lse2, *ndelta; // [slab][Lpad], slabs 3 Lpad apart: LSE * log2(e) (minus this launch's key bias), -Delta; padded with +inf, 0
   float *ndelta_out;          // where the Delta-only walk of dq_kernel writes (the same array as ndelta)
   const int32_t *row_ptr, *col_idx, *col_ptr, *row_idx;
   void *dq, *dk, *dv;
@@ -207,10 +207,10 @@ __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kDqWavesPerSimd)) void dq
     greg[s] = *reinterpret_cast<const bf16x8 *>(gs + (int64_t)qrow_c * a.to.sL + 16 * s + 8 * hl);
   }
   // rows past L have LSE = +inf there, so that every probability is exactly zero
-  const float lse2 = a.lse2[(int64_t)slab * a.Lpad + qrow];
+  const float lse2 = a.lse2[3 * (int64_t)slab * a.Lpad + qrow];
   // dP starts from -Delta instead of zero (the subtraction then costs nothing) where 16 registers for
   // it do not cost a wavefront
-  const float ndelta = DELTA_ONLY ? 0.f : a.ndelta[(int64_t)slab * a.Lpad + qrow];
+  const float ndelta = DELTA_ONLY ? 0.f : a.ndelta[3 * (int64_t)slab * a.Lpad + qrow];
   constexpr bool kInitDelta = !(BLK == 128 && D == 128) || DELTA_ONLY;
   f32x16 nd16;
 #pragma unroll
@@ -485,7 +485,7 @@ __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kDqWavesPerSimd)) void dq
   if (DELTA_ONLY) {
     // the two lane halves hold different keys of the same query; rows past L get 0 (their P is 0)
     const float total = dsum + swap_halves(dsum);
-    if (hl == 0) a.ndelta_out[(int64_t)slab * a.Lpad + qrow] = -total;
+    if (hl == 0) a.ndelta_out[3 * (int64_t)slab * a.Lpad + qrow] = -total;
     return;
   }
   if (qvalid) {
@@ -533,8 +533,9 @@ __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dkv_
   const bf16 *vs = slab_ptr(a.v, a.tv, slab, a.H);
   const bf16 *gs = slab_ptr(a.d_o, a.to, slab, a.H);
   // lanes 0..31 fetch the 32 LSE values of a tile, lanes 32..63 its 32 negated Deltas (both arrays
-  // are padded to whole blocks: no bounds test; the host puts lse2 behind ndelta, less than 4 GiB away)
-  const float *stat_s = a.ndelta + (int64_t)slab * a.Lpad;
+  // are padded to whole blocks: no bounds test; the LSE values of a slab stand one or two rows of Lpad
+  // values behind its Deltas, so the distance fits 32 bits)
+  const float *stat_s = a.ndelta + 3 * (int64_t)slab * a.Lpad;
   const uint32_t stat_off = (uint32_t)(n * 4) + (hl ? 0u : (uint32_t)((a.lse2 - a.ndelta) * 4));
   const bool dense = a.col_ptr == nullptr;   // no index lists: every query block
   const int t_begin = dense ? 0 : a.col_ptr[slab * (a.Nb + 1) + kb];
@@ -873,7 +874,7 @@ static size_t rowstat_bytes(const Problem &pb) {
   return round256((size_t)pb.n_slabs * pb.Lpad * sizeof(float));
 }
 size_t bwd_workspace_bytes(const Problem &pb) {
-  // three [slab][Lpad] fp32 arrays (Delta, LSE in log2 units, the same minus the pooled keys'
+  // [slab][3][Lpad] fp32 (-Delta, LSE in log2 units, the same minus the pooled keys'
   // bias), then the orders of the dK / dV and of the dQ workgroups
   return 3 * rowstat_bytes(pb) + 2 * order_bytes(pb);
 }
@@ -967,8 +968,8 @@ hipError_t launch_bwd(const Problem &pb, const void *q, const void *k, const voi
   unsigned char *ws = reinterpret_cast<unsigned char *>(workspace);
   const size_t rb = rowstat_bytes(pb);
   float *ndelta = reinterpret_cast<float *>(ws);
-  float *lse2 = reinterpret_cast<float *>(ws + rb);
-  float *lse2g = reinterpret_cast<float *>(ws + 2 * rb);
+  float *lse2 = ndelta + pb.Lpad;
+  float *lse2g = ndelta + 2 * pb.Lpad;
   int32_t *order = reinterpret_cast<int32_t *>(ws + 3 * rb);
 
   hipError_t e = hipSuccess;
