@@ -85,15 +85,20 @@ __device__ __forceinline__ void lds_dma16(const void *src, void *lds_dst) {
 // with an explicit vmcnt before reading the LDS image, and a kernel that uses this form uses
 // it for all of its direct loads (M0 is written here).
 // lds_byte_addr is the wave-uniform LDS address (lds_addr_of() of the LDS array + offset).
+// The load takes its base from a scalar copy made in front of it: a vector memory instruction must not
+// read a scalar register within 5 wait states of the vector instruction (v_readfirstlane, v_readlane of a
+// spilled register) that wrote it; the hardware does not check, the compiler does not look in here, and a
+// scalar move may read it at once.  The copy also is the wait state between M0 and the load.
 // FORCE = false leaves the operands as the compiler has them (it must then know them to be
 // uniform, or the assembler rejects the instruction).
 template <bool FORCE = true>
 __device__ __forceinline__ void lds_dma16_sv(const void *uniform_base, uint32_t lane_off,
                                              uint32_t lds_byte_addr) {
 #if defined(__HIP_DEVICE_COMPILE__)
+  uint64_t base_copy;
   if (!FORCE) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :: "v"(lane_off), "s"(uniform_base), "s"(lds_byte_addr) : "memory");
+    asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0"
+                 : "=&s"(base_copy) : "v"(lane_off), "s"(uniform_base), "s"(lds_byte_addr) : "memory");
     return;
   }
   // (readfirstlane costs nothing where the compiler already knows the value to be uniform and
@@ -103,18 +108,21 @@ __device__ __forceinline__ void lds_dma16_sv(const void *uniform_base, uint32_t 
   // into the high one)
   const uint64_t bu = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b) |
                       ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32)) << 32);
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-               :: "v"(lane_off), "s"(bu), "s"((uint32_t)__builtin_amdgcn_readfirstlane(lds_byte_addr)) : "memory");
+  asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0"
+               : "=&s"(base_copy)
+               : "v"(lane_off), "s"(bu), "s"((uint32_t)__builtin_amdgcn_readfirstlane(lds_byte_addr)) : "memory");
 #endif
 }
 // The same with 4 bytes per lane.
 __device__ __forceinline__ void lds_dma4_sv(const void *uniform_base, uint32_t lane_off, uint32_t lds_byte_addr) {
 #if defined(__HIP_DEVICE_COMPILE__)
+  uint64_t base_copy;
   const uint64_t b = reinterpret_cast<uint64_t>(uniform_base);
   const uint64_t bu = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b) |
                       ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32)) << 32);
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
-               :: "v"(lane_off), "s"(bu), "s"((uint32_t)__builtin_amdgcn_readfirstlane(lds_byte_addr)) : "memory");
+  asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dword %1, %0"
+               : "=&s"(base_copy)
+               : "v"(lane_off), "s"(bu), "s"((uint32_t)__builtin_amdgcn_readfirstlane(lds_byte_addr)) : "memory");
 #endif
 }
 // LDS byte address of an object that the compiler knows to live in LDS (apply it to the

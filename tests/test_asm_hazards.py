@@ -1,0 +1,140 @@
+"""Wait states around the instructions that the kernels write out themselves.
+
+The compiler places the wait states that the hardware does not enforce, but it does not look into inline
+assembly.  All tile loops write out direct-to-LDS loads.  These tests compile the sources to assembly and
+walk it backwards from each such instruction, over branches too:
+
+  a vector instruction that writes the scalar base of a load: 5 wait states before it
+"""
+
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2508_10774_amd import build
+
+LOAD_BASE = 5
+
+
+def _regs(text):
+    """The registers named in an operand list: {"v4", "a0", "s20", ...}."""
+    out = set()
+    for kind, lo, hi, one in re.findall(r"\b([vas])(?:\[(\d+):(\d+)\]|(\d+)\b)", text):
+        out.update(f"{kind}{i}" for i in (range(int(lo), int(hi) + 1) if lo else [int(one)]))
+    if re.search(r"\bvcc\b", text):
+        out.add("vcc")
+    return out
+
+
+class Listing:
+    """Instructions of one function with their predecessors and successors."""
+
+    def __init__(self, lines):
+        self.ins, labels, pending = [], {}, []
+        for line in lines:
+            inline = "ASMSTART" in line
+            line = line.split(";")[0].split("//")[0].strip()
+            if inline or not line or line.startswith("."):
+                if re.match(r"\.LBB\w+:", line):
+                    pending.append(line.split(":")[0])
+                continue
+            for name in pending:
+                labels[name] = len(self.ins)
+            pending = []
+            op, _, rest = line.partition(" ") if " " in line else line.partition("\t")
+            self.ins.append((op.strip(), rest.strip()))
+        n = len(self.ins)
+        self.succ, self.pred = [[] for _ in range(n)], [[] for _ in range(n)]
+        for i, (op, rest) in enumerate(self.ins):
+            to = []
+            if op.startswith(("s_branch", "s_cbranch")):
+                to += [labels[x] for x in re.findall(r"\.LBB\w+", rest) if x in labels]
+            if op not in ("s_branch", "s_endpgm", "s_setpc_b64") and i + 1 < n:
+                to.append(i + 1)
+            for t in to:
+                self.succ[i].append(t)
+                self.pred[t].append(i)
+
+    def _within(self, start, steps, states, stop=lambda j: False):
+        """(instruction, wait states between it and `start`) for everything closer than `states`; no further
+        than an instruction at which stop() holds."""
+        todo, best = [(j, 0) for j in steps[start]], {}
+        while todo:
+            j, ws = todo.pop()
+            if ws >= states or best.get(j, states) <= ws:
+                continue
+            best[j] = ws
+            if stop(j):
+                continue
+            op, rest = self.ins[j]
+            ws += int(rest, 0) + 1 if op == "s_nop" else 1
+            todo += [(t, ws) for t in steps[j]]
+        return best
+
+    def _writes(self, j):
+        op, rest = self.ins[j]
+        first = rest.split(",")[0]
+        if op.startswith(("v_cmp", "v_div_scale")) or "_co_" in op:
+            return _regs(",".join(rest.split(",")[:2]))
+        return _regs(first)
+
+    def faults(self):
+        found, seen = [], {"load": 0}
+        for i, (op, rest) in enumerate(self.ins):
+            if op.startswith("global_load_lds") and "s[" in rest:
+                seen["load"] += 1
+                for base in (x for x in _regs(rest) if x[0] == "s"):
+                    # (a scalar instruction that sets the register anew has waited for the vector one)
+                    def anew(j):
+                        return self.ins[j][0].startswith("s_") and base in self._writes(j)
+                    for j in self._within(i, self.pred, LOAD_BASE, anew):
+                        if self.ins[j][0].startswith("v_") and base in self._writes(j):
+                            found.append(f"{' '.join(self.ins[j])} too close in front of {op} {rest}")
+        return found, seen
+
+
+def _functions(text):
+    for m in re.finditer(r"^(_Z\w+):.*?^\.Lfunc_end\d+:", text, re.M | re.S):
+        yield m.group(1), m.group(0).splitlines()[1:]
+
+
+@pytest.fixture(scope="module")
+def assembly(tmp_path_factory):
+    out = tmp_path_factory.mktemp("asm")
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    running = {src: subprocess.Popen([hipcc, *build.HIPCC_FLAGS, "-S", "--cuda-device-only",
+                                      os.path.join(build.CSRC, src), "-o", str(out / src)],
+                                     stderr=subprocess.DEVNULL) for src in ("asa_bwd.hip", "asa_fwd.hip")}
+    for src, p in running.items():
+        assert p.wait() == 0, src
+    return {src: (out / src).read_text() for src in running}
+
+
+@pytest.mark.parametrize("src,kinds", [("asa_bwd.hip", ("load",)), ("asa_fwd.hip", ("load",))])
+def test_wait_states_around_written_out_instructions(assembly, src, kinds):
+    total = dict.fromkeys(("load",), 0)
+    for name, lines in _functions(assembly[src]):
+        found, seen = Listing(lines).faults()
+        assert not found, f"{name}: {found[:4]}"
+        for k in total:
+            total[k] += seen[k]
+    print(src, total)
+    assert all(total[k] > 0 for k in kinds)
+
+
+@pytest.mark.parametrize("between,faults", [("s_nop 0", 1), ("s_nop 1", 0), ("s_mov_b64 s[8:9], s[4:5]", 0)])
+def test_the_walk_finds_planted_load_hazards_over_a_branch(between, faults):
+    text = f"""\tv_readfirstlane_b32 s8, v1
+\t{between}
+\ts_branch .LBB0_2
+.LBB0_1:
+\ts_endpgm
+.LBB0_2:
+\ts_mov_b32 m0, s3
+\ts_nop 0
+\tglobal_load_lds_dwordx4 v2, s[8:9]
+\ts_branch .LBB0_1"""
+    found, seen = Listing(text.splitlines()).faults()
+    assert seen["load"] == 1 and len(found) == faults, found
