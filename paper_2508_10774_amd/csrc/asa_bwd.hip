@@ -102,6 +102,18 @@ struct BwdArgs {
   float pooled_bias_log2;
 };
 
+// The compiler places no wait states around a written-out MFMA (tests/test_asm_hazards.py walks the
+// assembly).  settle_acc in front of a loop and behind it keeps what the compiler does with the
+// accumulators (zeros, copies, reads) away from the loop's MFMAs: 2 states after a vector instruction has
+// written an operand, 19 before one reads a result.
+template <int N>
+__device__ __forceinline__ void settle_acc(f32x16 (&acc)[N]) {
+  static_assert(N == 4, "D = 128");
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_nop 15\n\ts_nop 3" : "+a"(acc[0]), "+a"(acc[1]), "+a"(acc[2]), "+a"(acc[3]));
+#endif
+}
+
 template <int BLK, int D>
 struct BwdCfg {
   static constexpr int kWaves = BLK / 32;
@@ -337,6 +349,7 @@ __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kDqWavesPerSimd)) void dq
   };
   const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
                          0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  constexpr bool kWrittenOut = C::kDqWavesPerSimd == 1 && !DELTA_ONLY;
   auto accumulate = [](f32x16 &d, bf16x8 x, bf16x8 y) __attribute__((always_inline)) {
 #if defined(__HIP_DEVICE_COMPILE__)
     if constexpr (C::kDqWavesPerSimd == 1)
@@ -468,6 +481,7 @@ __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kDqWavesPerSimd)) void dq
     }(std::make_integer_sequence<int, kDepth>{});
 #pragma unroll
     for (int s = 0; s < D / 16; ++s) row_at[s] -= first_off;
+    if constexpr (kWrittenOut) settle_acc(acc);
     if (odd) {
       body(std::integral_constant<int, 2>{}, s0, p0, s1, p1);
       body(std::integral_constant<int, 3>{}, s1, p1, s0, p0);
@@ -479,7 +493,7 @@ __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kDqWavesPerSimd)) void dq
       body(std::integral_constant<int, 3>{}, s1, p1, s0, p0);
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);          // stray copies must land before the LDS is given up
-    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    if constexpr (kWrittenOut) settle_acc(acc);
   }
 
   if (DELTA_ONLY) {
@@ -795,6 +809,10 @@ __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dkv_
 #pragma unroll
     for (int s = 0; s < D / 16; ++s) row_at[s] -= first_off;
     stat_at -= first_off;
+    if constexpr (C::kWavesPerSimd == 1) {
+      settle_acc(kacc);
+      settle_acc(vacc);
+    }
     if (odd) {
       body(std::integral_constant<int, 2>{}, s0, p0, s1, p1);
       body(std::integral_constant<int, 3>{}, s1, p1, s0, p0);
@@ -806,7 +824,10 @@ __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dkv_
       body(std::integral_constant<int, 3>{}, s1, p1, s0, p0);
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);          // stray copies must land before the LDS is given up
-    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    if constexpr (C::kWavesPerSimd == 1) {
+      settle_acc(kacc);
+      settle_acc(vacc);
+    }
   }
 
   // epilogue of one gradient: acc holds its transpose for my 32 keys

@@ -1,10 +1,13 @@
 """Wait states around the instructions that the kernels write out themselves.
 
 The compiler places the wait states that the hardware does not enforce, but it does not look into inline
-assembly.  All tile loops write out direct-to-LDS loads.  These tests compile the sources to assembly and
-walk it backwards from each such instruction, over branches too:
+assembly.  The backward kernels write out matrix instructions with accumulation registers, all tile loops
+write out direct-to-LDS loads.  These tests compile the sources to assembly and walk it backwards and
+forwards from each such instruction, over branches too:
 
-  a vector instruction that writes the scalar base of a load: 5 wait states before it
+  a vector instruction that writes an operand of a written-out MFMA: 2 wait states before it
+  anything but an MFMA that touches its result:                      19 after it (the longest MFMA)
+  a vector instruction that writes the scalar base of a load:        5 before it
 """
 
 import os
@@ -15,7 +18,7 @@ import pytest
 
 from paper_2508_10774_amd import build
 
-LOAD_BASE = 5
+MFMA_SRC, MFMA_DST, LOAD_BASE = 2, 19, 5
 
 
 def _regs(text):
@@ -81,8 +84,19 @@ class Listing:
         return _regs(first)
 
     def faults(self):
-        found, seen = [], {"load": 0}
+        found, seen = [], {"mfma": 0, "load": 0}
         for i, (op, rest) in enumerate(self.ins):
+            ops = [x.strip() for x in rest.split(",")]
+            if op.startswith("v_mfma") and ops[0].startswith("a"):
+                seen["mfma"] += 1
+                for j in self._within(i, self.pred, MFMA_SRC):
+                    o = self.ins[j][0]
+                    if o.startswith("v_") and not o.startswith("v_mfma") and self._writes(j) & _regs(rest):
+                        found.append(f"{' '.join(self.ins[j])} too close in front of {op} {rest}")
+                for j in self._within(i, self.succ, MFMA_DST):
+                    o, r = self.ins[j]
+                    if not o.startswith("v_mfma") and _regs(r) & _regs(ops[0]):
+                        found.append(f"{o} {r} too close behind {op} {rest}")
             if op.startswith("global_load_lds") and "s[" in rest:
                 seen["load"] += 1
                 for base in (x for x in _regs(rest) if x[0] == "s"):
@@ -112,9 +126,9 @@ def assembly(tmp_path_factory):
     return {src: (out / src).read_text() for src in running}
 
 
-@pytest.mark.parametrize("src,kinds", [("asa_bwd.hip", ("load",)), ("asa_fwd.hip", ("load",))])
+@pytest.mark.parametrize("src,kinds", [("asa_bwd.hip", ("mfma", "load")), ("asa_fwd.hip", ("load",))])
 def test_wait_states_around_written_out_instructions(assembly, src, kinds):
-    total = dict.fromkeys(("load",), 0)
+    total = dict.fromkeys(("mfma", "load"), 0)
     for name, lines in _functions(assembly[src]):
         found, seen = Listing(lines).faults()
         assert not found, f"{name}: {found[:4]}"
@@ -122,6 +136,31 @@ def test_wait_states_around_written_out_instructions(assembly, src, kinds):
             total[k] += seen[k]
     print(src, total)
     assert all(total[k] > 0 for k in kinds)
+
+
+LOOP = """.LBB0_1:
+\tds_read_b128 v[4:7], v20
+\t{front}
+\t{wait}
+\t;;#ASMSTART
+\tv_mfma_f32_32x32x16_bf16 a[0:15], v[4:7], v[8:11], a[0:15]
+\t;;#ASMEND
+\ts_cbranch_scc1 .LBB0_1
+\t{behind}
+\tv_accvgpr_read_b32 v30, a3
+\ts_endpgm"""
+
+
+@pytest.mark.parametrize("front,wait,behind,faults", [
+    ("v_mov_b32_e32 v12, v1", "s_nop 0", "s_nop 15\n\ts_nop 3", 0),
+    ("v_mov_b32_e32 v9, v1", "s_nop 0", "s_nop 15\n\ts_nop 3", 1),       # one state in front
+    ("v_cvt_pk_bf16_f32 v8, v1, v2", "s_nop 1", "s_nop 15\n\ts_nop 3", 0),
+    ("v_mov_b32_e32 v12, v1", "s_nop 0", "s_nop 15", 1),                 # 17 behind (branch included)
+    ("v_mov_b32_e32 v12, v1", "s_nop 0", "s_nop 15\n\ts_nop 1", 0),      # 19
+])
+def test_the_walk_finds_planted_matrix_hazards(front, wait, behind, faults):
+    found, seen = Listing(LOOP.format(front=front, wait=wait, behind=behind).splitlines()).faults()
+    assert seen["mfma"] == 1 and len(found) == faults, found
 
 
 @pytest.mark.parametrize("between,faults", [("s_nop 0", 1), ("s_nop 1", 0), ("s_mov_b64 s[8:9], s[4:5]", 0)])
