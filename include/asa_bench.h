@@ -55,10 +55,12 @@ int asa_add_rate_probe(int32_t atomic, int32_t workgroups, int32_t tiles_per_wor
 int asa_set_kernel_timing(void *start_event, void *stop_event);
 
 /*
- * Test switch: which forward kernel asa_attn_fwd launches.  0 = the library's own choice (the
- * default), 1 = the lock-step kernel only, 2 = the ping-pong kernel only (global tokens always
- * take the ping-pong kernel).  Process-wide; lets the tests put every edge case through both
- * kernels at every tile shape.  Returns an asa_status.
+ * Test switch: which forward kernel asa_attn_fwd and asa_attn_fwd_g launch.  0 = the library's own
+ * choice among its three (the default).  1 = without global tokens the lock-step kernel, which every
+ * tile shape has; with them the ping-pong kernel at block 128 / d 128, else the pipelined kernel.
+ * 2 = the ping-pong kernel where the shape has it (block 128 / d 128; with global tokens also d 64),
+ * else as 0.  Process-wide; lets the tests put their edge cases through kernels that the library
+ * chooses at larger sizes only.  Returns an asa_status.
  */
 int asa_test_force_fwd_kernel(int which);
 

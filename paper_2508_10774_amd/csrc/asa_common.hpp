@@ -54,8 +54,8 @@ void timing_end(hipStream_t st);
 // hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes), issued once per
 // (kernel, device) under a lock; later calls only look the pair up.
 hipError_t set_dynamic_lds_once(const void *fn, int bytes);
-// Which forward kernel the tests asked for (asa_test_force_fwd_kernel): 0 = the library's own
-// choice, 1 = the lock-step kernel, 2 = the ping-pong kernel.
+// Which forward kernel the tests asked for (asa_test_force_fwd_kernel in asa_bench.h): 0 = the
+// library's own choice, 1 = lock-step, 2 = ping-pong, where the call has them.
 int forced_fwd_kernel();
 
 // launchers (each returns a hipError_t from the launch)

@@ -178,7 +178,7 @@ struct FwdArgs {
   const void *vg;     // [slab][Nbg * block][d] bf16 pooled values
   int Lg, Nbg;        // pooled tokens per slab, key blocks they fill
   float bias_log2;    // log2(n): the additive ln(n) of the pooled scores, in the exp2 domain
-  // Choice between the two kernels per (batch, head) slab, made on the device from the slab's
+  // Choice between ping-pong and lock-step per (batch, head) slab, made on the device from the slab's
   // tile count: 0 = this launch takes every slab; +1 = only slabs whose rows hold at least
   // `select_min_tiles` tiles on average; -1 = only the others.
   int select, select_min_tiles;
@@ -215,8 +215,9 @@ struct FwdCfg {
 // Lock-step kernel: one workgroup per query block, all wavefronts in lock step.  With two LDS
 // stages (2 x 32 KB at d = 128) the copies of step s + 1 are requested right after the barrier
 // that opens step s; with one, the copies of a step are waited for right away and the other
-// workgroups on the CU compute meanwhile.  It serves large block 64 / d 64 calls and, at block 128 /
-// d 128, short rows and tensors that the ping-pong kernel below does not take (slabs of 4 GiB and more).
+// workgroups on the CU compute meanwhile.  It serves large block 64 / d 64 calls, large dense calls at the
+// mixed shapes and, at block 128 / d 128, short rows and tensors that the ping-pong kernel below does
+// not take (slabs of 4 GiB and more).
 // VT: the operand of the second product comes from the transposed copy of V (one 16-byte read)
 // instead of the rows of V (two transposing reads).
 template <int BLK, int D, bool VT>
@@ -1156,7 +1157,8 @@ __global__ __launch_bounds__(BLK * 2, (PipeCfg<BLK, D>::kWavesPerSimd)) void fwd
       ([&]() __attribute__((always_inline)) {
         constexpr int x = X;
         if constexpr (x == kBar) {
-          // K of tile t + 2 and V of tile t have landed (everyone's copies)
+          // K of tile t + 2 and V of tile t + 1 have landed (everyone's copies).  V of tile t landed one
+          // barrier earlier: the zeros that a ragged tile writes into it above rely on that.
           __builtin_amdgcn_s_waitcnt(0x0F70);
           asm volatile("s_barrier" ::: "memory");
           __builtin_amdgcn_sched_barrier(0);
@@ -1344,10 +1346,37 @@ static hipError_t launch_lock_step(const FwdArgs &a, int grid, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <int BLK, int D, bool GT>
+static hipError_t launch_pipe(const FwdArgs &a, int grid, hipStream_t st) {
+  using X = PipeCfg<BLK, D>;
+  const hipError_t e = set_dynamic_lds_once(reinterpret_cast<const void *>(&fwd_pipe_kernel<BLK, D, GT>), X::kLds);
+  if (e != hipSuccess) return e;
+  timing_begin(st);
+  hipLaunchKernelGGL((fwd_pipe_kernel<BLK, D, GT>), dim3(grid), dim3(X::kThreads), X::kLds, st, a);
+  return hipGetLastError();
+}
+
+// with a.select: the slabs of fewer than select_min_tiles tiles per row are left out
+template <int BLK, int D, bool GT>
+static hipError_t launch_ping_pong(const FwdArgs &a, int grid, hipStream_t st) {
+  using P = PpCfg<BLK, D>;
+  hipError_t e = launch_transpose(a.v, a.tv, a.H, a.L, a.Lpad, BLK, D, a.n_slabs, a.vt, st,
+                                  a.select ? a.row_ptr : nullptr, a.Nb, a.select_min_tiles * a.Nb);
+  if (e == hipSuccess && GT) {
+    // the pooled values: contiguous [slab][Nbg * block][d]
+    TensorView tvg;
+    tvg.sL = D; tvg.sH = (int64_t)a.Nbg * BLK * D; tvg.sB = tvg.sH * a.H;
+    e = launch_transpose(a.vg, tvg, a.H, a.Lg, a.Nbg * BLK, BLK, D, a.n_slabs, a.vgt, st);
+  }
+  if (e == hipSuccess) e = set_dynamic_lds_once(reinterpret_cast<const void *>(&fwd_pp_kernel<BLK, D, GT>), P::kLdsBytes);
+  if (e != hipSuccess) return e;
+  timing_begin(st);
+  hipLaunchKernelGGL((fwd_pp_kernel<BLK, D, GT>), dim3(grid), dim3(P::kThreads), P::kLdsBytes, st, a);
+  return hipGetLastError();
+}
+
 template <int BLK, int D>
 static hipError_t launch_fwd_t(const FwdArgs &a, hipStream_t st) {
-  using P = PpCfg<BLK, D>;
-  using X = PipeCfg<BLK, D>;
   const int total = a.n_slabs * a.Nb, grid = xcd_grid(total);
   // Which kernel.  Measured on MI355X, the transposition of V included where a kernel needs it:
   //   block 128 / d 128, long rows: ping-pong 1.56 ms, pipelined 1.84 ms (12 heads of 32 760 tokens, a
@@ -1368,79 +1397,55 @@ static hipError_t launch_fwd_t(const FwdArgs &a, hipStream_t st) {
   //     lengths from the host and stay pipelined: rows of one length are then 2-6 % slower than
   //     lock-step beyond 1000 workgroups (11 % at 1600 of 10 tiles, block 64 / d 128), uneven ones up to
   //     1.5x faster.
+  //   pooled tokens: ping-pong at block 128 / d 128, pipelined otherwise, except at d 64 where all ping-pong
+  //     workgroups (two groups of wavefronts per query block) start at once and their rows are long: from
+  //     16 tiles at block 128 (144 workgroups: 14 tiles 37 us against 35 pipelined, 36 tiles 65 against
+  //     76, 144 tiles 199 against 269) and 24 at block 64 (512 workgroups: 8 tiles 30 against 25, 26
+  //     tiles 45 and 48, 128 tiles 130 against 177).  Lists hide their lengths: an eighth of the blocks is
+  //     assumed (fixed budgets keep a quarter, the threshold alone a few per cent).
   // The ping-pong kernel addresses K tiles by 32-bit byte offsets inside a slab: slabs of 4 GiB and
-  // more take one of the others.  The tests can force the ping-pong or the lock-step kernel
-  // (asa_test_force_fwd_kernel).
+  // more take the lock-step kernel.  The tests can force the ping-pong (2) or the lock-step kernel (1) where
+  // the shape has it (asa_test_force_fwd_kernel).
   const bool fits32 = (uint64_t)a.Nb * BLK * (uint64_t)a.tk.sL * 2u < 0xFFFFFFFFull;
-  if (a.Nbg > 0 && (!fits32 || a.Nb + a.Nbg > kMaxNb || a.tk.sL != D)) return hipErrorNotSupported;
+  const bool pooled = a.Nbg > 0, dense = a.row_ptr == nullptr;
+  if (pooled && (!fits32 || a.Nb + a.Nbg > kMaxNb || a.tk.sL != D)) return hipErrorNotSupported;
   const int forced = forced_fwd_kernel();
   constexpr bool kPingPongShape = BLK == 128 && D == 128, kSmallTile = BLK == 64 && D == 64;
-  const bool dense = a.row_ptr == nullptr;
-  const int resident = kSmallTile ? 1024 : 512;      // pipelined workgroups on the chip
-  bool fits_pipe = total <= resident || (!kSmallTile && !dense);
-  if (BLK == 64 && D == 128)
-    fits_pipe |= (total + resident - 1) / resident * resident - total <= total / 20 ||
-                 (total > 2 * resident && total <= 3 * resident);
-  bool pipe = !kPingPongShape && (forced == 0 ? a.Nbg > 0 || fits_pipe : forced == 1 && a.Nbg > 0);
-  // Pooled tokens at d 64: the ping-pong kernel has two groups of wavefronts per query block and wins where
-  // all of its workgroups start at once and their rows are long: from 16 tiles at block 128 (144 workgroups:
-  // 14 tiles 37 us against 35 pipelined, 36 tiles 65 against 76, 144 tiles 199 against 269) and 24 at
-  // block 64 (512 workgroups: 8 tiles 30 against 25, 26 tiles 45 and 48, 128 tiles 130 against 177).
-  // Lists hide their lengths: an eighth of the blocks is assumed (fixed budgets keep a quarter, the
-  // threshold alone a few per cent).
-  const int tiles = dense ? a.Nb : a.Nb / 8;
-  if (D == 64 && a.Nbg > 0 && forced == 0 && total <= (BLK == 128 ? 256 : 512) && tiles >= (BLK == 128 ? 16 : 24))
-    pipe = false;
   FwdArgs b = a;
   b.select = 0;
-  hipError_t e = hipSuccess;
-  if (pipe) {
-    const void *fn = a.Nbg > 0 ? reinterpret_cast<const void *>(&fwd_pipe_kernel<BLK, D, true>)
-                               : reinterpret_cast<const void *>(&fwd_pipe_kernel<BLK, D, false>);
-    e = set_dynamic_lds_once(fn, X::kLds);
-    if (e != hipSuccess) return e;
-    timing_begin(st);
-    if (a.Nbg > 0)
-      hipLaunchKernelGGL((fwd_pipe_kernel<BLK, D, true>), dim3(grid), dim3(X::kThreads), X::kLds, st, b);
-    else
-      hipLaunchKernelGGL((fwd_pipe_kernel<BLK, D, false>), dim3(grid), dim3(X::kThreads), X::kLds, st, b);
-    return hipGetLastError();
-  }
-  // Short lists at block 128 / d 128: the ping-pong kernel costs ~8 us per workgroup around its steady
-  // state, the lock-step kernel ~3 us; they cross at 16-20 tiles per row.  The host cannot see the
-  // lists, so with lists BOTH kernels are launched and each workgroup leaves at once if its (batch,
-  // head) slab's tile count belongs to the other kernel (the launch that finds nothing to do costs
-  // 4-10 us); the transposition of V leaves out the slabs of the lock-step kernel, which reads the
-  // rows of V themselves there.  Without lists (dense) every row holds Nb tiles and the choice is
-  // made here.
-  constexpr int kPingPongMinTiles = 18;
-  b.select_min_tiles = kPingPongMinTiles;
-  const bool dense_short = !a.row_ptr && a.Nbg == 0 && a.Nb < kPingPongMinTiles && forced == 0;
-  if (fits32 && (a.Nbg > 0 || forced == 2 || (forced == 0 && kPingPongShape)) && !dense_short) {
-    const bool both = a.Nbg == 0 && a.row_ptr && forced == 0;
-    if (both) b.select = 1;
-    e = launch_transpose(a.v, a.tv, a.H, a.L, a.Lpad, BLK, D, a.n_slabs, a.vt, st, both ? a.row_ptr : nullptr,
-                         a.Nb, kPingPongMinTiles * a.Nb);
-    if (e == hipSuccess && a.Nbg > 0) {
-      // the pooled values: contiguous [slab][Nbg * block][d]
-      TensorView tvg;
-      tvg.sL = D; tvg.sH = (int64_t)a.Nbg * BLK * D; tvg.sB = tvg.sH * a.H;
-      e = launch_transpose(a.vg, tvg, a.H, a.Lg, a.Nbg * BLK, BLK, D, a.n_slabs, a.vgt, st);
+  if constexpr (!kPingPongShape) {
+    const int resident = kSmallTile ? 1024 : 512;      // pipelined workgroups on the chip
+    if (pooled) {
+      if constexpr (D == 64) {
+        const int tiles = dense ? a.Nb : a.Nb / 8;
+        const bool few_and_long = total <= (BLK == 128 ? 256 : 512) && tiles >= (BLK == 128 ? 16 : 24);
+        if (forced == 2 || (forced == 0 && few_and_long)) return launch_ping_pong<BLK, D, true>(b, grid, st);
+      }
+      return launch_pipe<BLK, D, true>(b, grid, st);
     }
-    if (e != hipSuccess) return e;
-    const void *fn = a.Nbg > 0 ? reinterpret_cast<const void *>(&fwd_pp_kernel<BLK, D, true>)
-                               : reinterpret_cast<const void *>(&fwd_pp_kernel<BLK, D, false>);
-    e = set_dynamic_lds_once(fn, P::kLdsBytes);
-    if (e != hipSuccess) return e;
-    timing_begin(st);
-    if (a.Nbg > 0)
-      hipLaunchKernelGGL((fwd_pp_kernel<BLK, D, true>), dim3(grid), dim3(P::kThreads), P::kLdsBytes, st, b);
-    else
-      hipLaunchKernelGGL((fwd_pp_kernel<BLK, D, false>), dim3(grid), dim3(P::kThreads), P::kLdsBytes, st, b);
-    e = hipGetLastError();
-    if (e != hipSuccess || !both) return e;
-    b.select = -1;
-    if constexpr (kPingPongShape) return launch_lock_step<BLK, D, false>(b, grid, st);
+    bool fits_pipe = total <= resident || (!kSmallTile && !dense);
+    if (BLK == 64 && D == 128)
+      fits_pipe |= (total + resident - 1) / resident * resident - total <= total / 20 ||
+                   (total > 2 * resident && total <= 3 * resident);
+    if (fits_pipe && forced != 1) return launch_pipe<BLK, D, false>(b, grid, st);
+  } else {
+    if (pooled) return launch_ping_pong<BLK, D, true>(b, grid, st);
+    // Short lists: the ping-pong kernel costs ~8 us per workgroup around its steady state, the lock-step
+    // kernel ~3 us; they cross at 16-20 tiles per row.  The host cannot see the lists, so with lists
+    // BOTH kernels are launched and each workgroup leaves at once if its (batch, head) slab's tile count
+    // belongs to the other kernel (the launch that finds nothing to do costs 4-10 us); the transposition
+    // of V leaves out the slabs of the lock-step kernel, which reads the rows of V themselves there.
+    // Without lists (dense) every row holds Nb tiles and the choice is made here.
+    constexpr int kPingPongMinTiles = 18;
+    b.select_min_tiles = kPingPongMinTiles;
+    if (fits32 && forced != 1 && !(forced == 0 && dense && a.Nb < kPingPongMinTiles)) {
+      const bool both = forced == 0 && !dense;
+      if (both) b.select = 1;
+      const hipError_t e = launch_ping_pong<BLK, D, false>(b, grid, st);
+      if (e != hipSuccess || !both) return e;
+      b.select = -1;
+      return launch_lock_step<BLK, D, false>(b, grid, st);
+    }
   }
   // The lock-step kernel reads V's rows or their transposed copy.  Block 64 / d 64: 1.25 ms, or 1.20 ms +
   // 0.035 for the copy (48 heads of 17 776 tokens).  Mixed shapes: the rows cost more per tile, the copy costs
@@ -1448,7 +1453,7 @@ static hipError_t launch_fwd_t(const FwdArgs &a, hipStream_t st) {
   // 43 and 48 us, 79 tiles 170 and 166; block 128 / d 64: 20 tiles 109 and 118, 79 tiles 311 and 303).
   const bool copy_v = kSmallTile || (!kPingPongShape && a.L >= 3584);
   if (copy_v) {
-    e = launch_transpose(a.v, a.tv, a.H, a.L, a.Lpad, BLK, D, a.n_slabs, a.vt, st);
+    const hipError_t e = launch_transpose(a.v, a.tv, a.H, a.L, a.Lpad, BLK, D, a.n_slabs, a.vt, st);
     if (e != hipSuccess) return e;
   }
   timing_begin(st);

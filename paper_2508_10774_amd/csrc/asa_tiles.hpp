@@ -70,17 +70,9 @@ __device__ __forceinline__ bf16x4 lds_read_tr16(const lds_char *p) {
 #endif
 }
 
-// One direct global->LDS load: every lane fetches 16 bytes from its own global address and the
-// wavefront's 64 x 16 B land contiguously at the (wave-uniform) LDS address.  Counted by vmcnt.
-// (The builtin only exists in the device pass; the host pass needs no body.)
-__device__ __forceinline__ void lds_dma16(const void *src, void *lds_dst) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  __builtin_amdgcn_global_load_lds(src, (lds_void *)lds_dst, 16, 0, 0);
-#endif
-}
-
-// The same load with the address split into a wave-uniform 64-bit base (scalar registers) and
-// a 32-bit per-lane byte offset: stepping to another tile then costs scalar adds only and the
+// One direct global->LDS load: every lane fetches 16 bytes and the wavefront's 64 x 16 B land contiguously
+// at the (wave-uniform) LDS address; counted by vmcnt.  The address is split into a wave-uniform 64-bit
+// base (scalar registers) and a 32-bit per-lane byte offset: stepping to another tile then costs scalar adds only and the
 // per-lane offsets stay 32 bits wide.  The compiler does not see this load: the caller waits
 // with an explicit vmcnt before reading the LDS image, and a kernel that uses this form uses
 // it for all of its direct loads (M0 is written here).
@@ -153,29 +145,15 @@ struct RowTileCopy {
       off[i] = (uint32_t)(row * pitch_bytes + ((pos ^ k_swz<D>(row)) * 16));
     }
   }
-  // copy the ROWS complete rows that start at byte address `base` into `stage`
   // row of the tile that instruction i of this lane copies; byte offset of its 1 KB LDS chunk
   __device__ __forceinline__ int row_of(int i) const {
     return (wave * kInstr + i) * (64 / kChunks) + lane / kChunks;
   }
   __device__ __forceinline__ uint32_t lds_chunk(int i) const { return (wave * kInstr + i) * 1024; }
-  // (the *_at forms take the LDS byte address of the stage)
+  // copy the ROWS complete rows that start at byte address `base` to the LDS byte address `stage`
   __device__ __forceinline__ void issue_at(uint32_t stage, const char *base) const {
 #pragma unroll
     for (int i = 0; i < kInstr; ++i) lds_dma16_sv(base, off[i], stage + (wave * kInstr + i) * 1024);
-  }
-  // instruction i of that copy alone (a kernel may spread the kInstr loads of a copy over time)
-  __device__ __forceinline__ void issue_one_at(int i, uint32_t stage, const char *base) const {
-    lds_dma16_sv(base, off[i], stage + (wave * kInstr + i) * 1024);
-  }
-  __device__ __forceinline__ void issue_one_at_ragged(int i, uint32_t stage, const char *base, int lim) const {
-    if (lim < 0) {
-      base += (int64_t)lim * pitch_bytes;
-      lim = 0;
-    }
-    const int row = (wave * kInstr + i) * (64 / kChunks) + lane / kChunks;
-    const uint32_t o = row > lim ? off[i] - (uint32_t)(row - lim) * (uint32_t)pitch_bytes : off[i];
-    lds_dma16_sv(base, o, stage + (wave * kInstr + i) * 1024);
   }
   // the same for a tile whose rows past `lim` (relative to the tile) re-read row `lim`.
   // lim < 0 (the whole tile lies past the last row) moves the base back to that row first:
@@ -190,23 +168,6 @@ struct RowTileCopy {
       const int row = (wave * kInstr + i) * (64 / kChunks) + lane / kChunks;
       const uint32_t o = row > lim ? off[i] - (uint32_t)(row - lim) * (uint32_t)pitch_bytes : off[i];
       lds_dma16_sv(base, o, stage + (wave * kInstr + i) * 1024);
-    }
-  }
-  // copy rows [row0, row0 + ROWS) of `tensor` (slab base) into `stage`
-  __device__ __forceinline__ void issue(bf16 *stage, const bf16 *tensor, int row0, int L) const {
-    const char *base = reinterpret_cast<const char *>(tensor) + (int64_t)row0 * pitch_bytes;
-    const int lim = L - 1 - row0;   // last valid row of the tile
-    if (lim >= ROWS - 1) {
-#pragma unroll
-      for (int i = 0; i < kInstr; ++i) lds_dma16(base + off[i], stage + (wave * kInstr + i) * 512);
-    } else {
-#pragma unroll
-      for (int i = 0; i < kInstr; ++i) {
-        const int row = (wave * kInstr + i) * (64 / kChunks) + lane / kChunks;
-        const char *src = base + off[i];
-        if (row > lim) src -= (int64_t)(row - lim) * pitch_bytes;
-        lds_dma16(src, stage + (wave * kInstr + i) * 512);
-      }
     }
   }
 };
@@ -226,11 +187,6 @@ struct ColTileCopy {
       const int row = (wave * kInstr + i) * 8 + lane / 8;
       off[i] = (uint32_t)((row * BLK + (((lane % 8) ^ v_swz(row)) * 8)) * 2);
     }
-  }
-  __device__ __forceinline__ void issue(bf16 *stage, const bf16 *tile, int col0) const {
-    const char *base = reinterpret_cast<const char *>(tile + col0);
-#pragma unroll
-    for (int i = 0; i < kInstr; ++i) lds_dma16(base + off[i], stage + (wave * kInstr + i) * 512);
   }
   __device__ __forceinline__ void issue_at(uint32_t stage, const char *base) const {
 #pragma unroll
@@ -273,10 +229,5 @@ struct TrTileCopy {
     lds_dma16_sv(base, last ? off_last[i] : off[i], stage + lds0 + i * 1024);
   }
 };
-
-// LDS address (elements) of the A fragment "row r, 16-byte chunk c" in the two images
-template <int D>
-__device__ __forceinline__ int row_tile_elem(int r, int c) { return r * D + ((c ^ k_swz<D>(r)) * 8); }
-__device__ __forceinline__ int col_tile_elem(int r, int c) { return r * 64 + ((c ^ v_swz(r)) * 8); }
 
 }  // namespace asa

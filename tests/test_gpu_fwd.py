@@ -107,11 +107,17 @@ def test_fwd_single_stage_kernel_is_still_correct():
 
 
 @pytest.mark.parametrize("L,d,block", [(1024, 64, 64), (520, 128, 64), (300, 64, 128)])
-def test_fwd_ping_pong_kernel_at_the_sizes_where_it_is_not_the_default(L, d, block):
-    binding.asa_test_force_fwd_kernel(2)
+def test_fwd_forcing_the_ping_pong_kernel_where_there_is_none_changes_nothing(L, d, block, kernel_choice):
+    if kernel_choice != "auto":
+        pytest.skip("this test picks the kernel itself")
     p = binding.Params(B=1, H=2, L=L, d=d, block=block)
     qb, kb, vb = _case(1, 2, L, d, block, seed=L)
-    _check_fwd(p, qb, kb, vb, synth.random_block_mask(p.Nb, 0.5, seed=L, slabs=2))
+    bufs = util.lists_from_mask(p, synth.random_block_mask(p.Nb, 0.5, seed=L, slabs=2), with_csc=False)
+    q, k, v = (util.dev_bf16(x) for x in (qb, kb, vb))
+    o, lse = util.run_fwd(p, q, k, v, bufs)
+    binding.asa_test_force_fwd_kernel(2)
+    o2, lse2 = util.run_fwd(p, q, k, v, bufs)
+    assert torch.equal(o.view(torch.int16), o2.view(torch.int16)) and torch.equal(lse, lse2)
 
 
 def test_fwd_each_slab_goes_to_the_kernel_that_suits_its_lists(kernel_choice):
