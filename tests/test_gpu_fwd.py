@@ -11,12 +11,27 @@ from tests import util
 pytestmark = pytest.mark.gpu
 
 
-@pytest.fixture(autouse=True, params=["auto", "pingpong"])
+FORCED = {"auto": 0, "lockstep": 1, "pingpong": 2}
+
+
+def picks_its_kernel(test):
+    """A test that is about the choice of the kernel, or forces one itself: runs once."""
+    test.picks_its_kernel = True
+    return test
+
+
+def pytest_generate_tests(metafunc):
+    once = getattr(metafunc.function, "picks_its_kernel", False)
+    metafunc.parametrize("kernel_choice", ["auto"] if once else list(FORCED), indirect=True)
+
+
+@pytest.fixture(autouse=True)
 def kernel_choice(request):
-    """Every test of this module runs twice: with the library's own choice of forward kernel (short
-    lists go to the lock-step kernel) and with the ping-pong kernel forced, so that both kernels
-    see every edge case."""
-    binding.asa_test_force_fwd_kernel(2 if request.param == "pingpong" else 0)
+    """Every other test of this module runs three times: with the library's own choice of forward kernel
+    (at the small sizes here the pipelined one, lock-step at block 128 / d 128), with the lock-step kernel,
+    which production calls reach at larger sizes, and with the ping-pong kernel, which block 128 / d 128 has
+    (the other shapes then run their own choice again)."""
+    binding.asa_test_force_fwd_kernel(FORCED[request.param])
     yield request.param
     binding.asa_test_force_fwd_kernel(0)
 
@@ -94,6 +109,7 @@ def test_fwd_dense_specialisation_needs_no_lists(L, d, block):
     util.assert_close_bf16(util.host_f32(o), want, "dense O")
 
 
+@picks_its_kernel
 def test_fwd_single_stage_kernel_is_still_correct():
     """The kernel that takes over for slabs of 4 GiB and more, forced by its switch."""
     binding.asa_test_force_fwd_kernel(1)
@@ -106,10 +122,9 @@ def test_fwd_single_stage_kernel_is_still_correct():
     _check_fwd(p, qb, kb, vb, synth.random_block_mask(p.Nb, 0.6, seed=6, slabs=1))
 
 
+@picks_its_kernel
 @pytest.mark.parametrize("L,d,block", [(1024, 64, 64), (520, 128, 64), (300, 64, 128)])
-def test_fwd_forcing_the_ping_pong_kernel_where_there_is_none_changes_nothing(L, d, block, kernel_choice):
-    if kernel_choice != "auto":
-        pytest.skip("this test picks the kernel itself")
+def test_fwd_forcing_the_ping_pong_kernel_where_there_is_none_changes_nothing(L, d, block):
     p = binding.Params(B=1, H=2, L=L, d=d, block=block)
     qb, kb, vb = _case(1, 2, L, d, block, seed=L)
     bufs = util.lists_from_mask(p, synth.random_block_mask(p.Nb, 0.5, seed=L, slabs=2), with_csc=False)
@@ -120,13 +135,12 @@ def test_fwd_forcing_the_ping_pong_kernel_where_there_is_none_changes_nothing(L,
     assert torch.equal(o.view(torch.int16), o2.view(torch.int16)) and torch.equal(lse, lse2)
 
 
-def test_fwd_each_slab_goes_to_the_kernel_that_suits_its_lists(kernel_choice):
+@picks_its_kernel
+def test_fwd_each_slab_goes_to_the_kernel_that_suits_its_lists():
     """Block 128 / d 128 without a lower retention clamp: both kernels are launched and each takes
     the (batch, head) slabs whose rows are long / short for it.  Head 0 keeps 32 of 40 blocks per
     row (ping-pong kernel), head 1 keeps 6 (lock-step kernel), head 2 sits just below the
     switch-over (17 per row), head 3 just above (18); every row must come from exactly one."""
-    if kernel_choice != "auto":
-        pytest.skip("the choice is what is tested")
     L, H = 128 * 40 - 9, 4
     p = binding.Params(B=1, H=H, L=L, d=128, block=128)
     qb, kb, vb = _case(1, H, L, 128, 128, seed=77)
@@ -221,6 +235,7 @@ def test_fwd_list_lengths_and_tails(block, d, tail, kernel_choice):
     _check_fwd(p, qb, kb, vb, mask)
 
 
+@picks_its_kernel
 @pytest.mark.parametrize("H,Nb", [(16, 64), (17, 64)])
 def test_fwd_block_64_d_64_on_both_sides_of_the_kernel_choice(H, Nb):
     """Up to 1024 query blocks the pipelined kernel runs, beyond that the lock-step kernel."""
@@ -231,25 +246,24 @@ def test_fwd_block_64_d_64_on_both_sides_of_the_kernel_choice(H, Nb):
     _check_fwd(p, qb, kb, vb, synth.random_block_mask(Nb, 0.2, seed=H, slabs=H), heads=[0, H - 1])
 
 
-@pytest.mark.parametrize("block,d,H,Nb,lists,lock_step", [
-    (128, 64, 12, 42, False, False),    # 504 query blocks: pipelined workgroups all start at once
-    (128, 64, 52, 10, False, True),     # 520, 1 271 keys per row: lock-step from V's rows
-    (128, 64, 13, 40, False, True),     # 520, 5 111 keys: lock-step from the transposed copy
-    (64, 128, 8, 64, False, False),     # 512
-    (64, 128, 19, 27, False, True),     # 513, 1 719 keys
-    (64, 128, 9, 57, False, True),      # 513, 3 639 keys
-    (64, 128, 16, 63, False, False),    # 1008: two rounds, the second one nearly full
-    (64, 128, 41, 25, False, False),    # 1025: a second round of lock-step workgroups
-    (64, 128, 53, 29, False, True),     # 1537: a fourth round of pipelined ones
-    (128, 64, 16, 60, True, False),     # lists: pipelined whatever the number (960, 600)
-    (64, 128, 20, 30, True, False),
+@picks_its_kernel
+@pytest.mark.parametrize("block,d,H,Nb,tail,lists,lock_step", [
+    (128, 64, 12, 42, 119, False, False),   # 504 query blocks: pipelined workgroups all start at once
+    (128, 64, 52, 10, 128, False, True),    # 520, 1 280 keys per row: lock-step from V's rows
+    (128, 64, 13, 40, 33, False, True),     # 520, 5 025 keys: lock-step from the transposed copy
+    (64, 128, 8, 64, 55, False, False),     # 512
+    (64, 128, 19, 27, 32, False, True),     # 513, 1 696 keys
+    (64, 128, 9, 57, 1, False, True),       # 513, 3 585 keys
+    (64, 128, 16, 63, 55, False, False),    # 1008: two rounds, the second one nearly full
+    (64, 128, 41, 25, 55, False, False),    # 1025: a second round of lock-step workgroups
+    (64, 128, 53, 29, 64, False, True),     # 1537: a fourth round of pipelined ones
+    (128, 64, 16, 60, 119, True, False),    # lists: pipelined whatever the number (960, 600)
+    (64, 128, 20, 30, 55, True, False),
 ])
-def test_fwd_mixed_shapes_on_both_sides_of_the_kernel_choice(block, d, H, Nb, lists, lock_step, kernel_choice):
+def test_fwd_mixed_shapes_on_both_sides_of_the_kernel_choice(block, d, H, Nb, tail, lists, lock_step):
     """Which kernel ran shows in the last bits (tiles of 64 keys or of 32): auto equals the forced lock-step
     kernel exactly where the choice falls on it.  One head against the oracle."""
-    if kernel_choice != "auto":
-        pytest.skip("the choice is what is tested")
-    L = Nb * block - 9
+    L = (Nb - 1) * block + tail
     print(f"case H={H} L={L} d={d} block={block} lists={lists}", flush=True)
     p = binding.Params(B=1, H=H, L=L, d=d, block=block)
     qb, kb, vb = _case(1, H, L, d, block, seed=H)
@@ -270,13 +284,12 @@ def test_fwd_mixed_shapes_on_both_sides_of_the_kernel_choice(block, d, H, Nb, li
     assert np.abs(lse[H - 1].cpu().numpy() - wl).max() <= util.LSE_ABS
 
 
+@picks_its_kernel
 @pytest.mark.parametrize("which", [0, 1, 2])
 @pytest.mark.parametrize("block,d", [(64, 64), (64, 128), (128, 64), (128, 128)])
-def test_fwd_infinite_value_in_the_last_row_stays_infinite(block, d, which, kernel_choice):
+def test_fwd_infinite_value_in_the_last_row_stays_infinite(block, d, which):
     """Keys past the end have probability zero and must not turn an infinite value of a real key into
     NaN (0 * inf), whatever stands in for their rows."""
-    if kernel_choice != "auto":
-        pytest.skip("this test picks the kernel itself")
     L = 2 * block + 5
     p = binding.Params(B=1, H=1, L=L, d=d, block=block)
     g = torch.Generator(device="cuda").manual_seed(1)
@@ -287,3 +300,30 @@ def test_fwd_infinite_value_in_the_last_row_stays_infinite(block, d, which, kern
     o, lse = util.run_fwd(p, q, k, v, bufs)
     assert torch.isposinf(o.float()).all()
     assert torch.isfinite(lse).all()
+
+
+@pytest.mark.parametrize("block,d", [(64, 64), (64, 128), (128, 64), (128, 128)])
+@pytest.mark.parametrize("tail", [1, 40, 64])
+def test_fwd_dense_packed_projection_with_the_low_half(block, d, tail):
+    """No lists, Q, K, V as slices of one [B, L, 3, H, d] projection, O and o_lo [B, L, H, d].  O against
+    plain soft-max attention; o_lo is what rounding left out of O: half a unit in its last place at most
+    (2^-8 of O with 8 significant bits)."""
+    B, H, L = 2, 2, 3 * block + tail
+    print(f"case L={L} d={d} block={block}", flush=True)
+    bits = [synth.make_iid((B, H, L, d), L, s) for s in range(3)]
+    qkv = torch.stack([util.dev_bf16(x).transpose(1, 2) for x in bits], dim=2).contiguous()
+    q, k, v = (qkv[:, :, i].transpose(1, 2) for i in range(3))
+    o, o_lo = (torch.full((B, L, H, d), float("nan"), dtype=torch.bfloat16, device="cuda").transpose(1, 2)
+               for _ in range(2))
+    lse = torch.empty((B * H, L), dtype=torch.float32, device="cuda")
+    p = binding.Params(B=B, H=H, L=L, d=d, block=block, q_stride=tuple(q.stride()[:3]),
+                       k_stride=tuple(k.stride()[:3]), v_stride=tuple(v.stride()[:3]), o_stride=tuple(o.stride()[:3]))
+    ws = binding.alloc_workspace(binding.asa_fwd_workspace_bytes(p))
+    binding.asa_attn_fwd(p, q, k, v, None, None, o, lse, ws, o_lo=o_lo)
+    torch.cuda.synchronize()
+    qf, kf, vf = (torch.from_numpy(synth.bf16_bits_to_f32(x).astype(np.float64)) for x in bits)
+    want = torch.nn.functional.scaled_dot_product_attention(qf, kf, vf).numpy()
+    util.assert_close_bf16(util.host_f32(o), want, "O")
+    hi, lo = util.host_f32(o).astype(np.float64), util.host_f32(o_lo).astype(np.float64)
+    util.assert_close_bf16(hi + lo, want, "O + o_lo")
+    assert (np.abs(lo) <= np.abs(hi) * 2.0 ** -8 + 1e-30).all() and (lo != 0).mean() > 0.9
