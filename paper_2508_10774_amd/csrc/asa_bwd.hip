@@ -102,18 +102,6 @@ struct BwdArgs {
   float pooled_bias_log2;
 };
 
-// The compiler places no wait states around a written-out MFMA (tests/test_asm_hazards.py walks the
-// assembly).  settle_acc in front of a loop and behind it keeps what the compiler does with the
-// accumulators (zeros, copies, reads) away from the loop's MFMAs: 2 states after a vector instruction has
-// written an operand, 19 before one reads a result.
-template <int N>
-__device__ __forceinline__ void settle_acc(f32x16 (&acc)[N]) {
-  static_assert(N == 4, "D = 128");
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_nop 15\n\ts_nop 3" : "+a"(acc[0]), "+a"(acc[1]), "+a"(acc[2]), "+a"(acc[3]));
-#endif
-}
-
 template <int BLK, int D>
 struct BwdCfg {
   static constexpr int kWaves = BLK / 32;

@@ -11,8 +11,8 @@
 //                    kappa; the V^T operand comes from a per-block transposed copy of V (both
 //                    LDS operand reads are then 16-byte loads) or, where making the copy costs
 //                    more than it gains, from V's rows by the transposing LDS read.
-// Three kernels (launch_fwd_t says which runs where): lock-step, ping-pong, pipelined.  A key block is
-// walked in steps of 64 (pipelined: 32) keys.  The K rows and the V^T slice (or V rows) of a step are copied
+// Four kernels (launch_fwd_t says which runs where): lock-step, ping-pong, pipelined, wide.  A key block is
+// walked in steps of 64 (pipelined, wide: 32) keys.  The K rows and the V^T slice (or V rows) of a step are copied
 // straight from global memory into LDS (no register staging) with an XOR swizzle of 16-byte
 // chunks instead of row padding, which keeps the 16-byte fragment reads conflict-free.
 #include <stdlib.h>
@@ -1336,6 +1336,692 @@ __global__ __launch_bounds__(BLK * 2, (PipeCfg<BLK, D>::kWavesPerSimd)) void fwd
   }
 }
 
+// ---------------------------------------------------------------------------------------
+// Wide forward: 64 query rows per wavefront, one wavefront per SIMD, with the software pipeline of the backward kernels
+// (see asa_bwd.hip) inside it.  QW wavefronts share the tiles of 32 keys: two (one query block of 128) with index lists,
+// four (256 rows of a dense call).  In iteration t a wavefront computes S^T of tile t + 1 for its two halves of 32 rows,
+// adds P V of tile t - 1, and between those MFMAs turns S^T of tile t into P.  Every operand read from LDS feeds two
+// MFMAs.  V comes from its rows by the transposing LDS read: no transposed copy.  O lives in accumulation registers.
+//
+// Bound: power and issue.  At one wavefront per SIMD every instruction, scalar ones too, takes an issue slot of 4-5
+// cycles; 200 of them per iteration stand beside 1024 matrix cycles.  12 heads of 32 760 tokens: a quarter of the tiles
+// matrix duty 0.69 at 1.53 GHz, dense 0.73 at 1.67 GHz (ping-pong: 0.62 at 1.57); without the copies the cycles stay and
+// the clock rises to 1.72 and 1.84.  What follows from that:
+//  * No row maximum per tile.  The exponentials are relative to a reference per row: the largest logit of the first tile
+//    and, where the list holds the query block itself, among the 32 keys of the row's own group (one extra product in
+//    the prologue).  As long as no row sum of a tile passes 2^30 the reference stays; then the tile is redone and O scaled.
+//  * A tile whose row sum is more than half of everything before it decides its row, and there the rounding of P to bf16
+//    (a key at the reference had P = 1 exactly) would show: what the rounding left out is added as a second product.
+//    Error of O + o_lo against 64 bits, rms, 13 x 30 x 45 tokens, a quarter of the tiles; in brackets with the running maximum as
+//    the reference (ping-pong): keys and queries with a smooth field of twice the noise 1.4e-4 (3.7e-4), as strong as the
+//    noise 3.2e-4 (5.9e-4), half as strong 8.9e-4 (8.4e-4), noise alone 1.63e-3 (1.52e-3).  The own block comes first in a
+//    row's order so that both happen rarely (1 and 4 % of the time above).
+//  * The loop has no ragged or pooled tiles: those are in a second copy of it behind the first.
+//  * A wavefront sets M0 and the base of its copies once per tile; addresses advance by scalar additions.
+//  * What a rare branch redefines the compiler would compute behind that branch, away from the MFMAs: pinned.
+// Times (with the transposition where there was one): a quarter of the tiles 1.60 -> 1.44 ms, dense 5.9 -> 5.2 ms, pooled
+// tokens 1.85 -> 1.55 ms against the ping-pong kernel.  (Row sums of the rounded P by v_dot2, as a normaliser, cost 14 cycles
+// each beside MFMAs, by small MFMAs 64 cycles per tile; the second product serves better.)
+// ---------------------------------------------------------------------------------------
+template <int BLK, int D, int QW>
+struct WideCfg {
+  static constexpr int kWaves = QW;                    // QW x 64 query rows per workgroup
+  static constexpr int kThreads = QW * 64;
+  static constexpr int kRows = QW * 64;
+  static constexpr int kST = 32;                       // keys per tile
+  static constexpr int kSub = BLK / kST;
+  static constexpr int kStages = 4;
+  static constexpr int kTile = kST * D * 2;            // bytes of one row tile
+  static constexpr int kLds = 2 * kStages * kTile;     // K stages, then V stages
+  static constexpr bool kAcc = D == 128;               // O in accumulation registers
+};
+
+template <int BLK, int D, int QW, bool GT>
+__global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
+  using C = WideCfg<BLK, D, QW>;
+  extern __shared__ __align__(1024) unsigned char smem[];
+  __shared__ int cols[kMaxNb];
+  constexpr int kStage = C::kTile, kVBase = C::kStages * C::kTile;
+  constexpr int kPooled = 1 << 30;             // flag of an entry of cols[]: a block of pooled tokens
+  constexpr int kDm = D / 32;
+  // for the row sum of a tile (16 keys of a lane): passes kRedo: new reference; passes kShare of all before + kLeast: second product
+  constexpr float kRedo = 1073741824.f, kShare = 0.5f, kLeast = 1.f;
+
+  const int n_q = C::kRows == BLK ? a.Nb : (a.L + C::kRows - 1) / C::kRows;   // query blocks of a slab
+  const int slot = xcd_contiguous_work(blockIdx.x, a.n_slabs * n_q);
+  if (slot < 0) return;
+  const int work = a.order ? a.order[slot] : slot;
+  const int slab = work / n_q;
+  if (slab_not_mine(a, slab)) return;
+  const int qb = work - slab * n_q;
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63, hl = lane >> 5, n = lane & 31;
+
+  const bf16 *qs = slab_ptr(a.q, a.tq, slab, a.H);
+  const bf16 *ks = slab_ptr(a.k, a.tk, slab, a.H);
+  const bf16 *vs = slab_ptr(a.v, a.tv, slab, a.H);
+  const bool dense = a.row_ptr == nullptr;   // no index lists: dense attention, every key block in order
+  const int t_begin = dense ? 0 : a.row_ptr[slab * (a.Nb + 1) + qb];
+  const int n_own_blocks = dense ? a.Nb : a.row_ptr[slab * (a.Nb + 1) + qb + 1] - t_begin;
+  const int n_blocks = n_own_blocks + (GT ? a.Nbg : 0);   // pooled blocks come after the row's own list
+  // Order of a row's own blocks: the query block's own tokens first where they are in the list (attention is strongest
+  // there as a rule), the block with the last row last (the loop below relies on it; a list that does not ascend may have
+  // it elsewhere).  Every wavefront looks through the list itself.
+  bool own_listed = dense;
+  {
+    constexpr int kOwn = C::kRows / BLK;       // key blocks of the workgroup's own tokens
+    const int32_t *g = a.col_idx + (int64_t)slab * a.Nb * a.Nb + t_begin;
+    const bool own_first = (qb + 1) * kOwn < a.Nb;
+    int own_at = qb * kOwn, last_at = n_own_blocks - 1;
+    if (!dense) {
+      own_at = 0;
+      for (int t0 = 0; t0 < n_own_blocks; t0 += 64) {
+        const int e = t0 + lane < n_own_blocks ? g[t0 + lane] : -1;
+        const uint64_t own = __ballot(e == qb), last = __ballot(e == a.Nb - 1);
+        if (own) {
+          own_listed = true;
+          own_at = t0 + (int)__builtin_ctzll(own);
+        }
+        if (last) last_at = t0 + (int)__builtin_ctzll(last);
+      }
+      if (own_at == n_own_blocks - 1) own_at = last_at;      // (where the exchange below puts it)
+    }
+    for (int t = tid; t < n_blocks; t += C::kThreads) {
+      int from = t;
+      if (t >= n_own_blocks) {
+        cols[t] = (t - n_own_blocks) | kPooled;
+        continue;
+      }
+      if (own_first) from = t < kOwn ? own_at + t : (t >= own_at && t < own_at + kOwn ? t - own_at : t);
+      from = from == last_at ? n_own_blocks - 1 : (from == n_own_blocks - 1 ? last_at : from);
+      cols[t] = dense ? from : g[from];
+    }
+  }
+  const bf16 *kgs = reinterpret_cast<const bf16 *>(a.kg) + (int64_t)slab * a.Nbg * BLK * D;
+  const bf16 *vgs = reinterpret_cast<const bf16 *>(a.vg) + (int64_t)slab * a.Nbg * BLK * D;
+
+  const int qrow0 = qb * C::kRows + wave * 64 + n;       // rows of my halves: qrow0, qrow0 + 32
+  bf16x8 qa[D / 16], qc[D / 16];
+  {
+    const bf16 *ra = qs + (int64_t)min(qrow0, a.L - 1) * a.tq.sL, *rc = qs + (int64_t)min(qrow0 + 32, a.L - 1) * a.tq.sL;
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) {
+      qa[s] = *reinterpret_cast<const bf16x8 *>(ra + 16 * s + 8 * hl);
+      qc[s] = *reinterpret_cast<const bf16x8 *>(rc + 16 * s + 8 * hl);
+    }
+  }
+  // Largest logit of each row among the 32 rows of its own group, where their keys are in the list
+  float own_a = -INFINITY, own_c = -INFINITY;
+  if (own_listed) {
+    const bf16 *ra = ks + (int64_t)min(qrow0, a.L - 1) * a.tk.sL + 8 * hl, *rc = ks + (int64_t)min(qrow0 + 32, a.L - 1) * a.tk.sL + 8 * hl;
+    f32x16 sa, sc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sa[i] = sc[i] = 0.f;
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) {
+      sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(ra + 16 * s), qa[s], sa, 0, 0, 0);
+      sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(rc + 16 * s), qc[s], sc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      own_a = fmaxf(own_a, sa[i]);
+      own_c = fmaxf(own_c, sc[i]);
+    }
+    own_a = max_of_halves(own_a) * a.scale_log2e;
+    own_c = max_of_halves(own_c) * a.scale_log2e;
+  }
+  f32x16 oa[kDm], oc[kDm];                               // O^T of the two halves
+#pragma unroll
+  for (int dm = 0; dm < kDm; ++dm)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) oa[dm][i] = oc[dm][i] = 0.f;
+  // per row: reference of the exponentials (log2 units), sum of P over my lane half's keys
+  float ma = 0.f, mc = 0.f, la = 0.f, lc = 0.f;
+  const float c = a.scale_log2e;
+
+  using Copy = TrTileCopy<C::kST, D, C::kWaves>;
+  Copy copy_k, copy_v, copy_p;
+  copy_k.init(wave, lane, a.tk.sL, a.L);
+  copy_v.init(wave, lane, a.tv.sL, a.L);
+  constexpr int kI = Copy::kInstr;
+  const int last_row0 = Copy::last_row0(a.L);
+  if (GT) copy_p.init(wave, lane, D, C::kST);   // pooled rows: D elements apart, never ragged
+
+  const uint32_t smem_addr = ASA_LDS_ADDR_OF(smem);
+  // A fragments of S^T = K Q^T: row kappa(n) of the 32 keys (see asa_bwd.hip)
+  const int kr = kappa(n);
+  uint32_t row_at[D / 16];
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s)
+    row_at[s] = (smem_addr + (uint32_t)(kr * D * 2 + (hl ^ t_swz<D>(kr)) * 16)) ^ (uint32_t)(32 * s);
+  // transposed A fragments "32 channels x 16 keys" of O^T += V^T P^T
+  const int tr_i = lane & 15, tr_w = tr_i & 3, tr_j = tr_i >> 2, tr_b = (lane >> 4) & 1;
+  const uint32_t tr_lane = smem_addr + kVBase + tr_piece<D>(8 * hl + tr_j, 16 * (tr_w & 1) + 8 * tr_b + 4 * (tr_w >> 1));
+  uint32_t tr_at[2 * kDm];
+#pragma unroll
+  for (int dm = 0; dm < kDm; ++dm) {
+    tr_at[2 * dm] = tr_lane ^ (uint32_t)(((4 * dm) ^ t_swz<D>(0)) * 16);
+    tr_at[2 * dm + 1] = tr_lane ^ (uint32_t)(((4 * dm) ^ t_swz<D>(4)) * 16);
+  }
+  const int n_it = n_blocks * C::kSub;
+
+  // Copies.  The kI loads of a wavefront's share of a tile have M0 and a scalar base in common (lds_dma_begin) and
+  // differ by the offset inside the instruction, which moves the LDS and the global address alike: the offsets per
+  // lane are lowered by as much (and raised by kBack, which the bases lack, to stay positive).
+  constexpr int kBack = (kI - 1) * 1024;
+  // offsets of the K and V loads of this iteration; others only where a tile with the last row, or a pooled one, is near
+  uint32_t off_k[kI], off_v[kI];
+  auto lane_offset = [&](const Copy &own, int i, bool last, bool pooled) __attribute__((always_inline)) {
+    return (GT && pooled ? copy_p.off[i] : (last ? own.off_last[i] : own.off[i])) + (uint32_t)(kBack - i * 1024);
+  };
+  // The tile whose K rows are copied next, and the tile before it, whose V rows are
+  int entry_v = 0, entry_at = 0, key_c = 0, block_c = 0;
+  bool last_k = false, last_v = false, pooled_k = false, pooled_v = false;
+  const char *base_k = nullptr, *base_v = nullptr, *base_v_next = nullptr;
+  // > 0: one of the tiles that the coming iteration copies, works on or has just worked on holds the last row, lies past
+  // it or is pooled (its K rows were copied at most five iterations ago)
+  int special = 0;
+  auto fetch_entry = [&]() __attribute__((always_inline)) {
+    entry_v = cols[entry_at < n_blocks ? entry_at : n_blocks - 1];
+    ++entry_at;
+  };
+  const char *const ks_b = reinterpret_cast<const char *>(ks) - kBack, *const vs_b = reinterpret_cast<const char *>(vs) - kBack;
+  const char *const kgs_b = reinterpret_cast<const char *>(kgs) - kBack, *const vgs_b = reinterpret_cast<const char *>(vgs) - kBack;
+  const int64_t tile_k = C::kST * a.tk.sL * 2, tile_v = C::kST * a.tv.sL * 2;   // bytes from tile to tile
+  // TAIL: the tile may hold the last row, lie past it or be pooled
+  auto next_tile = [&](auto part_tag, auto new_block_tag, auto tail_tag) __attribute__((always_inline)) {
+    constexpr int part = decltype(part_tag)::value;
+    constexpr bool new_block = decltype(new_block_tag)::value;
+    if constexpr (!decltype(tail_tag)::value) {
+      if constexpr (part == 0) {
+        base_v = base_v_next;
+        if constexpr (new_block) block_c = __builtin_amdgcn_readfirstlane(entry_v);
+        key_c = new_block ? block_c * BLK : key_c + C::kST;
+      } else if constexpr (part == 1) {
+        base_k = new_block ? ks_b + block_c * (C::kSub * tile_k) : base_k + tile_k;
+      } else {
+        base_v_next = new_block ? vs_b + block_c * (C::kSub * tile_v) : base_v_next + tile_v;
+      }
+    } else if constexpr (part == 0) {
+      last_v = last_k;
+      pooled_v = pooled_k;
+      base_v = base_v_next;
+      if constexpr (new_block) {
+        const int e = __builtin_amdgcn_readfirstlane(entry_v);
+        if (GT) pooled_k = (e & kPooled) != 0;
+        block_c = GT ? e & (kPooled - 1) : e;
+        key_c = block_c * BLK;
+      } else {
+        key_c += C::kST;
+      }
+      last_k = key_c >= last_row0;
+      special = (last_k || (GT && pooled_k)) ? 5 : max(special - 1, 0);
+    } else if constexpr (part == 1) {
+      if constexpr (new_block) {
+        base_k = ks_b + block_c * (C::kSub * tile_k);
+        if (GT) base_k = pooled_k ? kgs_b + (int64_t)key_c * (D * 2) : base_k;
+      } else {
+        // (a tile wholly past the last row is replaced by the one that holds it; pooled rows fill whole blocks)
+        if (GT) base_k += pooled_k ? C::kTile : (key_c <= last_row0 ? tile_k : 0);
+        else base_k += key_c <= last_row0 ? tile_k : 0;
+      }
+    } else {
+      if constexpr (new_block) {
+        base_v_next = vs_b + block_c * (C::kSub * tile_v);
+        if (GT) base_v_next = pooled_k ? vgs_b + (int64_t)key_c * (D * 2) : base_v_next;
+      } else {
+        if (GT) base_v_next += pooled_k ? C::kTile : (key_c <= last_row0 ? tile_v : 0);
+        else base_v_next += key_c <= last_row0 ? tile_v : 0;
+      }
+    }
+  };
+  auto set_offsets = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < kI; ++i) {
+      off_k[i] = lane_offset(copy_k, i, last_k, pooled_k);
+      off_v[i] = lane_offset(copy_v, i, last_v, pooled_v);
+    }
+  };
+  auto copy_one = [&](auto i_tag, uint64_t base, const uint32_t *off) __attribute__((always_inline)) {
+    constexpr int i = decltype(i_tag)::value;
+    lds_dma16_next<i * 1024>(base, off[i]);
+  };
+  auto wait_copies = [&](auto n_tag) __attribute__((always_inline)) {
+    constexpr int N = decltype(n_tag)::value;    // at most N instructions still in flight
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+  };
+  // The block of the tile in work, for the masks of the last block and the bias of pooled keys
+  int cur_v = 0, cur_at = 0, key_t = 0, key_end = 0;
+  int left = C::kST;                             // keys that the tile before it had (32 and more: all)
+  float bias = 0.f;
+  auto fetch_current = [&]() __attribute__((always_inline)) {
+    cur_v = cols[cur_at < n_blocks ? cur_at : n_blocks - 1];
+    ++cur_at;
+  };
+  auto next_current = [&](auto new_block_tag) __attribute__((always_inline)) {
+    left = key_end - key_t;
+    if constexpr (decltype(new_block_tag)::value) {
+      const int e = __builtin_amdgcn_readfirstlane(cur_v);
+      key_t = (GT ? e & (kPooled - 1) : e) * BLK;
+      const bool pooled = GT && (e & kPooled) != 0;
+      key_end = pooled ? a.Lg : a.L;             // keys at or past it do not exist
+      if (GT) bias = pooled ? a.bias_log2 : 0.f;
+    } else {
+      key_t += C::kST;
+    }
+  };
+
+  // An iteration is kN slots, one MFMA each.  Fragment f of the kF operands of an iteration (K rows of tile
+  // t + 1, then V of tile t - 1) feeds the slots 2 f and 2 f + 1 and is read kDepth fragments ahead, through a
+  // ring that runs on from iteration to iteration.
+  constexpr int kNS = D / 16, kNV = 2 * kDm, kF = kNS + kNV, kN = 2 * kF;
+  constexpr int kRing = 8, kDepth = 4;
+  static_assert(kF % kRing == 0 && kDepth <= kNS, "the ring continues across iterations");
+  constexpr int kHalf = 17;                         // exponentials in front of it
+  constexpr int kBar = 2 * kNS;                     // the barrier comes before this slot
+  bf16x8 row_ring[kRing];
+  bf16x4 lo_ring[kRing], hi_ring[kRing];
+  auto read_row = [&](auto f_tag, auto stage_tag) __attribute__((always_inline)) {
+    constexpr int f = decltype(f_tag)::value;
+    row_ring[f % kRing] = lds_read<bf16x8>(row_at[f] + (uint32_t)(decltype(stage_tag)::value * kStage));
+  };
+  auto read_tr = [&](auto f_tag, auto stage_tag, auto half_tag) __attribute__((always_inline)) {
+    constexpr int f = decltype(f_tag)::value, dm = f % kDm, tt = f / kDm, half = decltype(half_tag)::value;
+    constexpr int at = decltype(stage_tag)::value * kStage + 16 * tt * D * 2;
+    if constexpr (half == 0)
+      lo_ring[(kNS + f) % kRing] = lds_read_tr16((const lds_char *)(uintptr_t)(tr_at[2 * dm] + (uint32_t)at));
+    else
+      hi_ring[(kNS + f) % kRing] = lds_read_tr16((const lds_char *)(uintptr_t)(tr_at[2 * dm + 1] + (uint32_t)(at + 4 * D * 2)));
+  };
+  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
+                         0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  // LDS reads issued behind the last one of fragment f0 up to slot x of the iteration: a row fragment is one read, in its
+  // even slot, a transposed one two
+  constexpr auto reads_behind = [](int f0, int x) constexpr {
+    int n = 0;
+    for (int y = 2 * (f0 - kDepth) + 2; y <= x; ++y) {
+      const int f = ((y >> 1) + kDepth + kF) % kF;      // fragment read in slot y (of the iteration before if y < 0)
+      n += f < kNS ? ((y & 1) == 0) : 1;
+    }
+    return n;
+  };
+  auto wait_lds = [&](auto n_tag) __attribute__((always_inline)) {
+    constexpr int N = decltype(n_tag)::value;
+    __builtin_amdgcn_s_waitcnt(0xC07F | (N << 8));
+  };
+  f32x16 s0a, s0c, s1a, s1c;
+  uint32_t p0[16], p1[16];               // bf16 P of two tiles, both halves
+#pragma unroll
+  for (int i = 0; i < 16; ++i) p0[i] = p1[i] = 0;
+  auto accumulate = [](f32x16 &acc, bf16x8 x, bf16x8 y) __attribute__((always_inline)) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    if constexpr (C::kAcc) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(x), "v"(y));
+    else acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, acc, 0, 0, 0);
+#endif
+  };
+  auto pv = [&](auto f_tag, auto half_tag, const uint32_t *p) __attribute__((always_inline)) {
+    constexpr int f = decltype(f_tag)::value, dm = f % kDm, tt = f / kDm, half = decltype(half_tag)::value;
+    const u32x4 raw = {p[8 * half + 4 * tt], p[8 * half + 4 * tt + 1], p[8 * half + 4 * tt + 2], p[8 * half + 4 * tt + 3]};
+    const bf16x8 x = __builtin_shufflevector(lo_ring[(kNS + f) % kRing], hi_ring[(kNS + f) % kRing], 0, 1, 2, 3, 4, 5, 6, 7);
+    accumulate(half == 0 ? oa[dm] : oc[dm], x, __builtin_bit_cast(bf16x8, raw));
+  };
+  // (what the rare branch of an iteration overwrites would be computed behind it, without MFMAs to hide under)
+  auto pin = [](auto &x) __attribute__((always_inline)) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(x));
+#endif
+  };
+  auto pin_s = [](auto &x) __attribute__((always_inline)) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+s"(x));
+#endif
+  };
+  auto mask_tile = [&](f32x16 &sa, f32x16 &sc) __attribute__((always_inline)) {
+    const int mine = key_end - key_t - 8 * hl;
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (16 * (i >> 3) + (i & 7) >= mine) sa[i] = sc[i] = -INFINITY;
+  };
+  // keys past the end have P = 0: their V rows (in `stage`, read after this by my own wavefront) must be finite.
+  // Every wavefront writes all of the zeros itself.
+  auto zero_rows = [&](int stage, int left) __attribute__((always_inline)) {
+    u32x4 *z = reinterpret_cast<u32x4 *>(smem + kVBase + stage * kStage);
+    for (int r = max(0, left) * (D / 8) + lane; r < kStage / 16; r += 64) z[r] = u32x4{0, 0, 0, 0};
+  };
+  auto row_max = [&](const f32x16 &s, float bias_t) __attribute__((always_inline)) {
+    float mx = s[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
+    return max_of_halves(mx) * c + bias_t;
+  };
+  auto settle = [&]() __attribute__((always_inline)) {
+    if constexpr (C::kAcc) {
+      settle_acc(oa);
+      settle_acc(oc);
+    }
+  };
+
+  float share = -INFINITY;                           // (-inf * 0: no comparison holds at the first tile)
+  float ta_last = 0.f, tc_last = 0.f;                // row sums of the tile before, not yet in la, lc
+  auto body = [&](auto u_tag, auto tail_tag, f32x16 &sa, f32x16 &sc, f32x16 &na, f32x16 &nc, uint32_t *pn, const uint32_t *po) __attribute__((always_inline)) {
+    constexpr int U = decltype(u_tag)::value;        // tile index mod 4
+    constexpr bool kTail = decltype(tail_tag)::value;
+    using StK1 = std::integral_constant<int, (U + 1) & 3>;
+    using StK2 = std::integral_constant<int, (U + 2) & 3>;
+    using StVp = std::integral_constant<int, (U + 3) & 3>;   // V rows of tile t - 1
+    using StV = std::integral_constant<int, U>;
+    constexpr bool kNextNewBlock = (U + C::kStages) % C::kSub == 0;   // of the K tile that the next iteration copies
+    if constexpr (kTail) {
+      if (special > 0) {
+        set_offsets();
+        if (key_t + C::kST > key_end) mask_tile(sa, sc);
+        if (left < C::kST) zero_rows((U + 3) & 3, left);
+      }
+    }
+    const float bias_t = GT && kTail ? bias : 0.f;
+    const int left_now = kTail ? key_end - key_t : C::kST;
+    const float nma = GT && kTail ? bias_t - ma : -ma, nmc = GT && kTail ? bias_t - mc : -mc;
+    uint64_t from_k = 0, from_v = 0;
+    float ta = 0.f, tc = 0.f;                        // sums of this tile
+    float w[32];                                     // argument, then value of each exponential
+    constexpr int kES = kN - 2;                      // slots with exponentials
+    // first element of slot g
+    auto first = [](int g) constexpr { return g <= kBar ? g * kHalf / kBar : kHalf + (g - kBar) * (32 - kHalf) / (kES - kBar); };
+    auto arg = [&](auto g_tag) __attribute__((always_inline)) {
+      constexpr int g = decltype(g_tag)::value;
+#pragma unroll
+      for (int e = first(g); e < first(g + 1); ++e)
+        w[e] = e < 16 ? fmaf(sa[e & 15], c, nma) : fmaf(sc[e & 15], c, nmc);
+    };
+    auto finish = [&](auto g_tag) __attribute__((always_inline)) {
+      constexpr int g = decltype(g_tag)::value;
+#pragma unroll
+      for (int e = first(g); e < first(g + 1); ++e) {
+        if (e == 0) ta = w[e];
+        else if (e < 16) ta += w[e];
+        else if (e == 16) tc = w[e];
+        else tc += w[e];
+        if (e & 1) {
+          pn[e >> 1] = pack_bf16x2(w[e - 1], w[e]);
+          pin(pn[e >> 1]);
+        }
+      }
+    };
+    __builtin_amdgcn_sched_barrier(0);
+    [&]<int... X>(std::integer_sequence<int, X...>) __attribute__((always_inline)) {
+      ([&]() __attribute__((always_inline)) {
+        constexpr int x = X, f = x / 2;
+        if constexpr (x == kBar) {
+          // K of tile t + 2 and V of tile t have landed (everyone's copies)
+          wait_copies(std::integral_constant<int, 2 * kI>{});
+          asm volatile("s_barrier" ::: "memory");
+          from_v = lds_dma_begin(base_v, smem_addr + kVBase + ((U + 2) & 3) * kStage + copy_v.lds0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        // operand reads
+        constexpr int r = f + kDepth;
+        using Half = std::integral_constant<int, x & 1>;
+        if constexpr (r < kNS) { if constexpr ((x & 1) == 0) read_row(std::integral_constant<int, r>{}, StK1{}); }
+        else if constexpr (r < kF) read_tr(std::integral_constant<int, r - kNS>{}, StVp{}, Half{});
+        else { if constexpr ((x & 1) == 0) read_row(std::integral_constant<int, r - kF>{}, StK2{}); }
+        // (one wait for two fragments)
+        if constexpr (x % 4 == 0) wait_lds(std::integral_constant<int, reads_behind(f + 1, x)>{});
+        // the MFMA of this slot
+        if constexpr (f < kNS) {
+          if constexpr ((x & 1) == 0) na = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_ring[f % kRing], qa[f], f == 0 ? zero16 : na, 0, 0, 0);
+          else nc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_ring[f % kRing], qc[f], f == 0 ? zero16 : nc, 0, 0, 0);
+        } else {
+          pv(std::integral_constant<int, f - kNS>{}, Half{}, po);
+        }
+        // soft-max of tile t
+        if constexpr (x == 0) arg(std::integral_constant<int, 0>{});
+        if constexpr (x < kES) {
+#pragma unroll
+          for (int e = first(x); e < first(x + 1); ++e) w[e] = fast_exp2(w[e]);
+        }
+        if constexpr (x + 1 < kES) arg(std::integral_constant<int, x + 1>{});
+        if constexpr (x >= 1 && x <= kES) finish(std::integral_constant<int, x - 1>{});
+        if constexpr (x == 3) {
+          la += ta_last;
+          lc += tc_last;
+        }
+        // K of tile t + 3 in front of the barrier, V of tile t + 2 behind it (their stages were last read in
+        // iterations t - 2 and t - 1)
+        if constexpr (x == 0) from_k = lds_dma_begin(base_k, smem_addr + ((U + 3) & 3) * kStage + copy_k.lds0);
+        if constexpr (x >= 1 && x < kBar) {
+          constexpr int i0 = (x - 1) * kI / (kBar - 1), i1 = x * kI / (kBar - 1);
+          if constexpr (i1 > i0) copy_one(std::integral_constant<int, i0>{}, from_k, off_k);
+          static_assert(i1 - i0 <= 1, "a load per slot");
+        }
+        if constexpr (x >= kBar) {
+          constexpr int i0 = (x - kBar) * kI / (kN - kBar), i1 = (x - kBar + 1) * kI / (kN - kBar);
+          if constexpr (i1 > i0) copy_one(std::integral_constant<int, i0>{}, from_v, off_v);
+        }
+        // the tiles of the next iteration
+        if constexpr (x == kN - 8 && kNextNewBlock) fetch_entry();
+        if constexpr (kTail && x == kN - 8 && (U + 1) % C::kSub == 0) fetch_current();
+        if constexpr (x >= kN - 4 && x <= kN - 2) {
+          next_tile(std::integral_constant<int, x - (kN - 4)>{}, std::bool_constant<kNextNewBlock>{}, tail_tag);
+          if constexpr (x == kN - 3) pin_s(base_k);
+          if constexpr (x == kN - 2) pin_s(base_v_next);
+        }
+        if constexpr (kTail && x == kN - 1) next_current(std::bool_constant<(U + 1) % C::kSub == 0>{});
+        __builtin_amdgcn_sched_barrier(0);
+      }(), ...);
+    }(std::make_integer_sequence<int, kN>{});
+    if (__builtin_expect(__any(fmaxf(ta, tc) > kRedo), 0)) {
+      // some row grew far beyond its reference.  New references, this tile's P again, O and the sums scaled.
+      const float xa = fmaxf(ma, row_max(sa, bias_t)), xc = fmaxf(mc, row_max(sc, bias_t));
+      const float fa = fast_exp2(ma - xa), fc = fast_exp2(mc - xc);
+      ma = xa;
+      mc = xc;
+      ta = tc = 0.f;
+#pragma unroll
+      for (int e = 0; e < 32; e += 2) {
+        const float u = e < 16 ? fast_exp2(fmaf(sa[e & 15], c, bias_t - xa)) : fast_exp2(fmaf(sc[e & 15], c, bias_t - xc));
+        const float v = e < 16 ? fast_exp2(fmaf(sa[(e & 15) + 1], c, bias_t - xa)) : fast_exp2(fmaf(sc[(e & 15) + 1], c, bias_t - xc));
+        pn[e >> 1] = pack_bf16x2(u, v);
+        if (e < 16) ta += u + v;
+        else tc += u + v;
+      }
+      la *= fa;
+      lc *= fc;
+      settle();
+#pragma unroll
+      for (int dm = 0; dm < kDm; ++dm)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          oa[dm][i] *= fa;
+          oc[dm][i] *= fc;
+        }
+      settle();
+    }
+    if (__builtin_expect(__any(fmaxf(fmaf(share, la, ta), fmaf(share, lc, tc)) > kLeast), 0)) {
+      // what the rounding of P left out, as a second product
+      if constexpr (kTail) {
+        if (left_now < C::kST) zero_rows(U, left_now);
+      }
+      uint32_t rest[16];
+#pragma unroll
+      for (int e = 0; e < 32; e += 2) {
+        const float u = e < 16 ? fast_exp2(fmaf(sa[e & 15], c, bias_t - ma)) : fast_exp2(fmaf(sc[e & 15], c, bias_t - mc));
+        const float v = e < 16 ? fast_exp2(fmaf(sa[(e & 15) + 1], c, bias_t - ma)) : fast_exp2(fmaf(sc[(e & 15) + 1], c, bias_t - mc));
+        rest[e >> 1] = pack_bf16x2(u - bf16_bits_to_float(pn[e >> 1] & 0xffffu), v - bf16_bits_to_float(pn[e >> 1] >> 16));
+      }
+#if defined(__HIP_DEVICE_COMPILE__)
+      asm volatile("s_nop 1");                       // (vector results and the first MFMA that reads them)
+#endif
+      [&]<int... F>(std::integer_sequence<int, F...>) __attribute__((always_inline)) {
+        ([&]() __attribute__((always_inline)) {
+          constexpr int dm = F % kDm, tt = F / kDm, at = U * kStage + 16 * tt * D * 2;
+          const bf16x4 lo = lds_read_tr16((const lds_char *)(uintptr_t)(tr_at[2 * dm] + (uint32_t)at));
+          const bf16x4 hi = lds_read_tr16((const lds_char *)(uintptr_t)(tr_at[2 * dm + 1] + (uint32_t)(at + 4 * D * 2)));
+          const bf16x8 x = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+          const u32x4 ra4 = {rest[4 * tt], rest[4 * tt + 1], rest[4 * tt + 2], rest[4 * tt + 3]};
+          const u32x4 rc4 = {rest[8 + 4 * tt], rest[8 + 4 * tt + 1], rest[8 + 4 * tt + 2], rest[8 + 4 * tt + 3]};
+          accumulate(oa[dm], x, __builtin_bit_cast(bf16x8, ra4));
+          accumulate(oc[dm], x, __builtin_bit_cast(bf16x8, rc4));
+        }(), ...);
+      }(std::make_integer_sequence<int, kNV>{});
+    }
+    share = -kShare;
+    ta_last = ta;
+    tc_last = tc;
+  };
+
+  if (n_it > 0) {
+    const bool odd = C::kSub == 2 && (n_blocks & 1);
+    const uint32_t first_stage = odd ? 2u : 0u, first_off = first_stage * kStage;
+    {
+      // the products of tile -1 have P = 0: their V operand only has to be finite
+      u32x4 *z = reinterpret_cast<u32x4 *>(smem + kVBase + ((first_stage + 3) & 3) * kStage);
+      for (int x = tid; x < kStage / 16; x += C::kThreads) z[x] = u32x4{0, 0, 0, 0};
+    }
+    __syncthreads();   // cols[] is written
+    // K of tiles 0, 1, 2 and V of tiles 0, 1
+    for (int t = 0; t < 3; ++t) {
+      auto advance = [&](auto new_block) __attribute__((always_inline)) {
+        next_tile(std::integral_constant<int, 0>{}, new_block, std::true_type{});
+        next_tile(std::integral_constant<int, 1>{}, new_block, std::true_type{});
+        next_tile(std::integral_constant<int, 2>{}, new_block, std::true_type{});
+      };
+      if (t % C::kSub == 0) {
+        fetch_entry();
+        advance(std::true_type{});
+      } else {
+        advance(std::false_type{});
+      }
+      set_offsets();
+      auto issue = [&]<int... I>(std::integer_sequence<int, I...>, uint64_t base, const uint32_t *off) __attribute__((always_inline)) {
+        (copy_one(std::integral_constant<int, I>{}, base, off), ...);
+      };
+      issue(std::make_integer_sequence<int, kI>{}, lds_dma_begin(base_k, smem_addr + ((t + first_stage) & 3u) * kStage + copy_k.lds0), off_k);
+      if (t > 0)
+        issue(std::make_integer_sequence<int, kI>{}, lds_dma_begin(base_v, smem_addr + kVBase + ((t - 1 + first_stage) & 3u) * kStage + copy_v.lds0), off_v);
+    }
+    {
+      // the tiles of iteration 0
+      constexpr std::bool_constant<3 % C::kSub == 0> new_block{};
+      if constexpr (new_block) fetch_entry();
+      next_tile(std::integral_constant<int, 0>{}, new_block, std::true_type{});
+      next_tile(std::integral_constant<int, 1>{}, new_block, std::true_type{});
+      next_tile(std::integral_constant<int, 2>{}, new_block, std::true_type{});
+      set_offsets();
+    }
+    fetch_current();
+    next_current(std::true_type{});
+    left = C::kST;
+    wait_copies(std::integral_constant<int, 3 * kI>{});   // K of tiles 0 and 1
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) row_at[s] += first_off;
+    s0a = s0c = zero16;
+    [&]<int... E>(std::integer_sequence<int, E...>) __attribute__((always_inline)) {
+      ([&]() __attribute__((always_inline)) {
+        read_row(std::integral_constant<int, E>{}, std::integral_constant<int, 0>{});
+        s0a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_ring[E % kRing], qa[E], s0a, 0, 0, 0);
+        s0c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_ring[E % kRing], qc[E], s0c, 0, 0, 0);
+      }(), ...);
+    }(std::make_integer_sequence<int, kNS>{});
+    // first operands of iteration 0
+    [&]<int... E>(std::integer_sequence<int, E...>) __attribute__((always_inline)) {
+      (read_row(std::integral_constant<int, E>{}, std::integral_constant<int, 1>{}), ...);
+    }(std::make_integer_sequence<int, kDepth>{});
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) row_at[s] -= first_off;
+    // the first references: the row maxima of tile 0, which always has a key
+    if (key_t + C::kST > key_end) mask_tile(s0a, s0c);
+    ma = fmaxf(own_a, row_max(s0a, bias));
+    mc = fmaxf(own_c, row_max(s0c, bias));
+    ma = ma == -INFINITY ? 0.f : ma;
+    mc = mc == -INFINITY ? 0.f : mc;
+    settle();
+    const std::true_type tail{};
+    const std::false_type plain{};
+    const std::integral_constant<int, 0> u0{};
+    const std::integral_constant<int, 1> u1{};
+    const std::integral_constant<int, 2> u2{};
+    const std::integral_constant<int, 3> u3{};
+    int t = 0;
+    if (odd) {
+      body(u2, tail, s0a, s0c, s1a, s1c, p0, p1);
+      body(u3, tail, s1a, s1c, s0a, s0c, p1, p0);
+      t = 2;
+    }
+    // As long as the copies (three tiles ahead) stay inside the blocks in front of the last one of the row's own
+    // list nothing is ragged or pooled.
+    const int n_plain = (n_own_blocks - 1) * C::kSub - 6;
+    if (t <= n_plain) {
+      for (; t <= n_plain; t += 4) {
+        body(u0, plain, s0a, s0c, s1a, s1c, p0, p1);
+        body(u1, plain, s1a, s1c, s0a, s0c, p1, p0);
+        body(u2, plain, s0a, s0c, s1a, s1c, p0, p1);
+        body(u3, plain, s1a, s1c, s0a, s0c, p1, p0);
+      }
+      cur_at = t / C::kSub;
+      fetch_current();
+      next_current(tail);
+      left = C::kST;
+    }
+    for (; t < n_it; t += 4) {
+      body(u0, tail, s0a, s0c, s1a, s1c, p0, p1);
+      body(u1, tail, s1a, s1c, s0a, s0c, p1, p0);
+      body(u2, tail, s0a, s0c, s1a, s1c, p0, p1);
+      body(u3, tail, s1a, s1c, s0a, s0c, p1, p0);
+    }
+    // the last tile's P V (stage 3: the loop ends on a multiple of four)
+    __builtin_amdgcn_s_waitcnt(0x0F70);          // stray copies must land before the LDS is given up
+    if (left < C::kST) zero_rows(3, left);
+    la += ta_last;
+    lc += tc_last;
+    [&]<int... F>(std::integer_sequence<int, F...>) __attribute__((always_inline)) {
+      ([&]() __attribute__((always_inline)) {
+        read_tr(std::integral_constant<int, F>{}, std::integral_constant<int, 3>{}, std::integral_constant<int, 0>{});
+        read_tr(std::integral_constant<int, F>{}, std::integral_constant<int, 3>{}, std::integral_constant<int, 1>{});
+        pv(std::integral_constant<int, F>{}, std::integral_constant<int, 0>{}, p1);
+        pv(std::integral_constant<int, F>{}, std::integral_constant<int, 1>{}, p1);
+      }(), ...);
+    }(std::make_integer_sequence<int, kNV>{});
+    settle();
+  }
+
+  auto emit = [&](f32x16 (&acc)[kDm], int qrow, float m, float l_half) __attribute__((always_inline)) {
+    const float l_tot = l_half + swap_halves(l_half);
+    if (qrow >= a.L) return;
+    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+    bf16 *os = slab_ptr(a.o, a.to, slab, a.H) + (int64_t)qrow * a.to.sL;
+    bf16 *ls = a.o_lo ? slab_ptr(a.o_lo, a.to, slab, a.H) + (int64_t)qrow * a.to.sL : nullptr;
+#pragma unroll
+    for (int dm = 0; dm < kDm; ++dm) {
+      uint32_t w[8], r[8];
+#pragma unroll
+      for (int i = 0; i < 16; i += 2) {
+        const float v0 = acc[dm][i] * inv, v1 = acc[dm][i + 1] * inv;
+        const uint32_t pk = pack_bf16x2(v0, v1);
+        w[i >> 1] = pk;
+        r[i >> 1] = pack_bf16x2(v0 - bf16_bits_to_float(pk & 0xffffu),
+                                v1 - bf16_bits_to_float(pk >> 16));
+      }
+      uint4 *dst = reinterpret_cast<uint4 *>(os + dm * 32 + 16 * hl);
+      dst[0] = make_uint4(w[0], w[1], w[2], w[3]);
+      dst[1] = make_uint4(w[4], w[5], w[6], w[7]);
+      if (ls) {
+        uint4 *dl = reinterpret_cast<uint4 *>(ls + dm * 32 + 16 * hl);
+        dl[0] = make_uint4(r[0], r[1], r[2], r[3]);
+        dl[1] = make_uint4(r[4], r[5], r[6], r[7]);
+      }
+    }
+    if (hl == 0)
+      a.lse[(int64_t)slab * a.L + qrow] =
+          l_tot > 0.f ? m * 0.69314718055994530942f + __logf(l_tot) : -INFINITY;
+  };
+  emit(oa, qrow0, ma, la);
+  emit(oc, qrow0 + 32, mc, lc);
+}
+
 template <int BLK, int D, bool VT>
 static hipError_t launch_lock_step(const FwdArgs &a, int grid, hipStream_t st) {
   using C = FwdCfg<BLK, D>;
@@ -1353,6 +2039,17 @@ static hipError_t launch_pipe(const FwdArgs &a, int grid, hipStream_t st) {
   if (e != hipSuccess) return e;
   timing_begin(st);
   hipLaunchKernelGGL((fwd_pipe_kernel<BLK, D, GT>), dim3(grid), dim3(X::kThreads), X::kLds, st, a);
+  return hipGetLastError();
+}
+
+template <int BLK, int D, int QW, bool GT>
+static hipError_t launch_wide(const FwdArgs &a, hipStream_t st) {
+  using X = WideCfg<BLK, D, QW>;
+  const int n_q = X::kRows == BLK ? a.Nb : (a.L + X::kRows - 1) / X::kRows;
+  const hipError_t e = set_dynamic_lds_once(reinterpret_cast<const void *>(&fwd_wide_kernel<BLK, D, QW, GT>), X::kLds);
+  if (e != hipSuccess) return e;
+  timing_begin(st);
+  hipLaunchKernelGGL((fwd_wide_kernel<BLK, D, QW, GT>), dim3(xcd_grid(a.n_slabs * n_q)), dim3(X::kThreads), X::kLds, st, a);
   return hipGetLastError();
 }
 
@@ -1379,8 +2076,16 @@ template <int BLK, int D>
 static hipError_t launch_fwd_t(const FwdArgs &a, hipStream_t st) {
   const int total = a.n_slabs * a.Nb, grid = xcd_grid(total);
   // Which kernel.  Measured on MI355X, the transposition of V included where a kernel needs it:
-  //   block 128 / d 128, long rows: ping-pong 1.56 ms, pipelined 1.84 ms (12 heads of 32 760 tokens, a
-  //     quarter of the tiles); short rows: see below.
+  //   block 128 / d 128, more than 256 query blocks: the wide kernel, two of whose workgroups share a compute unit
+  //     (12 heads of 32 760 tokens, a quarter of the tiles 1.44 ms, ping-pong 1.60; 320 .. 3072 query blocks of 8 .. 64
+  //     tiles 1.0-1.5x, in the worst case, 513 .. 768 blocks of more than 32 tiles, 0.93-1.0).  Without lists the
+  //     workgroups of 256 rows (1.01-1.03x those of 128) and, in that worst case, ping-pong (632 blocks of 79 tiles 426
+  //     us and 461).  Rows of fewer than 8 tiles: lock-step from V's rows, which hides a workgroup's start and the second
+  //     products of the wide kernel better (lists of 5 tiles 302 us, mask included, and 338).
+  //   block 128 / d 128, up to 256 query blocks: half of the SIMDs would be idle with the wide kernel, so ping-pong from
+  //     18 tiles per row on (256 blocks of 64 tiles 138 us and 164, of 16: 60 and 48).
+  //   The host cannot see the lists: with lists both kernels of a pair are launched and each workgroup leaves at once
+  //     if its (batch, head) slab's tile count belongs to the other (an empty launch costs 4-10 us).
   //   block 64 / d 64: 48 heads of 17 776 tokens, 13 344 workgroups: lock-step 1.24 ms, pipelined 1.31 ms
   //     (four wavefronts per SIMD against two: vector throughput decides); 2 heads of 1 024 tokens,
   //     32 workgroups: pipelined 12 us, lock-step 17 us (one wavefront's own speed decides).  The
@@ -1397,14 +2102,15 @@ static hipError_t launch_fwd_t(const FwdArgs &a, hipStream_t st) {
   //     lengths from the host and stay pipelined: rows of one length are then 2-6 % slower than
   //     lock-step beyond 1000 workgroups (11 % at 1600 of 10 tiles, block 64 / d 128), uneven ones up to
   //     1.5x faster.
-  //   pooled tokens: ping-pong at block 128 / d 128, pipelined otherwise, except at d 64 where all ping-pong
+  //   pooled tokens: wide at block 128 / d 128 (12 heads of 32 760 tokens 1.85 -> 1.55 ms; ping-pong up to 256 query
+  //     blocks: 237 of 16 tiles equal, fewer 0.85-0.9 with the wide one), pipelined otherwise, except at d 64 where all ping-pong
   //     workgroups (two groups of wavefronts per query block) start at once and their rows are long: from
   //     16 tiles at block 128 (144 workgroups: 14 tiles 37 us against 35 pipelined, 36 tiles 65 against
   //     76, 144 tiles 199 against 269) and 24 at block 64 (512 workgroups: 8 tiles 30 against 25, 26
   //     tiles 45 and 48, 128 tiles 130 against 177).  Lists hide their lengths: an eighth of the blocks is
   //     assumed (fixed budgets keep a quarter, the threshold alone a few per cent).
   // The ping-pong kernel addresses K tiles by 32-bit byte offsets inside a slab: slabs of 4 GiB and
-  // more take the lock-step kernel.  The tests can force the ping-pong (2) or the lock-step kernel (1) where
+  // more take the wide and the lock-step kernel.  The tests can force the ping-pong (2) or the lock-step kernel (1) where
   // the shape has it (asa_test_force_fwd_kernel).
   const bool fits32 = (uint64_t)a.Nb * BLK * (uint64_t)a.tk.sL * 2u < 0xFFFFFFFFull;
   const bool pooled = a.Nbg > 0, dense = a.row_ptr == nullptr;
@@ -1429,37 +2135,50 @@ static hipError_t launch_fwd_t(const FwdArgs &a, hipStream_t st) {
                    (total > 2 * resident && total <= 3 * resident);
     if (fits_pipe && forced != 1) return launch_pipe<BLK, D, false>(b, grid, st);
   } else {
-    if (pooled) return launch_ping_pong<BLK, D, true>(b, grid, st);
-    // Short lists: the ping-pong kernel costs ~8 us per workgroup around its steady state, the lock-step
-    // kernel ~3 us; they cross at 16-20 tiles per row.  The host cannot see the lists, so with lists
-    // BOTH kernels are launched and each workgroup leaves at once if its (batch, head) slab's tile count
-    // belongs to the other kernel (the launch that finds nothing to do costs 4-10 us); the transposition
-    // of V leaves out the slabs of the lock-step kernel, which reads the rows of V themselves there.
-    // Without lists (dense) every row holds Nb tiles and the choice is made here.
-    constexpr int kPingPongMinTiles = 18;
-    b.select_min_tiles = kPingPongMinTiles;
-    if (fits32 && forced != 1 && !(forced == 0 && dense && a.Nb < kPingPongMinTiles)) {
-      const bool both = forced == 0 && !dense;
-      if (both) b.select = 1;
-      const hipError_t e = launch_ping_pong<BLK, D, false>(b, grid, st);
-      if (e != hipSuccess || !both) return e;
+    const bool few = total <= 256;
+    if (pooled) return few ? launch_ping_pong<BLK, D, true>(b, grid, st) : launch_wide<BLK, D, 2, true>(b, st);
+    constexpr int kPingPongMinTiles = 18, kWideMinTiles = 8;
+    if (fits32 && forced == 2) return launch_ping_pong<BLK, D, false>(b, grid, st);
+    if (forced == 0 && dense) {
+      const bool half_round = total > 512 && total <= 768;
+      if (fits32 && a.Nb >= kPingPongMinTiles && (few || half_round)) return launch_ping_pong<BLK, D, false>(b, grid, st);
+      return few ? launch_wide<BLK, D, 2, false>(b, st) : launch_wide<BLK, D, 4, false>(b, st);
+    }
+    if (forced == 0 && few) {
+      if (fits32) {
+        b.select = 1;
+        b.select_min_tiles = kPingPongMinTiles;
+        const hipError_t e = launch_ping_pong<BLK, D, false>(b, grid, st);
+        if (e != hipSuccess) return e;
+        b.select = -1;
+      }
+      return launch_wide<BLK, D, 2, false>(b, st);
+    }
+    if (forced == 0) {
+      b.select = 1;
+      b.select_min_tiles = kWideMinTiles;
+      const hipError_t e = launch_wide<BLK, D, 2, false>(b, st);
+      if (e != hipSuccess) return e;
       b.select = -1;
       return launch_lock_step<BLK, D, false>(b, grid, st);
     }
+    timing_begin(st);
+    return launch_lock_step<BLK, D, false>(b, grid, st);
   }
   // The lock-step kernel reads V's rows or their transposed copy.  Block 64 / d 64: 1.25 ms, or 1.20 ms +
   // 0.035 for the copy (48 heads of 17 776 tokens).  Mixed shapes: the rows cost more per tile, the copy costs
   // the same whatever the length of the rows; equal at about 3 500 keys per row (block 64 / d 128: 16 tiles
   // 43 and 48 us, 79 tiles 170 and 166; block 128 / d 64: 20 tiles 109 and 118, 79 tiles 311 and 303).
-  const bool copy_v = kSmallTile || (!kPingPongShape && a.L >= 3584);
-  if (copy_v) {
-    const hipError_t e = launch_transpose(a.v, a.tv, a.H, a.L, a.Lpad, BLK, D, a.n_slabs, a.vt, st);
-    if (e != hipSuccess) return e;
+  if constexpr (!kPingPongShape) {
+    const bool copy_v = kSmallTile || a.L >= 3584;
+    if (copy_v) {
+      const hipError_t e = launch_transpose(a.v, a.tv, a.H, a.L, a.Lpad, BLK, D, a.n_slabs, a.vt, st);
+      if (e != hipSuccess) return e;
+    }
+    timing_begin(st);
+    if constexpr (kSmallTile) return launch_lock_step<BLK, D, true>(b, grid, st);
+    else return copy_v ? launch_lock_step<BLK, D, true>(b, grid, st) : launch_lock_step<BLK, D, false>(b, grid, st);
   }
-  timing_begin(st);
-  if constexpr (kSmallTile) return launch_lock_step<BLK, D, true>(b, grid, st);
-  else if constexpr (kPingPongShape) return launch_lock_step<BLK, D, false>(b, grid, st);
-  else return copy_v ? launch_lock_step<BLK, D, true>(b, grid, st) : launch_lock_step<BLK, D, false>(b, grid, st);
 }
 
 hipError_t launch_fwd(const Problem &pb, const void *q, const void *k, const void *v, const void *vt,

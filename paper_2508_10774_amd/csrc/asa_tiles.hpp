@@ -105,6 +105,27 @@ __device__ __forceinline__ void lds_dma16_sv(const void *uniform_base, uint32_t 
                : "v"(lane_off), "s"(bu), "s"((uint32_t)__builtin_amdgcn_readfirstlane(lds_byte_addr)) : "memory");
 #endif
 }
+// The same for several loads in a row that share M0 and the base: lds_dma_begin sets M0 and returns the scalar copy of the
+// base, lds_dma16_next<X> loads with X bytes added to the global AND to the LDS address (X < 4096).  Nothing else may write
+// M0 in between (tests/test_asm_hazards.py looks).
+__device__ __forceinline__ uint64_t lds_dma_begin(const void *uniform_base, uint32_t lds_byte_addr) {
+  uint64_t base_copy = 0;
+#if defined(__HIP_DEVICE_COMPILE__)
+  const uint64_t b = reinterpret_cast<uint64_t>(uniform_base);
+  const uint64_t bu = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b) |
+                      ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32)) << 32);
+  asm volatile("s_mov_b32 m0, %2\n\ts_mov_b64 %0, %1"
+               : "=&s"(base_copy)
+               : "s"(bu), "s"((uint32_t)__builtin_amdgcn_readfirstlane(lds_byte_addr)) : "memory");
+#endif
+  return base_copy;
+}
+template <int X>
+__device__ __forceinline__ void lds_dma16_next(uint64_t base_copy, uint32_t lane_off) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" : : "v"(lane_off), "s"(base_copy), "n"(X) : "memory");
+#endif
+}
 // The same with 4 bytes per lane.
 __device__ __forceinline__ void lds_dma4_sv(const void *uniform_base, uint32_t lane_off, uint32_t lds_byte_addr) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -120,6 +141,18 @@ __device__ __forceinline__ void lds_dma4_sv(const void *uniform_base, uint32_t l
 // LDS byte address of an object that the compiler knows to live in LDS (apply it to the
 // __shared__ array itself, not to a pointer that travelled through generic address space)
 #define ASA_LDS_ADDR_OF(shared_array) ((uint32_t)(uintptr_t)(::asa::lds_void *)(shared_array))
+
+// The compiler places no wait states around a written-out MFMA (tests/test_asm_hazards.py walks the
+// assembly).  settle_acc in front of a loop and behind it keeps what the compiler does with the
+// accumulators (zeros, copies, reads) away from the loop's MFMAs: 2 states after a vector instruction has
+// written an operand, 19 before one reads a result.
+template <int N>
+__device__ __forceinline__ void settle_acc(f32x16 (&acc)[N]) {
+  static_assert(N == 4, "D = 128");
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_nop 15\n\ts_nop 3" : "+a"(acc[0]), "+a"(acc[1]), "+a"(acc[2]), "+a"(acc[3]));
+#endif
+}
 
 // ---------------------------------------------------------------------------------------
 // Cooperative tile copies global -> LDS for a workgroup of WAVES wavefronts.  Per-lane byte

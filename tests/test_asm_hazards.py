@@ -138,6 +138,26 @@ def test_wait_states_around_written_out_instructions(assembly, src, kinds):
     assert all(total[k] > 0 for k in kinds)
 
 
+def _m0_outside_inline_code(text):
+    """Instructions of the compiler's own that name M0."""
+    inline, found = False, []
+    for line in text.splitlines():
+        inline = (inline or "ASMSTART" in line) and "ASMEND" not in line
+        code = line.split(";")[0]
+        if not inline and re.search(r"\bm0\b", code):
+            found.append(code.strip())
+    return found
+
+
+def test_only_the_written_out_loads_of_a_tile_set_m0(assembly):
+    """Several loads in a row share one write of M0 (lds_dma_begin): the compiler must not use it in between."""
+    for name, lines in _functions(assembly["asa_fwd.hip"]):
+        if "fwd_wide_kernel" in name:
+            assert not _m0_outside_inline_code("\n".join(lines)), name
+    planted = "\t;;#ASMSTART\n\ts_mov_b32 m0, s1\n\t;;#ASMEND\n\ts_mov_b32 m0, s2"
+    assert _m0_outside_inline_code(planted) == ["s_mov_b32 m0, s2"]
+
+
 LOOP = """.LBB0_1:
 \tds_read_b128 v[4:7], v20
 \t{front}
