@@ -163,15 +163,13 @@ struct BwdCfg {
 // a.ndelta_out.  Used when the caller has not kept the low half of O: Delta from the bf16 O alone
 // is off by up to 0.05 in rows whose soft-max is spread over keys with similar values, and that
 // error goes into dQ and dK times the size of the keys / queries.
-template <int BLK, int D, bool GT, bool DELTA_ONLY = false>
-__global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kDqWavesPerSimd)) void dq_kernel(BwdArgs a) {
+template <int BLK, int D, bool GT, bool DELTA_ONLY>
+__device__ __forceinline__ void dq_walk(const BwdArgs &a, int workgroup, unsigned char *smem, int *cols) {
   using C = BwdCfg<BLK, D>;
-  extern __shared__ __align__(1024) unsigned char smem[];
-  __shared__ int cols[kMaxNb];
   constexpr int kVOff = C::kTile, kStage = C::kDqStage;
   constexpr int kPooled = 1 << 30;             // flag of an entry of cols[]: a block of pooled tokens
 
-  const int slot = xcd_contiguous_work(blockIdx.x, a.n_slabs * a.Nb);
+  const int slot = xcd_contiguous_work(workgroup, a.n_slabs * a.Nb);
   if (slot < 0) return;
   const int work = a.order_q ? a.order_q[slot] : slot;
   const int slab = work / a.Nb;
@@ -514,13 +512,11 @@ __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kDqWavesPerSimd)) void dq
 // Q or dO exists, in LDS or in memory.
 // ---------------------------------------------------------------------------------------
 template <int BLK, int D>
-__global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dkv_kernel(BwdArgs a) {
+__device__ __forceinline__ void dkv_walk(const BwdArgs &a, int workgroup, unsigned char *smem, int *rows) {
   using C = BwdCfg<BLK, D>;
-  extern __shared__ __align__(1024) unsigned char smem[];
-  __shared__ int rows[kMaxNb];
   constexpr int kGOff = C::kTile, kStatOff = 2 * C::kTile, kStage = C::kDkvStage;
 
-  const int work_c = xcd_contiguous_work(blockIdx.x, a.n_slabs * a.Nbk * a.q_chunks);
+  const int work_c = xcd_contiguous_work(workgroup, a.n_slabs * a.Nbk * a.q_chunks);
   if (work_c < 0) return;
   const int chunk = work_c % a.q_chunks;      // range of query blocks (1 range unless pooled keys)
   const int work = a.order ? a.order[work_c] : work_c / a.q_chunks;
@@ -876,6 +872,38 @@ __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dkv_
 }
 
 static size_t round256(size_t x) { return (x + 255) & ~(size_t)255; }
+template <int BLK, int D, bool GT, bool DELTA_ONLY = false>
+__global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kDqWavesPerSimd)) void dq_kernel(BwdArgs a) {
+  extern __shared__ __align__(1024) unsigned char smem[];
+  __shared__ int cols[kMaxNb];
+  dq_walk<BLK, D, GT, DELTA_ONLY>(a, blockIdx.x, smem, cols);
+}
+
+template <int BLK, int D>
+__global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dkv_kernel(BwdArgs a) {
+  extern __shared__ __align__(1024) unsigned char smem[];
+  __shared__ int rows[kMaxNb];
+  dkv_walk<BLK, D>(a, blockIdx.x, smem, rows);
+}
+
+// dK / dV and dQ in one launch: neither needs the other's results, so the dQ workgroups fill the compute
+// units that the last round of dK / dV leaves idle, and a small call is one chain of workgroups instead of two.
+// Bound of such calls: the longest workgroup and the start of a launch.  Backward of two launches -> one, same
+// bits (d 64 / block 64 unless stated): 34 workgroups per gradient 20.7 -> 15.3 us, 378 67 -> 51, 1016 180 -> 148,
+// 3048 380 -> 377; block 64 / d 128: 378 83 -> 69, 1016 267 -> 256, 3048 737 -> 732; block 128 / d 64: 192
+// 60 -> 44, 512 166 -> 137, 1536 362 -> 357; block 128 / d 128: 18 33 -> 22, 192 83 -> 75, 320 129 -> 115.
+// Many rounds hide the last one, and two kinds of lists at a time share less of the L2: 6144 workgroups of block 64
+// 1192 -> 1206 us at d 64, 2331 -> 2372 at d 128; block 128 / d 128, where dQ here has one wavefront per SIMD instead
+// of two, 768 equal, 1024 319 -> 324, 1280 581 -> 602.
+template <int BLK, int D, bool GT>
+__global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dkv_dq_kernel(BwdArgs a) {
+  extern __shared__ __align__(1024) unsigned char smem[];
+  __shared__ int list[kMaxNb];
+  const int first_dq = gridDim.x / 2;          // (a multiple of the number of XCDs)
+  if ((int)blockIdx.x < first_dq) dkv_walk<BLK, D>(a, blockIdx.x, smem, list);
+  else dq_walk<BLK, D, GT, false>(a, (int)blockIdx.x - first_dq, smem, list);
+}
+
 static size_t order_bytes(const Problem &pb) {
   return round256((size_t)pb.n_slabs * pb.Nb * sizeof(int32_t));
 }
@@ -926,8 +954,17 @@ static hipError_t launch_bwd_t(const BwdArgs &a, const BwdArgs *pooled_launch, h
     }
     hipError_t e0 = set_dynamic_lds_once(reinterpret_cast<const void *>(&dkv_kernel<BLK, D>), C::kDkvLds);
     if (e0 != hipSuccess) return e0;
+    const void *both_fns[2] = {reinterpret_cast<const void *>(&dkv_dq_kernel<BLK, D, false>),
+                               reinterpret_cast<const void *>(&dkv_dq_kernel<BLK, D, true>)};
+    for (const void *fn : both_fns) {
+      e0 = set_dynamic_lds_once(fn, C::kDkvLds);
+      if (e0 != hipSuccess) return e0;
+    }
   }
   const int grid = xcd_grid(a.n_slabs * a.Nb);
+  // One launch or two (see dkv_dq_kernel): the line is where the gain of filling the last round has gone.
+  const int resident = BLK == 64 && D == 64 ? 1024 : (BLK == 128 && D == 128 ? 256 : 512);
+  const bool together = a.n_slabs * a.Nb <= (BLK == D ? 3 : 6) * resident;
   hipError_t e = hipSuccess;
   if (a.ndelta_out) {
     // no low half of O from the caller: Delta from the tiles themselves, before anything uses it
@@ -954,6 +991,15 @@ static hipError_t launch_bwd_t(const BwdArgs &a, const BwdArgs *pooled_launch, h
     }
   }
   // ... then the tokens' own gradients, which add their share of the pooled ones
+  if (e == hipSuccess && together) {
+    if (pooled_launch)
+      hipLaunchKernelGGL((dkv_dq_kernel<BLK, D, true>), dim3(2 * grid), dim3(C::kThreads), C::kDkvLds, st, a);
+    else
+      hipLaunchKernelGGL((dkv_dq_kernel<BLK, D, false>), dim3(2 * grid), dim3(C::kThreads), C::kDkvLds, st, a);
+    e = hipGetLastError();
+    timing_end(st);
+    return e;
+  }
   if (e == hipSuccess) {
     hipLaunchKernelGGL((dkv_kernel<BLK, D>), dim3(grid), dim3(C::kThreads), C::kDkvLds, st, a);
     e = hipGetLastError();

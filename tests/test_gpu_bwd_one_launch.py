@@ -1,0 +1,84 @@
+"""GPU parity of the backward on both sides of the choice between one launch for dK / dV and dQ and two: the
+same tiles in the same order, so the gradients of a head are the same bits in a call with few heads (one launch)
+and in one with many (two), with lists, without, and with pooled tokens."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2508_10774_amd import binding, synth
+from tests import util
+
+pytestmark = pytest.mark.gpu
+
+NB, TAIL = 6, 21
+# heads on the last and on the first side of the line: 3 (block and d alike) or 6 rounds of resident workgroups
+LINE = {(64, 64): 3072, (128, 128): 768, (128, 64): 3072, (64, 128): 3072}
+
+
+@pytest.mark.parametrize("with_lo", [True, False])
+@pytest.mark.parametrize("lists", [True, False])
+@pytest.mark.parametrize("block,d", list(LINE))
+def test_a_head_has_the_same_gradients_in_one_launch_and_in_two(block, d, lists, with_lo):
+    L = (NB - 1) * block + TAIL
+    most = LINE[block, d] // NB
+    print(f"case block={block} d={d} lists={lists} lo={with_lo}", flush=True)
+    base = [synth.make_iid((1, 2, L, d), block + d, s) for s in range(4)]
+    base_mask = synth.random_block_mask(NB, 0.5, seed=d, slabs=2)
+    if not lists:
+        base_mask[:] = 1
+
+    def inputs(heads):
+        at = np.arange(heads) % 2
+        p = binding.Params(B=1, H=heads, L=L, d=d, block=block)
+        bufs = (util.lists_from_mask(p, base_mask[at]) if lists else
+                dict.fromkeys(("row_ptr", "col_idx", "col_ptr", "row_idx")))
+        return p, bufs, [util.dev_bf16(x[:, at]) for x in base]
+
+    p, bufs, (q, k, v, g) = inputs(2)
+    o, lse, o_lo = util.run_fwd(p, q, k, v, bufs, with_lo=True)
+    one = util.run_bwd(p, q, k, v, o, lse, g, bufs, o_lo=o_lo if with_lo else None)
+    qf, kf, vf, gf = (synth.bf16_bits_to_f32(x) for x in base)
+    for h in range(2):
+        want = oracle.attn_bwd(qf[0, h], kf[0, h], vf[0, h], gf[0, h], base_mask[h], block, None)
+        for got, w, name in zip(one, want, ("dQ", "dK", "dV")):
+            util.assert_close_bf16(util.host_f32(got)[0, h], w, f"{name}[{h}]")
+    for heads in (most, most + 1):
+        p, bufs, (q, k, v, g) = inputs(heads)
+        at = torch.arange(heads, device="cuda") % 2
+        many = util.run_bwd(p, q, k, v, o[:, at], lse[at], g, bufs, o_lo=o_lo[:, at] if with_lo else None)
+        for a, b, name in zip(many, one, ("dQ", "dK", "dV")):
+            assert torch.equal(a.view(torch.int16), b[:, at].view(torch.int16)), f"{name} {heads} heads"
+
+
+def test_the_same_with_pooled_tokens():
+    """(Block 128 / d 128: there the pooled tokens' own sums have as many parts on both sides of the line.)"""
+    block = d = 128
+    L, n = (NB - 1) * block + TAIL, 32
+    few, many = LINE[block, d] // NB - 1, LINE[block, d] // NB + 1
+    print(f"case pooled block={block} d={d}", flush=True)
+    base = [synth.make_iid((1, 2, L, d), block, s) for s in range(4)]
+    base_mask = synth.random_block_mask(NB, 0.5, seed=d, slabs=2)
+    grads = []
+    for heads in (few, many):
+        at = np.arange(heads) % 2
+        p = binding.Params(B=1, H=heads, L=L, d=d, block=block)
+        bufs = util.lists_from_mask(p, base_mask[at])
+        q, k, v, g = (util.dev_bf16(x[:, at]) for x in base)
+        G = binding.asa_global_token_count(p, n)
+        kg, vg = (torch.zeros(1, heads, G, d, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        ws = binding.alloc_workspace(max(binding.asa_fwd_g_workspace_bytes(p, n), binding.asa_bwd_g_workspace_bytes(p, n)))
+        o, o_lo = torch.empty_like(q), torch.empty_like(q)
+        lse = torch.empty((heads, L), dtype=torch.float32, device="cuda")
+        binding.asa_global_tokens(p, n, k, v, kg, vg)
+        binding.asa_attn_fwd_g(p, n, q, k, v, kg, vg, bufs["row_ptr"], bufs["col_idx"], o, lse, ws, o_lo=o_lo)
+        out = [torch.full_like(q, float("nan")) for _ in range(3)]
+        binding.asa_attn_bwd_g(p, n, q, k, v, kg, vg, o, g, lse, bufs["row_ptr"], bufs["col_idx"], bufs["col_ptr"],
+                               bufs["row_idx"], *out, ws, o_lo=o_lo)
+        grads.append(out)
+    for a, b, name in zip(*grads, ("dQ", "dK", "dV")):
+        assert torch.isfinite(a).all() and torch.isfinite(b).all()
+        # (the heads repeat with period 2)
+        assert torch.equal(a[:, 2:4].view(torch.int16), a[:, :2].view(torch.int16)), name
+        assert torch.equal(a[:, :2].view(torch.int16), b[:, :2].view(torch.int16)), name
