@@ -1339,7 +1339,7 @@ __global__ __launch_bounds__(BLK * 2, (PipeCfg<BLK, D>::kWavesPerSimd)) void fwd
 // ---------------------------------------------------------------------------------------
 // Wide forward: 64 query rows per wavefront, one wavefront per SIMD, with the software pipeline of the backward kernels
 // (see asa_bwd.hip) inside it.  QW wavefronts share the tiles of 32 keys: two (one query block of 128) with index lists,
-// four (256 rows of a dense call).  In iteration t a wavefront computes S^T of tile t + 1 for its two halves of 32 rows,
+// four (256 rows of a dense call, whatever its block size).  In iteration t a wavefront computes S^T of tile t + 1 for its two halves of 32 rows,
 // adds P V of tile t - 1, and between those MFMAs turns S^T of tile t into P.  Every operand read from LDS feeds two
 // MFMAs.  V comes from its rows by the transposing LDS read: no transposed copy.  O lives in accumulation registers.
 //
@@ -1373,7 +1373,7 @@ struct WideCfg {
   static constexpr int kStages = 4;
   static constexpr int kTile = kST * D * 2;            // bytes of one row tile
   static constexpr int kLds = 2 * kStages * kTile;     // K stages, then V stages
-  static constexpr bool kAcc = D == 128;               // O in accumulation registers
+  static_assert(BLK == 128, "the plain loop ends in front of the last block: four tiles in it");
 };
 
 template <int BLK, int D, int QW, bool GT>
@@ -1656,8 +1656,7 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
   for (int i = 0; i < 16; ++i) p0[i] = p1[i] = 0;
   auto accumulate = [](f32x16 &acc, bf16x8 x, bf16x8 y) __attribute__((always_inline)) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    if constexpr (C::kAcc) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(x), "v"(y));
-    else acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, acc, 0, 0, 0);
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(x), "v"(y));
 #endif
   };
   auto pv = [&](auto f_tag, auto half_tag, const uint32_t *p) __attribute__((always_inline)) {
@@ -1696,10 +1695,8 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
     return max_of_halves(mx) * c + bias_t;
   };
   auto settle = [&]() __attribute__((always_inline)) {
-    if constexpr (C::kAcc) {
-      settle_acc(oa);
-      settle_acc(oc);
-    }
+    settle_acc(oa);
+    settle_acc(oc);
   };
 
   float share = -INFINITY;                           // (-inf * 0: no comparison holds at the first tile)
@@ -1938,6 +1935,8 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
     mc = fmaxf(own_c, row_max(s0c, bias));
     ma = ma == -INFINITY ? 0.f : ma;
     mc = mc == -INFINITY ? 0.f : mc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) pin(p1[i]);     // (zeros in registers here, not right in front of an MFMA)
     settle();
     const std::true_type tail{};
     const std::false_type plain{};
@@ -2102,6 +2101,13 @@ static hipError_t launch_fwd_t(const FwdArgs &a, hipStream_t st) {
   //     lengths from the host and stay pipelined: rows of one length are then 2-6 % slower than
   //     lock-step beyond 1000 workgroups (11 % at 1600 of 10 tiles, block 64 / d 128), uneven ones up to
   //     1.5x faster.
+  //   block 64 without lists: the wide kernel, whose workgroups of 256 rows move a quarter of the bytes per product, where
+  //     rows are long and its rounds of 256 workgroups are filled.  d 128, workgroups x tokens: 192 x 4 030 146 -> 131 us,
+  //     256 x 8 100 332 -> 256, 384 x 8 100 492 -> 432, 768 x 8 100 982 -> 741, 3072 x 32 760 15.8 -> 10.8 ms; 384 x 4 030
+  //     equal, 128 x 8 100 169 and 208.  d 64: 256 x 8 100 193 -> 180, 768 x 8 100 555 -> 507, 3072 x 32 760 8.06 -> 6.97
+  //     ms; 384 x 8 100 307 and 326, 448 x 8 100 316 and 335, 256 x 4 030 98 and 103.  (Block 128 / d 64: 1.03-1.05x at 32 760 tokens, 0.8-1.0
+  //     below: not taken.  With lists at d 64 a wavefront's own copies bound it: 1461 us and 1526 at block 64, 48 heads
+  //     of 17 776 tokens.)
   //   pooled tokens: wide at block 128 / d 128 (12 heads of 32 760 tokens 1.85 -> 1.55 ms; ping-pong up to 256 query
   //     blocks: 237 of 16 tiles equal, fewer 0.85-0.9 with the wide one), pipelined otherwise, except at d 64 where all ping-pong
   //     workgroups (two groups of wavefronts per query block) start at once and their rows are long: from
@@ -2120,6 +2126,15 @@ static hipError_t launch_fwd_t(const FwdArgs &a, hipStream_t st) {
   FwdArgs b = a;
   b.select = 0;
   if constexpr (!kPingPongShape) {
+    if constexpr (BLK == 64) {
+      // Without lists the size of a block means nothing: 256 rows share the tiles of the wide kernel.
+      const int wide = a.n_slabs * ((a.L + 255) / 256), rounds = (wide + 255) / 256;
+      const bool filled = D == 128 ? 4 * wide >= 3 * 256 * rounds : 16 * wide >= 15 * 256 * rounds;
+      if (dense && !pooled && forced == 0 && filled && a.L >= (D == 128 ? 4000 : 8000)) {
+        b.Nb = (a.L + 127) / 128;
+        return launch_wide<128, D, 4, false>(b, st);
+      }
+    }
     const int resident = kSmallTile ? 1024 : 512;      // pipelined workgroups on the chip
     if (pooled) {
       if constexpr (D == 64) {

@@ -148,9 +148,10 @@ __device__ __forceinline__ void lds_dma4_sv(const void *uniform_base, uint32_t l
 // written an operand, 19 before one reads a result.
 template <int N>
 __device__ __forceinline__ void settle_acc(f32x16 (&acc)[N]) {
-  static_assert(N == 4, "D = 128");
+  static_assert(N == 2 || N == 4, "D = 64, 128");
 #if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_nop 15\n\ts_nop 3" : "+a"(acc[0]), "+a"(acc[1]), "+a"(acc[2]), "+a"(acc[3]));
+  if constexpr (N == 2) asm volatile("s_nop 15\n\ts_nop 3" : "+a"(acc[0]), "+a"(acc[1]));
+  else asm volatile("s_nop 15\n\ts_nop 3" : "+a"(acc[0]), "+a"(acc[1]), "+a"(acc[2]), "+a"(acc[3]));
 #endif
 }
 

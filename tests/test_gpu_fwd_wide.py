@@ -121,3 +121,16 @@ def test_pooled_tokens_behind_the_rows_own_list(n, tail):
         want, wl = og.attn_fwd_g(qf[0, h], kf[0, h], vf[0, h], mask[h], 128, n)
         util.assert_close_bf16(util.host_f32(o)[0, h], want, f"O[{h}]")
         assert np.abs(lse[h].cpu().numpy() - wl).max() <= util.LSE_ABS
+
+
+@pytest.mark.parametrize("d,heads,L", [(128, 12, 4030), (128, 12, 4097), (64, 8, 8100), (64, 15, 8197), (64, 8, 8064)])
+def test_block_64_without_lists(d, heads, L):
+    """Long dense calls of block 64 take the workgroups of 256 rows too: a last workgroup of 1, 5, 128 and more rows."""
+    print(f"case L={L} d={d}", flush=True)
+    p = binding.Params(B=1, H=heads, L=L, d=d, block=64)
+    base, (q, k, v) = _inputs(L, L, d, heads)
+    mask = np.ones((heads, p.Nb, p.Nb), np.uint8)
+    o, lse = util.run_fwd(p, q, k, v, {"row_ptr": None, "col_idx": None})
+    _check(p, base, mask, o, lse, heads=(1,))
+    even = [x[:, 0::2] for x in (o, lse.view(1, heads, L))]
+    assert all(torch.equal(x, x[:, :1].expand_as(x)) for x in even)
