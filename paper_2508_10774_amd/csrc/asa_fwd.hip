@@ -1381,6 +1381,7 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
   using C = WideCfg<BLK, D, QW>;
   extern __shared__ __align__(1024) unsigned char smem[];
   __shared__ int cols[kMaxNb];
+  __shared__ int again;
   constexpr int kStage = C::kTile, kVBase = C::kStages * C::kTile;
   constexpr int kPooled = 1 << 30;             // flag of an entry of cols[]: a block of pooled tokens
   constexpr int kDm = D / 32;
@@ -1472,13 +1473,11 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
     own_c = max_of_halves(own_c) * a.scale_log2e;
   }
   f32x16 oa[kDm], oc[kDm];                               // O^T of the two halves
-#pragma unroll
-  for (int dm = 0; dm < kDm; ++dm)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) oa[dm][i] = oc[dm][i] = 0.f;
   // per row: reference of the exponentials (log2 units), sum of P over my lane half's keys
   float ma = 0.f, mc = 0.f, la = 0.f, lc = 0.f;
   const float c = a.scale_log2e;
+  // limits of this walk over the list (see the end): row sum of a tile that moves the references, minus the share
+  float redo_at = kRedo, minus_share = -kShare;
 
   using Copy = TrTileCopy<C::kST, D, C::kWaves>;
   Copy copy_k, copy_v, copy_p;
@@ -1505,6 +1504,7 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
     tr_at[2 * dm + 1] = tr_lane ^ (uint32_t)(((4 * dm) ^ t_swz<D>(4)) * 16);
   }
   const int n_it = n_blocks * C::kSub;
+  if (tid == 0) again = 0;
 
   // Copies.  The kI loads of a wavefront's share of a tile have M0 and a scalar base in common (lds_dma_begin) and
   // differ by the offset inside the instruction, which moves the LDS and the global address alike: the offsets per
@@ -1652,8 +1652,6 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
   };
   f32x16 s0a, s0c, s1a, s1c;
   uint32_t p0[16], p1[16];               // bf16 P of two tiles, both halves
-#pragma unroll
-  for (int i = 0; i < 16; ++i) p0[i] = p1[i] = 0;
   auto accumulate = [](f32x16 &acc, bf16x8 x, bf16x8 y) __attribute__((always_inline)) {
 #if defined(__HIP_DEVICE_COMPILE__)
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(x), "v"(y));
@@ -1807,7 +1805,7 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
         __builtin_amdgcn_sched_barrier(0);
       }(), ...);
     }(std::make_integer_sequence<int, kN>{});
-    if (__builtin_expect(__any(fmaxf(ta, tc) > kRedo), 0)) {
+    if (__builtin_expect(__any(fmaxf(ta, tc) > redo_at), 0)) {
       // some row grew far beyond its reference.  New references, this tile's P again, O and the sums scaled.
       const float xa = fmaxf(ma, row_max(sa, bias_t)), xc = fmaxf(mc, row_max(sc, bias_t));
       const float fa = fast_exp2(ma - xa), fc = fast_exp2(mc - xc);
@@ -1862,143 +1860,26 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
         }(), ...);
       }(std::make_integer_sequence<int, kNV>{});
     }
-    share = -kShare;
+    share = minus_share;
     ta_last = ta;
     tc_last = tc;
   };
 
-  if (n_it > 0) {
-    const bool odd = C::kSub == 2 && (n_blocks & 1);
-    const uint32_t first_stage = odd ? 2u : 0u, first_off = first_stage * kStage;
-    {
-      // the products of tile -1 have P = 0: their V operand only has to be finite
-      u32x4 *z = reinterpret_cast<u32x4 *>(smem + kVBase + ((first_stage + 3) & 3) * kStage);
-      for (int x = tid; x < kStage / 16; x += C::kThreads) z[x] = u32x4{0, 0, 0, 0};
-    }
-    __syncthreads();   // cols[] is written
-    // K of tiles 0, 1, 2 and V of tiles 0, 1
-    for (int t = 0; t < 3; ++t) {
-      auto advance = [&](auto new_block) __attribute__((always_inline)) {
-        next_tile(std::integral_constant<int, 0>{}, new_block, std::true_type{});
-        next_tile(std::integral_constant<int, 1>{}, new_block, std::true_type{});
-        next_tile(std::integral_constant<int, 2>{}, new_block, std::true_type{});
-      };
-      if (t % C::kSub == 0) {
-        fetch_entry();
-        advance(std::true_type{});
-      } else {
-        advance(std::false_type{});
-      }
-      set_offsets();
-      auto issue = [&]<int... I>(std::integer_sequence<int, I...>, uint64_t base, const uint32_t *off) __attribute__((always_inline)) {
-        (copy_one(std::integral_constant<int, I>{}, base, off), ...);
-      };
-      issue(std::make_integer_sequence<int, kI>{}, lds_dma_begin(base_k, smem_addr + ((t + first_stage) & 3u) * kStage + copy_k.lds0), off_k);
-      if (t > 0)
-        issue(std::make_integer_sequence<int, kI>{}, lds_dma_begin(base_v, smem_addr + kVBase + ((t - 1 + first_stage) & 3u) * kStage + copy_v.lds0), off_v);
-    }
-    {
-      // the tiles of iteration 0
-      constexpr std::bool_constant<3 % C::kSub == 0> new_block{};
-      if constexpr (new_block) fetch_entry();
-      next_tile(std::integral_constant<int, 0>{}, new_block, std::true_type{});
-      next_tile(std::integral_constant<int, 1>{}, new_block, std::true_type{});
-      next_tile(std::integral_constant<int, 2>{}, new_block, std::true_type{});
-      set_offsets();
-    }
-    fetch_current();
-    next_current(std::true_type{});
-    left = C::kST;
-    wait_copies(std::integral_constant<int, 3 * kI>{});   // K of tiles 0 and 1
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_barrier" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int s = 0; s < D / 16; ++s) row_at[s] += first_off;
-    s0a = s0c = zero16;
-    [&]<int... E>(std::integer_sequence<int, E...>) __attribute__((always_inline)) {
-      ([&]() __attribute__((always_inline)) {
-        read_row(std::integral_constant<int, E>{}, std::integral_constant<int, 0>{});
-        s0a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_ring[E % kRing], qa[E], s0a, 0, 0, 0);
-        s0c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_ring[E % kRing], qc[E], s0c, 0, 0, 0);
-      }(), ...);
-    }(std::make_integer_sequence<int, kNS>{});
-    // first operands of iteration 0
-    [&]<int... E>(std::integer_sequence<int, E...>) __attribute__((always_inline)) {
-      (read_row(std::integral_constant<int, E>{}, std::integral_constant<int, 1>{}), ...);
-    }(std::make_integer_sequence<int, kDepth>{});
-#pragma unroll
-    for (int s = 0; s < D / 16; ++s) row_at[s] -= first_off;
-    // the first references: the row maxima of tile 0, which always has a key
-    if (key_t + C::kST > key_end) mask_tile(s0a, s0c);
-    ma = fmaxf(own_a, row_max(s0a, bias));
-    mc = fmaxf(own_c, row_max(s0c, bias));
-    ma = ma == -INFINITY ? 0.f : ma;
-    mc = mc == -INFINITY ? 0.f : mc;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) pin(p1[i]);     // (zeros in registers here, not right in front of an MFMA)
-    settle();
-    const std::true_type tail{};
-    const std::false_type plain{};
-    const std::integral_constant<int, 0> u0{};
-    const std::integral_constant<int, 1> u1{};
-    const std::integral_constant<int, 2> u2{};
-    const std::integral_constant<int, 3> u3{};
-    int t = 0;
-    if (odd) {
-      body(u2, tail, s0a, s0c, s1a, s1c, p0, p1);
-      body(u3, tail, s1a, s1c, s0a, s0c, p1, p0);
-      t = 2;
-    }
-    // As long as the copies (three tiles ahead) stay inside the blocks in front of the last one of the row's own
-    // list nothing is ragged or pooled.
-    const int n_plain = (n_own_blocks - 1) * C::kSub - 6;
-    if (t <= n_plain) {
-      for (; t <= n_plain; t += 4) {
-        body(u0, plain, s0a, s0c, s1a, s1c, p0, p1);
-        body(u1, plain, s1a, s1c, s0a, s0c, p1, p0);
-        body(u2, plain, s0a, s0c, s1a, s1c, p0, p1);
-        body(u3, plain, s1a, s1c, s0a, s0c, p1, p0);
-      }
-      cur_at = t / C::kSub;
-      fetch_current();
-      next_current(tail);
-      left = C::kST;
-    }
-    for (; t < n_it; t += 4) {
-      body(u0, tail, s0a, s0c, s1a, s1c, p0, p1);
-      body(u1, tail, s1a, s1c, s0a, s0c, p1, p0);
-      body(u2, tail, s0a, s0c, s1a, s1c, p0, p1);
-      body(u3, tail, s1a, s1c, s0a, s0c, p1, p0);
-    }
-    // the last tile's P V (stage 3: the loop ends on a multiple of four)
-    __builtin_amdgcn_s_waitcnt(0x0F70);          // stray copies must land before the LDS is given up
-    if (left < C::kST) zero_rows(3, left);
-    la += ta_last;
-    lc += tc_last;
-    [&]<int... F>(std::integer_sequence<int, F...>) __attribute__((always_inline)) {
-      ([&]() __attribute__((always_inline)) {
-        read_tr(std::integral_constant<int, F>{}, std::integral_constant<int, 3>{}, std::integral_constant<int, 0>{});
-        read_tr(std::integral_constant<int, F>{}, std::integral_constant<int, 3>{}, std::integral_constant<int, 1>{});
-        pv(std::integral_constant<int, F>{}, std::integral_constant<int, 0>{}, p1);
-        pv(std::integral_constant<int, F>{}, std::integral_constant<int, 1>{}, p1);
-      }(), ...);
-    }(std::make_integer_sequence<int, kNV>{});
-    settle();
-  }
-
+  // true if some value of the row is not finite
   auto emit = [&](f32x16 (&acc)[kDm], int qrow, float m, float l_half) __attribute__((always_inline)) {
     const float l_tot = l_half + swap_halves(l_half);
-    if (qrow >= a.L) return;
+    if (qrow >= a.L) return false;
     const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
     bf16 *os = slab_ptr(a.o, a.to, slab, a.H) + (int64_t)qrow * a.to.sL;
     bf16 *ls = a.o_lo ? slab_ptr(a.o_lo, a.to, slab, a.H) + (int64_t)qrow * a.to.sL : nullptr;
+    float finite = 0.f;
 #pragma unroll
     for (int dm = 0; dm < kDm; ++dm) {
       uint32_t w[8], r[8];
 #pragma unroll
       for (int i = 0; i < 16; i += 2) {
         const float v0 = acc[dm][i] * inv, v1 = acc[dm][i + 1] * inv;
+        finite = fmaf(v1, 0.f, fmaf(v0, 0.f, finite));      // (0 * inf, 0 * NaN)
         const uint32_t pk = pack_bf16x2(v0, v1);
         w[i >> 1] = pk;
         r[i >> 1] = pack_bf16x2(v0 - bf16_bits_to_float(pk & 0xffffu),
@@ -2016,9 +1897,152 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
     if (hl == 0)
       a.lse[(int64_t)slab * a.L + qrow] =
           l_tot > 0.f ? m * 0.69314718055994530942f + __logf(l_tot) : -INFINITY;
+    return finite != 0.f;
   };
-  emit(oa, qrow0, ma, la);
-  emit(oc, qrow0 + 32, mc, lc);
+  // One walk over the list, as a rule.  But P above 1 can overflow with a large V where P <= 1 would not, and the second
+  // product makes NaN of an infinite one (what the rounding left out is of either sign, and 0 where P was exact).  So a
+  // workgroup with a result that is not finite walks once more: the running maximum as the reference, P <= 1, no second
+  // product.  The look at the results costs 128 multiply-adds per workgroup.
+  for (int walk = 0;; ++walk) {
+#pragma unroll
+    for (int dm = 0; dm < kDm; ++dm)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) oa[dm][i] = oc[dm][i] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) p0[i] = p1[i] = 0;
+    la = lc = ta_last = tc_last = 0.f;
+    share = -INFINITY;
+    entry_at = cur_at = special = 0;
+    last_k = last_v = pooled_k = pooled_v = false;
+    if (n_it > 0) {
+      const bool odd = C::kSub == 2 && (n_blocks & 1);
+      const uint32_t first_stage = odd ? 2u : 0u, first_off = first_stage * kStage;
+      {
+        // the products of tile -1 have P = 0: their V operand only has to be finite
+        u32x4 *z = reinterpret_cast<u32x4 *>(smem + kVBase + ((first_stage + 3) & 3) * kStage);
+        for (int x = tid; x < kStage / 16; x += C::kThreads) z[x] = u32x4{0, 0, 0, 0};
+      }
+      __syncthreads();   // cols[] is written
+      // K of tiles 0, 1, 2 and V of tiles 0, 1
+      for (int t = 0; t < 3; ++t) {
+        auto advance = [&](auto new_block) __attribute__((always_inline)) {
+          next_tile(std::integral_constant<int, 0>{}, new_block, std::true_type{});
+          next_tile(std::integral_constant<int, 1>{}, new_block, std::true_type{});
+          next_tile(std::integral_constant<int, 2>{}, new_block, std::true_type{});
+        };
+        if (t % C::kSub == 0) {
+          fetch_entry();
+          advance(std::true_type{});
+        } else {
+          advance(std::false_type{});
+        }
+        set_offsets();
+        auto issue = [&]<int... I>(std::integer_sequence<int, I...>, uint64_t base, const uint32_t *off) __attribute__((always_inline)) {
+          (copy_one(std::integral_constant<int, I>{}, base, off), ...);
+        };
+        issue(std::make_integer_sequence<int, kI>{}, lds_dma_begin(base_k, smem_addr + ((t + first_stage) & 3u) * kStage + copy_k.lds0), off_k);
+        if (t > 0)
+          issue(std::make_integer_sequence<int, kI>{}, lds_dma_begin(base_v, smem_addr + kVBase + ((t - 1 + first_stage) & 3u) * kStage + copy_v.lds0), off_v);
+      }
+      {
+        // the tiles of iteration 0
+        constexpr std::bool_constant<3 % C::kSub == 0> new_block{};
+        if constexpr (new_block) fetch_entry();
+        next_tile(std::integral_constant<int, 0>{}, new_block, std::true_type{});
+        next_tile(std::integral_constant<int, 1>{}, new_block, std::true_type{});
+        next_tile(std::integral_constant<int, 2>{}, new_block, std::true_type{});
+        set_offsets();
+      }
+      fetch_current();
+      next_current(std::true_type{});
+      left = C::kST;
+      wait_copies(std::integral_constant<int, 3 * kI>{});   // K of tiles 0 and 1
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_barrier" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int s = 0; s < D / 16; ++s) row_at[s] += first_off;
+      s0a = s0c = zero16;
+      [&]<int... E>(std::integer_sequence<int, E...>) __attribute__((always_inline)) {
+        ([&]() __attribute__((always_inline)) {
+          read_row(std::integral_constant<int, E>{}, std::integral_constant<int, 0>{});
+          s0a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_ring[E % kRing], qa[E], s0a, 0, 0, 0);
+          s0c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_ring[E % kRing], qc[E], s0c, 0, 0, 0);
+        }(), ...);
+      }(std::make_integer_sequence<int, kNS>{});
+      // first operands of iteration 0
+      [&]<int... E>(std::integer_sequence<int, E...>) __attribute__((always_inline)) {
+        (read_row(std::integral_constant<int, E>{}, std::integral_constant<int, 1>{}), ...);
+      }(std::make_integer_sequence<int, kDepth>{});
+#pragma unroll
+      for (int s = 0; s < D / 16; ++s) row_at[s] -= first_off;
+      // the first references: the row maxima of tile 0, which always has a key
+      if (key_t + C::kST > key_end) mask_tile(s0a, s0c);
+      ma = fmaxf(own_a, row_max(s0a, bias));
+      mc = fmaxf(own_c, row_max(s0c, bias));
+      ma = ma == -INFINITY ? 0.f : ma;
+      mc = mc == -INFINITY ? 0.f : mc;
+      own_a = own_c = -INFINITY;                 // (not kept in registers for another walk)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) pin(p1[i]);     // (zeros in registers here, not right in front of an MFMA)
+      settle();
+      const std::true_type tail{};
+      const std::false_type plain{};
+      const std::integral_constant<int, 0> u0{};
+      const std::integral_constant<int, 1> u1{};
+      const std::integral_constant<int, 2> u2{};
+      const std::integral_constant<int, 3> u3{};
+      int t = 0;
+      if (odd) {
+        body(u2, tail, s0a, s0c, s1a, s1c, p0, p1);
+        body(u3, tail, s1a, s1c, s0a, s0c, p1, p0);
+        t = 2;
+      }
+      // As long as the copies (three tiles ahead) stay inside the blocks in front of the last one of the row's own
+      // list nothing is ragged or pooled.
+      const int n_plain = (n_own_blocks - 1) * C::kSub - 6;
+      if (t <= n_plain) {
+        for (; t <= n_plain; t += 4) {
+          body(u0, plain, s0a, s0c, s1a, s1c, p0, p1);
+          body(u1, plain, s1a, s1c, s0a, s0c, p1, p0);
+          body(u2, plain, s0a, s0c, s1a, s1c, p0, p1);
+          body(u3, plain, s1a, s1c, s0a, s0c, p1, p0);
+        }
+        cur_at = t / C::kSub;
+        fetch_current();
+        next_current(tail);
+        left = C::kST;
+      }
+      for (; t < n_it; t += 4) {
+        body(u0, tail, s0a, s0c, s1a, s1c, p0, p1);
+        body(u1, tail, s1a, s1c, s0a, s0c, p1, p0);
+        body(u2, tail, s0a, s0c, s1a, s1c, p0, p1);
+        body(u3, tail, s1a, s1c, s0a, s0c, p1, p0);
+      }
+      // the last tile's P V (stage 3: the loop ends on a multiple of four)
+      __builtin_amdgcn_s_waitcnt(0x0F70);          // stray copies must land before the LDS is given up
+      if (left < C::kST) zero_rows(3, left);
+      la += ta_last;
+      lc += tc_last;
+      [&]<int... F>(std::integer_sequence<int, F...>) __attribute__((always_inline)) {
+        ([&]() __attribute__((always_inline)) {
+          read_tr(std::integral_constant<int, F>{}, std::integral_constant<int, 3>{}, std::integral_constant<int, 0>{});
+          read_tr(std::integral_constant<int, F>{}, std::integral_constant<int, 3>{}, std::integral_constant<int, 1>{});
+          pv(std::integral_constant<int, F>{}, std::integral_constant<int, 0>{}, p1);
+          pv(std::integral_constant<int, F>{}, std::integral_constant<int, 1>{}, p1);
+        }(), ...);
+      }(std::make_integer_sequence<int, kNV>{});
+      settle();
+    }
+
+    const bool bad = emit(oa, qrow0, ma, la) | emit(oc, qrow0 + 32, mc, lc);
+    if (walk > 0) return;
+    if (__any(bad)) again = 1;
+    __syncthreads();                               // (everyone has also read its last V rows)
+    if (!__builtin_amdgcn_readfirstlane(again)) return;
+    redo_at = 1.f;
+    minus_share = -INFINITY;
+  }
 }
 
 template <int BLK, int D, bool VT>

@@ -134,3 +134,80 @@ def test_block_64_without_lists(d, heads, L):
     _check(p, base, mask, o, lse, heads=(1,))
     even = [x[:, 0::2] for x in (o, lse.view(1, heads, L))]
     assert all(torch.equal(x, x[:, :1].expand_as(x)) for x in even)
+
+
+# The calls of the wide kernel: lists of few blocks (up to 256 query blocks) and of eight and more, no lists, pooled tokens
+# behind lists, and blocks of 64 without lists at both head sizes
+CALLS = {"short lists": (128, 128, 42, 6), "lists": (128, 128, 33, 8), "dense": (128, 128, 43, 6),
+         "pooled": (128, 128, 43, 6), "block 64, d 128": (64, 128, 12, 64), "block 64, d 64": (64, 64, 8, 128)}
+
+
+def _run(call, L, q, k, v, mask, heads):
+    block, d = CALLS[call][:2]
+    p = binding.Params(B=1, H=heads, L=L, d=d, block=block)
+    if call == "pooled":
+        o, lse, _, _, _ = _run_fwd_g(p, 128, q, k, v, util.lists_from_mask(p, mask, with_csc=False))
+        return p, o, lse
+    bufs = util.lists_from_mask(p, mask, with_csc=False) if "lists" in call else {"row_ptr": None, "col_idx": None}
+    return (p, *util.run_fwd(p, q, k, v, bufs))
+
+
+@pytest.mark.parametrize("call", list(CALLS))
+def test_infinite_values_stay_infinite(call):
+    """An infinite element of V gives that infinity in its channel, in every row that sees the key (as P > 0 does), and
+    changes nothing else: in the first tiles of a row, where the rounding of P is made up for, in later ones and in the last."""
+    block, d, heads, nb = CALLS[call]
+    L = nb * block - 30
+    print(f"case {call} L={L}", flush=True)
+    (qb, kb, vb), (q, k, v) = _inputs(L, 21, d, heads)
+    mask = np.ones((heads, nb, nb), np.uint8)
+    if call in ("short lists", "pooled"):
+        mask[:, 1::2, 0] = 0
+    at = {0: 40, 1: 2 * block + 33, 2: L - 1}         # channel: key
+    vf = synth.bf16_bits_to_f32(vb).copy()
+    for c, key in at.items():
+        v[:, :, key, c] = float("inf") if c != 1 else -float("inf")
+        vf[..., c] = 0.0
+    p, o, lse = _run(call, L, q, k, v, mask, heads)
+    o = util.host_f32(o)
+    qf, kf = (synth.bf16_bits_to_f32(x) for x in (qb, kb))
+    for h in (0, 1):
+        if call == "pooled":                          # (every row sees the pooled infinities)
+            seen = {c: np.ones(L, bool) for c in at}
+            want, wl = og.attn_fwd_g(qf[0, h], kf[0, h], vf[0, h], mask[h], block, 128)
+        else:
+            seen = {c: np.repeat(mask[h, :, key // block], block)[:L] > 0 for c, key in at.items()}
+            want, wl = oracle.attn_fwd(qf[0, h], kf[0, h], vf[0, h], mask[h], block, None)
+        for c, rows in seen.items():
+            assert (o[0, h, rows, c] == (np.inf if c != 1 else -np.inf)).all(), f"channel {c}"
+            assert np.isfinite(o[0, h, ~rows, c]).all()
+        util.assert_close_bf16(o[0, h, :, 3:], want[:, 3:], f"O[{h}]")
+        assert np.abs(lse[h].cpu().numpy() - wl).max() <= util.LSE_ABS
+
+
+@pytest.mark.parametrize("call", list(CALLS))
+def test_large_values_do_not_overflow_on_the_way(call):
+    """Logits that grow by 2^25 from the first keys of a row to the last, V at 2^106: P relative to the row maximum has sums that
+    fit, P relative to an early logit does not."""
+    block, d, heads, nb = CALLS[call]
+    L = nb * block - 30
+    print(f"case {call} L={L}", flush=True)
+    (qb, kb, vb), _ = _inputs(L, 22, d, heads)
+    qf, kf = (synth.bf16_bits_to_f32(x).copy() for x in (qb, kb))
+    qf[..., 0] = 4.0
+    kf[..., 0] = 0.0
+    kf[:, :, L - 50:, 0] = np.float32(25 * np.log(2) * d ** 0.5 / 4)
+    qb, kb = synth.f32_to_bf16_bits(qf), synth.f32_to_bf16_bits(kf)
+    qf, kf, vf = (synth.bf16_bits_to_f32(x) for x in (qb, kb, vb))
+    of_head = np.arange(heads) % 2
+    q, k, v = (util.dev_bf16(x[:, of_head]) for x in (qb, kb, vb))
+    v = v * 2.0 ** 106                                # (a power of two: the same bits at another exponent)
+    mask = np.ones((heads, nb, nb), np.uint8)
+    p, o, _ = _run(call, L, q, k, v, mask, heads)
+    o = util.host_f32(o).astype(np.float64) / 2.0 ** 106
+    for h in (0, 1):
+        if call == "pooled":
+            want, _ = og.attn_fwd_g(qf[0, h], kf[0, h], vf[0, h], mask[h], block, 128)
+        else:
+            want, _ = oracle.attn_fwd(qf[0, h], kf[0, h], vf[0, h], mask[h], block, None)
+        util.assert_close_bf16(o[0, h], want, f"O[{h}]")
