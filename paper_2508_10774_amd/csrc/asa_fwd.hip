@@ -1980,8 +1980,9 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
       if (key_t + C::kST > key_end) mask_tile(s0a, s0c);
       ma = fmaxf(own_a, row_max(s0a, bias));
       mc = fmaxf(own_c, row_max(s0c, bias));
-      ma = ma == -INFINITY ? 0.f : ma;
-      mc = mc == -INFINITY ? 0.f : mc;
+      // (no finite logit yet: the lowest reference there is, which the first tile with one moves)
+      ma = fmaxf(ma, -3.402823466e38f);
+      mc = fmaxf(mc, -3.402823466e38f);
       own_a = own_c = -INFINITY;                 // (not kept in registers for another walk)
 #pragma unroll
       for (int i = 0; i < 16; ++i) pin(p1[i]);     // (zeros in registers here, not right in front of an MFMA)

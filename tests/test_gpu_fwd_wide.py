@@ -211,3 +211,35 @@ def test_large_values_do_not_overflow_on_the_way(call):
         else:
             want, _ = oracle.attn_fwd(qf[0, h], kf[0, h], vf[0, h], mask[h], block, None)
         util.assert_close_bf16(o[0, h], want, f"O[{h}]")
+
+
+@pytest.mark.parametrize("call", list(CALLS))
+def test_a_first_tile_without_a_finite_logit(call):
+    """The first block of a row has logits of minus infinity only (a product that overflows fp32), all others far below zero:
+    the first reference must not stay above them."""
+    block, d, heads, nb = CALLS[call]
+    L = nb * block - 30
+    print(f"case {call} L={L}", flush=True)
+    (qb, kb, vb), _ = _inputs(L, 23, d, heads)
+    qf, kf = (synth.bf16_bits_to_f32(x).copy() for x in (qb, kb))
+    qf[..., 0] = 2.0 ** 64
+    kf[..., 0] = -2.0 ** -52                          # -2^12 / sqrt(d): 370 (d 128) and 510 (d 64)
+    kf[:, :, :block, 0] = -2.0 ** 70
+    qb, kb = synth.f32_to_bf16_bits(qf), synth.f32_to_bf16_bits(kf)
+    of_head = np.arange(heads) % 2
+    q, k, v = (util.dev_bf16(x[:, of_head]) for x in (qb, kb, vb))
+    mask = np.ones((heads, nb, nb), np.uint8)
+    if call != "lists":
+        mask[:, np.arange(1, nb), np.arange(1, nb)] = 0
+    if "block 64" in call or call == "dense":
+        mask[:] = 1                                   # (the rows of the first block start with it)
+    p, o, lse = _run(call, L, q, k, v, mask, heads)
+    o = util.host_f32(o)
+    qf, kf, vf = (synth.bf16_bits_to_f32(x) for x in (qb, kb, vb))
+    for h in (0, 1):
+        if call == "pooled":
+            want, wl = og.attn_fwd_g(qf[0, h], kf[0, h], vf[0, h], mask[h], block, 128)
+        else:
+            want, wl = oracle.attn_fwd(qf[0, h], kf[0, h], vf[0, h], mask[h], block, None)
+        util.assert_close_bf16(o[0, h], want, f"O[{h}]")
+        assert np.abs(lse[h].cpu().numpy() - wl).max() <= util.LSE_ABS
