@@ -2072,7 +2072,7 @@ static hipError_t launch_wide(const FwdArgs &a, hipStream_t st) {
   const int n_q = X::kRows == BLK ? a.Nb : (a.L + X::kRows - 1) / X::kRows;
   const hipError_t e = set_dynamic_lds_once(reinterpret_cast<const void *>(&fwd_wide_kernel<BLK, D, QW, GT>), X::kLds);
   if (e != hipSuccess) return e;
-  timing_begin(st);
+  if (a.select >= 0) timing_begin(st);   // (behind the ping-pong kernel it is the second of a pair)
   hipLaunchKernelGGL((fwd_wide_kernel<BLK, D, QW, GT>), dim3(xcd_grid(a.n_slabs * n_q)), dim3(X::kThreads), X::kLds, st, a);
   return hipGetLastError();
 }

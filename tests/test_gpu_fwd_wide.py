@@ -243,3 +243,28 @@ def test_a_first_tile_without_a_finite_logit(call):
             want, wl = oracle.attn_fwd(qf[0, h], kf[0, h], vf[0, h], mask[h], block, None)
         util.assert_close_bf16(o[0, h], want, f"O[{h}]")
         assert np.abs(lse[h].cpu().numpy() - wl).max() <= util.LSE_ABS
+
+
+@pytest.mark.parametrize("heads,nb", [(4, 64), (33, 8), (66, 4)])
+def test_the_timing_hook_covers_both_kernels_of_a_pair(heads, nb):
+    """Rows of 64, 8 and 4 blocks: the ping-pong, the wide and the lock-step kernel do the work of the call, beside a launch
+    that finds none."""
+    p = binding.Params(B=1, H=heads, L=nb * 128, d=128, block=128)
+    _, (q, k, v) = _inputs(p.L, 5, 128, heads)
+    bufs = util.lists_from_mask(p, np.ones((heads, nb, nb), np.uint8), with_csc=False)
+    o, lse = torch.empty_like(q), torch.empty((heads, p.L), dtype=torch.float32, device="cuda")
+    ws = binding.alloc_workspace(binding.asa_fwd_workspace_bytes(p))
+    share = []
+    for _ in range(5):
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(4)]
+        for e in ev:
+            e.record()                                # (creates the handles)
+        for _ in range(10):                           # the host runs ahead of these
+            binding.asa_attn_fwd(p, q, k, v, bufs["row_ptr"], bufs["col_idx"], o, lse, ws)
+        ev[0].record()
+        binding.asa_set_kernel_timing(ev[1], ev[2])
+        binding.asa_attn_fwd(p, q, k, v, bufs["row_ptr"], bufs["col_idx"], o, lse, ws)
+        ev[3].record()
+        torch.cuda.synchronize()
+        share.append(ev[1].elapsed_time(ev[2]) / ev[0].elapsed_time(ev[3]))
+    assert max(share) <= 1.01 and sorted(share)[2] >= 0.5, share
