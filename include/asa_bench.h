@@ -56,11 +56,12 @@ int asa_set_kernel_timing(void *start_event, void *stop_event);
 
 /*
  * Test switch: which forward kernel asa_attn_fwd and asa_attn_fwd_g launch.  0 = the library's own
- * choice among its three (the default).  1 = without global tokens the lock-step kernel, which every
+ * choice among its four (the default).  1 = without global tokens the lock-step kernel, which every
  * tile shape has; with them the ping-pong kernel at block 128 / d 128, else the pipelined kernel.
  * 2 = the ping-pong kernel where the shape has it (block 128 / d 128; with global tokens also d 64),
- * else as 0.  Process-wide; lets the tests put their edge cases through kernels that the library
- * chooses at larger sizes only.  Returns an asa_status.
+ * else as 0.  3 = the wide kernel where the shape has it (block 128 / d 128; block 64 without index
+ * lists and global tokens), else as 0.  Process-wide; lets the tests put their edge cases through
+ * kernels that the library chooses at other sizes only.  Returns an asa_status.
  */
 int asa_test_force_fwd_kernel(int which);
 

@@ -178,8 +178,8 @@ struct FwdArgs {
   const void *vg;     // [slab][Nbg * block][d] bf16 pooled values
   int Lg, Nbg;        // pooled tokens per slab, key blocks they fill
   float bias_log2;    // log2(n): the additive ln(n) of the pooled scores, in the exp2 domain
-  // Choice between ping-pong and lock-step per (batch, head) slab, made on the device from the slab's
-  // tile count: 0 = this launch takes every slab; +1 = only slabs whose rows hold at least
+  // Choice between two kernels (lock-step and another) per (batch, head) slab, made on the device from the
+  // slab's tile count: 0 = this launch takes every slab; +1 = only slabs whose rows hold at least
   // `select_min_tiles` tiles on average; -1 = only the others.
   int select, select_min_tiles;
   const int32_t *order;   // work item of each workgroup slot (longest row first inside an XCD's share), or null
@@ -2073,7 +2073,7 @@ static hipError_t launch_wide(const FwdArgs &a, hipStream_t st) {
   const int n_q = X::kRows == BLK ? a.Nb : (a.L + X::kRows - 1) / X::kRows;
   const hipError_t e = set_dynamic_lds_once(reinterpret_cast<const void *>(&fwd_wide_kernel<BLK, D, QW, GT>), X::kLds);
   if (e != hipSuccess) return e;
-  if (a.select >= 0) timing_begin(st);   // (behind the ping-pong kernel it is the second of a pair)
+  timing_begin(st);
   hipLaunchKernelGGL((fwd_wide_kernel<BLK, D, QW, GT>), dim3(xcd_grid(a.n_slabs * n_q)), dim3(X::kThreads), X::kLds, st, a);
   return hipGetLastError();
 }
@@ -2098,19 +2098,28 @@ static hipError_t launch_ping_pong(const FwdArgs &a, int grid, hipStream_t st) {
 }
 
 template <int BLK, int D>
-static hipError_t launch_fwd_t(const FwdArgs &a, hipStream_t st) {
+static hipError_t launch_fwd_t(const FwdArgs &a, const Problem &pb, hipStream_t st) {
   const int total = a.n_slabs * a.Nb, grid = xcd_grid(total);
   // Which kernel.  Measured on MI355X, the transposition of V included where a kernel needs it:
-  //   block 128 / d 128, more than 256 query blocks: the wide kernel, two of whose workgroups share a compute unit
-  //     (12 heads of 32 760 tokens, a quarter of the tiles 1.44 ms, ping-pong 1.60; 320 .. 3072 query blocks of 8 .. 64
-  //     tiles 1.0-1.5x, in the worst case, 513 .. 768 blocks of more than 32 tiles, 0.93-1.0).  Without lists the
-  //     workgroups of 256 rows (1.01-1.03x those of 128) and, in that worst case, ping-pong (632 blocks of 79 tiles 426
-  //     us and 461).  Rows of fewer than 8 tiles: lock-step from V's rows, which hides a workgroup's start and the second
-  //     products of the wide kernel better (lists of 5 tiles 302 us, mask included, and 338).
-  //   block 128 / d 128, up to 256 query blocks: half of the SIMDs would be idle with the wide kernel, so ping-pong from
-  //     18 tiles per row on (256 blocks of 64 tiles 138 us and 164, of 16: 60 and 48).
-  //   The host cannot see the lists: with lists both kernels of a pair are launched and each workgroup leaves at once
-  //     if its (batch, head) slab's tile count belongs to the other (an empty launch costs 4-10 us).
+  //   block 128 / d 128: lock-step (V's rows) for short rows; ping-pong, the fastest on a single row, where few rows run at a
+  //     time; wide, two of whose workgroups share a compute unit, for long rows where its rounds of 512 query blocks are
+  //     filled.  The two long-row kernels meet lock-step at 16-20 tiles.  Time of the others relative to the wide
+  //     kernel, keys and queries with a smooth field of twice the noise, 1 014 to 32 760 tokens:
+  //       up to 256 query blocks: lock-step 0.55-0.83, ping-pong 0.45-0.70 (4 .. 16 tiles).
+  //       lists of one length (a fixed budget), 20, 28, 60 tiles, ping-pong: 512 query blocks 0.97-1.0, 0.98-1.01, 1.03; 600 .. 700
+  //       0.81-0.87; 800 .. 1024 0.96-1.03, 1.0-1.04, 1.04; 1100 .. 1280 0.91-0.95, 0.92-0.97, 0.93-0.97; 1500 0.98-1.02, 1.0-1.06, 1.05; 1600 0.96-0.98;
+  //       2000 .. 3072 1.0-1.04, 1.02-1.04, 1.05.  Lock-step, 12, 16, 20, 28 tiles: 1024 0.86-0.91, 0.93-0.96, 0.98-1.0, 1.03-1.06; 2000 .. 3072
+  //       0.88-0.92, 0.94-0.97, 0.99-1.01, 1.05.
+  //       uneven lists (the threshold alone, 15 .. 85 tiles on average, the longest 2-6 times that), where one long row holds a wide
+  //       workgroup for twice as long, ping-pong: 320 .. 768 blocks 0.57-0.93, 1024 0.66-1.0, 1280 0.68-1.02, 1500 .. 1800 0.76-1.07, 2048
+  //       0.90-1.08.  Always-kept prefix blocks, whose rows are as long as the sequence, 20 tiles on average: 0.52-0.99 up
+  //       to 1100 blocks; beyond, 0.55-0.87 where such a row is longer than two thirds of what a compute unit's half has to do in all, else 0.91-1.05.
+  //       no lists, 8 .. 22 tiles: lock-step (from 18 on ping-pong) 1.0-1.09 where the wide kernel needs at most half of the
+  //       ping-pong kernel's rounds; 27 .. 46 tiles 0.94-0.99 in one round, 0.96-1.07 in more; 56 and more 1.02-1.10, and 1.0-1.04 from 2048
+  //       blocks on with half-filled rounds too; elsewhere 0.53-0.98.
+  //     Without lists the choice is made here.  With them the host has only the parameters of the rule to go by, which say how
+  //     even the rows are, and both kernels of a pair are launched: each workgroup leaves at once if its (batch, head) slab's
+  //     tile count belongs to the other (an empty launch costs 3-10 us).
   //   block 64 / d 64: 48 heads of 17 776 tokens, 13 344 workgroups: lock-step 1.24 ms, pipelined 1.31 ms
   //     (four wavefronts per SIMD against two: vector throughput decides); 2 heads of 1 024 tokens,
   //     32 workgroups: pipelined 12 us, lock-step 17 us (one wavefront's own speed decides).  The
@@ -2134,8 +2143,10 @@ static hipError_t launch_fwd_t(const FwdArgs &a, hipStream_t st) {
   //     ms; 384 x 8 100 307 and 326, 448 x 8 100 316 and 335, 256 x 4 030 98 and 103.  (Block 128 / d 64: 1.03-1.05x at 32 760 tokens, 0.8-1.0
   //     below: not taken.  With lists at d 64 a wavefront's own copies bound it: 1461 us and 1526 at block 64, 48 heads
   //     of 17 776 tokens.)
-  //   pooled tokens: wide at block 128 / d 128 (12 heads of 32 760 tokens 1.85 -> 1.55 ms; ping-pong up to 256 query
-  //     blocks: 237 of 16 tiles equal, fewer 0.85-0.9 with the wide one), pipelined otherwise, except at d 64 where all ping-pong
+  //   pooled tokens, block 128 / d 128, ping-pong relative to wide, the same inputs: 896 .. 1600 query blocks 1.02-1.20 (12 heads of
+  //     32 760 tokens 1.85 -> 1.55 ms); 512 of one length 1.03-1.3, uneven 0.69-1.03; 576 .. 768 0.93-1.02; prefix blocks as above;
+  //     rows of at most 8 blocks 1.04-1.18 beyond 256.
+  //     Other shapes: pipelined, except at d 64 where all ping-pong
   //     workgroups (two groups of wavefronts per query block) start at once and their rows are long: from
   //     16 tiles at block 128 (144 workgroups: 14 tiles 37 us against 35 pipelined, 36 tiles 65 against
   //     76, 144 tiles 199 against 269) and 24 at block 64 (512 workgroups: 8 tiles 30 against 25, 26
@@ -2147,8 +2158,14 @@ static hipError_t launch_fwd_t(const FwdArgs &a, hipStream_t st) {
   const bool fits32 = (uint64_t)a.Nb * BLK * (uint64_t)a.tk.sL * 2u < 0xFFFFFFFFull;
   const bool pooled = a.Nbg > 0, dense = a.row_ptr == nullptr;
   if (pooled && (!fits32 || a.Nb + a.Nbg > kMaxNb || a.tk.sL != D)) return hipErrorNotSupported;
-  const int forced = forced_fwd_kernel();
+  // What the parameters of the rule say about lists that come from it (any others are served as well, at another speed):
+  // rows of about one length; a few rows much longer than the rest, in the units of the comparison above
+  const bool prefix = !dense && pb.n_prefix_blocks > 0;
+  const bool even_rows = dense || (pb.m_min == pb.m_max && !prefix);
+  const bool long_rows = prefix && (int64_t)a.Nb * 512 * 2 > (int64_t)total * pb.m_min * 3;
   constexpr bool kPingPongShape = BLK == 128 && D == 128, kSmallTile = BLK == 64 && D == 64;
+  const bool has_wide = kPingPongShape || (BLK == 64 && dense && !pooled);
+  const int forced = forced_fwd_kernel() == 3 && !has_wide ? 0 : forced_fwd_kernel();
   FwdArgs b = a;
   b.select = 0;
   if constexpr (!kPingPongShape) {
@@ -2156,7 +2173,7 @@ static hipError_t launch_fwd_t(const FwdArgs &a, hipStream_t st) {
       // Without lists the size of a block means nothing: 256 rows share the tiles of the wide kernel.
       const int wide = a.n_slabs * ((a.L + 255) / 256), rounds = (wide + 255) / 256;
       const bool filled = D == 128 ? 4 * wide >= 3 * 256 * rounds : 16 * wide >= 15 * 256 * rounds;
-      if (dense && !pooled && forced == 0 && filled && a.L >= (D == 128 ? 4000 : 8000)) {
+      if (dense && !pooled && (forced == 3 || (forced == 0 && filled && a.L >= (D == 128 ? 4000 : 8000)))) {
         b.Nb = (a.L + 127) / 128;
         return launch_wide<128, D, 4, false>(b, st);
       }
@@ -2176,32 +2193,31 @@ static hipError_t launch_fwd_t(const FwdArgs &a, hipStream_t st) {
                    (total > 2 * resident && total <= 3 * resident);
     if (fits_pipe && forced != 1) return launch_pipe<BLK, D, false>(b, grid, st);
   } else {
-    const bool few = total <= 256;
-    if (pooled) return few ? launch_ping_pong<BLK, D, true>(b, grid, st) : launch_wide<BLK, D, 2, true>(b, st);
-    constexpr int kPingPongMinTiles = 18, kWideMinTiles = 8;
+    // Rounds of ping-pong workgroups (one per compute unit); a round of the wide kernel takes as long as two of them.
+    const int rounds = (total + 255) / 256;
+    constexpr int kMinTiles = 18;
+    if (pooled) {
+      const bool pays = a.Nb <= 8 ? rounds > 1 : rounds > 3 || (rounds == 2 && even_rows);
+      const bool wide = forced == 3 || (forced == 0 && pays && !long_rows);
+      return wide ? launch_wide<BLK, D, 2, true>(b, st) : launch_ping_pong<BLK, D, true>(b, grid, st);
+    }
+    if (forced == 3) return dense ? launch_wide<BLK, D, 4, false>(b, st) : launch_wide<BLK, D, 2, false>(b, st);
     if (fits32 && forced == 2) return launch_ping_pong<BLK, D, false>(b, grid, st);
     if (forced == 0 && dense) {
-      const bool half_round = total > 512 && total <= 768;
-      if (fits32 && a.Nb >= kPingPongMinTiles && (few || half_round)) return launch_ping_pong<BLK, D, false>(b, grid, st);
-      return few ? launch_wide<BLK, D, 2, false>(b, st) : launch_wide<BLK, D, 4, false>(b, st);
-    }
-    if (forced == 0 && few) {
-      if (fits32) {
+      const bool filled = 2 * ((a.n_slabs * ((a.L + 255) / 256) + 255) / 256) <= rounds;
+      const bool wide = a.Nb >= 48 ? filled || rounds > 7 : filled && a.Nb >= 8 && (a.Nb < 24 || rounds > 2);
+      if (wide) return launch_wide<BLK, D, 4, false>(b, st);
+      if (fits32 && a.Nb >= kMinTiles) return launch_ping_pong<BLK, D, false>(b, grid, st);
+    } else if (forced == 0) {
+      const bool wide = !long_rows && (rounds > 7 || (rounds % 2 == 0 && even_rows));
+      if (a.Nb >= kMinTiles && (wide || fits32)) {
         b.select = 1;
-        b.select_min_tiles = kPingPongMinTiles;
-        const hipError_t e = launch_ping_pong<BLK, D, false>(b, grid, st);
+        b.select_min_tiles = kMinTiles;
+        const hipError_t e = wide ? launch_wide<BLK, D, 2, false>(b, st) : launch_ping_pong<BLK, D, false>(b, grid, st);
         if (e != hipSuccess) return e;
         b.select = -1;
+        return launch_lock_step<BLK, D, false>(b, grid, st);
       }
-      return launch_wide<BLK, D, 2, false>(b, st);
-    }
-    if (forced == 0) {
-      b.select = 1;
-      b.select_min_tiles = kWideMinTiles;
-      const hipError_t e = launch_wide<BLK, D, 2, false>(b, st);
-      if (e != hipSuccess) return e;
-      b.select = -1;
-      return launch_lock_step<BLK, D, false>(b, grid, st);
     }
     timing_begin(st);
     return launch_lock_step<BLK, D, false>(b, grid, st);
@@ -2239,10 +2255,10 @@ hipError_t launch_fwd(const Problem &pb, const void *q, const void *k, const voi
   a.scale_log2e = pb.scale * 1.44269504088896340736f;
   a.select = 0;
   a.select_min_tiles = 0;
-  if (pb.block == 128 && pb.d == 128) return launch_fwd_t<128, 128>(a, st);
-  if (pb.block == 128 && pb.d == 64) return launch_fwd_t<128, 64>(a, st);
-  if (pb.block == 64 && pb.d == 128) return launch_fwd_t<64, 128>(a, st);
-  if (pb.block == 64 && pb.d == 64) return launch_fwd_t<64, 64>(a, st);
+  if (pb.block == 128 && pb.d == 128) return launch_fwd_t<128, 128>(a, pb, st);
+  if (pb.block == 128 && pb.d == 64) return launch_fwd_t<128, 64>(a, pb, st);
+  if (pb.block == 64 && pb.d == 128) return launch_fwd_t<64, 128>(a, pb, st);
+  if (pb.block == 64 && pb.d == 64) return launch_fwd_t<64, 64>(a, pb, st);
   return hipErrorInvalidValue;
 }
 

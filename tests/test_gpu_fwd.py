@@ -11,7 +11,7 @@ from tests import util
 pytestmark = pytest.mark.gpu
 
 
-FORCED = {"auto": 0, "lockstep": 1, "pingpong": 2}
+FORCED = {"auto": 0, "lockstep": 1, "pingpong": 2, "wide": 3}
 
 
 def picks_its_kernel(test):
@@ -20,17 +20,26 @@ def picks_its_kernel(test):
     return test
 
 
+def equal_bits_without_lists(test):
+    """A test that a dense call has the bits of one with full lists: not so with the wide kernel, whose
+    workgroups of 256 rows start with two blocks of their own where those with lists start with one."""
+    test.equal_bits_without_lists = True
+    return test
+
+
 def pytest_generate_tests(metafunc):
     once = getattr(metafunc.function, "picks_its_kernel", False)
-    metafunc.parametrize("kernel_choice", ["auto"] if once else list(FORCED), indirect=True)
+    all_but = {"wide"} if getattr(metafunc.function, "equal_bits_without_lists", False) else set()
+    metafunc.parametrize("kernel_choice", ["auto"] if once else [x for x in FORCED if x not in all_but], indirect=True)
 
 
 @pytest.fixture(autouse=True)
 def kernel_choice(request):
-    """Every other test of this module runs three times: with the library's own choice of forward kernel
+    """Every other test of this module runs four times: with the library's own choice of forward kernel
     (at the small sizes here the pipelined one, lock-step at block 128 / d 128), with the lock-step kernel,
-    which production calls reach at larger sizes, and with the ping-pong kernel, which block 128 / d 128 has
-    (the other shapes then run their own choice again)."""
+    which production calls reach at larger sizes, with the ping-pong kernel, which block 128 / d 128 has, and
+    with the wide kernel, which that shape has and block 64 without lists (where a shape has not got it, its own
+    choice runs again)."""
     binding.asa_test_force_fwd_kernel(FORCED[request.param])
     yield request.param
     binding.asa_test_force_fwd_kernel(0)
@@ -91,6 +100,7 @@ def test_fwd_all_blocks_kept_is_dense_attention():
     util.assert_close_bf16(util.host_f32(o), want, "dense O")
 
 
+@equal_bits_without_lists
 @pytest.mark.parametrize("L,d,block", [(640, 128, 128), (1000, 64, 64), (333, 128, 64)])
 def test_fwd_dense_specialisation_needs_no_lists(L, d, block):
     """row_ptr = col_idx = NULL: every key block.  Same tiles in the same order as a full mask's
@@ -285,7 +295,7 @@ def test_fwd_mixed_shapes_on_both_sides_of_the_kernel_choice(block, d, H, Nb, ta
 
 
 @picks_its_kernel
-@pytest.mark.parametrize("which", [0, 1, 2])
+@pytest.mark.parametrize("which", [0, 1, 2, 3])
 @pytest.mark.parametrize("block,d", [(64, 64), (64, 128), (128, 64), (128, 128)])
 def test_fwd_infinite_value_in_the_last_row_stays_infinite(block, d, which):
     """Keys past the end have probability zero and must not turn an infinite value of a real key into

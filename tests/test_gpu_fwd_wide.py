@@ -1,6 +1,6 @@
-"""GPU parity of the forward kernel with 64 query rows per wavefront (block 128 / d 128, more than 256 query
-blocks, where nothing else is chosen), where it can go wrong: list lengths around its software pipeline, the
-ragged last tile, lists that do not ascend, references that have to be moved."""
+"""GPU parity of the forward kernel with 64 query rows per wavefront, forced here, where it can go wrong: list
+lengths around its software pipeline, the ragged last tile, lists that do not ascend, references that have to be
+moved; and the rule that chooses between it and the other kernels."""
 
 import numpy as np
 import pytest
@@ -15,6 +15,21 @@ from tests.test_gpu_global import _run_fwd_g
 pytestmark = pytest.mark.gpu
 
 HEADS, NB = 43, 6        # 258 query blocks
+LOCK_STEP, PING_PONG, WIDE = 1, 2, 3
+
+
+def own_choice(test):
+    """A test about the library's choice of the kernel."""
+    test.own_choice = True
+    return test
+
+
+@pytest.fixture(autouse=True)
+def wide_kernel(request):
+    """Calls of these sizes belong to other kernels: every test runs the wide one, unless it is about the choice."""
+    binding.asa_test_force_fwd_kernel(0 if getattr(request.function, "own_choice", False) else WIDE)
+    yield
+    binding.asa_test_force_fwd_kernel(0)
 
 
 def _inputs(L, seed, d=128, heads=HEADS):
@@ -47,6 +62,8 @@ def test_rows_of_every_length_with_the_ragged_block(tail):
         mask[1::2, i, :i + 1] = 1        # rows of 1 .. 6
     o, lse = util.run_fwd(p, q, k, v, util.lists_from_mask(p, mask, with_csc=False))
     _check(p, base, mask, o, lse)
+    binding.asa_test_force_fwd_kernel(LOCK_STEP)     # (the wide kernel did run: these are other bits)
+    assert not torch.equal(o, util.run_fwd(p, q, k, v, util.lists_from_mask(p, mask, with_csc=False))[0])
 
 
 @pytest.mark.parametrize("tail", [1, 100, 128])
@@ -136,8 +153,8 @@ def test_block_64_without_lists(d, heads, L):
     assert all(torch.equal(x, x[:, :1].expand_as(x)) for x in even)
 
 
-# The calls of the wide kernel: lists of few blocks (up to 256 query blocks) and of eight and more, no lists, pooled tokens
-# behind lists, and blocks of 64 without lists at both head sizes
+# The calls that the wide kernel has: lists, no lists, pooled tokens behind lists, and blocks of 64 without lists at both
+# head sizes
 CALLS = {"short lists": (128, 128, 42, 6), "lists": (128, 128, 33, 8), "dense": (128, 128, 43, 6),
          "pooled": (128, 128, 43, 6), "block 64, d 128": (64, 128, 12, 64), "block 64, d 64": (64, 64, 8, 128)}
 
@@ -245,10 +262,11 @@ def test_a_first_tile_without_a_finite_logit(call):
         assert np.abs(lse[h].cpu().numpy() - wl).max() <= util.LSE_ABS
 
 
-@pytest.mark.parametrize("heads,nb", [(4, 64), (33, 8), (66, 4)])
+@own_choice
+@pytest.mark.parametrize("heads,nb", [(4, 64), (60, 32), (33, 8)])
 def test_the_timing_hook_covers_both_kernels_of_a_pair(heads, nb):
-    """Rows of 64, 8 and 4 blocks: the ping-pong, the wide and the lock-step kernel do the work of the call, beside a launch
-    that finds none."""
+    """The ping-pong, the wide and the lock-step kernel do the work of the call; the first two stand beside a launch that
+    finds none."""
     p = binding.Params(B=1, H=heads, L=nb * 128, d=128, block=128)
     _, (q, k, v) = _inputs(p.L, 5, 128, heads)
     bufs = util.lists_from_mask(p, np.ones((heads, nb, nb), np.uint8), with_csc=False)
@@ -268,3 +286,49 @@ def test_the_timing_hook_covers_both_kernels_of_a_pair(heads, nb):
         torch.cuda.synchronize()
         share.append(ev[1].elapsed_time(ev[2]) / ev[0].elapsed_time(ev[3]))
     assert max(share) <= 1.01 and sorted(share)[2] >= 0.5, share
+
+
+# block 128 / d 128: what, heads, blocks per head, tiles per row, the kernel that the library chooses
+CHOICES = [
+    ("lists", 4, 64, 17, LOCK_STEP), ("lists", 4, 64, 18, PING_PONG),                # up to 256 query blocks
+    ("lists", 8, 64, 17, LOCK_STEP), ("lists", 8, 64, 18, PING_PONG),                # 512: two rounds, maybe uneven
+    ("fixed budget", 8, 64, 17, LOCK_STEP), ("fixed budget", 8, 64, 18, WIDE),       # 512 of one length
+    ("fixed budget", 9, 64, 18, PING_PONG), ("fixed budget", 28, 64, 18, PING_PONG),  # 576, 1792: an odd number of rounds
+    ("lists", 28, 64, 18, PING_PONG), ("lists", 29, 64, 18, WIDE), ("lists", 29, 64, 17, LOCK_STEP),    # 1792, 1856
+    ("prefix", 29, 64, 18, PING_PONG), ("prefix, budget", 29, 64, 18, WIDE),
+    ("lists", 16, 17, 17, LOCK_STEP), ("fixed budget", 29, 17, 17, LOCK_STEP),       # no slab can reach 18
+    ("dense", 4, 64, 64, PING_PONG), ("dense", 8, 64, 64, WIDE), ("dense", 9, 64, 64, PING_PONG),
+    ("dense", 28, 64, 64, PING_PONG), ("dense", 29, 64, 64, WIDE), ("dense", 36, 64, 64, WIDE),
+    ("dense", 30, 13, 13, WIDE), ("dense", 38, 13, 13, LOCK_STEP),                   # 494 blocks, but 266 times 256 rows
+    ("dense", 37, 7, 7, LOCK_STEP), ("dense", 33, 8, 8, WIDE), ("dense", 11, 24, 24, PING_PONG), ("dense", 12, 23, 23, WIDE),
+    ("dense", 10, 47, 47, PING_PONG), ("dense", 18, 47, 47, WIDE), ("dense", 10, 48, 48, WIDE),
+    ("pooled", 4, 64, 8, PING_PONG), ("pooled", 8, 64, 8, PING_PONG), ("pooled, budget", 8, 64, 8, WIDE),
+    ("pooled", 12, 64, 8, PING_PONG), ("pooled", 13, 64, 8, WIDE), ("pooled, prefix", 13, 64, 8, PING_PONG),
+    ("pooled", 33, 8, 8, WIDE), ("pooled", 90, 8, 4, WIDE), ("pooled", 30, 9, 8, PING_PONG),
+]
+
+
+@own_choice
+@pytest.mark.parametrize("what,heads,nb,tiles,kernel", CHOICES)
+def test_both_sides_of_the_lines_between_the_kernels(what, heads, nb, tiles, kernel):
+    """Which kernel ran shows in the last bits: the library's choice equals one forced kernel and differs from the others."""
+    budget = dict(r_min=(tiles - 0.5) / nb, r_max=(tiles - 0.5) / nb) if "budget" in what else {}
+    p = binding.Params(B=1, H=heads, L=nb * 128 - 5, d=128, block=128, n_prefix_dense=100 if "prefix" in what else 0, **budget)
+    print(f"case {what} {heads} x {nb} blocks of {tiles} tiles", flush=True)
+    _, (q, k, v) = _inputs(p.L, 31, 128, heads)
+    mask = np.zeros((nb, nb), np.uint8)
+    for i in range(nb):
+        mask[i, (i + np.arange(tiles)) % nb] = 1
+    mask = np.broadcast_to(mask, (heads, nb, nb))
+    bufs = {"row_ptr": None, "col_idx": None} if what == "dense" else util.lists_from_mask(p, mask, with_csc=False)
+    out = []
+    for which in (0, LOCK_STEP, PING_PONG, WIDE):
+        binding.asa_test_force_fwd_kernel(which)
+        o = _run_fwd_g(p, 128, q, k, v, bufs)[0] if "pooled" in what else util.run_fwd(p, q, k, v, bufs)[0]
+        assert torch.isfinite(o).all()
+        out.append(o)
+    same = [torch.equal(out[0], x) for x in out[1:]]
+    if "pooled" in what:                             # (has no lock-step kernel: that switch is the ping-pong one again)
+        assert same[1:] == [kernel == PING_PONG, kernel == WIDE]
+    else:
+        assert same == [kernel == x for x in (LOCK_STEP, PING_PONG, WIDE)], same
