@@ -167,7 +167,9 @@ int asa_attn_fwd(const asa_params *p, const void *q, const void *k, const void *
  * the gradient kernels (two tile products; about a quarter more time at the Wan2.1 shape).
  * With o_lo, Delta = rowsum(dO * (o + o_lo)) costs one pass over three tensors.  Both meet the
  * same tolerance; Delta from the bf16 o alone would not where keys and queries are large.
- * dq, dk, dv [B, H, L, d] bf16 (q/k/v strides); every row < L is written.
+ * dq, dk, dv [B, H, L, d] bf16 (q/k/v strides); every row < L is written.  dq may take the place
+ * of q (the same strides), of d_o (if o has q's strides) or of o / o_lo, dk and dv that of o / o_lo
+ * (if the strides agree); any other overlap of an output with an input or another output is undefined.
  * All four index-list pointers NULL selects the dense specialisation (see asa_attn_fwd);
  * some but not all NULL is ASA_ERR_INVALID_ARG.
  */

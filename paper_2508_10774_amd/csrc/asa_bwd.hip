@@ -940,8 +940,17 @@ size_t bwd_g_workspace_bytes(const Problem &pb, int Nbg) {
   return bwd_workspace_bytes(pb) + 2 * pooled_chunks(pb, Nbg) * pooled_rows_bytes(pb, Nbg, 4);
 }
 
+// Do two [B, H, L, d] bf16 tensors share memory, or stand in one another's gaps?
+static bool overlap(const Problem &pb, const void *x, const TensorView &tx, const void *y, const TensorView &ty) {
+  auto last = [&](const void *t, const TensorView &v) {
+    return reinterpret_cast<const bf16 *>(t) + (pb.B - 1) * v.sB + (pb.H - 1) * v.sH + (pb.L - 1) * v.sL + pb.d - 1;
+  };
+  return x <= static_cast<const void *>(last(y, ty)) && y <= static_cast<const void *>(last(x, tx));
+}
+
+// dq_over_inputs: dQ is written into memory that dK / dV reads (asa.h allows it): dK / dV must have ended before
 template <int BLK, int D>
-static hipError_t launch_bwd_t(const BwdArgs &a, const BwdArgs *pooled_launch, hipStream_t st) {
+static hipError_t launch_bwd_t(const BwdArgs &a, const BwdArgs *pooled_launch, bool dq_over_inputs, hipStream_t st) {
   using C = BwdCfg<BLK, D>;
   {
     const void *dq_fns[4] = {reinterpret_cast<const void *>(&dq_kernel<BLK, D, false>),
@@ -964,7 +973,7 @@ static hipError_t launch_bwd_t(const BwdArgs &a, const BwdArgs *pooled_launch, h
   const int grid = xcd_grid(a.n_slabs * a.Nb);
   // One launch or two (see dkv_dq_kernel): the line is where the gain of filling the last round has gone.
   const int resident = BLK == 64 && D == 64 ? 1024 : (BLK == 128 && D == 128 ? 256 : 512);
-  const bool together = a.n_slabs * a.Nb <= (BLK == D ? 3 : 6) * resident;
+  const bool together = !dq_over_inputs && a.n_slabs * a.Nb <= (BLK == D ? 3 : 6) * resident;
   hipError_t e = hipSuccess;
   if (a.ndelta_out) {
     // no low half of O from the caller: Delta from the tiles themselves, before anything uses it
@@ -1090,10 +1099,11 @@ hipError_t launch_bwd(const Problem &pb, const void *q, const void *k, const voi
     a.kg = gt->kg; a.vg = gt->vg; a.Lg = gt->Lg; a.Nbg = gt->Nbg;
     a.pooled_bias_log2 = bias;
   }
-  if (pb.block == 128 && pb.d == 128) return launch_bwd_t<128, 128>(a, pooled, st);
-  if (pb.block == 128 && pb.d == 64) return launch_bwd_t<128, 64>(a, pooled, st);
-  if (pb.block == 64 && pb.d == 128) return launch_bwd_t<64, 128>(a, pooled, st);
-  if (pb.block == 64 && pb.d == 64) return launch_bwd_t<64, 64>(a, pooled, st);
+  const bool over = overlap(pb, dq, pb.q, q, pb.q) || overlap(pb, dq, pb.q, d_o, pb.o);
+  if (pb.block == 128 && pb.d == 128) return launch_bwd_t<128, 128>(a, pooled, over, st);
+  if (pb.block == 128 && pb.d == 64) return launch_bwd_t<128, 64>(a, pooled, over, st);
+  if (pb.block == 64 && pb.d == 128) return launch_bwd_t<64, 128>(a, pooled, over, st);
+  if (pb.block == 64 && pb.d == 64) return launch_bwd_t<64, 64>(a, pooled, over, st);
   return hipErrorInvalidValue;
 }
 

@@ -82,3 +82,43 @@ def test_the_same_with_pooled_tokens():
         # (the heads repeat with period 2)
         assert torch.equal(a[:, 2:4].view(torch.int16), a[:, :2].view(torch.int16)), name
         assert torch.equal(a[:, :2].view(torch.int16), b[:, :2].view(torch.int16)), name
+
+
+@pytest.mark.parametrize("with_lo", [True, False])
+@pytest.mark.parametrize("block,d", list(LINE))
+@pytest.mark.parametrize("pooled", [False, True])
+def test_dq_in_the_place_of_an_input(block, d, with_lo, pooled):
+    """dQ may be written over Q, dO or O (asa.h): dK / dV read Q and dO of every row, so that they must have ended before."""
+    L, heads, n = (NB - 1) * block + TAIL, 4, 32
+    print(f"case block={block} d={d} lo={with_lo} pooled={pooled}", flush=True)
+    q, k, v, g = (util.dev_bf16(synth.make_iid((1, heads, L, d), block + d, s)) for s in range(4))
+    p = binding.Params(B=1, H=heads, L=L, d=d, block=block)
+    bufs = util.lists_from_mask(p, synth.random_block_mask(NB, 0.5, seed=d, slabs=heads))
+    lists = [bufs[x] for x in ("row_ptr", "col_idx", "col_ptr", "row_idx")]
+    o, o_lo = torch.empty_like(q), torch.empty_like(q)
+    lse = torch.empty((heads, L), dtype=torch.float32, device="cuda")
+    if pooled:
+        ws = binding.alloc_workspace(max(binding.asa_fwd_g_workspace_bytes(p, n), binding.asa_bwd_g_workspace_bytes(p, n)))
+        G = binding.asa_global_token_count(p, n)
+        kg, vg = (torch.zeros(1, heads, G, d, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        binding.asa_global_tokens(p, n, k, v, kg, vg)
+        binding.asa_attn_fwd_g(p, n, q, k, v, kg, vg, *lists[:2], o, lse, ws, o_lo=o_lo)
+    else:
+        ws = binding.alloc_workspace(max(binding.asa_fwd_workspace_bytes(p), binding.asa_bwd_workspace_bytes(p)))
+        binding.asa_attn_fwd(p, q, k, v, *lists[:2], o, lse, ws, o_lo=o_lo)
+
+    def run(over):
+        t = {"q": q.clone(), "d_o": g.clone(), "o": o.clone()}
+        dq = t[over] if over else torch.empty_like(q)
+        dk, dv = torch.empty_like(k), torch.empty_like(v)
+        lo = o_lo if with_lo else None
+        if pooled:
+            binding.asa_attn_bwd_g(p, n, t["q"], k, v, kg, vg, t["o"], t["d_o"], lse, *lists, dq, dk, dv, ws, o_lo=lo)
+        else:
+            binding.asa_attn_bwd(p, t["q"], k, v, t["o"], t["d_o"], lse, *lists, dq, dk, dv, ws, o_lo=lo)
+        return [x.view(torch.int16) for x in (dq, dk, dv)]
+
+    want = run(None)
+    for over in ("q", "d_o", "o"):
+        for a, b, name in zip(run(over), want, ("dQ", "dK", "dV")):
+            assert torch.equal(a, b), f"{name} with dQ over {over}"
