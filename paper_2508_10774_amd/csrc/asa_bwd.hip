@@ -164,7 +164,7 @@ struct BwdCfg {
 // is off by up to 0.05 in rows whose soft-max is spread over keys with similar values, and that
 // error goes into dQ and dK times the size of the keys / queries.
 template <int BLK, int D, bool GT, bool DELTA_ONLY>
-__device__ __forceinline__ void dq_walk(const BwdArgs &a, int workgroup, unsigned char *smem, int *cols) {
+__device__ __forceinline__ void dq_walk(const BwdArgs &a, int workgroup, uint32_t smem_addr, int *cols) {
   using C = BwdCfg<BLK, D>;
   constexpr int kVOff = C::kTile, kStage = C::kDqStage;
   constexpr int kPooled = 1 << 30;             // flag of an entry of cols[]: a block of pooled tokens
@@ -232,7 +232,6 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, int workgroup, unsigne
   if (GT) copy_p.init(wave, lane, D, C::kST);
 
   // (stages are absolute LDS addresses, multiples of 256: the XORs below touch lower bits only)
-  const uint32_t smem_addr = ASA_LDS_ADDR_OF(smem);
   // row-wise A fragments (S^T = K Q^T, dP^T = V dO^T): row kappa(n) of the 32 keys
   const int kr = kappa(n);
   uint32_t row_at[D / 16];
@@ -512,7 +511,7 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, int workgroup, unsigne
 // Q or dO exists, in LDS or in memory.
 // ---------------------------------------------------------------------------------------
 template <int BLK, int D>
-__device__ __forceinline__ void dkv_walk(const BwdArgs &a, int workgroup, unsigned char *smem, int *rows) {
+__device__ __forceinline__ void dkv_walk(const BwdArgs &a, int workgroup, uint32_t smem_addr, int *rows) {
   using C = BwdCfg<BLK, D>;
   constexpr int kGOff = C::kTile, kStatOff = 2 * C::kTile, kStage = C::kDkvStage;
 
@@ -568,7 +567,6 @@ __device__ __forceinline__ void dkv_walk(const BwdArgs &a, int workgroup, unsign
   const int last_row0 = TrTileCopy<C::kST, D, C::kWaves>::last_row0(a.L);
 
   // (stages are absolute LDS addresses, multiples of 256: the XORs below touch lower bits only)
-  const uint32_t smem_addr = ASA_LDS_ADDR_OF(smem);
   // row-wise A fragments (S = Q K^T, dP = dO V^T): row kappa(n) of the 32 queries, 16-byte chunk
   // (2 s + hl) ^ t_swz(row)
   const int kr = kappa(n);
@@ -876,14 +874,14 @@ template <int BLK, int D, bool GT, bool DELTA_ONLY = false>
 __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kDqWavesPerSimd)) void dq_kernel(BwdArgs a) {
   extern __shared__ __align__(1024) unsigned char smem[];
   __shared__ int cols[kMaxNb];
-  dq_walk<BLK, D, GT, DELTA_ONLY>(a, blockIdx.x, smem, cols);
+  dq_walk<BLK, D, GT, DELTA_ONLY>(a, blockIdx.x, ASA_LDS_ADDR_OF(smem), cols);
 }
 
 template <int BLK, int D>
 __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dkv_kernel(BwdArgs a) {
   extern __shared__ __align__(1024) unsigned char smem[];
   __shared__ int rows[kMaxNb];
-  dkv_walk<BLK, D>(a, blockIdx.x, smem, rows);
+  dkv_walk<BLK, D>(a, blockIdx.x, ASA_LDS_ADDR_OF(smem), rows);
 }
 
 // dK / dV and dQ in one launch: neither needs the other's results, so the dQ workgroups fill the compute
@@ -900,8 +898,8 @@ __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dkv_
   extern __shared__ __align__(1024) unsigned char smem[];
   __shared__ int list[kMaxNb];
   const int first_dq = gridDim.x / 2;          // (a multiple of the number of XCDs)
-  if ((int)blockIdx.x < first_dq) dkv_walk<BLK, D>(a, blockIdx.x, smem, list);
-  else dq_walk<BLK, D, GT, false>(a, (int)blockIdx.x - first_dq, smem, list);
+  if ((int)blockIdx.x < first_dq) dkv_walk<BLK, D>(a, blockIdx.x, ASA_LDS_ADDR_OF(smem), list);
+  else dq_walk<BLK, D, GT, false>(a, (int)blockIdx.x - first_dq, ASA_LDS_ADDR_OF(smem), list);
 }
 
 static size_t order_bytes(const Problem &pb) {

@@ -1916,11 +1916,9 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
     entry_at = cur_at = special = 0;
     last_k = last_v = pooled_k = pooled_v = false;
     if (n_it > 0) {
-      const bool odd = C::kSub == 2 && (n_blocks & 1);
-      const uint32_t first_stage = odd ? 2u : 0u, first_off = first_stage * kStage;
       {
         // the products of tile -1 have P = 0: their V operand only has to be finite
-        u32x4 *z = reinterpret_cast<u32x4 *>(smem + kVBase + ((first_stage + 3) & 3) * kStage);
+        u32x4 *z = reinterpret_cast<u32x4 *>(smem + kVBase + 3 * kStage);
         for (int x = tid; x < kStage / 16; x += C::kThreads) z[x] = u32x4{0, 0, 0, 0};
       }
       __syncthreads();   // cols[] is written
@@ -1941,17 +1939,15 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
         auto issue = [&]<int... I>(std::integer_sequence<int, I...>, uint64_t base, const uint32_t *off) __attribute__((always_inline)) {
           (copy_one(std::integral_constant<int, I>{}, base, off), ...);
         };
-        issue(std::make_integer_sequence<int, kI>{}, lds_dma_begin(base_k, smem_addr + ((t + first_stage) & 3u) * kStage + copy_k.lds0), off_k);
+        issue(std::make_integer_sequence<int, kI>{}, lds_dma_begin(base_k, smem_addr + t * kStage + copy_k.lds0), off_k);
         if (t > 0)
-          issue(std::make_integer_sequence<int, kI>{}, lds_dma_begin(base_v, smem_addr + kVBase + ((t - 1 + first_stage) & 3u) * kStage + copy_v.lds0), off_v);
+          issue(std::make_integer_sequence<int, kI>{}, lds_dma_begin(base_v, smem_addr + kVBase + (t - 1) * kStage + copy_v.lds0), off_v);
       }
       {
         // the tiles of iteration 0
-        constexpr std::bool_constant<3 % C::kSub == 0> new_block{};
-        if constexpr (new_block) fetch_entry();
-        next_tile(std::integral_constant<int, 0>{}, new_block, std::true_type{});
-        next_tile(std::integral_constant<int, 1>{}, new_block, std::true_type{});
-        next_tile(std::integral_constant<int, 2>{}, new_block, std::true_type{});
+        next_tile(std::integral_constant<int, 0>{}, std::false_type{}, std::true_type{});
+        next_tile(std::integral_constant<int, 1>{}, std::false_type{}, std::true_type{});
+        next_tile(std::integral_constant<int, 2>{}, std::false_type{}, std::true_type{});
         set_offsets();
       }
       fetch_current();
@@ -1961,8 +1957,6 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
       __builtin_amdgcn_sched_barrier(0);
       asm volatile("s_barrier" ::: "memory");
       __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int s = 0; s < D / 16; ++s) row_at[s] += first_off;
       s0a = s0c = zero16;
       [&]<int... E>(std::integer_sequence<int, E...>) __attribute__((always_inline)) {
         ([&]() __attribute__((always_inline)) {
@@ -1975,8 +1969,6 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
       [&]<int... E>(std::integer_sequence<int, E...>) __attribute__((always_inline)) {
         (read_row(std::integral_constant<int, E>{}, std::integral_constant<int, 1>{}), ...);
       }(std::make_integer_sequence<int, kDepth>{});
-#pragma unroll
-      for (int s = 0; s < D / 16; ++s) row_at[s] -= first_off;
       // the first references: the row maxima of tile 0, which always has a key
       if (key_t + C::kST > key_end) mask_tile(s0a, s0c);
       ma = fmaxf(own_a, row_max(s0a, bias));
@@ -1995,15 +1987,10 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
       const std::integral_constant<int, 2> u2{};
       const std::integral_constant<int, 3> u3{};
       int t = 0;
-      if (odd) {
-        body(u2, tail, s0a, s0c, s1a, s1c, p0, p1);
-        body(u3, tail, s1a, s1c, s0a, s0c, p1, p0);
-        t = 2;
-      }
       // As long as the copies (three tiles ahead) stay inside the blocks in front of the last one of the row's own
       // list nothing is ragged or pooled.
       const int n_plain = (n_own_blocks - 1) * C::kSub - 6;
-      if (t <= n_plain) {
+      if (n_plain >= 0) {
         for (; t <= n_plain; t += 4) {
           body(u0, plain, s0a, s0c, s1a, s1c, p0, p1);
           body(u1, plain, s1a, s1c, s0a, s0c, p1, p0);

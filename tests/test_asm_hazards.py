@@ -1,8 +1,8 @@
 """Wait states around the instructions that the kernels write out themselves.
 
 The compiler places the wait states that the hardware does not enforce, but it does not look into inline
-assembly.  The backward kernels write out matrix instructions with accumulation registers, all tile loops
-write out direct-to-LDS loads.  These tests compile the sources to assembly and walk it backwards and
+assembly.  The backward kernels and the wide forward write out matrix instructions with accumulation registers,
+all tile loops write out direct-to-LDS loads.  These tests compile the sources to assembly and walk it backwards and
 forwards from each such instruction, over branches too:
 
   a vector instruction that writes an operand of a written-out MFMA: 2 wait states before it
@@ -126,7 +126,7 @@ def assembly(tmp_path_factory):
     return {src: (out / src).read_text() for src in running}
 
 
-@pytest.mark.parametrize("src,kinds", [("asa_bwd.hip", ("mfma", "load")), ("asa_fwd.hip", ("load",))])
+@pytest.mark.parametrize("src,kinds", [("asa_bwd.hip", ("mfma", "load")), ("asa_fwd.hip", ("mfma", "load"))])
 def test_wait_states_around_written_out_instructions(assembly, src, kinds):
     total = dict.fromkeys(("mfma", "load"), 0)
     for name, lines in _functions(assembly[src]):
