@@ -264,7 +264,8 @@ def test_fwd_block_64_d_64_on_both_sides_of_the_kernel_choice(H, Nb):
     (64, 128, 8, 64, 55, False, False),     # 512
     (64, 128, 19, 27, 32, False, True),     # 513, 1 696 keys
     (64, 128, 9, 57, 1, False, True),       # 513, 3 585 keys
-    (64, 128, 16, 63, 55, False, False),    # 1008: two rounds, the second one nearly full
+    (64, 128, 16, 63, 55, False, False),    # 1008 of 4 023 keys: the wide kernel
+    (64, 128, 17, 59, 55, False, False),    # 1003 of 3 767: two rounds, the second one nearly full
     (64, 128, 41, 25, 55, False, False),    # 1025: a second round of lock-step workgroups
     (64, 128, 53, 29, 64, False, True),     # 1537: a fourth round of pipelined ones
     (128, 64, 16, 60, 119, True, False),    # lists: pipelined whatever the number (960, 600)

@@ -332,3 +332,22 @@ def test_both_sides_of_the_lines_between_the_kernels(what, heads, nb, tiles, ker
         assert same[1:] == [kernel == PING_PONG, kernel == WIDE]
     else:
         assert same == [kernel == x for x in (LOCK_STEP, PING_PONG, WIDE)], same
+
+
+@own_choice
+@pytest.mark.parametrize("d,heads,L,wide", [
+    (128, 12, 4000, True), (128, 12, 3999, False),       # 192 workgroups of 256 rows: three quarters of a round
+    (128, 11, 4096, False), (128, 24, 4000, True), (128, 23, 4090, False),
+    (64, 8, 8000, True), (64, 8, 7999, False),           # 256
+    (64, 7, 8192, False), (64, 15, 8192, True), (64, 14, 8192, False),    # 15 sixteenths
+])
+def test_block_64_without_lists_on_both_sides_of_the_line(d, heads, L, wide):
+    print(f"case L={L} d={d} heads={heads}", flush=True)
+    p = binding.Params(B=1, H=heads, L=L, d=d, block=64)
+    _, (q, k, v) = _inputs(L, 33, d, heads)
+    out = []
+    for which in (0, WIDE):
+        binding.asa_test_force_fwd_kernel(which)
+        out.append(util.run_fwd(p, q, k, v, {"row_ptr": None, "col_idx": None})[0])
+    assert torch.isfinite(out[0]).all()
+    assert torch.equal(*out) == wide
