@@ -70,8 +70,8 @@ def parse():
 
 def pmc_summary(fetch_dir, write_dir):
     """HBM bytes per launch of every asa:: kernel from two rocprofv3 --pmc passes (KiB per
-    dispatch, averaged), scaled by what the same counters read for the V transposition kernel,
-    a plain copy of known size.  Writes TRAFFIC_FILE."""
+    dispatch, averaged), scaled by what the same counters read for delta_kernel, which reads three
+    whole tensors and the LSE once and writes two floats per row.  Writes TRAFFIC_FILE."""
     import collections
     import csv
     import glob
@@ -90,11 +90,10 @@ def pmc_summary(fetch_dir, write_dir):
     fetch, write = read(fetch_dir, "FETCH_SIZE"), read(write_dir, "WRITE_SIZE")
     from paper_2508_10774_amd import synth
     w = synth.WAN
-    lpad = w.Nb * w.block
-    copy = [k for k in fetch if "transpose_kernel" in k]
-    assert copy, "the calibration kernel (transpose_kernel) is not in the trace"
-    read_kib = w.B * w.H * w.L * w.d * 2 / 1024.0          # what it reads: V once
-    write_kib = w.B * w.H * lpad * w.d * 2 / 1024.0        # what it writes: the padded tiles
+    copy = [k for k in fetch if "delta_kernel" in k]
+    assert copy, "the calibration kernel (delta_kernel) is not in the trace"
+    read_kib = w.B * w.H * w.L * (3 * w.d * 2 + 4) / 1024.0      # O, o_lo, dO and the LSE
+    write_kib = w.B * w.H * w.Nb * w.block * 2 * 4 / 1024.0      # -Delta and the LSE in log2 units, padded rows too
     f_fac = read_kib / fetch[copy[0]][0]
     w_fac = write_kib / write[copy[0]][0]
     kernels = {}
@@ -472,7 +471,8 @@ def main():
     # quarter, half or all of the 256 compute units hold a workgroup: the same work per workgroup,
     # only the number of busy compute units differs.  A workgroup that runs faster on an emptier
     # chip shows that the full-chip rate is set by something shared (power / clock), not by the
-    # kernel's schedule inside a compute unit.
+    # kernel's schedule inside a compute unit.  (Up to 256 workgroups that is the ping-pong kernel; the
+    # six rounds run in the wide kernel, two of whose workgroups share a compute unit.)
     occupancy = None
     try:
         if not args.no_sweep and (p.block, p.d) == (128, 128):
@@ -497,6 +497,7 @@ def main():
                 t_ms = float(np.median([a_ev.elapsed_time(b_ev) for a_ev, b_ev in o_ev[3:]]))
                 wgs = hh * nb
                 occupancy.append({"workgroups": wgs, "rounds": -(-wgs // 256),
+                                  "kernel": "fwd_pp_kernel" if wgs <= 256 else "fwd_wide_kernel",
                                   "us_per_round": round(t_ms * 1e3 / -(-wgs // 256), 1),
                                   "tflops": round(wgs * 64 * tile_flops_const / (t_ms * 1e-3) / 1e12, 1)})
                 del tq, tk, tv, oo
@@ -612,6 +613,12 @@ def main():
     mask_bytes = 2 * p.B * p.H * Nk * p.d * 2 + p.B * p.H * (p.Nb * p.Nb * (1 + 4 + 4) + nnz * 0)
     mask_gbs = mask_bytes / (np.median(mask_ms) * 1e-3) / 1e9
 
+    # the kernel that these workloads' forward spends its time in
+    if p.block == 128:
+        fwd_name = f"fwd_wide_kernel<128,{p.d},2,false>" if nnz >= 18 * p.B * p.H * p.Nb else f"fwd_kernel<128,{p.d},false>"
+    else:
+        fwd_name = f"fwd_pipe_kernel<64,{p.d},false>" if p.B * p.H * p.Nb <= 1024 else f"fwd_kernel<64,{p.d},true>"
+
     out = {
         "metric": "ASA forward effective TFLOP/s on executed tiles (fwd ms beside it), "
                   f"{w.name} shape, {dens:.0%} block density",
@@ -661,8 +668,7 @@ def main():
         "fwd_workgroup_round_vs_busy_compute_units": occupancy,
         "side_measurement_errors": side_errors or None,
         "roofline": {
-            "kernel": (f"fwd_pp_kernel<{p.block},{p.d}>" if (p.block, p.d) == (128, 128)
-                       else f"fwd_kernel<{p.block},{p.d}>"),
+            "kernel": fwd_name,
             "bound": "mfma",
             "achieved": round(float(kern_tflops), 2),
             "peak": PEAK_BF16_TFLOPS,
@@ -672,7 +678,7 @@ def main():
             "frac_of_measured_mfma_only_rate": (None if measured is None else
                                                 round(float(kern_tflops / measured["mfma_only_tflops"]), 4)),
             "flops_per_launch": fwd_flops,
-            "traffic": (traffic_of(f"fwd_pp_kernel<{p.block},{p.d}") if (
+            "traffic": (traffic_of(fwd_name) if (
                 args.workload == "wan" and abs(dens - 0.25) < 1e-9 and args.seed == 42) else None),
             "traffic_unit": "HBM bytes per launch, from " + os.path.relpath(TRAFFIC_FILE, ROOT),
         },
@@ -705,7 +711,7 @@ def cog_point(args, binding, synth, torch, measure_point, dev):
     r, bufs, o = measure_point(pc, q, k, v, with_bwd=None if args.no_bwd else g)
     r["setting"] = (f"{w.name}: B={w.B} H={w.H} L={w.L} d={w.d} block={w.block}, tau=0.9, "
                     f"r_min=r_max={dens} (fixed budget) + {w.n_text} always-kept text tokens, seed={args.seed}")
-    r["kernel"] = f"fwd_kernel<{w.block},{w.d}>"
+    r["kernel"] = f"fwd_kernel<{w.block},{w.d},true>"
     # At d = 64 the vector ALU has more to do than the matrix cores: per 64-key step a wavefront needs 16
     # MFMAs (512 matrix-pipe cycles) and 32 exponentials of 8 cycles + 96 other vector instructions of 4
     # (640 cycles) + 16 MFMA issue slots (64): the soft-max caps the matrix duty at 512 / 704.

@@ -1345,17 +1345,20 @@ __global__ __launch_bounds__(BLK * 2, (PipeCfg<BLK, D>::kWavesPerSimd)) void fwd
 //
 // Bound: power and issue.  At one wavefront per SIMD every instruction, scalar ones too, takes an issue slot of 4-5
 // cycles; 200 of them per iteration stand beside 1024 matrix cycles.  12 heads of 32 760 tokens: a quarter of the tiles
-// matrix duty 0.69 at 1.53 GHz, dense 0.73 at 1.67 GHz (ping-pong: 0.62 at 1.57); without the copies the cycles stay and
-// the clock rises to 1.72 and 1.84.  What follows from that:
+// matrix duty 0.66 at 1.56 GHz, dense 0.68 at 1.70 (ping-pong, a quarter: 0.62 at 1.58); a build without the copies in the loop has 8
+// and 4 % fewer cycles.  What follows from that:
 //  * No row maximum per tile.  The exponentials are relative to a reference per row: the largest logit of the first tile
 //    and, where the list holds the query block itself, among the 32 keys of the row's own group (one extra product in
 //    the prologue).  As long as no row sum of a tile passes 2^30 the reference stays; then the tile is redone and O scaled.
-//  * A tile whose row sum is more than half of everything before it decides its row, and there the rounding of P to bf16
-//    (a key at the reference had P = 1 exactly) would show: what the rounding left out is added as a second product.
-//    Error of O + o_lo against 64 bits, rms, 13 x 30 x 45 tokens, a quarter of the tiles; in brackets with the running maximum as
-//    the reference (ping-pong): keys and queries with a smooth field of twice the noise 1.4e-4 (3.7e-4), as strong as the
-//    noise 3.2e-4 (5.9e-4), half as strong 8.9e-4 (8.4e-4), noise alone 1.63e-3 (1.52e-3).  The own block comes first in a
-//    row's order so that both happen rarely (1 and 4 % of the time above).
+//  * The rounding of P to bf16 shows where few keys carry a row (a key at the reference has P = 1 exactly, one above it has not; with the
+//    running maximum every key that was ever the largest is exact).  Where the square of a tile's row sum is large against those before it,
+//    what the rounding left out is added as a second product.  The own block comes first in a row's order so that this and new references are rare.
+//    Error of O + o_lo against 64 bits, relative, 1e-4, in brackets ping-pong with its running maximum, 13 x 30 x 45 tokens, a quarter of
+//    the tiles: keys and queries with a smooth field of twice the noise 1.4 (3.7), as strong as the noise 2.3 (5.9), half as strong
+//    6.1 (8.6); noise alone 14.9 (15.3), 1.5 times that 11.6 (12.3), twice 6.3 (8.8), three times 2.6 (5.3).  With a quarter to all of
+//    the tiles, 1 014 to 32 760 tokens it is nowhere larger than with the running maximum.  (A row sum of more than half of everything before as the condition: 1.4,
+//    3.1, 9.0; 16.4, 15.6, 12.5, 5.9.  It saves 1 % with a field, and much of the second products with noise, which is where they cost: 12 heads of 32 760
+//    tokens, noise alone 1.53 ms, 1.5 times that 1.75, twice 2.0, ping-pong 1.58 .. 1.60.)
 //  * The loop has no ragged or pooled tiles: those are in a second copy of it behind the first.
 //  * A wavefront sets M0 and the base of its copies once per tile; addresses advance by scalar additions.
 //  * What a rare branch redefines the compiler would compute behind that branch, away from the MFMAs: pinned.
@@ -1385,8 +1388,9 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
   constexpr int kStage = C::kTile, kVBase = C::kStages * C::kTile;
   constexpr int kPooled = 1 << 30;             // flag of an entry of cols[]: a block of pooled tokens
   constexpr int kDm = D / 32;
-  // for the row sum of a tile (16 keys of a lane): passes kRedo: new reference; passes kShare of all before + kLeast: second product
-  constexpr float kRedo = 1073741824.f, kShare = 0.5f, kLeast = 1.f;
+  // for the row sum of a tile (16 keys of a lane): passes kRedo: new reference; its square passes kLeast + the share kEarly
+  // (in the first fifth of the row) or kLate, over the number of tiles, of the sum of all squares before: second product
+  constexpr float kRedo = 1073741824.f, kEarly = 25.f, kLate = 60.f, kLeast = 2.25f;
 
   const int n_q = C::kRows == BLK ? a.Nb : (a.L + C::kRows - 1) / C::kRows;   // query blocks of a slab
   const int slot = xcd_contiguous_work(blockIdx.x, a.n_slabs * n_q);
@@ -1476,6 +1480,7 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
   // per row: reference of the exponentials (log2 units), sum of P over my lane half's keys
   float ma = 0.f, mc = 0.f, la = 0.f, lc = 0.f;
   const float c = a.scale_log2e;
+  float va = 0.f, vc = 0.f;                              // sum of the squares of the tiles' row sums
   // limits of this walk over the list (see the end): for the row sums of a tile that move the references, and for a second product
   float redo_at = kRedo, least = kLeast;
 
@@ -1504,6 +1509,9 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
     tr_at[2 * dm + 1] = tr_lane ^ (uint32_t)(((4 * dm) ^ t_swz<D>(4)) * 16);
   }
   const int n_it = n_blocks * C::kSub;
+  const int t_late = n_it / 5;
+  const float minus_early = -kEarly / (float)n_it, minus_late = -kLate / (float)n_it;
+  float minus_share = minus_early;
   if (tid == 0) again = 0;
 
   // Copies.  The kI loads of a wavefront's share of a tile have M0 and a scalar base in common (lds_dma_begin) and
@@ -1779,6 +1787,8 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
         if constexpr (x == 3) {
           la += ta_last;
           lc += tc_last;
+          va = fmaf(ta_last, ta_last, va);
+          vc = fmaf(tc_last, tc_last, vc);
         }
         // K of tile t + 3 in front of the barrier, V of tile t + 2 behind it (their stages were last read in
         // iterations t - 2 and t - 1)
@@ -1821,6 +1831,8 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
       }
       la *= fa;
       lc *= fc;
+      va *= fa * fa;
+      vc *= fc * fc;
       settle();
 #pragma unroll
       for (int dm = 0; dm < kDm; ++dm)
@@ -1831,7 +1843,7 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
         }
       settle();
     }
-    if (__builtin_expect(__any(fmaxf(fmaf(share, la, ta), fmaf(share, lc, tc)) > least), 0)) {
+    if (__builtin_expect(__any(fmaxf(fmaf(share, va, ta * ta), fmaf(share, vc, tc * tc)) > least), 0)) {
       // what the rounding of P left out, as a second product
       if constexpr (kTail) {
         if (left_now < C::kST) zero_rows(U, left_now);
@@ -1859,7 +1871,7 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
         }(), ...);
       }(std::make_integer_sequence<int, kNV>{});
     }
-    share = -kShare;
+    share = minus_share;
     ta_last = ta;
     tc_last = tc;
   };
@@ -1911,7 +1923,7 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
       for (int i = 0; i < 16; ++i) oa[dm][i] = oc[dm][i] = 0.f;
 #pragma unroll
     for (int i = 0; i < 16; ++i) p0[i] = p1[i] = 0;
-    la = lc = ta_last = tc_last = 0.f;
+    la = lc = va = vc = ta_last = tc_last = 0.f;
     share = -INFINITY;
     entry_at = cur_at = special = 0;
     last_k = last_v = pooled_k = pooled_v = false;
@@ -1987,6 +1999,7 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
       const std::integral_constant<int, 2> u2{};
       const std::integral_constant<int, 3> u3{};
       int t = 0;
+      minus_share = minus_early;
       // As long as the copies (three tiles ahead) stay inside the blocks in front of the last one of the row's own
       // list nothing is ragged or pooled.
       const int n_plain = (n_own_blocks - 1) * C::kSub - 6;
@@ -1996,6 +2009,7 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
           body(u1, plain, s1a, s1c, s0a, s0c, p1, p0);
           body(u2, plain, s0a, s0c, s1a, s1c, p0, p1);
           body(u3, plain, s1a, s1c, s0a, s0c, p1, p0);
+          if (t >= t_late) minus_share = minus_late;
         }
         cur_at = t / C::kSub;
         fetch_current();
@@ -2007,6 +2021,7 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
         body(u1, tail, s1a, s1c, s0a, s0c, p1, p0);
         body(u2, tail, s0a, s0c, s1a, s1c, p0, p1);
         body(u3, tail, s1a, s1c, s0a, s0c, p1, p0);
+        if (t >= t_late) minus_share = minus_late;
       }
       // the last tile's P V (stage 3: the loop ends on a multiple of four)
       __builtin_amdgcn_s_waitcnt(0x0F70);          // stray copies must land before the LDS is given up
