@@ -216,8 +216,8 @@ struct FwdCfg {
 // stages (2 x 32 KB at d = 128) the copies of step s + 1 are requested right after the barrier
 // that opens step s; with one, the copies of a step are waited for right away and the other
 // workgroups on the CU compute meanwhile.  It serves large block 64 / d 64 calls, large dense calls at the
-// mixed shapes and, at block 128 / d 128, short rows and tensors that the ping-pong kernel below does
-// not take (slabs of 4 GiB and more).
+// mixed shapes and, at block 128 / d 128, short rows (launch_fwd_t draws the line) and tensors that the ping-pong
+// kernel below does not take (slabs of 4 GiB and more).
 // VT: the operand of the second product comes from the transposed copy of V (one 16-byte read)
 // instead of the rows of V (two transposing reads).
 template <int BLK, int D, bool VT>
@@ -1339,32 +1339,36 @@ __global__ __launch_bounds__(BLK * 2, (PipeCfg<BLK, D>::kWavesPerSimd)) void fwd
 // ---------------------------------------------------------------------------------------
 // Wide forward: 64 query rows per wavefront, one wavefront per SIMD, with the software pipeline of the backward kernels
 // (see asa_bwd.hip) inside it.  QW wavefronts share the tiles of 32 keys: two (one query block of 128) with index lists,
-// four (256 rows of a dense call, whatever its block size).  In iteration t a wavefront computes S^T of tile t + 1 for its two halves of 32 rows,
-// adds P V of tile t - 1, and between those MFMAs turns S^T of tile t into P.  Every operand read from LDS feeds two
-// MFMAs.  V comes from its rows by the transposing LDS read: no transposed copy.  O lives in accumulation registers.
+// four (256 rows of a dense call, whatever its block size).  In iteration t a wavefront computes S^T of tile t + 1 for
+// its two halves of 32 rows, adds P V of tile t - 1, and between those MFMAs turns S^T of tile t into P.  Every operand
+// read from LDS feeds two MFMAs.  V comes from its rows by the transposing LDS read: no transposed copy.  O lives in
+// accumulation registers.
 //
 // Bound: power and issue.  At one wavefront per SIMD every instruction, scalar ones too, takes an issue slot of 4-5
-// cycles; 200 of them per iteration stand beside 1024 matrix cycles.  12 heads of 32 760 tokens: a quarter of the tiles
-// matrix duty 0.66 at 1.56 GHz, dense 0.68 at 1.70 (ping-pong, a quarter: 0.62 at 1.58); a build without the copies in the loop has 8
+// cycles; 200 of them per iteration stand beside 1024 matrix cycles.  12 heads of 32 760 tokens, a quarter of the tiles:
+// matrix duty 0.65 at 1.59 GHz (ping-pong 0.62 at 1.58), dense 0.68 at 1.70; a build without the copies in the loop has 8
 // and 4 % fewer cycles.  What follows from that:
 //  * No row maximum per tile.  The exponentials are relative to a reference per row: the largest logit of the first tile
-//    and, where the list holds the query block itself, among the 32 keys of the row's own group (one extra product in
-//    the prologue).  As long as no row sum of a tile passes 2^30 the reference stays; then the tile is redone and O scaled.
-//  * The rounding of P to bf16 shows where few keys carry a row (a key at the reference has P = 1 exactly, one above it has not; with the
-//    running maximum every key that was ever the largest is exact).  Where the square of a tile's row sum is large against those before it,
-//    what the rounding left out is added as a second product.  The own block comes first in a row's order so that this and new references are rare.
-//    Error of O + o_lo against 64 bits, relative, 1e-4, in brackets ping-pong with its running maximum, 13 x 30 x 45 tokens, a quarter of
-//    the tiles: keys and queries with a smooth field of twice the noise 1.4 (3.7), as strong as the noise 2.3 (5.9), half as strong
-//    6.1 (8.6); noise alone 14.9 (15.3), 1.5 times that 11.6 (12.3), twice 6.3 (8.8), three times 2.6 (5.3).  With a quarter to all of
-//    the tiles, 1 014 to 32 760 tokens it is nowhere larger than with the running maximum.  (A row sum of more than half of everything before as the condition: 1.4,
-//    3.1, 9.0; 16.4, 15.6, 12.5, 5.9.  It saves 1 % with a field, and much of the second products with noise, which is where they cost: 12 heads of 32 760
-//    tokens, noise alone 1.53 ms, 1.5 times that 1.75, twice 2.0, ping-pong 1.58 .. 1.60.)
+//    and, where the list holds the query block itself, among the 32 keys of the row's own group (one extra product in the
+//    prologue).  As long as no row sum of a tile passes 2^30 the reference stays; then the tile is redone and O scaled.
+//  * The rounding of P to bf16 shows where few keys carry a row (a key at the reference has P = 1 exactly, one above it
+//    has not; with the running maximum every key that was ever the largest is exact).  Where the square of a tile's row
+//    sum is large against those before it, what the rounding left out is added as a second product.  The own block comes
+//    first in a row's order so that this and new references are rare.
+//    Error of O + o_lo against 64 bits, relative, 1e-4, in brackets ping-pong with its running maximum, 13 x 30 x 45
+//    tokens, a quarter of the tiles: keys and queries with a smooth field of twice the noise 1.0 (3.7), as strong as the
+//    noise 1.8 (5.9), half as strong 5.6 (8.6); noise alone 14.8 (15.3), 1.5 times that 10.7 (12.3), twice 5.6 (8.8),
+//    three times 2.3 (5.3).  With a quarter to all of the tiles, 1 014 to 32 760 tokens, it is nowhere larger than with
+//    the running maximum.  (A row sum of more than half of everything before as the condition: 1.4, 3.1, 9.0; 16.4,
+//    15.6, 12.5, 5.9.  That saves 1 % with the strong field and most of the second products with noise, which is where
+//    they cost: 12 heads of 32 760 tokens, noise alone 1.56 ms, 1.5 times that 1.83, twice 2.05, half a field 1.69,
+//    ping-pong 1.58 .. 1.60.)
 //  * The loop has no ragged or pooled tiles: those are in a second copy of it behind the first.
 //  * A wavefront sets M0 and the base of its copies once per tile; addresses advance by scalar additions.
 //  * What a rare branch redefines the compiler would compute behind that branch, away from the MFMAs: pinned.
-// Times (with the transposition where there was one): a quarter of the tiles 1.60 -> 1.44 ms, dense 5.9 -> 5.2 ms, pooled
-// tokens 1.85 -> 1.55 ms against the ping-pong kernel.  (Row sums of the rounded P by v_dot2, as a normaliser, cost 14 cycles
-// each beside MFMAs, by small MFMAs 64 cycles per tile; the second product serves better.)
+// Times (with the transposition where there was one): a quarter of the tiles 1.58 -> 1.49 ms, dense 5.9 -> 5.4 ms, pooled
+// tokens 1.85 -> 1.57 ms against the ping-pong kernel.  (Row sums of the rounded P by v_dot2, as a normaliser, cost 14
+// cycles each beside MFMAs, by small MFMAs 64 cycles per tile; the second product serves better.)
 // ---------------------------------------------------------------------------------------
 template <int BLK, int D, int QW>
 struct WideCfg {
@@ -1388,8 +1392,8 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
   constexpr int kStage = C::kTile, kVBase = C::kStages * C::kTile;
   constexpr int kPooled = 1 << 30;             // flag of an entry of cols[]: a block of pooled tokens
   constexpr int kDm = D / 32;
-  // for the row sum of a tile (16 keys of a lane): passes kRedo: new reference; its square passes kLeast + the share kEarly
-  // (in the first fifth of the row) or kLate, over the number of tiles, of the sum of all squares before: second product
+  // For the row sum of a tile (16 keys of a lane): passes kRedo: new reference; its square passes kLeast + the sum of all
+  // squares before, times kEarly (those of the first fifth of the row) or kLate over the number of tiles: second product
   constexpr float kRedo = 1073741824.f, kEarly = 25.f, kLate = 60.f, kLeast = 2.25f;
 
   const int n_q = C::kRows == BLK ? a.Nb : (a.L + C::kRows - 1) / C::kRows;   // query blocks of a slab
@@ -1480,7 +1484,7 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
   // per row: reference of the exponentials (log2 units), sum of P over my lane half's keys
   float ma = 0.f, mc = 0.f, la = 0.f, lc = 0.f;
   const float c = a.scale_log2e;
-  float va = 0.f, vc = 0.f;                              // sum of the squares of the tiles' row sums
+  float wa = 0.f, wc = 0.f;                              // what the square of a tile's row sum must pass for a second product
   // limits of this walk over the list (see the end): for the row sums of a tile that move the references, and for a second product
   float redo_at = kRedo, least = kLeast;
 
@@ -1510,8 +1514,8 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
   }
   const int n_it = n_blocks * C::kSub;
   const int t_late = n_it / 5;
-  const float minus_early = -kEarly / (float)n_it, minus_late = -kLate / (float)n_it;
-  float minus_share = minus_early;
+  const float early = kEarly / (float)n_it, late = kLate / (float)n_it;
+  float share = early;
   if (tid == 0) again = 0;
 
   // Copies.  The kI loads of a wavefront's share of a tile have M0 and a scalar base in common (lds_dma_begin) and
@@ -1705,7 +1709,7 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
     settle_acc(oc);
   };
 
-  float share = -INFINITY;                           // (-inf * 0: no comparison holds at the first tile)
+  float sq_a = 0.f, sq_c = 0.f;                      // squares of the row sums of the tile before, not yet in wa, wc
   float ta_last = 0.f, tc_last = 0.f;                // row sums of the tile before, not yet in la, lc
   auto body = [&](auto u_tag, auto tail_tag, f32x16 &sa, f32x16 &sc, f32x16 &na, f32x16 &nc, uint32_t *pn, const uint32_t *po) __attribute__((always_inline)) {
     constexpr int U = decltype(u_tag)::value;        // tile index mod 4
@@ -1787,8 +1791,8 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
         if constexpr (x == 3) {
           la += ta_last;
           lc += tc_last;
-          va = fmaf(ta_last, ta_last, va);
-          vc = fmaf(tc_last, tc_last, vc);
+          wa = fmaf(share, sq_a, wa);
+          wc = fmaf(share, sq_c, wc);
         }
         // K of tile t + 3 in front of the barrier, V of tile t + 2 behind it (their stages were last read in
         // iterations t - 2 and t - 1)
@@ -1831,8 +1835,8 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
       }
       la *= fa;
       lc *= fc;
-      va *= fa * fa;
-      vc *= fc * fc;
+      wa = fmaf(wa - least, fa * fa, least);
+      wc = fmaf(wc - least, fc * fc, least);
       settle();
 #pragma unroll
       for (int dm = 0; dm < kDm; ++dm)
@@ -1843,7 +1847,9 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
         }
       settle();
     }
-    if (__builtin_expect(__any(fmaxf(fmaf(share, va, ta * ta), fmaf(share, vc, tc * tc)) > least), 0)) {
+    sq_a = ta * ta;
+    sq_c = tc * tc;
+    if (__builtin_expect(__any(sq_a > wa || sq_c > wc), 0)) {
       // what the rounding of P left out, as a second product
       if constexpr (kTail) {
         if (left_now < C::kST) zero_rows(U, left_now);
@@ -1871,7 +1877,6 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
         }(), ...);
       }(std::make_integer_sequence<int, kNV>{});
     }
-    share = minus_share;
     ta_last = ta;
     tc_last = tc;
   };
@@ -1923,8 +1928,8 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
       for (int i = 0; i < 16; ++i) oa[dm][i] = oc[dm][i] = 0.f;
 #pragma unroll
     for (int i = 0; i < 16; ++i) p0[i] = p1[i] = 0;
-    la = lc = va = vc = ta_last = tc_last = 0.f;
-    share = -INFINITY;
+    la = lc = ta_last = tc_last = sq_a = sq_c = 0.f;
+    wa = wc = least;
     entry_at = cur_at = special = 0;
     last_k = last_v = pooled_k = pooled_v = false;
     if (n_it > 0) {
@@ -1999,7 +2004,7 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
       const std::integral_constant<int, 2> u2{};
       const std::integral_constant<int, 3> u3{};
       int t = 0;
-      minus_share = minus_early;
+      share = early;
       // As long as the copies (three tiles ahead) stay inside the blocks in front of the last one of the row's own
       // list nothing is ragged or pooled.
       const int n_plain = (n_own_blocks - 1) * C::kSub - 6;
@@ -2009,7 +2014,7 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
           body(u1, plain, s1a, s1c, s0a, s0c, p1, p0);
           body(u2, plain, s0a, s0c, s1a, s1c, p0, p1);
           body(u3, plain, s1a, s1c, s0a, s0c, p1, p0);
-          if (t >= t_late) minus_share = minus_late;
+          if (t >= t_late) share = late;
         }
         cur_at = t / C::kSub;
         fetch_current();
@@ -2021,7 +2026,7 @@ __global__ __launch_bounds__(QW * 64, 1) void fwd_wide_kernel(FwdArgs a) {
         body(u1, tail, s1a, s1c, s0a, s0c, p1, p0);
         body(u2, tail, s0a, s0c, s1a, s1c, p0, p1);
         body(u3, tail, s1a, s1c, s0a, s0c, p1, p0);
-        if (t >= t_late) minus_share = minus_late;
+        if (t >= t_late) share = late;
       }
       // the last tile's P V (stage 3: the loop ends on a multiple of four)
       __builtin_amdgcn_s_waitcnt(0x0F70);          // stray copies must land before the LDS is given up
@@ -2106,19 +2111,25 @@ static hipError_t launch_fwd_t(const FwdArgs &a, const Problem &pb, hipStream_t 
   //   block 128 / d 128: lock-step (V's rows) for short rows; ping-pong, the fastest on a single row, where few rows run at a
   //     time; wide, two of whose workgroups share a compute unit, for long rows where its rounds of 512 query blocks are
   //     filled.  The two long-row kernels meet lock-step at 16-20 tiles.  Time of the others relative to the wide
-  //     kernel, keys and queries with a smooth field of twice the noise, 1 014 to 32 760 tokens:
+  //     kernel (taken when that was 1 % faster), keys and queries with a smooth field of twice the noise, 1 014 to
+  //     32 760 tokens:
   //       up to 256 query blocks: lock-step 0.55-0.83, ping-pong 0.45-0.70 (4 .. 16 tiles).
-  //       lists of one length (a fixed budget), 20, 28, 60 tiles, ping-pong: 512 query blocks 0.97-1.0, 0.98-1.01, 1.03; 600 .. 700
-  //       0.81-0.87; 800 .. 1024 0.96-1.03, 1.0-1.04, 1.04; 1100 .. 1280 0.91-0.95, 0.92-0.97, 0.93-0.97; 1500 0.98-1.02, 1.0-1.06, 1.05; 1600 0.96-0.98;
-  //       2000 .. 3072 1.0-1.04, 1.02-1.04, 1.05.  Lock-step, 12, 16, 20, 28 tiles: 1024 0.86-0.91, 0.93-0.96, 0.98-1.0, 1.03-1.06; 2000 .. 3072
-  //       0.88-0.92, 0.94-0.97, 0.99-1.01, 1.05.
-  //       uneven lists (the threshold alone, 15 .. 85 tiles on average, the longest 2-6 times that), where one long row holds a wide
-  //       workgroup for twice as long, ping-pong: 320 .. 768 blocks 0.57-0.93, 1024 0.66-1.0, 1280 0.68-1.02, 1500 .. 1800 0.76-1.07, 2048
-  //       0.90-1.08.  Always-kept prefix blocks, whose rows are as long as the sequence, 20 tiles on average: 0.52-0.99 up
-  //       to 1100 blocks; beyond, 0.55-0.87 where such a row is longer than two thirds of what a compute unit's half has to do in all, else 0.91-1.05.
-  //       no lists, 8 .. 22 tiles: lock-step (from 18 on ping-pong) 1.0-1.09 where the wide kernel needs at most half of the
-  //       ping-pong kernel's rounds; 27 .. 46 tiles 0.94-0.99 in one round, 0.96-1.07 in more; 56 and more 1.02-1.10, and 1.0-1.04 from 2048
-  //       blocks on with half-filled rounds too; elsewhere 0.53-0.98.
+  //       lists of one length (a fixed budget), ping-pong at 20, 28 and 60 tiles:
+  //            512 query blocks   0.97-1.0   0.98-1.01  1.03         1100 .. 1280  0.91-0.95  0.92-0.97  0.93-0.97
+  //            600 .. 700         0.81-0.84  0.81-0.85  0.84-0.87    1500          0.98-1.02  1.0-1.06   1.05
+  //            800 .. 1024        0.96-1.03  1.0-1.04   1.04         1600          0.96-0.98  0.96-0.97  0.97
+  //                                                                  2000 .. 3072  1.0-1.04   1.02-1.04  1.05
+  //         lock-step at 12, 16, 20, 28 tiles: 1024 blocks 0.86-0.91, 0.93-0.96, 0.98-1.0, 1.03-1.06; 2000 .. 3072
+  //         0.88-0.92, 0.94-0.97, 0.99-1.01, 1.05.
+  //       uneven lists (the threshold alone, 15 .. 85 tiles on average, the longest 2-6 times that), where one long
+  //         row holds a wide workgroup for twice as long, ping-pong: 320 .. 768 blocks 0.57-0.93, 1024 0.66-1.0,
+  //         1280 0.68-1.02, 1500 .. 1800 0.76-1.07, 2048 0.90-1.08.
+  //       always-kept prefix blocks, whose rows are as long as the sequence, 20 tiles on average, ping-pong: 0.52-0.99
+  //         up to 1100 blocks; beyond, 0.55-0.87 where such a row is longer than one and a half times what half a
+  //         compute unit has to do in all, else 0.91-1.05.
+  //       no lists: lock-step (from 18 tiles on ping-pong) at 8 .. 22 tiles 1.0-1.09 where the wide kernel needs at most
+  //         half of the ping-pong kernel's rounds, at 27 .. 46 tiles 0.94-0.99 in one round and 0.96-1.07 in more, at 56
+  //         and more 1.02-1.10, and 1.0-1.04 from 2048 blocks on with half-filled rounds too; elsewhere 0.53-0.98.
   //     Without lists the choice is made here.  With them the host has only the parameters of the rule to go by, which say how
   //     even the rows are, and both kernels of a pair are launched: each workgroup leaves at once if its (batch, head) slab's
   //     tile count belongs to the other (an empty launch costs 3-10 us).
@@ -2146,7 +2157,7 @@ static hipError_t launch_fwd_t(const FwdArgs &a, const Problem &pb, hipStream_t 
   //     below: not taken.  With lists at d 64 a wavefront's own copies bound it: 1461 us and 1526 at block 64, 48 heads
   //     of 17 776 tokens.)
   //   pooled tokens, block 128 / d 128, ping-pong relative to wide, the same inputs: 896 .. 1600 query blocks 1.02-1.20 (12 heads of
-  //     32 760 tokens 1.85 -> 1.55 ms); 512 of one length 1.03-1.3, uneven 0.69-1.03; 576 .. 768 0.93-1.02; prefix blocks as above;
+  //     32 760 tokens 1.85 -> 1.57 ms); 512 of one length 1.03-1.3, uneven 0.69-1.03; 576 .. 768 0.93-1.02; prefix blocks as above;
   //     rows of at most 8 blocks 1.04-1.18 beyond 256.
   //     Other shapes: pipelined, except at d 64 where all ping-pong
   //     workgroups (two groups of wavefronts per query block) start at once and their rows are long: from
