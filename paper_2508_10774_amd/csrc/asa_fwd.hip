@@ -1346,7 +1346,7 @@ __global__ __launch_bounds__(BLK * 2, (PipeCfg<BLK, D>::kWavesPerSimd)) void fwd
 //
 // Bound: power and issue.  At one wavefront per SIMD every instruction, scalar ones too, takes an issue slot of 4-5
 // cycles; 200 of them per iteration stand beside 1024 matrix cycles.  12 heads of 32 760 tokens, a quarter of the tiles:
-// matrix duty 0.65 at 1.59 GHz (ping-pong 0.62 at 1.58), dense 0.68 at 1.70; a build without the copies in the loop has 8
+// matrix duty 0.65 at 1.53-1.59 GHz (ping-pong 0.62 at 1.58), dense 0.68 at 1.70; a build without the copies in the loop has 8
 // and 4 % fewer cycles.  What follows from that:
 //  * No row maximum per tile.  The exponentials are relative to a reference per row: the largest logit of the first tile
 //    and, where the list holds the query block itself, among the 32 keys of the row's own group (one extra product in the
