@@ -59,7 +59,7 @@ int asa_set_kernel_timing(void *start_event, void *stop_event);
  * choice among its four (the default).  1 = without global tokens the lock-step kernel, which every
  * tile shape has; with them the ping-pong kernel at block 128 / d 128, else the pipelined kernel.
  * 2 = the ping-pong kernel where the shape has it (block 128 / d 128; with global tokens also d 64),
- * else as 0.  3 = the wide kernel where the shape has it (block 128 / d 128; block 64 without index
+ * else as 0.  4 = the wide kernel where the shape has it (block 128 / d 128; block 64 without index
  * lists and global tokens), else as 0.  Process-wide; lets the tests put their edge cases through
  * kernels that the library chooses at other sizes only.  Returns an asa_status.
  */

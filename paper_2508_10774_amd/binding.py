@@ -217,7 +217,7 @@ def asa_add_rate_probe(atomic: bool, workgroups: int, tiles_per_workgroup: int, 
 
 
 def asa_test_force_fwd_kernel(which: int):
-    """asa_bench.h: 0 = the library's choice, 1 = lock-step kernel, 2 = ping-pong kernel, 3 = wide kernel."""
+    """asa_bench.h: 0 = the library's choice, 1 = lock-step kernel, 2 = ping-pong kernel, 4 = wide kernel."""
     _check(load().asa_test_force_fwd_kernel(int(which)), "asa_test_force_fwd_kernel")
 
 

@@ -150,7 +150,7 @@ const char *asa_error_string(int status) {
 const char *asa_last_hip_error(void) { return g_hip_error; }
 
 int asa_test_force_fwd_kernel(int which) {
-  if (which < 0 || which > 3) return ASA_ERR_INVALID_ARG;
+  if (which < 0 || which > 4 || which == 3) return ASA_ERR_INVALID_ARG;
   g_forced_fwd_kernel.store(which, std::memory_order_relaxed);
   return ASA_OK;
 }

@@ -55,7 +55,7 @@ void timing_end(hipStream_t st);
 // (kernel, device) under a lock; later calls only look the pair up.
 hipError_t set_dynamic_lds_once(const void *fn, int bytes);
 // Which forward kernel the tests asked for (asa_test_force_fwd_kernel in asa_bench.h): 0 = the
-// library's own choice, 1 = lock-step, 2 = ping-pong, 3 = wide, where the call has them.
+// library's own choice, 1 = lock-step, 2 = ping-pong, 4 = wide, where the call has them.
 int forced_fwd_kernel();
 
 // launchers (each returns a hipError_t from the launch)

@@ -2166,8 +2166,8 @@ static hipError_t launch_fwd_t(const FwdArgs &a, const Problem &pb, hipStream_t 
   //     tiles 45 and 48, 128 tiles 130 against 177).  Lists hide their lengths: an eighth of the blocks is
   //     assumed (fixed budgets keep a quarter, the threshold alone a few per cent).
   // The ping-pong kernel addresses K tiles by 32-bit byte offsets inside a slab: slabs of 4 GiB and
-  // more take the wide and the lock-step kernel.  The tests can force the ping-pong (2) or the lock-step kernel (1) where
-  // the shape has it (asa_test_force_fwd_kernel).
+  // more take the wide and the lock-step kernel.  The tests can force the lock-step (1), the ping-pong (2) or the wide
+  // kernel (4) where the shape has it (asa_test_force_fwd_kernel).
   const bool fits32 = (uint64_t)a.Nb * BLK * (uint64_t)a.tk.sL * 2u < 0xFFFFFFFFull;
   const bool pooled = a.Nbg > 0, dense = a.row_ptr == nullptr;
   if (pooled && (!fits32 || a.Nb + a.Nbg > kMaxNb || a.tk.sL != D)) return hipErrorNotSupported;
@@ -2178,7 +2178,7 @@ static hipError_t launch_fwd_t(const FwdArgs &a, const Problem &pb, hipStream_t 
   const bool long_rows = prefix && (int64_t)a.Nb * 512 * 2 > (int64_t)total * pb.m_min * 3;
   constexpr bool kPingPongShape = BLK == 128 && D == 128, kSmallTile = BLK == 64 && D == 64;
   const bool has_wide = kPingPongShape || (BLK == 64 && dense && !pooled);
-  const int forced = forced_fwd_kernel() == 3 && !has_wide ? 0 : forced_fwd_kernel();
+  const int forced = forced_fwd_kernel() == 4 && !has_wide ? 0 : forced_fwd_kernel();
   FwdArgs b = a;
   b.select = 0;
   if constexpr (!kPingPongShape) {
@@ -2186,7 +2186,7 @@ static hipError_t launch_fwd_t(const FwdArgs &a, const Problem &pb, hipStream_t 
       // Without lists the size of a block means nothing: 256 rows share the tiles of the wide kernel.
       const int wide = a.n_slabs * ((a.L + 255) / 256), rounds = (wide + 255) / 256;
       const bool filled = D == 128 ? 4 * wide >= 3 * 256 * rounds : 16 * wide >= 15 * 256 * rounds;
-      if (dense && !pooled && (forced == 3 || (forced == 0 && filled && a.L >= (D == 128 ? 4000 : 8000)))) {
+      if (dense && !pooled && (forced == 4 || (forced == 0 && filled && a.L >= (D == 128 ? 4000 : 8000)))) {
         b.Nb = (a.L + 127) / 128;
         return launch_wide<128, D, 4, false>(b, st);
       }
@@ -2211,10 +2211,10 @@ static hipError_t launch_fwd_t(const FwdArgs &a, const Problem &pb, hipStream_t 
     constexpr int kMinTiles = 18;
     if (pooled) {
       const bool pays = a.Nb <= 8 ? rounds > 1 : rounds > 3 || (rounds == 2 && even_rows);
-      const bool wide = forced == 3 || (forced == 0 && pays && !long_rows);
+      const bool wide = forced == 4 || (forced == 0 && pays && !long_rows);
       return wide ? launch_wide<BLK, D, 2, true>(b, st) : launch_ping_pong<BLK, D, true>(b, grid, st);
     }
-    if (forced == 3) return dense ? launch_wide<BLK, D, 4, false>(b, st) : launch_wide<BLK, D, 2, false>(b, st);
+    if (forced == 4) return dense ? launch_wide<BLK, D, 4, false>(b, st) : launch_wide<BLK, D, 2, false>(b, st);
     if (fits32 && forced == 2) return launch_ping_pong<BLK, D, false>(b, grid, st);
     if (forced == 0 && dense) {
       const bool filled = 2 * ((a.n_slabs * ((a.L + 255) / 256) + 255) / 256) <= rounds;

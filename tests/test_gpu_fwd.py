@@ -11,7 +11,7 @@ from tests import util
 pytestmark = pytest.mark.gpu
 
 
-FORCED = {"auto": 0, "lockstep": 1, "pingpong": 2, "wide": 3}
+FORCED = {"auto": 0, "lockstep": 1, "pingpong": 2, "wide": 4}
 
 
 def picks_its_kernel(test):
@@ -296,7 +296,7 @@ def test_fwd_mixed_shapes_on_both_sides_of_the_kernel_choice(block, d, H, Nb, ta
 
 
 @picks_its_kernel
-@pytest.mark.parametrize("which", [0, 1, 2, 3])
+@pytest.mark.parametrize("which", [0, 1, 2, 4])
 @pytest.mark.parametrize("block,d", [(64, 64), (64, 128), (128, 64), (128, 128)])
 def test_fwd_infinite_value_in_the_last_row_stays_infinite(block, d, which):
     """Keys past the end have probability zero and must not turn an infinite value of a real key into

@@ -15,7 +15,7 @@ from tests.test_gpu_global import _run_fwd_g
 pytestmark = pytest.mark.gpu
 
 HEADS, NB = 43, 6        # 258 query blocks
-LOCK_STEP, PING_PONG, WIDE = 1, 2, 3
+LOCK_STEP, PING_PONG, WIDE = 1, 2, 4
 
 
 def own_choice(test):

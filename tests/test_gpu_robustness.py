@@ -36,7 +36,7 @@ def _canaries_intact(store, view, what):
 
 
 @pytest.mark.parametrize("L,d,block", [(1000, 128, 128), (333, 64, 64), (450, 128, 64), (300, 64, 128)])
-@pytest.mark.parametrize("forced", [0, 1, 2, 3])
+@pytest.mark.parametrize("forced", [0, 1, 2, 4])
 def test_nothing_is_written_outside_the_outputs(L, d, block, forced):
     print(f"case L={L} d={d} block={block} forced kernel {forced}", flush=True)
     B, H = 1, 2
