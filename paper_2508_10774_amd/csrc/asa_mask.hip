@@ -2,8 +2,10 @@
 // the threshold rule (Alg. 3 steps 6-11) and the CSR / CSC index lists that drive the
 // block-sparse attention kernels.
 #include <type_traits>
+#include <utility>
 
 #include "asa_common.hpp"
+#include "asa_tiles.hpp"
 
 namespace asa {
 
@@ -11,17 +13,16 @@ namespace asa {
 // Probe: P_imp[i][j] = max over sampled rows of block i and sampled keys of block j of the
 // soft-max (over ALL sampled keys of the slab) of scale * Qs Ks^T.
 //
-// Alg. 1 of the paper, reorganised for 64-wide wavefronts.  A workgroup of 8 wavefronts owns 8
-// query blocks and sweeps one range of the key blocks of its slab:
-// wavefronts w and w + 4 share two query blocks and split every chunk of key blocks between them.  The sampled key rows (Alg. 2
-// steps 1-3) are gathered from K by direct global->LDS loads, 8 key blocks (128 rows) per
+// Alg. 1 of the paper, reorganised for 64-wide wavefronts.  A workgroup of 4 wavefronts owns 8
+// query blocks, two per wavefront, and sweeps one range of the key blocks of its slab.  The sampled key rows (Alg. 2
+// steps 1-3) are gathered from K by direct global->LDS loads, 4 key blocks (64 rows) per
 // chunk, double-buffered and shared by all wavefronts.  One chain of 32x32x16
 // bf16 MFMAs gives a 32 x 32 logit tile: 2 key blocks x 16 samples on the M axis, 2 query
 // blocks x 16 samples on the N axis.  The rows of the A operand are ordered so that lane half h
 // holds, for ONE sampled query, all 16 samples of key block j0 + h: the block-row maximum
 // Rt[query][j] of Alg. 1 is then a lane-local maximum, and the running reference / denominator of
 // the row is kept lane-locally over the key blocks of that parity and merged across the two
-// halves (and the two wavefronts of a pair) once, at the end.  No cross-lane traffic inside the
+// halves once, at the end.  No cross-lane traffic inside the
 // sweep.  Rt (unscaled logits) and each wavefront's (reference, denominator) pair go to a
 // workspace in global memory; finish_rule_kernel merges the pairs of a sampled row, turns Rt
 // into probabilities, max-pools over the sampled rows and applies the rule to the row.
@@ -30,10 +31,13 @@ struct ProbeArgs {
   const void *q, *k;
   float *p_imp;
   float *rt;         // workspace [query group][pair][Nb rounded up to 8][32]: block-row maxima
-  float *stat_r;     // workspace [work item][wave][32]: reference exponent of the wavefront's keys
+  float *stat_r;     // workspace [work item][pair][32]: reference exponent of the wavefront's keys
   double *stat_l;    //           and the denominator relative to 2^reference
   TensorView tq, tk;
   int H, L, Nb, n_slabs, block, ks;
+  int ranges;        // of key blocks per query group
+  int64_t chunk_bytes;   // from a chunk's first token to the next one's
+  int n_full_chunks; // chunks with no token >= L (none if a chunk's rows span 4 GiB or more: 32-bit offsets)
   int n_valid_last;  // sampled tokens of the last block that lie below L
   float c2;          // scale * log2(e)
   float rest;        // ln(2) * what the rounding of c2 left out
@@ -43,25 +47,16 @@ struct ProbeArgs {
 };
 
 constexpr int kProbeQBlocks = 8;   // query blocks per workgroup
-constexpr int kProbeKBlocks = 8;   // key blocks per LDS chunk (a wavefront takes two pairs of them)
-// The key blocks of a slab are cut into this many ranges, one workgroup each: at the Wan2.1 shape
-// 12 heads x 32 query groups x 2 = 768 workgroups, three per compute unit (one range per group
-// gave 384 workgroups for 512 resident slots: half of the compute units carried twice the load;
-// four ranges, whole rounds of 512, are slower by 11 %: a workgroup's start costs more than the
-// half-empty round).
-constexpr int kProbeKeySplits = 2;
+constexpr int kProbeKBlocks = 4;   // key blocks per LDS chunk: two pairs, one 32 x 32 logit tile per wavefront each
+constexpr int kProbePairs = kProbeQBlocks / 2;
+constexpr int kProbePad = 8;       // the rows of block maxima are this many key blocks long, rounded up
+// The key blocks of a slab are cut into ranges, one workgroup each (probe_ranges).
+constexpr int kProbeMaxRanges = 4;
 
 // The exponent of 2 of a raw logit s is s * c2 with c2 = scale * log2(e), rounded to fp32.  What the
 // rounding leaves out multiplies exp2(s * c2) by 1 + s * rest.  That is used up to this exponent (logits
 // beyond it are themselves rounded by more than that).
 constexpr float kMaxExactExponent = 8192.f;
-
-typedef __attribute__((address_space(3))) void lds_void_m;
-__device__ __forceinline__ void probe_dma16(const void *src, void *lds_dst) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  __builtin_amdgcn_global_load_lds(src, (lds_void_m *)lds_dst, 16, 0, 0);
-#endif
-}
 
 // chunk-position swizzle of the sampled-key rows in LDS (16 rows read together differ in row
 // bits 0..2 and 4; at D = 64 a row is half the banks and parity picks the half)
@@ -70,56 +65,62 @@ __device__ __forceinline__ int probe_swz(int row) {
   return D == 128 ? ((row & 7) | (((row >> 4) & 1) << 3)) : (((row >> 1) & 3) | (((row >> 4) & 1) << 2));
 }
 
+// Bound: the vector ALU.  An entry costs an exponential (8 cycles of 64 lanes), a multiply-add, an addition and half a
+// maximum (10), 576 cycles per wavefront and chunk, beside 512 (d = 128) or 256 matrix cycles; with what a chunk costs
+// as a whole the vector ALU is busy 88 % of the cycles at d = 64 (48 heads, Nb = 278) and 68 % at d = 128 (12 heads,
+// Nb = 256).  So the products of the next chunk stand between the vector instructions of this one, and one wavefront
+// takes whole chunks (against 8 wavefronts that share chunks of twice the size and run products and vector work one behind the
+// other: 75 -> 68 us at d = 128, 252 -> 225 us at d = 64).  Three wavefronts per SIMD: two (256 registers), with chunks of
+// 4 or of 8 key blocks, are 3 % slower for the whole mask.
 // TAB: the sample positions differ from block to block and come from a table (seeded random
 // sampling) instead of one offset vector for all blocks.
 template <int D, bool TAB>
-__global__ __launch_bounds__(512, 4) void probe_kernel(ProbeArgs a) {   // (4 wavefronts per SIMD: two workgroups per CU)
+__global__ __launch_bounds__(256, 3) void probe_kernel(ProbeArgs a) {
   constexpr int ROWS = kProbeKBlocks * 16;          // sampled rows per chunk
   constexpr int CH = D / 8;                         // 16-byte chunks per row
-  constexpr int DMA_PER_WAVE = ROWS * CH / 64 / 8;  // 1 KB per wave instruction, 8 wavefronts
-  extern __shared__ __align__(1024) unsigned char probe_smem[];
-  bf16 (*Kc)[ROWS * D] = reinterpret_cast<bf16 (*)[ROWS * D]>(probe_smem);   // two buffers
+  constexpr int DMA_PER_WAVE = ROWS * CH / 64 / kProbePairs;  // 1 KB per wave instruction
+  constexpr int NT = kProbeKBlocks / 2;             // logit tiles per chunk
+  __shared__ __align__(1024) bf16 Kc[2][ROWS * D];
 
   const int n_groups = (a.Nb + kProbeQBlocks - 1) / kProbeQBlocks;
-  const int item = xcd_contiguous_work(blockIdx.x, a.n_slabs * n_groups * kProbeKeySplits);
+  const int item = xcd_contiguous_work(blockIdx.x, a.n_slabs * n_groups * a.ranges);
   if (item < 0) return;
-  const int work = item / kProbeKeySplits;          // (slab, query group)
-  const int split = item - work * kProbeKeySplits;  // which range of key blocks
+  const int work = item / a.ranges;          // (slab, query group)
+  const int range = item - work * a.ranges;  // which range of key blocks
   const int slab = work / n_groups;
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
-  const int pair = wave & 3;      // which two query blocks
-  const int half = wave >> 2;     // which half of every chunk of key blocks
+  const int pair = wave;          // which two query blocks
   const int i_base = (work - slab * n_groups) * kProbeQBlocks;
   const int i0 = i_base + 2 * pair;
   const int hl = lane >> 5;  // operand k-half on loads, key-block parity on results
   const int n = lane & 31;   // A row on loads; query column on results
-  const int nb_pad = (a.Nb + kProbeKBlocks - 1) / kProbeKBlocks * kProbeKBlocks;
-  float *rt = a.rt + ((int64_t)work * 4 + pair) * nb_pad * 32;
+  const int nb_pad = (a.Nb + kProbePad - 1) / kProbePad * kProbePad;
+  float *rt = a.rt + ((int64_t)work * kProbePairs + pair) * nb_pad * 32;
 
   const bf16 *qs = slab_ptr(a.q, a.tq, slab, a.H);
   const bf16 *ks = slab_ptr(a.k, a.tk, slab, a.H);
 
   // TAB: this slab's table in LDS; positions ascend inside a block, so the samples of the last
   // block that lie below L are a prefix
-  __shared__ uint8_t tab[TAB ? kMaxNb * kMaxSamples : 16];
+  __shared__ uint8_t tab[TAB ? kMaxNb * kMaxSamples : kMaxSamples];
   int n_valid_last = a.n_valid_last;
   if (TAB) {
     const uint8_t *g = a.table + (int64_t)slab * a.Nb * a.ks;
-    for (int t = tid; t < a.Nb * a.ks; t += 512) tab[t] = g[t];
-    __syncthreads();
+    for (int t = tid; t < a.Nb * a.ks; t += 256) tab[t] = g[t];
+  } else if (tid < kMaxSamples) {
+    tab[tid] = (uint8_t)a.offs[tid];           // (below the block size, 128 at most)
+  }
+  __syncthreads();
+  if (TAB) {
     n_valid_last = 0;
     for (int u = 0; u < a.ks; ++u)
       if ((a.Nb - 1) * a.block + tab[(a.Nb - 1) * a.ks + u] < a.L) ++n_valid_last;
   }
   auto offset_of = [&](int blk, int u) {
     if (TAB) return (blk < a.Nb && u < a.ks) ? (int)tab[blk * a.ks + u] : 0;
-    int o = 0;
-#pragma unroll
-    for (int x = 0; x < kMaxSamples; ++x)
-      if (x == u) o = a.offs[x];
-    return o;
+    return (int)tab[u];
   };
   auto valid_in_block = [&](int blk) {
     return blk >= a.Nb ? 0 : (blk == a.Nb - 1 ? n_valid_last : a.ks);
@@ -138,26 +139,29 @@ __global__ __launch_bounds__(512, 4) void probe_kernel(ProbeArgs a) {   // (4 wa
 
   // producer: my share of a chunk of sampled key rows (row r of a chunk = key block r / 16,
   // sample r % 16)
-  int dma_tok[DMA_PER_WAVE];   // token offset inside the chunk, or -1 for a sample slot >= ks
-  int dma_pos[DMA_PER_WAVE];   // swizzled 16-byte position to fetch
-#pragma unroll
-  for (int i = 0; i < DMA_PER_WAVE; ++i) {
-    const int seg = wave * DMA_PER_WAVE + i;
-    const int row = seg * (64 / CH) + lane / CH;
-    dma_tok[i] = (row / 16) * a.block + (TAB ? 0 : offset_of(0, row % 16));
-    dma_pos[i] = ((lane % CH) ^ probe_swz<D>(row)) * 8;
-  }
+  const uint32_t lds_at = ASA_LDS_ADDR_OF(Kc);
+  // (addresses of a chunk come from its number by scalar arithmetic, at each use: pointers that run along
+  // would be kept in vector registers)
+  auto opaque = [](int chunk) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+s"(chunk));
+#endif
+    return chunk;
+  };
+  auto lds_of = [&](int i, int buf) { return lds_at + (uint32_t)(buf * ROWS * D * 2 + (wave * DMA_PER_WAVE + i) * 1024); };
+  auto row_of = [&](int i, int l) { return (wave * DMA_PER_WAVE + i) * (64 / CH) + l / CH; };
+  auto pos_of = [&](int i, int l) { return ((l % CH) ^ probe_swz<D>(row_of(i, l))) * 8; };   // swizzled 16-byte position
   auto fetch = [&](int chunk, int buf) __attribute__((always_inline)) {
+    int l = lane;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(l));   // (rare: nothing of it is to be kept in registers across the sweep)
+#endif
 #pragma unroll
     for (int i = 0; i < DMA_PER_WAVE; ++i) {
-      const int seg = wave * DMA_PER_WAVE + i;
-      int64_t tok = (int64_t)chunk * kProbeKBlocks * a.block + dma_tok[i];
-      if (TAB) {
-        const int row = seg * (64 / CH) + lane / CH;
-        tok += offset_of(chunk * kProbeKBlocks + row / 16, row % 16);
-      }
+      const int row = row_of(i, l), blk = chunk * kProbeKBlocks + row / 16;
+      int64_t tok = (int64_t)blk * a.block + offset_of(blk, row % 16);
       tok = tok < a.L ? tok : 0;   // padded samples: any valid row, masked out below
-      probe_dma16(ks + tok * a.tk.sL + dma_pos[i], &Kc[buf][seg * 512]);
+      lds_dma16_v(ks + tok * a.tk.sL + pos_of(i, l), lds_of(i, buf));
     }
   };
 
@@ -166,17 +170,19 @@ __global__ __launch_bounds__(512, 4) void probe_kernel(ProbeArgs a) {   // (4 wa
   // the chunk, per chunk one wave-uniform base.
   uint32_t dma_off0[DMA_PER_WAVE];   // bytes from the first token of the chunk
 #pragma unroll
-  for (int i = 0; i < DMA_PER_WAVE; ++i)
-    dma_off0[i] = (uint32_t)(((int64_t)dma_tok[i] * a.tk.sL + dma_pos[i]) * 2);
-  const int64_t chunk_stride = (int64_t)kProbeKBlocks * a.block * a.tk.sL * 2;   // bytes
-  // chunks with no token >= L (none if a chunk's rows span 4 GiB or more: 32-bit offsets)
-  const int n_full_chunks = (TAB || chunk_stride >= ((int64_t)1 << 32)) ? 0 : a.L / (kProbeKBlocks * a.block);
+  for (int i = 0; i < DMA_PER_WAVE; ++i) {
+    const uint32_t tok = (row_of(i, lane) / 16) * a.block + (TAB ? 0 : offset_of(0, row_of(i, lane) % 16));
+    dma_off0[i] = (tok * (uint32_t)a.tk.sL + (uint32_t)pos_of(i, lane)) * 2;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(dma_off0[i]));      // (else kept as the low half of a 64-bit product)
+#endif
+  }
+  const int n_full_chunks = TAB ? 0 : a.n_full_chunks;
   auto fetch_any = [&](int chunk, int buf) __attribute__((always_inline)) {
     if (chunk < n_full_chunks) {
-      const char *base = reinterpret_cast<const char *>(ks) + chunk * chunk_stride;   // wave-uniform
+      const char *base = reinterpret_cast<const char *>(ks) + opaque(chunk) * a.chunk_bytes;   // wave-uniform
 #pragma unroll
-      for (int i = 0; i < DMA_PER_WAVE; ++i)
-        probe_dma16(base + dma_off0[i], &Kc[buf][(wave * DMA_PER_WAVE + i) * 512]);
+      for (int i = 0; i < DMA_PER_WAVE; ++i) lds_dma16_sv(base, dma_off0[i], lds_of(i, buf));
     } else {
       fetch(chunk, buf);
     }
@@ -185,106 +191,157 @@ __global__ __launch_bounds__(512, 4) void probe_kernel(ProbeArgs a) {   // (4 wa
   // consumer: A row r = 8g + 4h + j is sample 4g + j of key block j0 + h
   const int a_row = ((n >> 2) & 1) * 16 + 4 * (n >> 3) + (n & 3);   // row inside a pair of key blocks
   const int a_swz = probe_swz<D>(a_row);
-  // my fragment s of the first pair of key blocks of my half of a chunk (elements from the
-  // start of the buffer); the second pair and the other buffer are constant distances away
-  int a_off[D / 16];
+  // my fragment s of the first pair of key blocks of a chunk in buffer 0 (LDS address); the
+  // second pair and the other buffer are constant distances away
+  uint32_t a_at[D / 16];
 #pragma unroll
-  for (int s = 0; s < D / 16; ++s)
-    a_off[s] = (half * (kProbeKBlocks / 4) * 32 + a_row) * D + (((2 * s + hl) ^ a_swz) * 8);
-  // where my block-row maxima of chunk 0 go (floats from the start of rt)
-  const int rt_off = (2 * half * (kProbeKBlocks / 4) + hl) * 32 + n;
+  for (int s = 0; s < D / 16; ++s) a_at[s] = lds_at + (uint32_t)((a_row * D + (((2 * s + hl) ^ a_swz) * 8)) * 2);
+  const uint32_t rt_off = hl * 32 + n;       // where my block-row maxima of a chunk's first pair go (floats)
 
-  float rt_pend[kProbeKBlocks / 4];   // block-row maxima of the chunk just swept
+  float rt_pend[NT];     // block-row maxima of the chunk just swept
   float Rr = -INFINITY;  // reference exponent of my query over the key blocks of parity hl (an integer)
   double lt = 0.0;       // running denominator over the same keys, relative to 2^Rr
   const float c2 = a.c2;
+  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f,
+                         0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
-  // One chunk out of LDS buffer BUF (a compile-time constant: every LDS address of the sweep is
-  // a per-lane register plus an immediate): both pairs of key blocks of my half at once.  The
-  // exponentials are taken relative to the power of two at or below the running maximum's, brought up
+  // One turn of the sweep, a software pipeline inside each wavefront: the products of chunk t + 1 (out of
+  // LDS buffer BUF, a compile-time constant: every LDS address is a per-lane register plus an
+  // immediate) and between them, slot by slot, the maxima and exponentials of chunk t.
+  // The exponentials are taken relative to the power of two at or below the running maximum's, brought up
   // to date first (no branch for it): one fp64 update per 32 keys, and neither the reference nor a
   // change of it is rounded (at or below: no numerator underflows that would not underflow relative
   // to the maximum).  finish_rule_kernel forms the numerators from the same product s * c2; the rest of
-  // the rounded c2 is put right there per entry and here per chunk.  Against exponentials relative to each
-  // pair's own maximum: at d = 64, 48 heads, Nb = 278: 270 -> 252 us (vector instructions
-  // 86 -> 75 million), at d = 128, 12 heads, Nb = 256: 80 -> 75 us.
-  auto sweep_chunk = [&](int chunk, auto buf_tag) __attribute__((always_inline)) {
-    constexpr int BUF = decltype(buf_tag)::value, NT = kProbeKBlocks / 4;
-    const bf16 *Kb = Kc[BUF];
-    f32x16 acc[NT];
-#pragma unroll
-    for (int sb = 0; sb < NT; ++sb)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[sb][i] = 0.f;
-#pragma unroll
-    for (int sb = 0; sb < NT; ++sb)
-#pragma unroll
-      for (int s = 0; s < D / 16; ++s) {
-        bf16x8 ka = *reinterpret_cast<const bf16x8 *>(Kb + sb * 32 * D + a_off[s]);
-        acc[sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qreg[s], acc[sb], 0, 0, 0);
-      }
-    float mnew = -INFINITY;
-#pragma unroll
-    for (int sb = 0; sb < NT; ++sb) {
-      const int j0 = chunk * kProbeKBlocks + 2 * (half * NT + sb);
+  // the rounded c2 is put right there per entry and here per chunk.
+  constexpr int kNE = NT * (D / 16);              // products of a chunk
+  constexpr int kRing = 4, kDepth = 3;            // LDS operands read this many products ahead
+  constexpr int kMaxSlots = kNE / 4;              // slots that form the maxima; the exponentials fill the others
+  auto turn = [&](int chunk, auto buf_tag, auto mul_tag, auto vec_tag, f32x16 (&cur)[NT], f32x16 (&nxt)[NT])
+      __attribute__((always_inline)) {
+    constexpr int BUF = decltype(buf_tag)::value;
+    constexpr bool kMul = decltype(mul_tag)::value, kVec = decltype(vec_tag)::value;
+    bf16x8 ring[kRing];
+    auto read = [&](auto e_tag) __attribute__((always_inline)) {
+      constexpr int e = decltype(e_tag)::value, sb = e / (D / 16), s = e % (D / 16);
+      ring[e % kRing] = lds_read<bf16x8>(a_at[s] + (uint32_t)((BUF * ROWS + sb * 32) * D * 2));
+    };
+    if constexpr (kMul)
+      [&]<int... E>(std::integer_sequence<int, E...>) __attribute__((always_inline)) {
+        (read(std::integral_constant<int, E>{}), ...);
+      }(std::make_integer_sequence<int, kDepth>{});
+    if (kVec && (a.ks < kMaxSamples || (chunk + 1) * kProbeKBlocks >= a.Nb)) {
       // register i of lane half hl is sample i of key block j0 + hl; samples past L (only in
       // the last block), past the last block, or in sample slots >= k are masked out
-      if (a.ks < kMaxSamples || j0 + 2 >= a.Nb) {
-        const int nv = valid_in_block(j0 + hl);
+#pragma unroll
+      for (int sb = 0; sb < NT; ++sb) {
+        const int nv = valid_in_block(chunk * kProbeKBlocks + 2 * sb + hl);
 #pragma unroll
         for (int i = 0; i < 16; ++i)
-          if (i >= nv) acc[sb][i] = -INFINITY;
+          if (i >= nv) cur[sb][i] = -INFINITY;
       }
-      float mraw = -INFINITY;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) mraw = fmaxf(mraw, acc[sb][i]);
-      rt_pend[sb] = mraw;                                // block-row maximum, Alg. 1 step 12 (unscaled)
-      mnew = fmaxf(mnew, mraw);
     }
-    // Alg. 1 steps 12-15 with the exponentials exp(scale * (s - reference)) as one fused multiply-add
-    // and one exp2 each
-    const float r_new = fmaxf(Rr, floorf(mnew * c2));
-    const float bias = (r_new == -INFINITY) ? 0.f : -r_new;   // (no key has been seen yet: all sums stay 0)
-    const int shift = (int)fmaxf(Rr - r_new, -2000.f);        // (-inf - x and -inf - -inf: the old sum is 0)
-    float sum[NT];
+    float mraw[NT], sum[NT], mnew = -INFINITY, bias = 0.f;
+    int shift = 0;
 #pragma unroll
-    for (int sb = 0; sb < NT; ++sb) {
-      sum[sb] = 0.f;
+    for (int sb = 0; sb < NT; ++sb) mraw[sb] = -INFINITY, sum[sb] = 0.f;
+    __builtin_amdgcn_sched_barrier(0);
+    [&]<int... E>(std::integer_sequence<int, E...>) __attribute__((always_inline)) {
+      ([&]() __attribute__((always_inline)) {
+        constexpr int e = E;
+        if constexpr (kMul) {
+          constexpr int sb = e / (D / 16), s = e % (D / 16);
+          if constexpr (e + kDepth < kNE) read(std::integral_constant<int, e + kDepth>{});
+          nxt[sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[e % kRing], qreg[s], s == 0 ? zero16 : nxt[sb], 0, 0, 0);
+        }
+        if constexpr (kVec && e < kMaxSlots) {
+          constexpr int i0 = e * 16 / kMaxSlots, i1 = (e + 1) * 16 / kMaxSlots;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) sum[sb] += fast_exp2(fmaf(acc[sb][i], c2, bias));
-    }
-    lt = fma((double)(sum[0] + sum[1]), fma((double)__builtin_amdgcn_fmed3f(mnew, -a.s_bound, a.s_bound), (double)a.rest, 1.0),
-             __builtin_amdgcn_ldexp(lt, shift));
-    Rr = r_new;
+          for (int i = i0; i < i1; ++i)
+#pragma unroll
+            for (int sb = 0; sb < NT; ++sb) mraw[sb] = fmaxf(mraw[sb], cur[sb][i]);
+          if constexpr (e == kMaxSlots - 1) {
+#pragma unroll
+            for (int sb = 0; sb < NT; ++sb) {
+              rt_pend[sb] = mraw[sb];                    // block-row maximum, Alg. 1 step 12 (unscaled)
+              mnew = fmaxf(mnew, mraw[sb]);
+            }
+            // Alg. 1 steps 12-15 with the exponentials exp(scale * (s - reference)) as one fused multiply-add
+            // and one exp2 each
+            const float r_new = fmaxf(Rr, floorf(mnew * c2));
+            bias = (r_new == -INFINITY) ? 0.f : -r_new;     // (no key has been seen yet: all sums stay 0)
+            shift = (int)fmaxf(Rr - r_new, -2000.f);        // (-inf - x and -inf - -inf: the old sum is 0)
+            Rr = r_new;
+          }
+        }
+        if constexpr (kVec && e >= kMaxSlots) {
+          // element x of the chunk: tile x % NT, register x / NT; summed one slot after its exponential
+          constexpr int n_slots = kNE - kMaxSlots, f = e - kMaxSlots, all = 16 * NT;
+          constexpr int x0 = f * all / n_slots, x1 = (f + 1) * all / n_slots;
+          constexpr int y0 = f == 0 ? 0 : (f - 1) * all / n_slots, y1 = f == n_slots - 1 ? all : x0;
+#pragma unroll
+          for (int x = x0; x < x1; ++x) cur[x % NT][x / NT] = fast_exp2(fmaf(cur[x % NT][x / NT], c2, bias));
+#pragma unroll
+          for (int x = y0; x < y1; ++x) sum[x % NT] += cur[x % NT][x / NT];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }(), ...);
+    }(std::make_integer_sequence<int, kNE>{});
+    if constexpr (kVec)
+      lt = fma((double)(sum[0] + sum[1]), fma((double)__builtin_amdgcn_fmed3f(mnew, -a.s_bound, a.s_bound), (double)a.rest, 1.0),
+               __builtin_amdgcn_ldexp(lt, shift));
   };
 
-  // The block-row maxima of a chunk are stored at the start of the NEXT chunk's turn, just before
-  // its loads are requested: the wait for those loads at the top of the turn after that also
+  // The block-row maxima of a chunk are stored at the start of the turn after its own, just before
+  // loads are requested: the wait for those loads at the top of the turn after that also
   // waits for the stores (one counter), and a store issued in the middle of a turn was not yet
   // acknowledged at its end.
   auto store_rt = [&](int chunk) __attribute__((always_inline)) {
-    float *rt_c = rt + (int64_t)chunk * kProbeKBlocks * 32;
+    float *rt_c = rt + (int64_t)opaque(chunk) * kProbeKBlocks * 32;
 #pragma unroll
-    for (int sb = 0; sb < kProbeKBlocks / 4; ++sb) rt_c[rt_off + sb * 64] = rt_pend[sb];
+    for (int sb = 0; sb < NT; ++sb) rt_c[rt_off + sb * 64] = rt_pend[sb];
   };
-  const int n_chunks = nb_pad / kProbeKBlocks;
-  const int per_split = (n_chunks + kProbeKeySplits - 1) / kProbeKeySplits;
-  const int c0 = min(n_chunks, split * per_split), c1 = min(n_chunks, c0 + per_split);   // my chunks
-  if (c0 < c1) fetch_any(c0, 0);
-  for (int chunk = c0; chunk < c1; chunk += 2) {
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): my loads of this chunk have landed
-    __syncthreads();                     // everyone's have, and the other buffer is free
-    if (chunk > c0) store_rt(chunk - 1);
-    if (chunk + 1 < c1) fetch_any(chunk + 1, 1);
-    sweep_chunk(chunk, std::integral_constant<int, 0>{});
-    if (chunk + 1 >= c1) break;
-    __builtin_amdgcn_s_waitcnt(0x0F70);
+  const int n_chunks = (a.Nb + kProbeKBlocks - 1) / kProbeKBlocks;
+  const int per_range = (n_chunks + a.ranges - 1) / a.ranges;
+  const int c0 = min(n_chunks, range * per_range), c1 = min(n_chunks, c0 + per_range);   // my chunks
+  f32x16 s0[NT], s1[NT];
+  using Yes = std::true_type;
+  using No = std::false_type;
+  using Buf0 = std::integral_constant<int, 0>;
+  using Buf1 = std::integral_constant<int, 1>;
+  // the loads of a chunk have landed (everyone's), and nobody reads the other buffer any more
+  auto landed = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     __syncthreads();
-    store_rt(chunk);
-    if (chunk + 2 < c1) fetch_any(chunk + 2, 0);
-    sweep_chunk(chunk + 1, std::integral_constant<int, 1>{});
+  };
+  if (c0 < c1) {
+    fetch_any(c0, 0);
+    landed();
+    if (c0 + 1 < c1) fetch_any(c0 + 1, 1);
+    turn(c0, Buf0{}, Yes{}, No{}, s1, s0);       // the products of my first chunk
+    for (int chunk = c0;; chunk += 2) {
+      // s0: products of `chunk`, whose successor is in buffer 1
+      if (chunk + 1 >= c1) {
+        if (chunk > c0) store_rt(chunk - 1);
+        turn(chunk, Buf1{}, No{}, Yes{}, s0, s1);
+        store_rt(chunk);
+        break;
+      }
+      landed();
+      if (chunk > c0) store_rt(chunk - 1);
+      if (chunk + 2 < c1) fetch_any(chunk + 2, 0);
+      turn(chunk, Buf1{}, Yes{}, Yes{}, s0, s1);
+      if (chunk + 2 >= c1) {
+        store_rt(chunk);
+        turn(chunk + 1, Buf0{}, No{}, Yes{}, s1, s0);
+        store_rt(chunk + 1);
+        break;
+      }
+      landed();
+      store_rt(chunk);
+      if (chunk + 3 < c1) fetch_any(chunk + 3, 1);
+      turn(chunk + 1, Buf0{}, Yes{}, Yes{}, s1, s0);
+    }
   }
-  if (c0 < c1) store_rt(c1 - 1);
   // merge the two parities of each query; the pair (reference, denominator) of this wavefront's
   // share of the keys goes to the workspace (the kernel that follows merges the shares)
   {
@@ -294,23 +351,31 @@ __global__ __launch_bounds__(512, 4) void probe_kernel(ProbeArgs a) {   // (4 wa
     const double lall = __builtin_amdgcn_ldexp(lt, (int)fmaxf(Rr - Rall, -2000.f)) +
                         __builtin_amdgcn_ldexp(lo, (int)fmaxf(Ro - Rall, -2000.f));
     if (hl == 0) {
-      a.stat_r[((int64_t)item * 8 + wave) * 32 + n] = Rall;
-      a.stat_l[((int64_t)item * 8 + wave) * 32 + n] = lall;
+      a.stat_r[((int64_t)item * kProbePairs + pair) * 32 + n] = Rall;
+      a.stat_l[((int64_t)item * kProbePairs + pair) * 32 + n] = lall;
     }
   }
 }
 
-static size_t probe_rt_bytes(const Problem &pb) {
-  const size_t n_groups = (pb.Nb + kProbeQBlocks - 1) / kProbeQBlocks;
-  const size_t nb_pad = (pb.Nb + kProbeKBlocks - 1) / kProbeKBlocks * kProbeKBlocks;
-  return ((size_t)pb.n_slabs * n_groups * 4 * nb_pad * 32 * sizeof(float) + 255) & ~(size_t)255;
+static size_t probe_groups(const Problem &pb) {
+  return (size_t)pb.n_slabs * ((pb.Nb + kProbeQBlocks - 1) / kProbeQBlocks);
 }
-static size_t probe_items(const Problem &pb) {
-  return (size_t)pb.n_slabs * ((pb.Nb + kProbeQBlocks - 1) / kProbeQBlocks) * kProbeKeySplits;
+static size_t probe_rt_bytes(const Problem &pb) {
+  const size_t nb_pad = (pb.Nb + kProbePad - 1) / kProbePad * kProbePad;
+  return (probe_groups(pb) * kProbePairs * nb_pad * 32 * sizeof(float) + 255) & ~(size_t)255;
+}
+// wavefronts that write soft-max statistics, at most
+static size_t probe_stats(const Problem &pb) { return probe_groups(pb) * kProbeMaxRanges * kProbePairs; }
+// As many ranges as fill the chip, whose compute units hold three of these workgroups each, and at least two.  The whole mask with 2,
+// 3 and 4 ranges, us: 256 blocks of 128, d = 128: 1 head 47, -, 38; 2 heads 50, -, 41; 6 heads 66, -, 60; 8 heads 70, 69.4,
+// 70.6; 12 heads 89, 93, 90 (one range: 101); 512 blocks of 64, d = 64: 3 heads 94, -, 80.
+static int probe_ranges(const Problem &pb) {
+  const int n = (int)(768 / probe_groups(pb));
+  return n < 2 ? 2 : (n > kProbeMaxRanges ? kProbeMaxRanges : n);
 }
 size_t probe_workspace_bytes(const Problem &pb) {
   // block-row maxima, then the per-wavefront soft-max statistics (fp64 denominators first)
-  return probe_rt_bytes(pb) + probe_items(pb) * 8 * 32 * (sizeof(double) + sizeof(float));
+  return probe_rt_bytes(pb) + probe_stats(pb) * 32 * (sizeof(double) + sizeof(float));
 }
 
 static void fill_probe_args(const Problem &pb, const void *q, const void *k, float *p_imp,
@@ -320,9 +385,12 @@ static void fill_probe_args(const Problem &pb, const void *q, const void *k, flo
   unsigned char *ws = reinterpret_cast<unsigned char *>(workspace);
   a->rt = reinterpret_cast<float *>(ws);
   a->stat_l = reinterpret_cast<double *>(ws + probe_rt_bytes(pb));
-  a->stat_r = reinterpret_cast<float *>(ws + probe_rt_bytes(pb) + probe_items(pb) * 8 * 32 * sizeof(double));
+  a->stat_r = reinterpret_cast<float *>(ws + probe_rt_bytes(pb) + probe_stats(pb) * 32 * sizeof(double));
   a->tq = pb.q; a->tk = pb.k;
   a->H = pb.H; a->L = pb.L; a->Nb = pb.Nb; a->n_slabs = pb.n_slabs; a->block = pb.block; a->ks = pb.ks;
+  a->ranges = probe_ranges(pb);
+  a->chunk_bytes = (int64_t)kProbeKBlocks * pb.block * pb.k.sL * 2;
+  a->n_full_chunks = a->chunk_bytes >= ((int64_t)1 << 32) ? 0 : pb.L / (kProbeKBlocks * pb.block);
   a->c2 = pb.scale * 1.44269504088896340736f;
   a->rest = (float)(((double)pb.scale * 1.44269504088896340736 - (double)a->c2) * 0.69314718055994530942);
   a->s_bound = fminf(kMaxExactExponent / a->c2, 3.0e38f);   // (finite: the -inf of a tile without keys is bounded too)
@@ -336,22 +404,11 @@ hipError_t launch_probe(const Problem &pb, const void *q, const void *k, void *w
                         hipStream_t st, const uint8_t *table) {
   ProbeArgs a;
   fill_probe_args(pb, q, k, nullptr, workspace, table, &a);
-  const int grid = xcd_grid((int)probe_items(pb));
-  const int lds = 2 * kProbeKBlocks * 16 * pb.d * 2;   // two chunks of sampled key rows
-  if (pb.d == 128) {
-    const void *fn = table ? reinterpret_cast<const void *>(&probe_kernel<128, true>)
-                           : reinterpret_cast<const void *>(&probe_kernel<128, false>);
-    hipError_t e = set_dynamic_lds_once(fn, 2 * kProbeKBlocks * 16 * 128 * 2);
-    if (e != hipSuccess) return e;
-  }
-  if (pb.d == 128 && table)
-    hipLaunchKernelGGL((probe_kernel<128, true>), dim3(grid), dim3(512), lds, st, a);
-  else if (pb.d == 128)
-    hipLaunchKernelGGL((probe_kernel<128, false>), dim3(grid), dim3(512), lds, st, a);
-  else if (table)
-    hipLaunchKernelGGL((probe_kernel<64, true>), dim3(grid), dim3(512), lds, st, a);
-  else
-    hipLaunchKernelGGL((probe_kernel<64, false>), dim3(grid), dim3(512), lds, st, a);
+  const dim3 grid(xcd_grid((int)probe_groups(pb) * a.ranges)), block(64 * kProbePairs);
+  if (pb.d == 128 && table) hipLaunchKernelGGL((probe_kernel<128, true>), grid, block, 0, st, a);
+  else if (pb.d == 128) hipLaunchKernelGGL((probe_kernel<128, false>), grid, block, 0, st, a);
+  else if (table) hipLaunchKernelGGL((probe_kernel<64, true>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((probe_kernel<64, false>), grid, block, 0, st, a);
   return hipGetLastError();
 }
 
@@ -605,31 +662,30 @@ __global__ __launch_bounds__(256) void finish_rule_kernel(ProbeArgs a, RuleArgs 
   if (row >= ra.n_rows) return;
   const int slab = row / a.Nb, i = row - slab * a.Nb;
   const int n_groups = (a.Nb + kProbeQBlocks - 1) / kProbeQBlocks;
-  const int nb_pad = (a.Nb + kProbeKBlocks - 1) / kProbeKBlocks * kProbeKBlocks;
+  const int nb_pad = (a.Nb + kProbePad - 1) / kProbePad * kProbePad;
   const int work = slab * n_groups + i / kProbeQBlocks;      // the query group that swept this block
   const int w = i % kProbeQBlocks, pr_ = w >> 1, qb = w & 1;  // its pair and position in the pair
-  const float *rtq = a.rt + ((int64_t)work * 4 + pr_) * nb_pad * 32 + qb * 16;
-  // merge the shares: wavefronts pr_ and pr_ + 4 of every key range
+  const float *rtq = a.rt + ((int64_t)work * kProbePairs + pr_) * nb_pad * 32 + qb * 16;
+  // merge the shares: wavefront pr_ of every key range
   // (the denominator is summed in fp64; its reciprocal is kept in two fp32 halves)
   // Lane u < 16 merges the shares of sampled row u; the 16 results are then handed to every
   // lane through scalar registers (all lanes doing all 16 rows cost 16 fp64 divisions a lane).
   float my_r = -INFINITY, my_inv = 0.f, my_inv_lo = 0.f, my_inv_rest = 0.f;
   {
     const int u = lane & 15;
-    float pr[2 * kProbeKeySplits];
-    double pl[2 * kProbeKeySplits];
+    float pr[kProbeMaxRanges];
+    double pl[kProbeMaxRanges];
 #pragma unroll
-    for (int sp = 0; sp < kProbeKeySplits; ++sp)
-#pragma unroll
-      for (int hf = 0; hf < 2; ++hf) {
-        const int64_t at = (((int64_t)work * kProbeKeySplits + sp) * 8 + pr_ + 4 * hf) * 32 + qb * 16 + u;
-        pr[2 * sp + hf] = a.stat_r[at];
-        pl[2 * sp + hf] = a.stat_l[at];
-        my_r = fmaxf(my_r, pr[2 * sp + hf]);
-      }
+    for (int x = 0; x < kProbeMaxRanges; ++x) {
+      const int64_t at = (((int64_t)work * a.ranges + min(x, a.ranges - 1)) * kProbePairs + pr_) * 32 + qb * 16 + u;
+      pr[x] = a.stat_r[at];
+      pl[x] = a.stat_l[at];
+      my_r = fmaxf(my_r, pr[x]);
+    }
     double l = 0.0;
 #pragma unroll
-    for (int x = 0; x < 2 * kProbeKeySplits; ++x) l += __builtin_amdgcn_ldexp(pl[x], (int)fmaxf(pr[x] - my_r, -2000.f));
+    for (int x = 0; x < kProbeMaxRanges; ++x)
+      if (x < a.ranges) l += __builtin_amdgcn_ldexp(pl[x], (int)fmaxf(pr[x] - my_r, -2000.f));
     const double inv = 1.0 / l;
     my_inv = (float)inv;
     my_inv_lo = (float)(inv - (double)my_inv);

@@ -105,6 +105,13 @@ __device__ __forceinline__ void lds_dma16_sv(const void *uniform_base, uint32_t 
                : "v"(lane_off), "s"(bu), "s"((uint32_t)__builtin_amdgcn_readfirstlane(lds_byte_addr)) : "memory");
 #endif
 }
+// The same from a 64-bit address per lane.
+__device__ __forceinline__ void lds_dma16_v(const void *lane_addr, uint32_t lds_byte_addr) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+               : : "v"(lane_addr), "s"((uint32_t)__builtin_amdgcn_readfirstlane(lds_byte_addr)) : "memory");
+#endif
+}
 // The same for several loads in a row that share M0 and the base: lds_dma_begin sets M0 and returns the scalar copy of the
 // base, lds_dma16_next<X> loads with X bytes added to the global AND to the LDS address (X < 4096).  Nothing else may write
 // M0 in between (tests/test_asm_hazards.py looks).

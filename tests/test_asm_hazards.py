@@ -120,13 +120,14 @@ def assembly(tmp_path_factory):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     running = {src: subprocess.Popen([hipcc, *build.HIPCC_FLAGS, "-S", "--cuda-device-only",
                                       os.path.join(build.CSRC, src), "-o", str(out / src)],
-                                     stderr=subprocess.DEVNULL) for src in ("asa_bwd.hip", "asa_fwd.hip")}
+                                     stderr=subprocess.DEVNULL) for src in ("asa_bwd.hip", "asa_fwd.hip", "asa_mask.hip")}
     for src, p in running.items():
         assert p.wait() == 0, src
     return {src: (out / src).read_text() for src in running}
 
 
-@pytest.mark.parametrize("src,kinds", [("asa_bwd.hip", ("mfma", "load")), ("asa_fwd.hip", ("mfma", "load"))])
+@pytest.mark.parametrize("src,kinds", [("asa_bwd.hip", ("mfma", "load")), ("asa_fwd.hip", ("mfma", "load")),
+                                       ("asa_mask.hip", ("load",))])
 def test_wait_states_around_written_out_instructions(assembly, src, kinds):
     total = dict.fromkeys(("mfma", "load"), 0)
     for name, lines in _functions(assembly[src]):

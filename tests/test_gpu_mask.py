@@ -240,6 +240,19 @@ def test_build_mask_ragged_and_sampled(grid, n_text, d, block, ks, offs_seed):
     _check_build(p, qb, kb, offs, f"L={w.L}")
 
 
+@pytest.mark.parametrize("Nb,tail,d,block,ks", [
+    (1, 5, 64, 64, 16), (3, 64, 128, 64, 16), (4, 1, 128, 64, 16), (5, 64, 64, 64, 7), (8, 33, 128, 128, 16),
+    (9, 128, 64, 128, 16), (13, 2, 128, 128, 5), (16, 64, 64, 64, 16), (17, 100, 128, 128, 16), (25, 64, 64, 64, 1)])
+def test_importance_map_at_the_edges_of_its_chunks(Nb, tail, d, block, ks):
+    """The probe takes the key blocks in chunks of four and in two ranges: ranges without a chunk, of one chunk, of
+    an odd and an even number of them, a last chunk that is part empty and a last block of `tail` tokens."""
+    L = (Nb - 1) * block + tail
+    rng = np.random.default_rng(Nb)
+    qb, kb = (synth.f32_to_bf16_bits(rng.standard_normal((1, 2, L, d), dtype=np.float32) * s) for s in (1.0, 2.0))
+    p = binding.Params(B=1, H=2, L=L, d=d, block=block, k_samples=ks, tau=0.9)
+    _check_build(p, qb, kb, synth.default_sample_offsets(block, ks), f"Nb={Nb} tail={tail} d={d}")
+
+
 def test_build_mask_noise_only_inputs_variable_m():
     # nearly flat scores: many rows, m varies, thresholds are crossed with small margins
     shape = (1, 4, 64 * 48, 64)
