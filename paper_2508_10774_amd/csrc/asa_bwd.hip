@@ -137,8 +137,9 @@ struct BwdCfg {
 // there is one workgroup barrier per tile.  A wavefront issues one instruction every ~5 cycles, so
 // the number of instructions matters as much as the MFMAs: four LDS stages with the loop unrolled
 // by four make every LDS address a register plus an immediate; -Delta is the initial value of the
-// dP accumulator; a tile that reaches past the last row uses a second set of copy offsets instead
-// of a branch.
+// dP accumulator; the copies take their addresses from RunningTileCopy (dK / dV at block 128 / d 128 231 -> 210
+// instructions per tile; whole backward at block 64 / d 128, 8 heads of 17 776 tokens, 990 -> 970 us, block 128 / d 128,
+// 12 heads of 32 760, 4.90 -> 4.86 ms, d 64 within 0.5 %).  Operands two at a time, with one wait for both, change nothing.
 // Registers: dK / dV at d = 128 (and dQ at block 64 / d 128) run one wavefront per SIMD with the
 // gradients in accumulation registers (the instruction is written out for that: the compiler would
 // move S and P there as well, at a vector instruction per register and tile), the others two.
@@ -222,9 +223,21 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, int workgroup, uint32_
     for (int i = 0; i < 16; ++i) acc[dm][i] = 0.f;
 
   using Copy = TrTileCopy<C::kST, D, C::kWaves>;
+  // (at block 128 / d 128 the 256 registers of dQ are full without the running copies' offsets: the walk for Delta 2065
+  // -> 2156 us at 4 heads of 32 760 tokens)
+  constexpr bool kRun = !GT && !(BLK == 128 && D == 128);
+  using RunCopy = RunningTileCopy<C::kST, D, C::kWaves>;
   Copy copy_k, copy_v;
-  copy_k.init(wave, lane, a.tk.sL, a.L);
-  copy_v.init(wave, lane, a.tv.sL, a.L);
+  RunCopy run_k, run_v;
+  LastTileWatch watch;
+  if constexpr (!kRun) {
+    copy_k.init(wave, lane, a.tk.sL, a.L);
+    copy_v.init(wave, lane, a.tv.sL, a.L);
+  } else {
+    run_k.init(wave, lane, ks, a.tk.sL, a.L);
+    run_v.init(wave, lane, vs, a.tv.sL, a.L);
+    watch.init(RunCopy::last_row0(a.L));
+  }
   constexpr int kI = Copy::kInstr;
   constexpr int kBatch = 2 * kI;                // copy instructions per tile and wavefront
   const int last_row0 = Copy::last_row0(a.L);
@@ -269,6 +282,13 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, int workgroup, uint32_
       } else {
         key_c += C::kST;
       }
+    } else if constexpr (part == 1 && kRun) {
+      if constexpr (new_block) run_k.block(key_c);
+      else run_k.step();
+    } else if constexpr (kRun) {
+      if constexpr (new_block) run_v.block(key_c);
+      else run_v.step();
+      watch.tile(key_c, a.L, run_k, run_v);
     } else if constexpr (part == 1) {
       base_k = reinterpret_cast<const char *>(ks) + (int64_t)min(key_c, last_row0) * (a.tk.sL * 2);
       last_tile = key_c >= last_row0;
@@ -278,17 +298,26 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, int workgroup, uint32_
       if (GT) base_v = pooled_c ? reinterpret_cast<const char *>(vgs) + (int64_t)key_c * (D * 2) : base_v;
     }
   };
-  auto copy_one = [&](int i, uint32_t st) __attribute__((always_inline)) {
-    if (GT) {
-      const int x = i < kI ? i : i - kI;
+  uint64_t started = 0;
+  auto copy_one = [&](auto i_tag, uint32_t st) __attribute__((always_inline)) {
+    constexpr int i = decltype(i_tag)::value, x = i < kI ? i : i - kI;
+    if constexpr (!kRun) {
       const Copy &own = i < kI ? copy_k : copy_v;
-      const uint32_t off = pooled_c ? copy_p.off[x] : (last_tile ? own.off_last[x] : own.off[x]);
+      const uint32_t off = GT && pooled_c ? copy_p.off[x] : (last_tile ? own.off_last[x] : own.off[x]);
       lds_dma16_sv(i < kI ? base_k : base_v, off, st + (i < kI ? 0 : kVOff) + own.lds0 + x * 1024);
-    } else if (i < kI) {
-      copy_k.issue_one(i, st, base_k, last_tile);
+    } else if constexpr (i < kI) {
+      if constexpr (x == 0) started = run_k.start(st);
+      run_k.template load<x>(started);
     } else {
-      copy_v.issue_one(i - kI, st + kVOff, base_v, last_tile);
+      if constexpr (x == 0) started = run_v.start(st + kVOff);
+      run_v.template load<x>(started);
     }
+  };
+  auto copy_some = [&](auto from_tag, auto n_tag, uint32_t st) __attribute__((always_inline)) {
+    constexpr int from = decltype(from_tag)::value;
+    [&]<int... I>(std::integer_sequence<int, I...>) __attribute__((always_inline)) {
+      (copy_one(std::integral_constant<int, from + I>{}, st), ...);
+    }(std::make_integer_sequence<int, decltype(n_tag)::value>{});
   };
   auto wait_copies = [&](auto n_tag) __attribute__((always_inline)) {
     constexpr int N = decltype(n_tag)::value;    // at most N instructions still in flight
@@ -414,9 +443,7 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, int workgroup, uint32_
         // copies of tile t + kStages - 1, spread over the slots behind the barrier
         if constexpr (x >= kBar) {
           constexpr int i0 = (x - kBar) * kBatch / (kN - kBar), i1 = (x - kBar + 1) * kBatch / (kN - kBar);
-#pragma unroll
-          for (int i = i0; i < i1; ++i)
-            copy_one(i, smem_addr + ((U + 3) & 3) * kStage);
+          copy_some(std::integral_constant<int, i0>{}, std::integral_constant<int, i1 - i0>{}, smem_addr + ((U + 3) & 3) * kStage);
         }
         if constexpr (x == kN - 1) next_current(std::bool_constant<(U + 1) % C::kSub == 0>{});
         __builtin_amdgcn_sched_barrier(0);
@@ -432,16 +459,18 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, int workgroup, uint32_
     const uint32_t first_stage = odd ? 2u : 0u, first_off = first_stage * kStage;
     // tiles 0 .. kStages - 2
     for (int t = 0; t < C::kStages - 1; ++t) {
+      auto all_parts = [&](auto new_block_tag) __attribute__((always_inline)) {
+        next_tile(std::integral_constant<int, 0>{}, new_block_tag);
+        next_tile(std::integral_constant<int, 1>{}, new_block_tag);
+        next_tile(std::integral_constant<int, 2>{}, new_block_tag);
+      };
       if (t % C::kSub == 0) {
         fetch_entry();
-        next_tile(std::integral_constant<int, 0>{}, std::true_type{});
+        all_parts(std::true_type{});
       } else {
-        next_tile(std::integral_constant<int, 0>{}, std::false_type{});
+        all_parts(std::false_type{});
       }
-      next_tile(std::integral_constant<int, 1>{}, std::false_type{});
-      next_tile(std::integral_constant<int, 2>{}, std::false_type{});
-#pragma unroll
-      for (int i = 0; i < kBatch; ++i) copy_one(i, smem_addr + ((t + first_stage) & 3u) * kStage);
+      copy_some(std::integral_constant<int, 0>{}, std::integral_constant<int, kBatch>{}, smem_addr + ((t + first_stage) & 3u) * kStage);
     }
     if ((C::kStages - 1) % C::kSub == 0) fetch_entry();
     fetch_current();
@@ -559,12 +588,14 @@ __device__ __forceinline__ void dkv_walk(const BwdArgs &a, int workgroup, uint32
 #pragma unroll
     for (int i = 0; i < 16; ++i) kacc[dm][i] = vacc[dm][i] = 0.f;
 
-  TrTileCopy<C::kST, D, C::kWaves> copy_q, copy_g;
-  copy_q.init(wave, lane, a.tq.sL, a.L);
-  copy_g.init(wave, lane, a.to.sL, a.L);
-  constexpr int kI = TrTileCopy<C::kST, D, C::kWaves>::kInstr;
+  using Copy = RunningTileCopy<C::kST, D, C::kWaves>;
+  Copy copy_q, copy_g;
+  copy_q.init(wave, lane, qs, a.tq.sL, a.L);
+  copy_g.init(wave, lane, gs, a.to.sL, a.L);
+  constexpr int kI = Copy::kInstr;
   constexpr int kBatch = 2 * kI + 1;            // copy instructions per tile and wavefront
-  const int last_row0 = TrTileCopy<C::kST, D, C::kWaves>::last_row0(a.L);
+  LastTileWatch last_tile;
+  last_tile.init(Copy::last_row0(a.L));
 
   // (stages are absolute LDS addresses, multiples of 256: the XORs below touch lower bits only)
   // row-wise A fragments (S = Q K^T, dP = dO V^T): row kappa(n) of the 32 queries, 16-byte chunk
@@ -592,8 +623,7 @@ __device__ __forceinline__ void dkv_walk(const BwdArgs &a, int workgroup, uint32
   // addresses.  Tiles past the end repeat the last block: the number of copies in flight stays the
   // same and their data is not used.
   int entry_v = 0, entry_at = 0, q0 = 0;
-  bool last_tile = false;
-  const char *base_q = nullptr, *base_g = nullptr, *base_st = nullptr;
+  const char *base_st = nullptr;
   auto fetch_entry = [&]() __attribute__((always_inline)) {      // (read well before it is used)
     entry_v = rows[entry_at < n_blocks ? entry_at : n_blocks - 1];
     ++entry_at;
@@ -603,19 +633,40 @@ __device__ __forceinline__ void dkv_walk(const BwdArgs &a, int workgroup, uint32
     constexpr int part = decltype(part_tag)::value;
     constexpr bool new_block = decltype(new_block_tag)::value;
     if constexpr (part == 0) {
-      q0 = new_block ? __builtin_amdgcn_readfirstlane(entry_v) * BLK : q0 + C::kST;
-      base_st = reinterpret_cast<const char *>(stat_s + q0);
+      if constexpr (new_block) {
+        q0 = __builtin_amdgcn_readfirstlane(entry_v) * BLK;
+        base_st = reinterpret_cast<const char *>(stat_s) + (uint32_t)q0 * 4u;
+      } else {
+        q0 += C::kST;
+        base_st += C::kST * 4;
+      }
     } else if constexpr (part == 1) {
-      base_q = reinterpret_cast<const char *>(qs) + (int64_t)min(q0, last_row0) * (a.tq.sL * 2);
-      last_tile = q0 >= last_row0;
+      if constexpr (new_block) copy_q.block(q0);
+      else copy_q.step();
     } else {
-      base_g = reinterpret_cast<const char *>(gs) + (int64_t)min(q0, last_row0) * (a.to.sL * 2);
+      if constexpr (new_block) copy_g.block(q0);
+      else copy_g.step();
+      last_tile.tile(q0, a.L, copy_q, copy_g);
     }
   };
-  auto copy_one = [&](int i, uint32_t st) __attribute__((always_inline)) {
-    if (i < kI) copy_q.issue_one(i, st, base_q, last_tile);
-    else if (i < 2 * kI) copy_g.issue_one(i - kI, st + kGOff, base_g, last_tile);
-    else lds_dma4_sv(base_st, stat_off, st + kStatOff);
+  uint64_t started = 0;
+  auto copy_one = [&](auto i_tag, uint32_t st) __attribute__((always_inline)) {
+    constexpr int i = decltype(i_tag)::value;
+    if constexpr (i < kI) {
+      if constexpr (i == 0) started = copy_q.start(st);
+      copy_q.template load<i>(started);
+    } else if constexpr (i < 2 * kI) {
+      if constexpr (i == kI) started = copy_g.start(st + kGOff);
+      copy_g.template load<i - kI>(started);
+    } else {
+      lds_dma4_sv(base_st, stat_off, st + kStatOff);
+    }
+  };
+  auto copy_some = [&](auto from_tag, auto n_tag, uint32_t st) __attribute__((always_inline)) {
+    constexpr int from = decltype(from_tag)::value;
+    [&]<int... I>(std::integer_sequence<int, I...>) __attribute__((always_inline)) {
+      (copy_one(std::integral_constant<int, from + I>{}, st), ...);
+    }(std::make_integer_sequence<int, decltype(n_tag)::value>{});
   };
   auto wait_copies = [&](auto n_tag) __attribute__((always_inline)) {
     constexpr int N = decltype(n_tag)::value;    // at most N instructions still in flight
@@ -736,9 +787,7 @@ __device__ __forceinline__ void dkv_walk(const BwdArgs &a, int workgroup, uint32
         if constexpr (f == 0 && kNextNewBlock) fetch_entry();
         // copies of tile t + kStages - 1, spread over the slots
         constexpr int i0 = f * kBatch / kNB, i1 = (f + 1) * kBatch / kNB;
-#pragma unroll
-        for (int i = i0; i < i1; ++i)
-          copy_one(i, smem_addr + ((U + 3) & 3) * kStage);
+        copy_some(std::integral_constant<int, i0>{}, std::integral_constant<int, i1 - i0>{}, smem_addr + ((U + 3) & 3) * kStage);
         __builtin_amdgcn_sched_barrier(0);
       }(), ...);
     }(std::make_integer_sequence<int, kNB>{});
@@ -752,16 +801,18 @@ __device__ __forceinline__ void dkv_walk(const BwdArgs &a, int workgroup, uint32
     const uint32_t first_stage = odd ? 2u : 0u, first_off = first_stage * kStage;
     // tiles 0 .. kStages - 2
     for (int t = 0; t < C::kStages - 1; ++t) {
+      auto all_parts = [&](auto new_block_tag) __attribute__((always_inline)) {
+        next_tile(std::integral_constant<int, 0>{}, new_block_tag);
+        next_tile(std::integral_constant<int, 1>{}, new_block_tag);
+        next_tile(std::integral_constant<int, 2>{}, new_block_tag);
+      };
       if (t % C::kSub == 0) {
         fetch_entry();
-        next_tile(std::integral_constant<int, 0>{}, std::true_type{});
+        all_parts(std::true_type{});
       } else {
-        next_tile(std::integral_constant<int, 0>{}, std::false_type{});
+        all_parts(std::false_type{});
       }
-      next_tile(std::integral_constant<int, 1>{}, std::false_type{});
-      next_tile(std::integral_constant<int, 2>{}, std::false_type{});
-#pragma unroll
-      for (int i = 0; i < kBatch; ++i) copy_one(i, smem_addr + ((t + first_stage) & 3u) * kStage);
+      copy_some(std::integral_constant<int, 0>{}, std::integral_constant<int, kBatch>{}, smem_addr + ((t + first_stage) & 3u) * kStage);
     }
     if ((C::kStages - 1) % C::kSub == 0) fetch_entry();
     wait_copies(std::integral_constant<int, (C::kStages - 3) * kBatch>{});   // tiles 0 and 1

@@ -271,4 +271,68 @@ struct TrTileCopy {
   }
 };
 
+// The same for a walk that goes tile by tile through blocks, with as few instructions per tile as it takes (a wavefront
+// issues one per ~5 cycles, scalar ones too): the base runs along by one addition, a wavefront's kInstr loads of a tile
+// have M0 and the base in common (start / load<i>), and the tile that holds row L - 1 changes the per-lane offsets where it
+// is entered and left, in a branch that is otherwise not taken (watch), instead of choosing between two sets each time.
+// Load i adds 1024 i to the LDS and to the global address alike: the per-lane offsets are less by that.  (Not below zero: a load's
+// rows are 1024 / (2 D) apart from the next one's, at 2 D bytes or more each.  In the tile that holds the last row they
+// come closer: there the base is less by 1024 (kInstr - 1) instead.)
+template <int ROWS, int D, int WAVES>
+struct RunningTileCopy {
+  static constexpr int kChunks = D / 8;                       // 16-byte chunks per row
+  static constexpr int kInstr = ROWS * kChunks / 64 / WAVES;  // wave instructions per copy
+  static_assert(kInstr * 64 * WAVES == ROWS * kChunks && kInstr * 1024 <= 4096, "whole instructions per wavefront, 12-bit distances");
+  uint32_t off[kInstr], to_last[kInstr];
+  uint32_t lds0;                                              // LDS distance of my first instruction
+  uint32_t pitch;
+  const char *slab, *base;                                    // (wave-uniform)
+
+  static __device__ __forceinline__ int last_row0(int L) { return (L - 1) / ROWS * ROWS; }
+  __device__ __forceinline__ void init(int wave, int lane, const void *slab_rows, int64_t sL, int L) {
+    slab = base = reinterpret_cast<const char *>(slab_rows);
+    pitch = (uint32_t)(sL * 2);
+    lds0 = (uint32_t)(wave * kInstr * 1024);
+#pragma unroll
+    for (int i = 0; i < kInstr; ++i) {
+      const int row = (wave * kInstr + i) * (64 / kChunks) + lane / kChunks;
+      const int row_c = min(row, L - 1 - last_row0(L));
+      off[i] = (uint32_t)row * pitch + (uint32_t)(((lane % kChunks) ^ t_swz<D>(row)) * 16) - 1024u * i;
+      to_last[i] = (uint32_t)(row_c - row) * pitch + 1024u * (kInstr - 1);
+    }
+  }
+  __device__ __forceinline__ void block(int row0) { base = slab + (uint64_t)(uint32_t)row0 * pitch; }
+  __device__ __forceinline__ void step() { base += (uint32_t)ROWS * pitch; }
+  // the tile that holds row L - 1, or one wholly past it, which is replaced by the former
+  __device__ __forceinline__ void at_last(int L) { base = slab + (uint64_t)(uint32_t)last_row0(L) * pitch - 1024 * (kInstr - 1); }
+  __device__ __forceinline__ void turn(bool into_last) {
+#pragma unroll
+    for (int i = 0; i < kInstr; ++i) off[i] += into_last ? to_last[i] : 0u - to_last[i];
+  }
+  __device__ __forceinline__ uint64_t start(uint32_t stage) const { return lds_dma_begin(base, stage + lds0); }
+  template <int I>
+  __device__ __forceinline__ void load(uint64_t started) const { lds_dma16_next<I * 1024>(started, off[I]); }
+};
+// Which branch of two such walks a tile takes.  watch: a tile whose first row is at or past it has something to do.
+struct LastTileWatch {
+  int last_row0, watch;
+  bool inside;
+  __device__ __forceinline__ void init(int last) { last_row0 = watch = last; inside = false; }
+  template <typename C>
+  __device__ __forceinline__ void tile(int row0, int L, C &x, C &y) {
+    if (__builtin_expect(row0 < watch, 1)) return;
+    const bool now = row0 >= last_row0;
+    if (now != inside) {
+      x.turn(now);
+      y.turn(now);
+      inside = now;
+      watch = now ? 0 : last_row0;
+    }
+    if (now) {
+      x.at_last(L);
+      y.at_last(L);
+    }
+  }
+};
+
 }  // namespace asa
