@@ -84,6 +84,34 @@ def test_the_same_with_pooled_tokens():
         assert torch.equal(a[:, :2].view(torch.int16), b[:, :2].view(torch.int16)), name
 
 
+@pytest.mark.parametrize("block,d,heads,text", [
+    (64, 64, 43, 1), (64, 64, 44, 64 * NB), (64, 128, 47, 70), (128, 64, 50, 300), (128, 128, 44, 129), (128, 128, 64, 10 ** 4)])
+def test_rows_of_a_prefix_start_early(block, d, heads, text):
+    """With prefix blocks some of dQ's workgroups come before the rest of dK / dV's (more than 256 lists): every one
+    runs once, whatever the number of prefix blocks, so the gradients are those of the two launches that dQ over Q takes."""
+    L = (NB - 1) * block + TAIL
+    print(f"case block={block} d={d} heads={heads} text={text}", flush=True)
+    q, k, v, g = (util.dev_bf16(synth.make_iid((1, heads, L, d), block + d, s)) for s in range(4))
+    p = binding.Params(B=1, H=heads, L=L, d=d, block=block, n_prefix_dense=min(text, L))
+    mask = synth.random_block_mask(NB, 0.3, seed=text, slabs=heads).reshape(heads, NB, NB)
+    first = -(-p.n_prefix_dense // block)
+    mask[:, :first] = 1
+    mask[:, :, :first] = 1
+    bufs = util.lists_from_mask(p, mask)
+    lists = [bufs[x] for x in ("row_ptr", "col_idx", "col_ptr", "row_idx")]
+    o, lse, o_lo = util.run_fwd(p, q, k, v, bufs, with_lo=True)
+    ws = binding.alloc_workspace(binding.asa_bwd_workspace_bytes(p))
+    out = []
+    for over in (False, True):
+        qq = q.clone()
+        dq, dk, dv = qq if over else torch.full_like(q, float("nan")), torch.full_like(k, float("nan")), torch.full_like(v, float("nan"))
+        binding.asa_attn_bwd(p, qq, k, v, o, g, lse, *lists, dq, dk, dv, ws, o_lo=o_lo)
+        out.append([x.view(torch.int16) for x in (dq, dk, dv)])
+    for a, b, name in zip(*out, ("dQ", "dK", "dV")):
+        assert torch.equal(a, b), name
+        assert torch.isfinite(a.view(torch.bfloat16).float()).all(), name
+
+
 @pytest.mark.parametrize("with_lo", [True, False])
 @pytest.mark.parametrize("block,d", list(LINE))
 @pytest.mark.parametrize("pooled", [False, True])
