@@ -949,7 +949,8 @@ __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dkv_
 // The rows and columns of always-kept prefix blocks are as long as the sequence, and a workgroup takes one alone: those of dQ
 // start right behind those of dK / dV (`lead` of each XCD's share) and not behind all of dK / dV.  Same bits; us: block 64, 17 776 tokens of
 // which 226 are text, d 64: 1 head 313 -> 244, 3 heads 330 -> 309, d 128: 3 heads 495 -> 442; 4 heads of 4 276 85 -> 68; block 128 /
-// d 128, 3 heads of 12 780, 300 text, 346 -> 295.  (All of dQ between dK / dV, one by one: 0.96-0.98x where there is no prefix.)
+// d 128, 3 heads of 12 780, 300 text, 346 -> 295.  Where such a row is not the last to end (prefix_rows_last) it costs 1 %. (All of dQ between dK / dV, one by
+// one: 0.96-0.98x where there is no prefix.)
 template <int BLK, int D, bool GT>
 __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dkv_dq_kernel(BwdArgs a) {
   extern __shared__ __align__(1024) unsigned char smem[];
@@ -1007,6 +1008,9 @@ static bool overlap(const Problem &pb, const void *x, const TensorView &tx, cons
   return x <= static_cast<const void *>(last(y, ty)) && y <= static_cast<const void *>(last(x, tx));
 }
 
+// workgroups of dK / dV on the chip
+static int bwd_resident(int block, int d) { return block == 64 && d == 64 ? 1024 : (block == 128 && d == 128 ? 256 : 512); }
+
 // dq_over_inputs: dQ is written into memory that dK / dV reads (asa.h allows it): dK / dV must have ended before
 template <int BLK, int D>
 static hipError_t launch_bwd_t(const BwdArgs &a, const BwdArgs *pooled_launch, bool dq_over_inputs, hipStream_t st) {
@@ -1031,7 +1035,7 @@ static hipError_t launch_bwd_t(const BwdArgs &a, const BwdArgs *pooled_launch, b
   }
   const int grid = xcd_grid(a.n_slabs * a.Nb);
   // One launch or two (see dkv_dq_kernel): the line is where the gain of filling the last round has gone.
-  const int resident = BLK == 64 && D == 64 ? 1024 : (BLK == 128 && D == 128 ? 256 : 512);
+  const int resident = bwd_resident(BLK, D);
   const bool together = !dq_over_inputs && a.n_slabs * a.Nb <= (BLK == D ? 3 : 6) * resident;
   hipError_t e = hipSuccess;
   if (a.ndelta_out) {
@@ -1132,7 +1136,8 @@ hipError_t launch_bwd(const Problem &pb, const void *q, const void *k, const voi
       if (e != hipSuccess) return e;
       a.order = order;
       a.order_q = order_q;
-      a.lead = std::min((pb.n_slabs + kNumXcd - 1) / kNumXcd * pb.n_prefix_blocks, (total + kNumXcd - 1) / kNumXcd);
+      if (prefix_rows_last(pb, bwd_resident(pb.block, pb.d), 0))
+        a.lead = std::min((pb.n_slabs + kNumXcd - 1) / kNumXcd * pb.n_prefix_blocks, (total + kNumXcd - 1) / kNumXcd);
     }
   }
   a.Lk = pb.L; a.Nbk = pb.Nb;

@@ -959,12 +959,12 @@ __global__ __launch_bounds__(BLK * 4, (BLK == 64 && D == 64) ? 2 : 1) void fwd_p
 // wavefront's own speed counts: few workgroups, or shapes whose lock-step workgroup leaves the SIMDs
 // idle (launch_fwd_t has the figures).
 // ---------------------------------------------------------------------------------------
-template <int BLK, int D>
+template <int BLK, int D, int KS>
 struct PipeCfg {
-  static constexpr int kWaves = BLK / 32;
-  static constexpr int kThreads = kWaves * 64;
+  static constexpr int kWaves = BLK / 32;              // of a group
+  static constexpr int kThreads = kWaves * 64;         // of a group
   static constexpr int kST = 32;                       // keys per tile
-  static constexpr int kSub = BLK / kST;
+  static constexpr int kSub = BLK / kST / KS;          // tiles of a block that a group takes
   static constexpr int kStages = 4;
   static constexpr int kTile = kST * D * 2;            // bytes of one row tile
   static constexpr int kLds = 2 * kStages * kTile;     // K stages, then V stages
@@ -972,9 +972,14 @@ struct PipeCfg {
 };
 
 // GT: with the pooled (global) tokens of ASA_G appended to every query block's list
-template <int BLK, int D, bool GT>
-__global__ __launch_bounds__(BLK * 2, (PipeCfg<BLK, D>::kWavesPerSimd)) void fwd_pipe_kernel(FwdArgs a) {
-  using C = PipeCfg<BLK, D>;
+// KS: groups of wavefronts that share a row.  Two groups walk the same list, each with tiles in LDS of its own and half
+// of every block's keys (so both have as many tiles, and one list of any length is two of half the length); their O,
+// maxima and sums are put together at the end.  A row takes half as long, and a compute unit holds half as many rows: pipe_in_two says
+// where that pays.  (Two rows to such a workgroup where rows are short, so that only the long ones are split: the groups
+// wait for one another at every barrier, 10-18 % slower than two workgroups.)
+template <int BLK, int D, bool GT, int KS>
+__global__ __launch_bounds__(BLK * 2 * KS, (PipeCfg<BLK, D, KS>::kWavesPerSimd)) void fwd_pipe_kernel(FwdArgs a) {
+  using C = PipeCfg<BLK, D, KS>;
   extern __shared__ __align__(1024) unsigned char smem[];
   __shared__ int cols[kMaxNb];
   constexpr int kStage = C::kTile, kVBase = C::kStages * C::kTile;
@@ -985,7 +990,8 @@ __global__ __launch_bounds__(BLK * 2, (PipeCfg<BLK, D>::kWavesPerSimd)) void fwd
   const int work = a.order ? a.order[slot] : slot;
   const int slab = work / a.Nb;
   const int qb = work - slab * a.Nb;
-  const int tid = threadIdx.x;
+  const int group = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / C::kThreads);
+  const int tid = KS == 1 ? threadIdx.x : threadIdx.x % C::kThreads;      // in the group
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63, hl = lane >> 5, n = lane & 31;
 
@@ -998,7 +1004,7 @@ __global__ __launch_bounds__(BLK * 2, (PipeCfg<BLK, D>::kWavesPerSimd)) void fwd
   const int n_blocks = n_own_blocks + (GT ? a.Nbg : 0);   // pooled blocks come after the row's own list
   {
     const int32_t *g = a.col_idx + (int64_t)slab * a.Nb * a.Nb + t_begin;
-    for (int t = tid; t < n_blocks; t += C::kThreads)
+    for (int t = threadIdx.x; t < n_blocks; t += C::kThreads * KS)
       cols[t] = t >= n_own_blocks ? (t - n_own_blocks) | kPooled : (dense ? t : g[t]);
   }
   const bf16 *kgs = reinterpret_cast<const bf16 *>(a.kg) + (int64_t)slab * a.Nbg * BLK * D;
@@ -1027,7 +1033,9 @@ __global__ __launch_bounds__(BLK * 2, (PipeCfg<BLK, D>::kWavesPerSimd)) void fwd
   const int last_row0 = Copy::last_row0(a.L);
   if (GT) copy_p.init(wave, lane, D, C::kST);   // pooled rows: D elements apart, never ragged
 
-  const uint32_t smem_addr = ASA_LDS_ADDR_OF(smem);
+  unsigned char *group_smem = smem + group * C::kLds;
+  const uint32_t smem_addr = ASA_LDS_ADDR_OF(smem) + (uint32_t)(group * C::kLds);
+  const int group_key = group * (BLK / KS);    // my part of a block
   // A fragments of S^T = K Q^T: row kappa(n) of the 32 keys (see asa_bwd.hip)
   const int kr = kappa(n);
   uint32_t row_at[D / 16];
@@ -1063,7 +1071,7 @@ __global__ __launch_bounds__(BLK * 2, (PipeCfg<BLK, D>::kWavesPerSimd)) void fwd
       if constexpr (new_block) {
         const int e = __builtin_amdgcn_readfirstlane(entry_v);
         if (GT) pooled_k = (e & kPooled) != 0;
-        key_c = (GT ? e & (kPooled - 1) : e) * BLK;
+        key_c = (GT ? e & (kPooled - 1) : e) * BLK + group_key;
       } else {
         key_c += C::kST;
       }
@@ -1094,7 +1102,7 @@ __global__ __launch_bounds__(BLK * 2, (PipeCfg<BLK, D>::kWavesPerSimd)) void fwd
   auto next_current = [&](auto new_block_tag) __attribute__((always_inline)) {
     if constexpr (decltype(new_block_tag)::value) {
       const int e = __builtin_amdgcn_readfirstlane(cur_v);
-      key_t = (GT ? e & (kPooled - 1) : e) * BLK;
+      key_t = (GT ? e & (kPooled - 1) : e) * BLK + group_key;
       const bool pooled = GT && (e & kPooled) != 0;
       key_end = pooled ? a.Lg : a.L;             // keys at or past it do not exist
       if (GT) bias = pooled ? a.bias_log2 : 0.f;
@@ -1144,7 +1152,7 @@ __global__ __launch_bounds__(BLK * 2, (PipeCfg<BLK, D>::kWavesPerSimd)) void fwd
       for (int i = 0; i < 16; ++i)
         if (16 * (i >> 3) + (i & 7) >= left) sc[i] = -INFINITY;
       // their V rows (in LDS since the last barrier, read after the next one) must be finite
-      u32x4 *z = reinterpret_cast<u32x4 *>(smem + kVBase + U * kStage);
+      u32x4 *z = reinterpret_cast<u32x4 *>(group_smem + kVBase + U * kStage);
       for (int x = max(0, key_end - key_t) * (D / 8) + tid; x < kStage / 16; x += C::kThreads) z[x] = u32x4{0, 0, 0, 0};
       __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
     }
@@ -1231,11 +1239,12 @@ __global__ __launch_bounds__(BLK * 2, (PipeCfg<BLK, D>::kWavesPerSimd)) void fwd
   };
 
   if (n_it > 0) {
-    const bool odd = C::kSub == 2 && (n_blocks & 1);
-    const uint32_t first_stage = odd ? 2u : 0u, first_off = first_stage * kStage;
+    // The loop takes four tiles at a time, one per stage: what is left over comes first.
+    const int first = C::kSub == 4 ? 0 : -n_it & 3;
+    const uint32_t first_stage = (uint32_t)first;
     {
       // the products of tile -1 have P = 0: their V operand only has to be finite
-      u32x4 *z = reinterpret_cast<u32x4 *>(smem + kVBase + ((first_stage + 3) & 3) * kStage);
+      u32x4 *z = reinterpret_cast<u32x4 *>(group_smem + kVBase + ((first_stage + 3) & 3) * kStage);
       for (int x = tid; x < kStage / 16; x += C::kThreads) z[x] = u32x4{0, 0, 0, 0};
     }
     __syncthreads();   // cols[] is written
@@ -1261,8 +1270,12 @@ __global__ __launch_bounds__(BLK * 2, (PipeCfg<BLK, D>::kWavesPerSimd)) void fwd
     next_current(std::true_type{});
     __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * kI));   // K of tiles 0 and 1
     __syncthreads();
+    auto move_rows = [&](uint32_t by) __attribute__((always_inline)) {
 #pragma unroll
-    for (int s = 0; s < D / 16; ++s) row_at[s] += first_off;
+      for (int s = 0; s < D / 16; ++s) row_at[s] += by;
+    };
+    const uint32_t stage0 = first_stage * kStage, stage1 = ((first_stage + 1) & 3u) * kStage;
+    move_rows(stage0);
     s0 = zero16;
     [&]<int... E>(std::integer_sequence<int, E...>) __attribute__((always_inline)) {
       ([&]() __attribute__((always_inline)) {
@@ -1271,25 +1284,30 @@ __global__ __launch_bounds__(BLK * 2, (PipeCfg<BLK, D>::kWavesPerSimd)) void fwd
       }(), ...);
     }(std::make_integer_sequence<int, kNS>{});
     // first operands of iteration 0 (all of them where it has fewer rows than the ring is deep)
+    move_rows(stage1 - stage0);
     [&]<int... E>(std::integer_sequence<int, E...>) __attribute__((always_inline)) {
-      (read_row(std::integral_constant<int, E>{}, std::integral_constant<int, 1>{}), ...);
+      (read_row(std::integral_constant<int, E>{}, std::integral_constant<int, 0>{}), ...);
     }(std::make_integer_sequence<int, (kNS < kDepth ? kNS : kDepth)>{});
-#pragma unroll
-    for (int s = 0; s < D / 16; ++s) row_at[s] -= first_off;
+    move_rows(0u - stage1);
     if constexpr (kNS < kDepth) {
+      const uint32_t stage3 = ((first_stage + 3) & 3u) * kStage;         // (of tile -1)
 #pragma unroll
-      for (int x = 0; x < 2 * (D / 32); ++x) tr_at[x] -= first_off;      // stage 3, or 1
+      for (int x = 0; x < 2 * (D / 32); ++x) tr_at[x] += stage3;
       [&]<int... F>(std::integer_sequence<int, F...>) __attribute__((always_inline)) {
-        (read_tr(std::integral_constant<int, F>{}, std::integral_constant<int, 3>{}), ...);
+        (read_tr(std::integral_constant<int, F>{}, std::integral_constant<int, 0>{}), ...);
       }(std::make_integer_sequence<int, kDepth - kNS>{});
 #pragma unroll
-      for (int x = 0; x < 2 * (D / 32); ++x) tr_at[x] += first_off;
+      for (int x = 0; x < 2 * (D / 32); ++x) tr_at[x] -= stage3;
     }
-    if (odd) {
-      body(std::integral_constant<int, 2>{}, s0, s1);
-      body(std::integral_constant<int, 3>{}, s1, s0);
+    if constexpr (C::kSub == 1) {
+      if (first & 1) s1 = s0;
+      if (first == 1) body(std::integral_constant<int, 1>{}, s1, s0);
     }
-    for (int t = odd ? 2 : 0; t < n_it; t += 4) {
+    if constexpr (C::kSub <= 2) {
+      if (first == 2 || (C::kSub == 1 && first == 1)) body(std::integral_constant<int, 2>{}, s0, s1);
+      if (first != 0) body(std::integral_constant<int, 3>{}, s1, s0);
+    }
+    for (int t = -first & 3; t < n_it; t += 4) {
       body(std::integral_constant<int, 0>{}, s0, s1);
       body(std::integral_constant<int, 1>{}, s1, s0);
       body(std::integral_constant<int, 2>{}, s0, s1);
@@ -1305,7 +1323,33 @@ __global__ __launch_bounds__(BLK * 2, (PipeCfg<BLK, D>::kWavesPerSimd)) void fwd
     }(std::make_integer_sequence<int, kNV>{});
   }
 
-  const float l_tot = l_run + swap_halves(l_run);
+  float l_tot = l_run + swap_halves(l_run);
+  if constexpr (KS > 1) {
+    // the groups' parts of the row meet in the LDS that the tiles have left
+    constexpr int kPart = (D / 8 + 1) * 64 * 16;   // bytes per wavefront: O, then maximum and sum
+    static_assert(KS == 2 && C::kWaves * kPart <= KS * C::kLds, "the second group's part");
+    __syncthreads();                               // (nobody reads a tile any more, no copy is in flight)
+    f32x4 *part = reinterpret_cast<f32x4 *>(smem + wave * kPart) + lane;
+    if (group > 0) {
+#pragma unroll
+      for (int x = 0; x < D / 8; ++x)
+        part[64 * x] = f32x4{oacc[x / 4][4 * (x % 4)], oacc[x / 4][4 * (x % 4) + 1], oacc[x / 4][4 * (x % 4) + 2], oacc[x / 4][4 * (x % 4) + 3]};
+      part[64 * (D / 8)] = f32x4{m_run, l_tot, 0.f, 0.f};
+    }
+    __syncthreads();
+    if (group > 0) return;
+    const f32x4 ml = part[64 * (D / 8)];
+    const float m_new = fmaxf(m_run, ml[0]), m_fin = (m_new == -INFINITY) ? 0.f : m_new;
+    const float mine = fast_exp2(m_run - m_fin), other = fast_exp2(ml[0] - m_fin);
+    m_run = m_new;
+    l_tot = fmaf(l_tot, mine, ml[1] * other);
+#pragma unroll
+    for (int x = 0; x < D / 8; ++x) {
+      const f32x4 v = part[64 * x];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) oacc[x / 4][4 * (x % 4) + e] = fmaf(oacc[x / 4][4 * (x % 4) + e], mine, v[e] * other);
+    }
+  }
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
   if (qvalid) {
     bf16 *os = slab_ptr(a.o, a.to, slab, a.H) + (int64_t)qrow * a.to.sL;
@@ -2064,13 +2108,13 @@ static hipError_t launch_lock_step(const FwdArgs &a, int grid, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int BLK, int D, bool GT>
+template <int BLK, int D, bool GT, int KS>
 static hipError_t launch_pipe(const FwdArgs &a, int grid, hipStream_t st) {
-  using X = PipeCfg<BLK, D>;
-  const hipError_t e = set_dynamic_lds_once(reinterpret_cast<const void *>(&fwd_pipe_kernel<BLK, D, GT>), X::kLds);
+  using X = PipeCfg<BLK, D, KS>;
+  const hipError_t e = set_dynamic_lds_once(reinterpret_cast<const void *>(&fwd_pipe_kernel<BLK, D, GT, KS>), KS * X::kLds);
   if (e != hipSuccess) return e;
   timing_begin(st);
-  hipLaunchKernelGGL((fwd_pipe_kernel<BLK, D, GT>), dim3(grid), dim3(X::kThreads), X::kLds, st, a);
+  hipLaunchKernelGGL((fwd_pipe_kernel<BLK, D, GT, KS>), dim3(grid), dim3(X::kThreads * KS), KS * X::kLds, st, a);
   return hipGetLastError();
 }
 
@@ -2102,6 +2146,47 @@ static hipError_t launch_ping_pong(const FwdArgs &a, int grid, hipStream_t st) {
   timing_begin(st);
   hipLaunchKernelGGL((fwd_pp_kernel<BLK, D, GT>), dim3(grid), dim3(P::kThreads), P::kLdsBytes, st, a);
   return hipGetLastError();
+}
+
+// The rules of the shapes other than block 128 / d 128 (see launch_fwd_t for what they rest on).  Without lists the size of
+// a block means nothing: 256 rows share the tiles of the wide kernel.
+static bool small_shape_wide(const Problem &pb, bool dense, bool pooled) {
+  if (pb.block != 64 || !dense || pooled) return false;
+  if (forced_fwd_kernel() != 0) return forced_fwd_kernel() == 4;
+  const int wide = pb.n_slabs * ((pb.L + 255) / 256), rounds = (wide + 255) / 256;
+  const bool filled = pb.d == 128 ? 4 * wide >= 3 * 256 * rounds : 16 * wide >= 15 * 256 * rounds;
+  return filled && pb.L >= (pb.d == 128 ? 4000 : 8000);
+}
+static bool small_shape_ping_pong(const Problem &pb, bool dense, bool pooled) {
+  if (!pooled || pb.d != 64) return false;
+  const int total = pb.n_slabs * pb.Nb, tiles = dense ? pb.Nb : pb.Nb / 8, forced = forced_fwd_kernel();
+  const bool few_and_long = total <= (pb.block == 128 ? 256 : 512) && tiles >= (pb.block == 128 ? 16 : 24);
+  return forced == 2 || ((forced == 0 || forced == 4) && few_and_long);
+}
+static bool small_shape_pipe(const Problem &pb, bool dense, bool pooled) {
+  if (small_shape_wide(pb, dense, pooled)) return false;
+  if (pooled) return !small_shape_ping_pong(pb, dense, pooled);
+  const bool small_tile = pb.block == 64 && pb.d == 64;
+  const int resident = small_tile ? 1024 : 512, total = pb.n_slabs * pb.Nb;      // pipelined workgroups on the chip
+  bool fits = total <= resident || (!small_tile && !dense);
+  if (pb.block == 64 && pb.d == 128)
+    fits |= (total + resident - 1) / resident * resident - total <= total / 20 || (total > 2 * resident && total <= 3 * resident);
+  return fits && forced_fwd_kernel() != 1;
+}
+// Do two groups of wavefronts share a row (fwd_pipe_kernel)?  Where both halves of every row start at once; where one row
+// can end the launch late: prefix rows (prefix_rows_last), and uneven rows
+// where all of them start at once.  One group and two, us, mask included; d 64: 16 heads of 3 510 tokens, uneven, block 128 50
+// and 45, block 64 51 and 47; with 100 text tokens 77 and 64, 82 and 59; 3 heads of 17 776 tokens, text, block 64, 297 and
+// 193; without text 139 and 143; forward alone, 1 head of 2 266 tokens, 37 and 21; d 128, block 64: 4 heads of
+// 3 510 tokens 40 and 34, 12 slabs of 4 332, text, with backward 343 and 335; 16 heads of 3 510 tokens 56 and 66, fixed budget 75
+// and 86.
+static bool pipe_in_two(const Problem &pb, bool dense, int pooled_blocks) {
+  const int resident = pb.block == 64 && pb.d == 64 ? 1024 : 512;      // groups on the chip
+  const int64_t total = (int64_t)pb.n_slabs * pb.Nb;
+  if (2 * total <= resident) return true;
+  if (dense) return false;
+  if (pb.n_prefix_blocks > 0) return prefix_rows_last(pb, resident, pooled_blocks);
+  return pb.m_min != pb.m_max && pooled_blocks == 0 && total <= resident;
 }
 
 template <int BLK, int D>
@@ -2183,28 +2268,18 @@ static hipError_t launch_fwd_t(const FwdArgs &a, const Problem &pb, hipStream_t 
   b.select = 0;
   if constexpr (!kPingPongShape) {
     if constexpr (BLK == 64) {
-      // Without lists the size of a block means nothing: 256 rows share the tiles of the wide kernel.
-      const int wide = a.n_slabs * ((a.L + 255) / 256), rounds = (wide + 255) / 256;
-      const bool filled = D == 128 ? 4 * wide >= 3 * 256 * rounds : 16 * wide >= 15 * 256 * rounds;
-      if (dense && !pooled && (forced == 4 || (forced == 0 && filled && a.L >= (D == 128 ? 4000 : 8000)))) {
+      if (small_shape_wide(pb, dense, pooled)) {
         b.Nb = (a.L + 127) / 128;
         return launch_wide<128, D, 4, false>(b, st);
       }
     }
-    const int resident = kSmallTile ? 1024 : 512;      // pipelined workgroups on the chip
     if (pooled) {
-      if constexpr (D == 64) {
-        const int tiles = dense ? a.Nb : a.Nb / 8;
-        const bool few_and_long = total <= (BLK == 128 ? 256 : 512) && tiles >= (BLK == 128 ? 16 : 24);
-        if (forced == 2 || (forced == 0 && few_and_long)) return launch_ping_pong<BLK, D, true>(b, grid, st);
-      }
-      return launch_pipe<BLK, D, true>(b, grid, st);
+      if constexpr (D == 64)
+        if (small_shape_ping_pong(pb, dense, pooled)) return launch_ping_pong<BLK, D, true>(b, grid, st);
+      return pipe_in_two(pb, dense, a.Nbg) ? launch_pipe<BLK, D, true, 2>(b, grid, st) : launch_pipe<BLK, D, true, 1>(b, grid, st);
     }
-    bool fits_pipe = total <= resident || (!kSmallTile && !dense);
-    if (BLK == 64 && D == 128)
-      fits_pipe |= (total + resident - 1) / resident * resident - total <= total / 20 ||
-                   (total > 2 * resident && total <= 3 * resident);
-    if (fits_pipe && forced != 1) return launch_pipe<BLK, D, false>(b, grid, st);
+    if (small_shape_pipe(pb, dense, pooled))
+      return pipe_in_two(pb, dense, 0) ? launch_pipe<BLK, D, false, 2>(b, grid, st) : launch_pipe<BLK, D, false, 1>(b, grid, st);
   } else {
     // Rounds of ping-pong workgroups (one per compute unit); a round of the wide kernel takes as long as two of them.
     const int rounds = (total + 255) / 256;

@@ -338,3 +338,35 @@ def test_fwd_dense_packed_projection_with_the_low_half(block, d, tail):
     hi, lo = util.host_f32(o).astype(np.float64), util.host_f32(o_lo).astype(np.float64)
     util.assert_close_bf16(hi + lo, want, "O + o_lo")
     assert (np.abs(lo) <= np.abs(hi) * 2.0 ** -8 + 1e-30).all() and (lo != 0).mean() > 0.9
+
+
+@picks_its_kernel
+@pytest.mark.parametrize("block,d,many", [(64, 64, 120), (64, 128, 110), (128, 64, 110)])
+@pytest.mark.parametrize("tail", [1, 31, 33, 64])
+def test_one_and_two_groups_of_wavefronts_per_row(block, d, many, tail):
+    """Few rows: two groups of wavefronts share a row, each with half of every block's keys; many rows: one group.  Lists of
+    0 .. 5 blocks, so every remainder of the loop over four tiles; a last block whose second half may hold no key.
+    The groups' parts are put together in fp32: both are as near to the oracle."""
+    Nb = 5
+    L = (Nb - 1) * block + tail
+    base = [synth.make_iid((1, 3, L, d), block + d, s) for s in range(3)]
+    rng = np.random.default_rng(tail)
+    mask = np.stack([(rng.random((Nb, Nb)).argsort(axis=1) < (np.arange(Nb)[:, None] + h) % 6) for h in range(3)]).astype(np.uint8)
+    qf, kf, vf = (synth.bf16_bits_to_f32(x) for x in base)
+    out = []
+    for heads in (3, many):
+        print(f"case block={block} d={d} tail={tail} heads={heads}", flush=True)
+        at = np.arange(heads) % 3
+        p = binding.Params(B=1, H=heads, L=L, d=d, block=block, r_min=0.5, r_max=0.5)
+        bufs = util.lists_from_mask(p, mask[at], with_csc=False)
+        o, lse = util.run_fwd(p, *(util.dev_bf16(x[:, at]) for x in base), bufs)
+        out.append((o, lse))
+        for h in range(3):
+            want, want_lse = oracle.attn_fwd(qf[0, h], kf[0, h], vf[0, h], mask[h], block)
+            for copy in (h, heads - 3 + (h - (heads - 3)) % 3):
+                util.assert_close_bf16(util.host_f32(o)[0, copy], want, f"O[{copy}]")
+                got = lse[copy].cpu().numpy()
+                empty = np.isneginf(want_lse)
+                assert np.array_equal(np.isneginf(got), empty)
+                assert np.abs(got[~empty] - want_lse[~empty]).max() <= 1e-3
+    assert not torch.equal(out[0][0].view(torch.int16), out[1][0][:, :3].view(torch.int16))   # (two kernels ran)
