@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from dataclasses import dataclass
 from typing import Optional, Sequence
 
@@ -34,6 +35,10 @@ class asa_params(ctypes.Structure):
         ("v_stride", ctypes.c_int64 * 3), ("o_stride", ctypes.c_int64 * 3),
     ]
 
+
+# The same fields in one call (native sizes and alignment): setting them one by one takes 4 us, as long as a launch.
+_PACKED = struct.Struct("@6iP3fif12q")
+assert _PACKED.size == ctypes.sizeof(asa_params)
 
 EXPORTS = ["asa_version", "asa_error_string", "asa_last_hip_error", "asa_mask_workspace_bytes",
            "asa_fwd_workspace_bytes", "asa_bwd_workspace_bytes", "asa_build_mask",
@@ -120,6 +125,14 @@ class Params:
         return (self.L + self.block - 1) // self.block
 
     def c(self) -> asa_params:
+        if self.sample_offsets is None:
+            try:
+                (q0, q1, q2), (k0, k1, k2), (v0, v1, v2), (o0, o1, o2) = self.q_stride, self.k_stride, self.v_stride, self.o_stride
+                return asa_params.from_buffer_copy(_PACKED.pack(
+                    self.B, self.H, self.L, self.d, self.block, self.k_samples, 0, self.tau, self.r_min, self.r_max,
+                    self.n_prefix_dense, self.scale, q0, q1, q2, k0, k1, k2, v0, v1, v2, o0, o1, o2))
+            except (struct.error, TypeError, ValueError, OverflowError):
+                pass            # values that want converting, or that ctypes refuses: one by one
         p = asa_params()
         p.B, p.H, p.L, p.d, p.block, p.k_samples = self.B, self.H, self.L, self.d, self.block, self.k_samples
         if self.sample_offsets is not None:
@@ -138,12 +151,19 @@ def _ptr(t: Optional[torch.Tensor]):
         return None
     if not t.is_cuda:
         raise AsaError("libasa takes device tensors")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+# (the stream's handle without a Stream object around it, where this torch has that)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(stream) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _check(rc: int, what: str):
@@ -173,7 +193,7 @@ def asa_bwd_workspace_bytes(p: Params) -> int:
 
 def asa_build_mask(p: Params, q, k, mask, row_ptr, col_idx, col_ptr=None, row_idx=None,
                    p_imp=None, workspace=None, stream=None):
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    ws_bytes = workspace.nbytes if workspace is not None else 0
     rc = load().asa_build_mask(ctypes.byref(p.c()), _ptr(q), _ptr(k), _ptr(mask), _ptr(row_ptr),
                                _ptr(col_idx), _ptr(col_ptr), _ptr(row_idx), _ptr(p_imp),
                                _ptr(workspace), ws_bytes, _stream(stream))
@@ -192,7 +212,7 @@ def asa_csr_from_mask(p: Params, mask, row_ptr, col_idx, col_ptr=None, row_idx=N
 
 
 def asa_attn_fwd(p: Params, q, k, v, row_ptr, col_idx, o, lse, workspace, o_lo=None, stream=None):
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    ws_bytes = workspace.nbytes if workspace is not None else 0
     _check(load().asa_attn_fwd(ctypes.byref(p.c()), _ptr(q), _ptr(k), _ptr(v), _ptr(row_ptr),
                                _ptr(col_idx), _ptr(o), _ptr(o_lo), _ptr(lse), _ptr(workspace),
                                ws_bytes, _stream(stream)), "asa_attn_fwd")
@@ -200,7 +220,7 @@ def asa_attn_fwd(p: Params, q, k, v, row_ptr, col_idx, o, lse, workspace, o_lo=N
 
 def asa_attn_bwd(p: Params, q, k, v, o, d_o, lse, row_ptr, col_idx, col_ptr, row_idx, dq, dk, dv,
                  workspace, o_lo=None, stream=None):
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    ws_bytes = workspace.nbytes if workspace is not None else 0
     _check(load().asa_attn_bwd(ctypes.byref(p.c()), _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(o_lo),
                                _ptr(d_o), _ptr(lse), _ptr(row_ptr), _ptr(col_idx), _ptr(col_ptr),
                                _ptr(row_idx), _ptr(dq), _ptr(dk), _ptr(dv), _ptr(workspace),
@@ -238,7 +258,7 @@ def asa_mask_seeded_workspace_bytes(p: Params) -> int:
 
 def asa_build_mask_seeded(p: Params, seed: int, q, k, mask, row_ptr, col_idx, col_ptr, row_idx,
                           p_imp, workspace, stream=None):
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    ws_bytes = workspace.nbytes if workspace is not None else 0
     _check(load().asa_build_mask_seeded(ctypes.byref(p.c()), seed, _ptr(q), _ptr(k), _ptr(mask),
                                         _ptr(row_ptr), _ptr(col_idx), _ptr(col_ptr), _ptr(row_idx),
                                         _ptr(p_imp), _ptr(workspace), ws_bytes, _stream(stream)),
@@ -265,7 +285,7 @@ def asa_fwd_g_workspace_bytes(p: Params, n: int) -> int:
 
 def asa_attn_fwd_g(p: Params, n: int, q, k, v, kg, vg, row_ptr, col_idx, o, lse, workspace,
                    o_lo=None, stream=None):
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    ws_bytes = workspace.nbytes if workspace is not None else 0
     _check(load().asa_attn_fwd_g(ctypes.byref(p.c()), n, _ptr(q), _ptr(k), _ptr(v), _ptr(kg),
                                  _ptr(vg), _ptr(row_ptr), _ptr(col_idx), _ptr(o), _ptr(o_lo),
                                  _ptr(lse), _ptr(workspace), ws_bytes, _stream(stream)),
@@ -278,7 +298,7 @@ def asa_bwd_g_workspace_bytes(p: Params, n: int) -> int:
 
 def asa_attn_bwd_g(p: Params, n: int, q, k, v, kg, vg, o, d_o, lse, row_ptr, col_idx, col_ptr,
                    row_idx, dq, dk, dv, workspace, o_lo=None, stream=None):
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    ws_bytes = workspace.nbytes if workspace is not None else 0
     _check(load().asa_attn_bwd_g(ctypes.byref(p.c()), n, _ptr(q), _ptr(k), _ptr(v), _ptr(kg),
                                  _ptr(vg), _ptr(o), _ptr(o_lo), _ptr(d_o), _ptr(lse), _ptr(row_ptr),
                                  _ptr(col_idx), _ptr(col_ptr), _ptr(row_idx), _ptr(dq), _ptr(dk),
