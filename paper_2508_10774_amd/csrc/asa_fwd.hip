@@ -17,6 +17,7 @@
 // chunks instead of row padding, which keeps the 16-byte fragment reads conflict-free.
 #include <stdlib.h>
 
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -989,6 +990,7 @@ __global__ __launch_bounds__(BLK * 2 * KS, (PipeCfg<BLK, D, KS>::kWavesPerSimd))
   if (slot < 0) return;
   const int work = a.order ? a.order[slot] : slot;
   const int slab = work / a.Nb;
+  if (slab_not_mine(a, slab)) return;
   const int qb = work - slab * a.Nb;
   const int group = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / C::kThreads);
   const int tid = KS == 1 ? threadIdx.x : threadIdx.x % C::kThreads;      // in the group
@@ -2113,7 +2115,7 @@ static hipError_t launch_pipe(const FwdArgs &a, int grid, hipStream_t st) {
   using X = PipeCfg<BLK, D, KS>;
   const hipError_t e = set_dynamic_lds_once(reinterpret_cast<const void *>(&fwd_pipe_kernel<BLK, D, GT, KS>), KS * X::kLds);
   if (e != hipSuccess) return e;
-  timing_begin(st);
+  if (a.select >= 0) timing_begin(st);       // (else the first kernel of the pair has)
   hipLaunchKernelGGL((fwd_pipe_kernel<BLK, D, GT, KS>), dim3(grid), dim3(X::kThreads * KS), KS * X::kLds, st, a);
   return hipGetLastError();
 }
@@ -2291,6 +2293,15 @@ static hipError_t launch_fwd_t(const FwdArgs &a, const Problem &pb, hipStream_t 
     }
     if (forced == 4) return dense ? launch_wide<BLK, D, 4, false>(b, st) : launch_wide<BLK, D, 2, false>(b, st);
     if (fits32 && forced == 2) return launch_ping_pong<BLK, D, false>(b, grid, st);
+    // Up to three quarters of a workgroup per compute unit: two groups of wavefronts per row, pipelined, take the place of the
+    // lock-step kernel where rows have more than two blocks.  Where the host knows the lengths one kernel is launched, not two.
+    // Lock-step (with what ping-pong's empty launch costs) and this, us: 37 blocks, 1 head, 4 / 11 tiles 20.5 / 44.5 and 16.1 / 30.1,
+    // 4 heads 21 / 45 and 17 / 33, prefix rows among short ones 127 and 87; 62 blocks, 6 tiles 30 and 21; 13 blocks, 2 tiles 10.8 and
+    // 11.8, 4 tiles 17.1 and 15.9; no lists, 12 heads, 4, 7, 13 blocks: 17.5, 26, 45 and 16.5, 22, 35.  (256 workgroups, two of
+    // whose wavefronts share every SIMD then: 31 and 27, ping-pong's rows 54 and 53.)
+    const bool few = forced == 0 && total <= 192 && (dense ? a.Nb : std::min(a.Nb, pb.m_max + pb.n_prefix_blocks)) > 2;
+    if (few && (a.Nb < kMinTiles || (!dense && even_rows && pb.m_min < kMinTiles))) return launch_pipe<BLK, D, false, 2>(b, grid, st);
+    if (few && even_rows && fits32) return launch_ping_pong<BLK, D, false>(b, grid, st);
     if (forced == 0 && dense) {
       const bool filled = 2 * ((a.n_slabs * ((a.L + 255) / 256) + 255) / 256) <= rounds;
       const bool wide = a.Nb >= 48 ? filled || rounds > 7 : filled && a.Nb >= 8 && (a.Nb < 24 || rounds > 2);
@@ -2304,7 +2315,7 @@ static hipError_t launch_fwd_t(const FwdArgs &a, const Problem &pb, hipStream_t 
         const hipError_t e = wide ? launch_wide<BLK, D, 2, false>(b, st) : launch_ping_pong<BLK, D, false>(b, grid, st);
         if (e != hipSuccess) return e;
         b.select = -1;
-        return launch_lock_step<BLK, D, false>(b, grid, st);
+        return few ? launch_pipe<BLK, D, false, 2>(b, grid, st) : launch_lock_step<BLK, D, false>(b, grid, st);
       }
     }
     timing_begin(st);

@@ -341,10 +341,10 @@ def test_fwd_dense_packed_projection_with_the_low_half(block, d, tail):
 
 
 @picks_its_kernel
-@pytest.mark.parametrize("block,d,many", [(64, 64, 120), (64, 128, 110), (128, 64, 110)])
+@pytest.mark.parametrize("block,d,many", [(64, 64, 120), (64, 128, 110), (128, 64, 110), (128, 128, 39)])
 @pytest.mark.parametrize("tail", [1, 31, 33, 64])
 def test_one_and_two_groups_of_wavefronts_per_row(block, d, many, tail):
-    """Few rows: two groups of wavefronts share a row, each with half of every block's keys; many rows: one group.  Lists of
+    """Few rows: two groups of wavefronts share a row, each with half of every block's keys; many rows: one group (block 128 / d 128: lock-step).  Lists of
     0 .. 5 blocks, so every remainder of the loop over four tiles; a last block whose second half may hold no key.
     The groups' parts are put together in fp32: both are as near to the oracle."""
     Nb = 5
