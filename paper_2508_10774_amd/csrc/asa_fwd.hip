@@ -1029,8 +1029,21 @@ __global__ __launch_bounds__(BLK * 2 * KS, (PipeCfg<BLK, D, KS>::kWavesPerSimd))
 
   using Copy = TrTileCopy<C::kST, D, C::kWaves>;
   Copy copy_k, copy_v, copy_p;
-  copy_k.init(wave, lane, a.tk.sL, a.L);
-  copy_v.init(wave, lane, a.tv.sL, a.L);
+  // Running copies where one wavefront per SIMD issues everything (block 64 / d 128: 1.05x); with two of them the branches
+  // they bring cost more (d 64 0.88-1.0x, block 128 / d 128 0.97-1.01x).
+  constexpr bool kRun = !GT && C::kWavesPerSimd == 1;
+  using RunCopy = RunningTileCopy<C::kST, D, C::kWaves>;
+  RunCopy run_k, run_v;
+  LastTileWatch watch_k, watch_v;
+  if constexpr (!kRun) {
+    copy_k.init(wave, lane, a.tk.sL, a.L);
+    copy_v.init(wave, lane, a.tv.sL, a.L);
+  } else {
+    run_k.init(wave, lane, ks, a.tk.sL, a.L);
+    run_v.init(wave, lane, vs, a.tv.sL, a.L);
+    watch_k.init(RunCopy::last_row0(a.L));
+    watch_v.init(RunCopy::last_row0(a.L));
+  }
   constexpr int kI = Copy::kInstr;
   const int last_row0 = Copy::last_row0(a.L);
   if (GT) copy_p.init(wave, lane, D, C::kST);   // pooled rows: D elements apart, never ragged
@@ -1056,20 +1069,22 @@ __global__ __launch_bounds__(BLK * 2 * KS, (PipeCfg<BLK, D, KS>::kWavesPerSimd))
   const int n_it = n_blocks * C::kSub;
 
   // The tile whose K rows are copied next, and the tile before it, whose V rows are
-  int entry_v = 0, entry_at = 0, key_c = 0;
+  int entry_v = 0, entry_at = 0, key_c = 0, key_v = 0;
   bool last_k = false, last_v = false, pooled_k = false, pooled_v = false;
   const char *base_k = nullptr, *base_v = nullptr, *base_v_next = nullptr;
   auto fetch_entry = [&]() __attribute__((always_inline)) {
     entry_v = cols[entry_at < n_blocks ? entry_at : n_blocks - 1];
     ++entry_at;
   };
-  auto next_tile = [&](auto part_tag, auto new_block_tag) __attribute__((always_inline)) {
+  // (new_block_v: of the tile whose V rows are copied)
+  auto next_tile = [&](auto part_tag, auto new_block_tag, auto new_block_v_tag) __attribute__((always_inline)) {
     constexpr int part = decltype(part_tag)::value;
-    constexpr bool new_block = decltype(new_block_tag)::value;
+    constexpr bool new_block = decltype(new_block_tag)::value, new_block_v = decltype(new_block_v_tag)::value;
     if constexpr (part == 0) {
       last_v = last_k;
       pooled_v = pooled_k;
       base_v = base_v_next;
+      key_v = key_c;
       if constexpr (new_block) {
         const int e = __builtin_amdgcn_readfirstlane(entry_v);
         if (GT) pooled_k = (e & kPooled) != 0;
@@ -1078,6 +1093,16 @@ __global__ __launch_bounds__(BLK * 2 * KS, (PipeCfg<BLK, D, KS>::kWavesPerSimd))
         key_c += C::kST;
       }
       last_k = key_c >= last_row0;
+    } else if constexpr (kRun) {
+      if constexpr (part == 1) {
+        if constexpr (new_block) run_k.block(key_c);
+        else run_k.step();
+        watch_k.tile(key_c, a.L, run_k);
+      } else {
+        if constexpr (new_block_v) run_v.block(key_v);
+        else run_v.step();
+        watch_v.tile(key_v, a.L, run_v);
+      }
     } else if constexpr (part == 1) {
       base_k = reinterpret_cast<const char *>(ks) + (int64_t)min(key_c, last_row0) * (a.tk.sL * 2);
       if (GT) base_k = pooled_k ? reinterpret_cast<const char *>(kgs) + (int64_t)key_c * (D * 2) : base_k;
@@ -1086,13 +1111,39 @@ __global__ __launch_bounds__(BLK * 2 * KS, (PipeCfg<BLK, D, KS>::kWavesPerSimd))
       if (GT) base_v_next = pooled_k ? reinterpret_cast<const char *>(vgs) + (int64_t)key_c * (D * 2) : base_v_next;
     }
   };
-  auto copy_k_one = [&](int i, uint32_t st) __attribute__((always_inline)) {
-    if (GT) lds_dma16_sv(base_k, pooled_k ? copy_p.off[i] : (last_k ? copy_k.off_last[i] : copy_k.off[i]), st + copy_k.lds0 + i * 1024);
-    else copy_k.issue_one(i, st, base_k, last_k);
+  uint64_t started = 0;
+  auto copy_k_one = [&](auto i_tag, uint32_t st) __attribute__((always_inline)) {
+    constexpr int i = decltype(i_tag)::value;
+    if constexpr (GT) {
+      lds_dma16_sv(base_k, pooled_k ? copy_p.off[i] : (last_k ? copy_k.off_last[i] : copy_k.off[i]), st + copy_k.lds0 + i * 1024);
+    } else if constexpr (!kRun) {
+      copy_k.issue_one(i, st, base_k, last_k);
+    } else {
+      if constexpr (i == 0) started = run_k.start(st);
+      run_k.template load<i>(started);
+    }
   };
-  auto copy_v_one = [&](int i, uint32_t st) __attribute__((always_inline)) {
-    if (GT) lds_dma16_sv(base_v, pooled_v ? copy_p.off[i] : (last_v ? copy_v.off_last[i] : copy_v.off[i]), st + kVBase + copy_v.lds0 + i * 1024);
-    else copy_v.issue_one(i, st + kVBase, base_v, last_v);
+  auto copy_v_one = [&](auto i_tag, uint32_t st) __attribute__((always_inline)) {
+    constexpr int i = decltype(i_tag)::value;
+    if constexpr (GT) {
+      lds_dma16_sv(base_v, pooled_v ? copy_p.off[i] : (last_v ? copy_v.off_last[i] : copy_v.off[i]), st + kVBase + copy_v.lds0 + i * 1024);
+    } else if constexpr (!kRun) {
+      copy_v.issue_one(i, st + kVBase, base_v, last_v);
+    } else {
+      if constexpr (i == 0) started = run_v.start(st + kVBase);
+      run_v.template load<i>(started);
+    }
+  };
+  // copies from .. from + n - 1 of a turn's: K's to stage `to_k`, then V's to stage `to_v`
+  auto copy_some = [&](auto from_tag, auto n_tag, uint32_t to_k, uint32_t to_v) __attribute__((always_inline)) {
+    constexpr int from = decltype(from_tag)::value;
+    [&]<int... I>(std::integer_sequence<int, I...>) __attribute__((always_inline)) {
+      ([&]() __attribute__((always_inline)) {
+        constexpr int i = from + I;
+        if constexpr (i < kI) copy_k_one(std::integral_constant<int, i>{}, to_k);
+        else copy_v_one(std::integral_constant<int, i - kI>{}, to_v);
+      }(), ...);
+    }(std::make_integer_sequence<int, decltype(n_tag)::value>{});
   };
   // The block of the tile in work, for the masks of the last block and the bias of pooled keys
   int cur_v = 0, cur_at = 0, key_t = 0, key_end = 0;
@@ -1148,6 +1199,7 @@ __global__ __launch_bounds__(BLK * 2 * KS, (PipeCfg<BLK, D, KS>::kWavesPerSimd))
     using StVp = std::integral_constant<int, (U + 3) & 3>;   // V rows of tile t - 1
     constexpr bool kNewBlock = (U + C::kStages - 1) % C::kSub == 0;   // of the K tile copied here
     constexpr bool kNextNewBlock = (U + C::kStages) % C::kSub == 0;
+    constexpr bool kNewBlockV = (U + C::kStages - 2) % C::kSub == 0;  // of the V tile copied here
     if (key_t + C::kST > key_end) {                  // (uniform, rare) keys past the end
       const int left = key_end - key_t - 8 * hl;     // (compared with constants: nothing to keep in registers)
 #pragma unroll
@@ -1210,20 +1262,17 @@ __global__ __launch_bounds__(BLK * 2 * KS, (PipeCfg<BLK, D, KS>::kWavesPerSimd))
             }
           }
         }
-        if constexpr (x == 1) next_tile(std::integral_constant<int, 0>{}, std::bool_constant<kNewBlock>{});
-        if constexpr (x == 2) next_tile(std::integral_constant<int, 1>{}, std::bool_constant<kNewBlock>{});
-        if constexpr (x == 3) next_tile(std::integral_constant<int, 2>{}, std::bool_constant<kNewBlock>{});
+        if constexpr (x == 1) next_tile(std::integral_constant<int, 0>{}, std::bool_constant<kNewBlock>{}, std::bool_constant<kNewBlockV>{});
+        if constexpr (x == 2) next_tile(std::integral_constant<int, 1>{}, std::bool_constant<kNewBlock>{}, std::bool_constant<kNewBlockV>{});
+        if constexpr (x == 3) next_tile(std::integral_constant<int, 2>{}, std::bool_constant<kNewBlock>{}, std::bool_constant<kNewBlockV>{});
         if constexpr (x == 2 && (U + 1) % C::kSub == 0) fetch_current();
         if constexpr (x == kN - 2 && kNextNewBlock) fetch_entry();
         // copies of K of tile t + 3 and V of tile t + 2, spread over the slots behind the barrier
         // (their stages were last read in iteration t - 1)
         if constexpr (x >= kBar) {
           constexpr int i0 = (x - kBar) * 2 * kI / (kN - kBar), i1 = (x - kBar + 1) * 2 * kI / (kN - kBar);
-#pragma unroll
-          for (int i = i0; i < i1; ++i) {
-            if (i < kI) copy_k_one(i, smem_addr + ((U + 3) & 3) * kStage);
-            else copy_v_one(i - kI, smem_addr + ((U + 2) & 3) * kStage);
-          }
+          copy_some(std::integral_constant<int, i0>{}, std::integral_constant<int, i1 - i0>{}, smem_addr + ((U + 3) & 3) * kStage,
+                    smem_addr + ((U + 2) & 3) * kStage);
         }
         if constexpr (x == kN - 1) next_current(std::bool_constant<(U + 1) % C::kSub == 0>{});
         __builtin_amdgcn_sched_barrier(0);
@@ -1251,22 +1300,18 @@ __global__ __launch_bounds__(BLK * 2 * KS, (PipeCfg<BLK, D, KS>::kWavesPerSimd))
     }
     __syncthreads();   // cols[] is written
     // K of tiles 0, 1, 2 and V of tiles 0, 1
-    for (int t = 0; t < 3; ++t) {
-      if (t % C::kSub == 0) {
-        fetch_entry();
-        next_tile(std::integral_constant<int, 0>{}, std::true_type{});
-      } else {
-        next_tile(std::integral_constant<int, 0>{}, std::false_type{});
-      }
-      next_tile(std::integral_constant<int, 1>{}, std::false_type{});
-      next_tile(std::integral_constant<int, 2>{}, std::false_type{});
-#pragma unroll
-      for (int i = 0; i < kI; ++i) copy_k_one(i, smem_addr + ((t + first_stage) & 3u) * kStage);
-      if (t > 0) {
-#pragma unroll
-        for (int i = 0; i < kI; ++i) copy_v_one(i, smem_addr + ((t - 1 + first_stage) & 3u) * kStage);
-      }
-    }
+    [&]<int... T>(std::integer_sequence<int, T...>) __attribute__((always_inline)) {
+      ([&]() __attribute__((always_inline)) {
+        constexpr int t = T;
+        constexpr bool new_block = t % C::kSub == 0, new_block_v = t > 0 && (t - 1) % C::kSub == 0;
+        if constexpr (new_block) fetch_entry();
+        next_tile(std::integral_constant<int, 0>{}, std::bool_constant<new_block>{}, std::bool_constant<new_block_v>{});
+        next_tile(std::integral_constant<int, 1>{}, std::bool_constant<new_block>{}, std::bool_constant<new_block_v>{});
+        if constexpr (t > 0 || !kRun) next_tile(std::integral_constant<int, 2>{}, std::bool_constant<new_block>{}, std::bool_constant<new_block_v>{});
+        copy_some(std::integral_constant<int, 0>{}, std::integral_constant<int, t == 0 ? kI : 2 * kI>{},
+                  smem_addr + ((t + first_stage) & 3u) * kStage, smem_addr + ((t + 3 + first_stage) & 3u) * kStage);
+      }(), ...);
+    }(std::make_integer_sequence<int, 3>{});
     if (3 % C::kSub == 0) fetch_entry();
     fetch_current();
     next_current(std::true_type{});

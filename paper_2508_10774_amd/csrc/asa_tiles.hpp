@@ -313,25 +313,21 @@ struct RunningTileCopy {
   template <int I>
   __device__ __forceinline__ void load(uint64_t started) const { lds_dma16_next<I * 1024>(started, off[I]); }
 };
-// Which branch of two such walks a tile takes.  watch: a tile whose first row is at or past it has something to do.
+// Which branch of one or more such walks a tile takes.  watch: a tile whose first row is at or past it has something to do.
 struct LastTileWatch {
   int last_row0, watch;
   bool inside;
   __device__ __forceinline__ void init(int last) { last_row0 = watch = last; inside = false; }
-  template <typename C>
-  __device__ __forceinline__ void tile(int row0, int L, C &x, C &y) {
+  template <typename... C>
+  __device__ __forceinline__ void tile(int row0, int L, C &...x) {
     if (__builtin_expect(row0 < watch, 1)) return;
     const bool now = row0 >= last_row0;
     if (now != inside) {
-      x.turn(now);
-      y.turn(now);
+      (x.turn(now), ...);
       inside = now;
       watch = now ? 0 : last_row0;
     }
-    if (now) {
-      x.at_last(L);
-      y.at_last(L);
-    }
+    if (now) (x.at_last(L), ...);
   }
 };
 
