@@ -492,8 +492,8 @@ __device__ __forceinline__ float key_score(uint32_t k) {
   return __uint_as_float(u);
 }
 
-// The rule on one row whose Nb scores sit in the wavefront's registers as sort keys, in any
-// order (key = order image of the score in the high word, block index in the low word; slots
+// The rule on one row whose Nb scores sit in the wavefront's registers as sort keys, score j in register j / 64 of lane
+// j % 64 (key = order image of the score in the high word, block index in the low word; slots
 // beyond Nb hold ~0).  cum: NPAD doubles of LDS owned by this wavefront.  Every step is
 // wave-synchronous: no workgroup barrier.  Writes the row's Nb mask bytes to dst.
 template <int NPAD>
@@ -504,32 +504,39 @@ __device__ __forceinline__ void rule_on_keys(unsigned long long (&key)[NPAD / 64
   if (m_min == m_max) {
     // A fixed budget: the running sums cannot change the outcome, the m_min smallest keys are kept.
     // The largest of them is found bit by bit (keys are distinct: the block index is part of them),
-    // by counting the keys below a trial value with ballots.  At 13 344 rows of 278: 138 us with the
-    // sorting network and the sums, 67 us so; at 3072 rows of 256: 29 and 18 us.
-    auto below = [&](unsigned long long trial) __attribute__((always_inline)) {
+    // by counting the keys below a trial value with ballots.
+    // A trial value with exactly m_min keys below it ends the search (adjacent scores part after a dozen bits or so, not 32);
+    // registers that hold padding only are not counted.
+    const int used = (Nb + 63) / 64;
+    unsigned long long end = 0;              // the keys below it are kept
+    bool found = false;
+    uint32_t last = 0;                       // score part of the m_min-th smallest key
+    for (int bit = 31; bit >= 0 && !found; --bit) {
+      const uint32_t trial = last | (1u << bit);
       int n = 0;
 #pragma unroll
-      for (int r = 0; r < E; ++r) n += __popcll(__ballot(key[r] < trial));
-      return n;
-    };
-    unsigned long long last = 0;             // the m_min-th smallest key
-    for (int bit = 63; bit >= 32; --bit) {
-      const unsigned long long trial = last | (1ull << bit);
-      int n = 0;
-#pragma unroll
-      for (int r = 0; r < E; ++r) n += __popcll(__ballot((uint32_t)(key[r] >> 32) < (uint32_t)(trial >> 32)));
+      for (int r = 0; r < E; ++r)
+        if (r < used) n += __popcll(__ballot((uint32_t)(key[r] >> 32) < trial));
       if (n < m_min) last = trial;
+      if (n == m_min) found = true, end = (unsigned long long)trial << 32;
     }
-    if (below(last + (1ull << 32)) == m_min) {
-      last |= 0xffffffffull;                 // every key with that score is in
-    } else {
-      for (int bit = 9; bit >= 0; --bit)     // ties: the lower block indices (at most 1023) are in
-        if (below(last | (1ull << bit)) < m_min) last |= 1ull << bit;
+    if (!found) {
+      // the m_min-th key has this score; of several with it the lower block indices (at most 1023) are in
+      unsigned long long at = (unsigned long long)last << 32;
+      for (int bit = 9; bit >= 0; --bit) {
+        const unsigned long long trial = at | (1ull << bit);
+        int n = 0;
+#pragma unroll
+        for (int r = 0; r < E; ++r)
+          if (r < used) n += __popcll(__ballot(key[r] < trial));
+        if (n < m_min) at = trial;
+      }
+      end = at + 1;
     }
 #pragma unroll
     for (int r = 0; r < E; ++r) {
       const int j = (int)(key[r] & 0xffffffffu);
-      if (j < Nb && j >= 0) dst[j] = (key[r] <= last) || (i < n_prefix_blocks) || (j < n_prefix_blocks);
+      if (j < Nb && j >= 0) dst[j] = (key[r] < end) || (i < n_prefix_blocks) || (j < n_prefix_blocks);
     }
     return;
   }
@@ -638,7 +645,7 @@ __global__ __launch_bounds__(256) void rule_kernel(RuleArgs a) {
   unsigned long long key[E];
 #pragma unroll
   for (int r = 0; r < E; ++r) {
-    const int j = lane * E + r;
+    const int j = lane + 64 * r;
     key[r] = j < a.Nb ? (((unsigned long long)desc_key(src[j]) << 32) | (unsigned)j)
                       : ~0ull;        // padding sorts last
   }
@@ -766,7 +773,8 @@ hipError_t launch_finish_rule(const Problem &pb, void *workspace, float *p_imp, 
   ra.n_prefix_blocks = pb.n_prefix_blocks; ra.tau = pb.tau;
   ra.n_rows = pb.n_slabs * pb.Nb;
   const dim3 grid((ra.n_rows + 3) / 4), block(256);
-  if (pb.Nb <= 128) hipLaunchKernelGGL(finish_rule_kernel<128>, grid, block, 0, st, a, ra);
+  if (pb.Nb <= 64) hipLaunchKernelGGL(finish_rule_kernel<64>, grid, block, 0, st, a, ra);
+  else if (pb.Nb <= 128) hipLaunchKernelGGL(finish_rule_kernel<128>, grid, block, 0, st, a, ra);
   else if (pb.Nb <= 256) hipLaunchKernelGGL(finish_rule_kernel<256>, grid, block, 0, st, a, ra);
   else if (pb.Nb <= 512) hipLaunchKernelGGL(finish_rule_kernel<512>, grid, block, 0, st, a, ra);
   else hipLaunchKernelGGL(finish_rule_kernel<1024>, grid, block, 0, st, a, ra);
@@ -779,8 +787,9 @@ hipError_t launch_rule(const Problem &pb, const float *scores, uint8_t *mask, hi
   a.n_prefix_blocks = pb.n_prefix_blocks; a.tau = pb.tau;
   a.n_rows = pb.n_slabs * pb.Nb;
   const dim3 grid((a.n_rows + 3) / 4), block(256);
-  // network size: power of two >= Nb (and >= 128 so that every lane owns a pair)
-  if (pb.Nb <= 128) hipLaunchKernelGGL(rule_kernel<128>, grid, block, 0, st, a);
+  // network size: power of two >= Nb
+  if (pb.Nb <= 64) hipLaunchKernelGGL(rule_kernel<64>, grid, block, 0, st, a);
+  else if (pb.Nb <= 128) hipLaunchKernelGGL(rule_kernel<128>, grid, block, 0, st, a);
   else if (pb.Nb <= 256) hipLaunchKernelGGL(rule_kernel<256>, grid, block, 0, st, a);
   else if (pb.Nb <= 512) hipLaunchKernelGGL(rule_kernel<512>, grid, block, 0, st, a);
   else hipLaunchKernelGGL(rule_kernel<1024>, grid, block, 0, st, a);
