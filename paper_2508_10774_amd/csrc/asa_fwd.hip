@@ -351,7 +351,7 @@ __global__ __launch_bounds__(BLK * 2, (BLK == 64 && D == 64) ? 4 : 2) void fwd_k
     for (int mt = 0; mt < C::kKT / 32; ++mt)
 #pragma unroll
       for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sacc[mt][i]);
-    mx = fmaxf(mx, swap_halves(mx)) * c;
+    mx = max_of_halves(mx) * c;
     if (__any(mx > m_run)) {
       const float m_new = fmaxf(m_run, mx);
       const float alpha = fast_exp2(m_run - ((m_new == -INFINITY) ? 0.f : m_new));
