@@ -287,13 +287,41 @@ __global__ __launch_bounds__(BLK * 2, (BLK == 64 && D == 64) ? 4 : 2) void fwd_k
   const uint32_t lds_addr = ASA_LDS_ADDR_OF(smem);
   // copies of one step into one of the two stages, issued in the form the compiler does not
   // track (it would otherwise wait for them before the next LDS read of the other stage)
-  auto fetch = [&](int step, int stage) __attribute__((always_inline)) {
-    const int j = cols[step / C::kSub];
-    const int sub = step % C::kSub;
+  // (M0 and base in common for a wavefront's loads of a tile where their distances fit the instruction: lds_dma16_next adds 1024 i
+  // to both addresses, the offsets are less by that; a load's rows are at least 1024 bytes from the next one's)
+  constexpr bool kShared = VT && copy_k.kInstr <= 4 && copy_vt.kInstr <= 4;
+  if constexpr (kShared) {
+#pragma unroll
+    for (int i = 0; i < copy_k.kInstr; ++i) copy_k.off[i] -= 1024u * i;
+#pragma unroll
+    for (int i = 0; i < copy_vt.kInstr; ++i) copy_vt.off[i] -= 1024u * i;
+  }
+  auto fetch = [&](int j, int sub, int stage) __attribute__((always_inline)) {
     const int row0 = j * BLK + sub * C::kKT;
     const uint32_t st = lds_addr + stage * kStageElems * 2;
-    const char *kbase = reinterpret_cast<const char *>(ks) + (int64_t)row0 * a.tk.sL * 2;
+    const char *kbase = reinterpret_cast<const char *>(ks) + (uint64_t)(uint32_t)row0 * (uint32_t)(a.tk.sL * 2);
     const int lim = a.L - 1 - row0;
+    if constexpr (kShared) {
+      const char *vtbase = reinterpret_cast<const char *>(vts) + (uint64_t)(uint32_t)j * (D * BLK * 2) + sub * (C::kKT * 2);
+      if (lim >= C::kKT - 1) {
+        const uint64_t k0 = lds_dma_begin(kbase, st + copy_k.lds_chunk(0));
+        [&]<int... I>(std::integer_sequence<int, I...>) __attribute__((always_inline)) {
+          (lds_dma16_next<I * 1024>(k0, copy_k.off[I]), ...);
+        }(std::make_integer_sequence<int, copy_k.kInstr>{});
+      } else {                              // (rare) rows past the last one re-read it; the whole tile may lie past it
+        const char *base = lim < 0 ? kbase + (int64_t)lim * (a.tk.sL * 2) : kbase;
+#pragma unroll
+        for (int i = 0; i < copy_k.kInstr; ++i) {
+          const int past = max(0, copy_k.row_of(i) - max(lim, 0));
+          lds_dma16_sv(base, copy_k.off[i] + 1024u * i - (uint32_t)past * (uint32_t)(a.tk.sL * 2), st + copy_k.lds_chunk(i));
+        }
+      }
+      const uint64_t v0 = lds_dma_begin(vtbase, st + C::kKElems * 2 + copy_vt.wave * copy_vt.kInstr * 1024);
+      [&]<int... I>(std::integer_sequence<int, I...>) __attribute__((always_inline)) {
+        (lds_dma16_next<I * 1024>(v0, copy_vt.off[I]), ...);
+      }(std::make_integer_sequence<int, copy_vt.kInstr>{});
+      return;
+    }
     if (lim >= C::kKT - 1) copy_k.issue_at(st, kbase);
     else copy_k.issue_at_ragged(st, kbase, lim);
     if (VT) {
@@ -306,19 +334,26 @@ __global__ __launch_bounds__(BLK * 2, (BLK == 64 && D == 64) ? 4 : 2) void fwd_k
   };
   if (C::kStages == 2) {
     __syncthreads();                      // cols[] is complete
-    if (n_steps > 0) fetch(0, 0);
+    if (n_steps > 0) fetch(cols[0], 0, 0);
+  }
+  // With one stage the next step's entry of the list is read during this one: the copies are requested right behind the barrier.
+  int j_now = 0, j_next = 0;
+  if (C::kStages == 1) {
+    __syncthreads();                      // cols[] is complete
+    j_now = __builtin_amdgcn_readfirstlane(n_steps > 0 ? cols[0] : 0);
   }
   for (int step = 0; step < n_steps; ++step) {
     if (C::kStages == 1) {
-      __syncthreads();                    // cols[] is complete; the stage is free again
-      fetch(step, 0);
+      if (step > 0) __syncthreads();      // the stage is free again
+      fetch(j_now, step % C::kSub, 0);
+      j_next = cols[min(step + 1, n_steps - 1) / C::kSub];
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);   // my copies of this step have landed
     __syncthreads();                      // everyone's have; everyone is done with the other stage
-    if (C::kStages == 2 && step + 1 < n_steps) fetch(step + 1, (step + 1) & 1);
+    if (C::kStages == 2 && step + 1 < n_steps) fetch(cols[(step + 1) / C::kSub], (step + 1) % C::kSub, (step + 1) & 1);
     const bf16 *Ks = lds + (C::kStages == 2 ? (step & 1) : 0) * kStageElems;
     const uint32_t v_at = lds_addr + ((C::kStages == 2 ? (step & 1) : 0) * kStageElems + C::kKElems) * 2;
-    const int key0 = cols[step / C::kSub] * BLK + (step % C::kSub) * C::kKT;
+    const int key0 = (C::kStages == 1 ? j_now : cols[step / C::kSub]) * BLK + (step % C::kSub) * C::kKT;
     if (!VT && key0 + C::kKT > a.L) {
       // (uniform, once at most) keys past the end have P = 0: their V rows must be finite
       const int first = max(0, a.L - key0);
@@ -395,6 +430,7 @@ __global__ __launch_bounds__(BLK * 2, (BLK == 64 && D == 64) ? 4 : 2) void fwd_k
       }
     }
     l_run += lsum;
+    if (C::kStages == 1) j_now = __builtin_amdgcn_readfirstlane(j_next);
   }
 
   const float l_tot = l_run + swap_halves(l_run);

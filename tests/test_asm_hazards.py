@@ -153,7 +153,7 @@ def _m0_outside_inline_code(text):
 def test_only_the_written_out_loads_of_a_tile_set_m0(assembly):
     """Several loads in a row share one write of M0 (lds_dma_begin): the compiler must not use it in between."""
     for name, lines in [*_functions(assembly["asa_fwd.hip"]), *_functions(assembly["asa_bwd.hip"])]:
-        if any(x in name for x in ("fwd_wide_kernel", "dkv_kernel", "dq_kernel")):
+        if any(x in name for x in ("fwd_wide_kernel", "fwd_pipe_kernel", "fwd_kernel", "dkv_kernel", "dq_kernel")):
             assert not _m0_outside_inline_code("\n".join(lines)), name
     planted = "\t;;#ASMSTART\n\ts_mov_b32 m0, s1\n\t;;#ASMEND\n\ts_mov_b32 m0, s2"
     assert _m0_outside_inline_code(planted) == ["s_mov_b32 m0, s2"]
