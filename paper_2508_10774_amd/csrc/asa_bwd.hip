@@ -139,9 +139,9 @@ struct BwdCfg {
 // there is one workgroup barrier per tile.  A wavefront issues one instruction every ~5 cycles, so
 // the number of instructions matters as much as the MFMAs: four LDS stages with the loop unrolled
 // by four make every LDS address a register plus an immediate; -Delta is the initial value of the
-// dP accumulator; the copies take their addresses from RunningTileCopy (dK / dV at block 128 / d 128 231 -> 210
+// dP accumulator; at d = 128 the copies take their addresses from RunningTileCopy (dK / dV at block 128 / d 128 231 -> 210
 // instructions per tile; whole backward at block 64 / d 128, 8 heads of 17 776 tokens, 990 -> 970 us, block 128 / d 128,
-// 12 heads of 32 760, 4.90 -> 4.86 ms, d 64 within 0.5 %).  Operands two at a time, with one wait for both, change nothing.
+// 12 heads of 32 760, 4.90 -> 4.86 ms).  Operands two at a time, with one wait for both, change nothing.
 // Registers: dK / dV at d = 128 (and dQ at block 64 / d 128) run one wavefront per SIMD with the
 // gradients in accumulation registers (the instruction is written out for that: the compiler would
 // move S and P there as well, at a vector instruction per register and tile), the others two.
@@ -226,8 +226,8 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, int workgroup, uint32_
 
   using Copy = TrTileCopy<C::kST, D, C::kWaves>;
   // (at block 128 / d 128 the 256 registers of dQ are full without the running copies' offsets: the walk for Delta 2065
-  // -> 2156 us at 4 heads of 32 760 tokens)
-  constexpr bool kRun = !GT && !(BLK == 128 && D == 128);
+  // -> 2156 us at 4 heads of 32 760 tokens; d 64, small calls: 0.98x)
+  constexpr bool kRun = !GT && BLK == 64 && D == 128;
   using RunCopy = RunningTileCopy<C::kST, D, C::kWaves>;
   Copy copy_k, copy_v;
   RunCopy run_k, run_v;
@@ -590,14 +590,23 @@ __device__ __forceinline__ void dkv_walk(const BwdArgs &a, int workgroup, uint32
 #pragma unroll
     for (int i = 0; i < 16; ++i) kacc[dm][i] = vacc[dm][i] = 0.f;
 
-  using Copy = RunningTileCopy<C::kST, D, C::kWaves>;
+  using Copy = TrTileCopy<C::kST, D, C::kWaves>;
+  using RunCopy = RunningTileCopy<C::kST, D, C::kWaves>;
+  constexpr bool kRun = D == 128;               // (d 64, small calls: 0.98x)
   Copy copy_q, copy_g;
-  copy_q.init(wave, lane, qs, a.tq.sL, a.L);
-  copy_g.init(wave, lane, gs, a.to.sL, a.L);
+  RunCopy run_q, run_g;
+  LastTileWatch watch;
+  if constexpr (kRun) {
+    run_q.init(wave, lane, qs, a.tq.sL, a.L);
+    run_g.init(wave, lane, gs, a.to.sL, a.L);
+    watch.init(RunCopy::last_row0(a.L));
+  } else {
+    copy_q.init(wave, lane, a.tq.sL, a.L);
+    copy_g.init(wave, lane, a.to.sL, a.L);
+  }
   constexpr int kI = Copy::kInstr;
   constexpr int kBatch = 2 * kI + 1;            // copy instructions per tile and wavefront
-  LastTileWatch last_tile;
-  last_tile.init(Copy::last_row0(a.L));
+  const int last_row0 = Copy::last_row0(a.L);
 
   // (stages are absolute LDS addresses, multiples of 256: the XORs below touch lower bits only)
   // row-wise A fragments (S = Q K^T, dP = dO V^T): row kappa(n) of the 32 queries, 16-byte chunk
@@ -625,7 +634,8 @@ __device__ __forceinline__ void dkv_walk(const BwdArgs &a, int workgroup, uint32
   // addresses.  Tiles past the end repeat the last block: the number of copies in flight stays the
   // same and their data is not used.
   int entry_v = 0, entry_at = 0, q0 = 0;
-  const char *base_st = nullptr;
+  bool last_tile = false;
+  const char *base_q = nullptr, *base_g = nullptr, *base_st = nullptr;
   auto fetch_entry = [&]() __attribute__((always_inline)) {      // (read well before it is used)
     entry_v = rows[entry_at < n_blocks ? entry_at : n_blocks - 1];
     ++entry_at;
@@ -642,24 +652,33 @@ __device__ __forceinline__ void dkv_walk(const BwdArgs &a, int workgroup, uint32
         q0 += C::kST;
         base_st += C::kST * 4;
       }
+    } else if constexpr (part == 1 && kRun) {
+      if constexpr (new_block) run_q.block(q0);
+      else run_q.step();
+    } else if constexpr (kRun) {
+      if constexpr (new_block) run_g.block(q0);
+      else run_g.step();
+      watch.tile(q0, a.L, run_q, run_g);
     } else if constexpr (part == 1) {
-      if constexpr (new_block) copy_q.block(q0);
-      else copy_q.step();
+      base_q = reinterpret_cast<const char *>(qs) + (int64_t)min(q0, last_row0) * (a.tq.sL * 2);
+      last_tile = q0 >= last_row0;
     } else {
-      if constexpr (new_block) copy_g.block(q0);
-      else copy_g.step();
-      last_tile.tile(q0, a.L, copy_q, copy_g);
+      base_g = reinterpret_cast<const char *>(gs) + (int64_t)min(q0, last_row0) * (a.to.sL * 2);
     }
   };
   uint64_t started = 0;
   auto copy_one = [&](auto i_tag, uint32_t st) __attribute__((always_inline)) {
     constexpr int i = decltype(i_tag)::value;
-    if constexpr (i < kI) {
-      if constexpr (i == 0) started = copy_q.start(st);
-      copy_q.template load<i>(started);
+    if constexpr (i < kI && kRun) {
+      if constexpr (i == 0) started = run_q.start(st);
+      run_q.template load<i>(started);
+    } else if constexpr (i < 2 * kI && kRun) {
+      if constexpr (i == kI) started = run_g.start(st + kGOff);
+      run_g.template load<i - kI>(started);
+    } else if constexpr (i < kI) {
+      copy_q.issue_one(i, st, base_q, last_tile);
     } else if constexpr (i < 2 * kI) {
-      if constexpr (i == kI) started = copy_g.start(st + kGOff);
-      copy_g.template load<i - kI>(started);
+      copy_g.issue_one(i - kI, st + kGOff, base_g, last_tile);
     } else {
       lds_dma4_sv(base_st, stat_off, st + kStatOff);
     }
@@ -949,7 +968,7 @@ __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dkv_
 // The rows and columns of always-kept prefix blocks are as long as the sequence, and a workgroup takes one alone: those of dQ
 // start right behind those of dK / dV (`lead` of each XCD's share) and not behind all of dK / dV.  Same bits; us: block 64, 17 776 tokens of
 // which 226 are text, d 64: 1 head 313 -> 244, 3 heads 330 -> 309, d 128: 3 heads 495 -> 442; 4 heads of 4 276 85 -> 68; block 128 /
-// d 128, 3 heads of 12 780, 300 text, 346 -> 295.  Where such a row is not the last to end (prefix_rows_last) it costs 1 %. (All of dQ between dK / dV, one by
+// d 128, 3 heads of 12 780, 300 text, 346 -> 295.  Where all workgroups start at once, or such a row is not the last to end (prefix_rows_last), it costs 1-2 %. (All of dQ between dK / dV, one by
 // one: 0.96-0.98x where there is no prefix.)
 template <int BLK, int D, bool GT>
 __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dkv_dq_kernel(BwdArgs a) {
@@ -1136,7 +1155,7 @@ hipError_t launch_bwd(const Problem &pb, const void *q, const void *k, const voi
       if (e != hipSuccess) return e;
       a.order = order;
       a.order_q = order_q;
-      if (prefix_rows_last(pb, bwd_resident(pb.block, pb.d), 0))
+      if (2 * total > bwd_resident(pb.block, pb.d) && prefix_rows_last(pb, bwd_resident(pb.block, pb.d), 0))
         a.lead = std::min((pb.n_slabs + kNumXcd - 1) / kNumXcd * pb.n_prefix_blocks, (total + kNumXcd - 1) / kNumXcd);
     }
   }

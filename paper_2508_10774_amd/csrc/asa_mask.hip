@@ -154,14 +154,14 @@ __global__ __launch_bounds__(256, 3) void probe_kernel(ProbeArgs a) {
   auto fetch = [&](int chunk, int buf) __attribute__((always_inline)) {
     int l = lane;
 #if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("" : "+v"(l));   // (rare: nothing of it is to be kept in registers across the sweep)
+    if (!TAB) asm volatile("" : "+v"(l));   // (rare: nothing of it is to be kept in registers across the sweep)
 #endif
 #pragma unroll
     for (int i = 0; i < DMA_PER_WAVE; ++i) {
       const int row = row_of(i, l), blk = chunk * kProbeKBlocks + row / 16;
-      int64_t tok = (int64_t)blk * a.block + offset_of(blk, row % 16);
-      tok = tok < a.L ? tok : 0;   // padded samples: any valid row, masked out below
-      lds_dma16_v(ks + tok * a.tk.sL + pos_of(i, l), lds_of(i, buf));
+      const int tok = blk * a.block + offset_of(blk, row % 16);
+      const uint32_t at = tok < a.L ? tok : 0;   // padded samples: any valid row, masked out below
+      lds_dma16_v(reinterpret_cast<const char *>(ks) + (uint64_t)at * (uint32_t)(a.tk.sL * 2) + 2 * pos_of(i, l), lds_of(i, buf));
     }
   };
 
