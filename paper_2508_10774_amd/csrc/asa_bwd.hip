@@ -968,7 +968,8 @@ __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dkv_
 // The rows and columns of always-kept prefix blocks are as long as the sequence, and a workgroup takes one alone: those of dQ
 // start right behind those of dK / dV (`lead` of each XCD's share) and not behind all of dK / dV.  Same bits; us: block 64, 17 776 tokens of
 // which 226 are text, d 64: 1 head 313 -> 244, 3 heads 330 -> 309, d 128: 3 heads 495 -> 442; 4 heads of 4 276 85 -> 68; block 128 /
-// d 128, 3 heads of 12 780, 300 text, 346 -> 295.  Where all workgroups start at once, or such a row is not the last to end (prefix_rows_last), it costs 1-2 %. (All of dQ between dK / dV, one by
+// d 128, 3 heads of 12 780, 300 text, 346 -> 295.  Where such a row is not the last to end (prefix_rows_last) it costs 1 %. (Also where
+// all workgroups start at once: without it there, 1 head 311 us.) (All of dQ between dK / dV, one by
 // one: 0.96-0.98x where there is no prefix.)
 template <int BLK, int D, bool GT>
 __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dkv_dq_kernel(BwdArgs a) {
@@ -1155,7 +1156,7 @@ hipError_t launch_bwd(const Problem &pb, const void *q, const void *k, const voi
       if (e != hipSuccess) return e;
       a.order = order;
       a.order_q = order_q;
-      if (2 * total > bwd_resident(pb.block, pb.d) && prefix_rows_last(pb, bwd_resident(pb.block, pb.d), 0))
+      if (prefix_rows_last(pb, bwd_resident(pb.block, pb.d), 0))
         a.lead = std::min((pb.n_slabs + kNumXcd - 1) / kNumXcd * pb.n_prefix_blocks, (total + kNumXcd - 1) / kNumXcd);
     }
   }
