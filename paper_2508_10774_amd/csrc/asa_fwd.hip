@@ -2266,7 +2266,6 @@ static bool small_shape_pipe(const Problem &pb, bool dense, bool pooled) {
 static bool pipe_in_two(const Problem &pb, bool dense, int pooled_blocks) {
   const int resident = pb.block == 64 && pb.d == 64 ? 1024 : 512;      // groups on the chip
   const int64_t total = (int64_t)pb.n_slabs * pb.Nb;
-  if ((dense ? pb.Nb : std::min(pb.Nb, pb.m_max + pb.n_prefix_blocks)) + pooled_blocks <= 2) return false;   // (0.97x)
   if (2 * total <= resident) return true;
   if (dense) return false;
   if (pb.n_prefix_blocks > 0) return prefix_rows_last(pb, resident, pooled_blocks);
