@@ -14,7 +14,7 @@ namespace asa {
 // soft-max (over ALL sampled keys of the slab) of scale * Qs Ks^T.
 //
 // Alg. 1 of the paper, reorganised for 64-wide wavefronts.  A workgroup of 4 wavefronts owns 8
-// query blocks, two per wavefront, and sweeps one range of the key blocks of its slab.  The sampled key rows (Alg. 2
+// query blocks, two per wavefront, and sweeps one of the four shares of its slab's key blocks.  The sampled key rows (Alg. 2
 // steps 1-3) are gathered from K by direct global->LDS loads, 4 key blocks (64 rows) per
 // chunk, double-buffered and shared by all wavefronts.  One chain of 32x32x16
 // bf16 MFMAs gives a 32 x 32 logit tile: 2 key blocks x 16 samples on the M axis, 2 query
@@ -31,11 +31,10 @@ struct ProbeArgs {
   const void *q, *k;
   float *p_imp;
   float *rt;         // workspace [query group][pair][Nb rounded up to 8][32]: block-row maxima
-  float *stat_r;     // workspace [work item][pair][32]: reference exponent of the wavefront's keys
+  float *stat_r;     // workspace [query group][share][pair][32]: reference exponent of the share's keys
   double *stat_l;    //           and the denominator relative to 2^reference
   TensorView tq, tk;
   int H, L, Nb, n_slabs, block, ks;
-  int ranges;        // of key blocks per query group
   int64_t chunk_bytes;   // from a chunk's first token to the next one's
   int n_full_chunks; // chunks with no token >= L (none if a chunk's rows span 4 GiB or more: 32-bit offsets)
   int n_valid_last;  // sampled tokens of the last block that lie below L
@@ -50,8 +49,12 @@ constexpr int kProbeQBlocks = 8;   // query blocks per workgroup
 constexpr int kProbeKBlocks = 4;   // key blocks per LDS chunk: two pairs, one 32 x 32 logit tile per wavefront each
 constexpr int kProbePairs = kProbeQBlocks / 2;
 constexpr int kProbePad = 8;       // the rows of block maxima are this many key blocks long, rounded up
-// The key blocks of a slab are cut into ranges, one workgroup each (probe_ranges).
-constexpr int kProbeMaxRanges = 4;
+// The key blocks of a slab are cut into four shares, each with a reference and a denominator of its own: the first and the second
+// half of the even chunks and of the odd ones, one workgroup per share.  The cut is the same whatever the size of the call, so a head's
+// map is too: a share's numerators and denominator are rounded relative to the share's own reference.  (Contiguous ranges, as many as
+// the chip holds at once: 2 % of a map's entries differed in the last bits with the number of heads.  Two of them instead of four shares,
+// us for the whole mask: 12 heads of 256 blocks, d = 128, 90.7 and 91.8; 24 heads of 313, d = 64, 190 and 187; 1 head of 256, 47 and 38.)
+constexpr int kProbeShares = 4;
 
 // The exponent of 2 of a raw logit s is s * c2 with c2 = scale * log2(e), rounded to fp32.  What the
 // rounding leaves out multiplies exp2(s * c2) by 1 + s * rest.  That is used up to this exponent (logits
@@ -83,10 +86,9 @@ __global__ __launch_bounds__(256, 3) void probe_kernel(ProbeArgs a) {
   __shared__ __align__(1024) bf16 Kc[2][ROWS * D];
 
   const int n_groups = (a.Nb + kProbeQBlocks - 1) / kProbeQBlocks;
-  const int item = xcd_contiguous_work(blockIdx.x, a.n_slabs * n_groups * a.ranges);
+  const int item = xcd_contiguous_work(blockIdx.x, a.n_slabs * n_groups * kProbeShares);
   if (item < 0) return;
-  const int work = item / a.ranges;          // (slab, query group)
-  const int range = item - work * a.ranges;  // which range of key blocks
+  const int work = item / kProbeShares, share = item % kProbeShares;   // (slab, query group)
   const int slab = work / n_groups;
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -300,9 +302,10 @@ __global__ __launch_bounds__(256, 3) void probe_kernel(ProbeArgs a) {
 #pragma unroll
     for (int sb = 0; sb < NT; ++sb) rt_c[rt_off + sb * 64] = rt_pend[sb];
   };
-  const int n_chunks = (a.Nb + kProbeKBlocks - 1) / kProbeKBlocks;
-  const int per_range = (n_chunks + a.ranges - 1) / a.ranges;
-  const int c0 = min(n_chunks, range * per_range), c1 = min(n_chunks, c0 + per_range);   // my chunks
+  // my chunks: every other one from c0 on
+  constexpr int kStep = 2;
+  const int n_chunks = (a.Nb + kProbeKBlocks - 1) / kProbeKBlocks, per_half = (n_chunks + 3) / 4 * 2;
+  const int c0 = share / 2 * per_half + share % 2, c1 = min(n_chunks, (share / 2 + 1) * per_half);
   f32x16 s0[NT], s1[NT];
   using Yes = std::true_type;
   using No = std::false_type;
@@ -316,34 +319,34 @@ __global__ __launch_bounds__(256, 3) void probe_kernel(ProbeArgs a) {
   if (c0 < c1) {
     fetch_any(c0, 0);
     landed();
-    if (c0 + 1 < c1) fetch_any(c0 + 1, 1);
+    if (c0 + kStep < c1) fetch_any(c0 + kStep, 1);
     turn(c0, Buf0{}, Yes{}, No{}, s1, s0);       // the products of my first chunk
-    for (int chunk = c0;; chunk += 2) {
+    for (int chunk = c0;; chunk += 2 * kStep) {
       // s0: products of `chunk`, whose successor is in buffer 1
-      if (chunk + 1 >= c1) {
-        if (chunk > c0) store_rt(chunk - 1);
+      if (chunk + kStep >= c1) {
+        if (chunk > c0) store_rt(chunk - kStep);
         turn(chunk, Buf1{}, No{}, Yes{}, s0, s1);
         store_rt(chunk);
         break;
       }
       landed();
-      if (chunk > c0) store_rt(chunk - 1);
-      if (chunk + 2 < c1) fetch_any(chunk + 2, 0);
+      if (chunk > c0) store_rt(chunk - kStep);
+      if (chunk + 2 * kStep < c1) fetch_any(chunk + 2 * kStep, 0);
       turn(chunk, Buf1{}, Yes{}, Yes{}, s0, s1);
-      if (chunk + 2 >= c1) {
+      if (chunk + 2 * kStep >= c1) {
         store_rt(chunk);
-        turn(chunk + 1, Buf0{}, No{}, Yes{}, s1, s0);
-        store_rt(chunk + 1);
+        turn(chunk + kStep, Buf0{}, No{}, Yes{}, s1, s0);
+        store_rt(chunk + kStep);
         break;
       }
       landed();
       store_rt(chunk);
-      if (chunk + 3 < c1) fetch_any(chunk + 3, 1);
-      turn(chunk + 1, Buf0{}, Yes{}, Yes{}, s1, s0);
+      if (chunk + 3 * kStep < c1) fetch_any(chunk + 3 * kStep, 1);
+      turn(chunk + kStep, Buf0{}, Yes{}, Yes{}, s1, s0);
     }
   }
-  // merge the two parities of each query; the pair (reference, denominator) of this wavefront's
-  // share of the keys goes to the workspace (the kernel that follows merges the shares)
+  // merge the two parities of each query; the pair (reference, denominator) of my share of the
+  // keys goes to the workspace (the kernel that follows merges the shares)
   {
     const float Ro = __shfl_xor(Rr, 32, 64);
     const double lo = __shfl_xor(lt, 32, 64);
@@ -364,18 +367,10 @@ static size_t probe_rt_bytes(const Problem &pb) {
   const size_t nb_pad = (pb.Nb + kProbePad - 1) / kProbePad * kProbePad;
   return (probe_groups(pb) * kProbePairs * nb_pad * 32 * sizeof(float) + 255) & ~(size_t)255;
 }
-// wavefronts that write soft-max statistics, at most
-static size_t probe_stats(const Problem &pb) { return probe_groups(pb) * kProbeMaxRanges * kProbePairs; }
-// As many ranges as fill the chip, whose compute units hold three of these workgroups each, and at least two.  The whole mask with 2,
-// 3 and 4 ranges, us: 256 blocks of 128, d = 128: 1 head 47, -, 38; 2 heads 50, -, 41; 6 heads 66, -, 60; 8 heads 70, 69.4,
-// 70.6; 12 heads 89, 93, 90 (one range: 101); 512 blocks of 64, d = 64: 3 heads 94, -, 80.
-static int probe_ranges(const Problem &pb) {
-  const int n = (int)(768 / probe_groups(pb));
-  return n < 2 ? 2 : (n > kProbeMaxRanges ? kProbeMaxRanges : n);
-}
+static size_t probe_items(const Problem &pb) { return probe_groups(pb) * kProbeShares; }
 size_t probe_workspace_bytes(const Problem &pb) {
   // block-row maxima, then the per-wavefront soft-max statistics (fp64 denominators first)
-  return probe_rt_bytes(pb) + probe_stats(pb) * 32 * (sizeof(double) + sizeof(float));
+  return probe_rt_bytes(pb) + probe_items(pb) * kProbePairs * 32 * (sizeof(double) + sizeof(float));
 }
 
 static void fill_probe_args(const Problem &pb, const void *q, const void *k, float *p_imp,
@@ -385,10 +380,9 @@ static void fill_probe_args(const Problem &pb, const void *q, const void *k, flo
   unsigned char *ws = reinterpret_cast<unsigned char *>(workspace);
   a->rt = reinterpret_cast<float *>(ws);
   a->stat_l = reinterpret_cast<double *>(ws + probe_rt_bytes(pb));
-  a->stat_r = reinterpret_cast<float *>(ws + probe_rt_bytes(pb) + probe_stats(pb) * 32 * sizeof(double));
+  a->stat_r = reinterpret_cast<float *>(ws + probe_rt_bytes(pb) + probe_items(pb) * kProbePairs * 32 * sizeof(double));
   a->tq = pb.q; a->tk = pb.k;
   a->H = pb.H; a->L = pb.L; a->Nb = pb.Nb; a->n_slabs = pb.n_slabs; a->block = pb.block; a->ks = pb.ks;
-  a->ranges = probe_ranges(pb);
   a->chunk_bytes = (int64_t)kProbeKBlocks * pb.block * pb.k.sL * 2;
   a->n_full_chunks = a->chunk_bytes >= ((int64_t)1 << 32) ? 0 : pb.L / (kProbeKBlocks * pb.block);
   a->c2 = pb.scale * 1.44269504088896340736f;
@@ -404,7 +398,7 @@ hipError_t launch_probe(const Problem &pb, const void *q, const void *k, void *w
                         hipStream_t st, const uint8_t *table) {
   ProbeArgs a;
   fill_probe_args(pb, q, k, nullptr, workspace, table, &a);
-  const dim3 grid(xcd_grid((int)probe_groups(pb) * a.ranges)), block(64 * kProbePairs);
+  const dim3 grid(xcd_grid((int)probe_items(pb))), block(64 * kProbePairs);
   if (pb.d == 128 && table) hipLaunchKernelGGL((probe_kernel<128, true>), grid, block, 0, st, a);
   else if (pb.d == 128) hipLaunchKernelGGL((probe_kernel<128, false>), grid, block, 0, st, a);
   else if (table) hipLaunchKernelGGL((probe_kernel<64, true>), grid, block, 0, st, a);
@@ -656,7 +650,7 @@ __global__ __launch_bounds__(256) void rule_kernel(RuleArgs a) {
 // ---------------------------------------------------------------------------------------
 // Second half of the probe (Alg. 1, second loop) fused with the rule: one wavefront per query
 // block.  It merges the soft-max statistics of the wavefronts that swept this block's sampled
-// rows (two halves of every chunk x the ranges of key blocks), turns the block-row maxima into
+// rows (the shares of the key blocks), turns the block-row maxima into
 // probabilities, max-pools them over the sampled rows -- the row P_imp[i][:], written out if the
 // caller wants it -- and applies the rule to that row while it is still in registers.
 // ---------------------------------------------------------------------------------------
@@ -673,26 +667,25 @@ __global__ __launch_bounds__(256) void finish_rule_kernel(ProbeArgs a, RuleArgs 
   const int work = slab * n_groups + i / kProbeQBlocks;      // the query group that swept this block
   const int w = i % kProbeQBlocks, pr_ = w >> 1, qb = w & 1;  // its pair and position in the pair
   const float *rtq = a.rt + ((int64_t)work * kProbePairs + pr_) * nb_pad * 32 + qb * 16;
-  // merge the shares: wavefront pr_ of every key range
+  // merge the shares
   // (the denominator is summed in fp64; its reciprocal is kept in two fp32 halves)
   // Lane u < 16 merges the shares of sampled row u; the 16 results are then handed to every
   // lane through scalar registers (all lanes doing all 16 rows cost 16 fp64 divisions a lane).
   float my_r = -INFINITY, my_inv = 0.f, my_inv_lo = 0.f, my_inv_rest = 0.f;
   {
     const int u = lane & 15;
-    float pr[kProbeMaxRanges];
-    double pl[kProbeMaxRanges];
+    float pr[kProbeShares];
+    double pl[kProbeShares];
 #pragma unroll
-    for (int x = 0; x < kProbeMaxRanges; ++x) {
-      const int64_t at = (((int64_t)work * a.ranges + min(x, a.ranges - 1)) * kProbePairs + pr_) * 32 + qb * 16 + u;
+    for (int x = 0; x < kProbeShares; ++x) {
+      const int64_t at = (((int64_t)work * kProbeShares + x) * kProbePairs + pr_) * 32 + qb * 16 + u;
       pr[x] = a.stat_r[at];
       pl[x] = a.stat_l[at];
       my_r = fmaxf(my_r, pr[x]);
     }
     double l = 0.0;
 #pragma unroll
-    for (int x = 0; x < kProbeMaxRanges; ++x)
-      if (x < a.ranges) l += __builtin_amdgcn_ldexp(pl[x], (int)fmaxf(pr[x] - my_r, -2000.f));
+    for (int x = 0; x < kProbeShares; ++x) l += __builtin_amdgcn_ldexp(pl[x], (int)fmaxf(pr[x] - my_r, -2000.f));
     const double inv = 1.0 / l;
     my_inv = (float)inv;
     my_inv_lo = (float)(inv - (double)my_inv);

@@ -253,6 +253,31 @@ def test_importance_map_at_the_edges_of_its_chunks(Nb, tail, d, block, ks):
     _check_build(p, qb, kb, synth.default_sample_offsets(block, ks), f"Nb={Nb} tail={tail} d={d}")
 
 
+@pytest.mark.parametrize("seeded", [False, True])
+@pytest.mark.parametrize("d,block", [(64, 64), (128, 128)])
+def test_a_head_has_the_same_map_in_calls_of_any_size(d, block, seeded):
+    """The soft-max statistics of a sampled row are kept per share of the key blocks, the same shares in every call: P_imp of
+    the first two heads is the same bits alone, among 24 and among 40 (18, 216 and 360 groups of eight query blocks)."""
+    L = 68 * block + 40
+    base = [synth.make_iid((1, 2, L, d), block, s) for s in range(2)]
+    maps = []
+    for heads in (2, 24, 40):
+        print(f"case d={d} block={block} seeded={seeded} heads={heads}", flush=True)
+        p = binding.Params(B=1, H=heads, L=L, d=d, block=block)
+        q, k = (util.dev_bf16(x[:, np.arange(heads) % 2]) for x in base)
+        bufs = binding.alloc_index_lists(p)
+        pimp = torch.empty((heads, p.Nb, p.Nb), dtype=torch.float32, device="cuda")
+        ws = binding.alloc_workspace(binding.asa_mask_seeded_workspace_bytes(p))
+        outs = (q, k, bufs["mask"], bufs["row_ptr"], bufs["col_idx"], bufs["col_ptr"], bufs["row_idx"], pimp, ws)
+        if seeded:
+            binding.asa_build_mask_seeded(p, 3, *outs)
+        else:
+            binding.asa_build_mask(p, *outs)
+        torch.cuda.synchronize()
+        maps.append(pimp[:2].view(torch.int32).clone())
+    assert torch.equal(maps[0], maps[1]) and torch.equal(maps[0], maps[2])
+
+
 def test_build_mask_noise_only_inputs_variable_m():
     # nearly flat scores: many rows, m varies, thresholds are crossed with small margins
     shape = (1, 4, 64 * 48, 64)
