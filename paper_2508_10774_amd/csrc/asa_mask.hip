@@ -41,7 +41,7 @@ struct ProbeArgs {
   float c2;          // scale * log2(e)
   float rest;        // ln(2) * what the rounding of c2 left out
   float s_bound;     // kMaxExactExponent / c2
-  int offs[kMaxSamples];
+  uint32_t offs[kMaxSamples / 4];   // sample positions inside a block (below 128), a byte each
   const uint8_t *table;   // per-block sample positions [slab][Nb][ks] (TAB kernels), else null
 };
 
@@ -106,23 +106,21 @@ __global__ __launch_bounds__(256, 3) void probe_kernel(ProbeArgs a) {
 
   // TAB: this slab's table in LDS; positions ascend inside a block, so the samples of the last
   // block that lie below L are a prefix
-  __shared__ uint8_t tab[TAB ? kMaxNb * kMaxSamples : kMaxSamples];
+  __shared__ uint8_t tab[TAB ? kMaxNb * kMaxSamples : 1];
   int n_valid_last = a.n_valid_last;
   if (TAB) {
     const uint8_t *g = a.table + (int64_t)slab * a.Nb * a.ks;
     for (int t = tid; t < a.Nb * a.ks; t += 256) tab[t] = g[t];
-  } else if (tid < kMaxSamples) {
-    tab[tid] = (uint8_t)a.offs[tid];           // (below the block size, 128 at most)
-  }
-  __syncthreads();
-  if (TAB) {
+    __syncthreads();
     n_valid_last = 0;
     for (int u = 0; u < a.ks; ++u)
       if ((a.Nb - 1) * a.block + tab[(a.Nb - 1) * a.ks + u] < a.L) ++n_valid_last;
   }
   auto offset_of = [&](int blk, int u) {
     if (TAB) return (blk < a.Nb && u < a.ks) ? (int)tab[blk * a.ks + u] : 0;
-    return (int)tab[u];
+    // (from scalar registers: an indexed read of the kernel's arguments is a load from memory, which all that follows would wait for)
+    const uint32_t lo = u & 4 ? a.offs[1] : a.offs[0], hi = u & 4 ? a.offs[3] : a.offs[2];
+    return (int)(((u & 8 ? hi : lo) >> (8 * (u & 3))) & 255u);
   };
   auto valid_in_block = [&](int blk) {
     return blk >= a.Nb ? 0 : (blk == a.Nb - 1 ? n_valid_last : a.ks);
@@ -388,7 +386,8 @@ static void fill_probe_args(const Problem &pb, const void *q, const void *k, flo
   a->c2 = pb.scale * 1.44269504088896340736f;
   a->rest = (float)(((double)pb.scale * 1.44269504088896340736 - (double)a->c2) * 0.69314718055994530942);
   a->s_bound = fminf(kMaxExactExponent / a->c2, 3.0e38f);   // (finite: the -inf of a tile without keys is bounded too)
-  for (int u = 0; u < kMaxSamples; ++u) a->offs[u] = pb.offs[u];
+  for (int u = 0; u < kMaxSamples; u += 4)
+    a->offs[u / 4] = (uint32_t)pb.offs[u] | (uint32_t)pb.offs[u + 1] << 8 | (uint32_t)pb.offs[u + 2] << 16 | (uint32_t)pb.offs[u + 3] << 24;
   a->n_valid_last = 0;
   for (int u = 0; u < pb.ks; ++u)
     if ((int64_t)(pb.Nb - 1) * pb.block + pb.offs[u] < pb.L) ++a->n_valid_last;

@@ -159,6 +159,28 @@ def test_only_the_written_out_loads_of_a_tile_set_m0(assembly):
     assert _m0_outside_inline_code(planted) == ["s_mov_b32 m0, s2"]
 
 
+def _argument_loads(lines):
+    """Vector loads from the kernel's arguments (s[0:1] until something else is put there)."""
+    found = []
+    for line in lines:
+        code = line.split(";")[0].strip()
+        if re.match(r"global_load_(?!lds)\w+ .*, s\[0:1\]", code):
+            found.append(code)
+        if re.match(r"s_\w+ s(0|1|\[0:\d+\])\s*,", code):
+            break
+    return found
+
+
+def test_kernel_arguments_are_read_by_scalar_loads(assembly):
+    """An argument array that is indexed per lane becomes a load from the memory that holds the arguments, and all that
+    depends on it waits for that: the probe's sample positions come out of scalar registers."""
+    for src in assembly:
+        for name, lines in _functions(assembly[src]):
+            assert not _argument_loads(lines), (src, name)
+    planted = ["\ts_load_dword s3, s[0:1], 0x78", "\tglobal_load_dword v1, v6, s[0:1] offset:156"]
+    assert _argument_loads(planted) and not _argument_loads(["\ts_mov_b64 s[0:1], s[4:5]", *planted])
+
+
 LOOP = """.LBB0_1:
 \tds_read_b128 v[4:7], v20
 \t{front}
