@@ -49,7 +49,7 @@ def test_rule_kernel_is_bit_exact(Nb, tau, r_min, r_max):
 
 @pytest.mark.parametrize("Nb", [2, 63, 64, 65, 127, 128, 129, 255, 257, 511, 512, 513, 1023])
 def test_rule_kernel_at_the_edges_of_its_network_sizes(Nb):
-    """The sorting network is built for 128, 256, 512 or 1024 keys; rows just below, at and just
+    """The sorting network is built for 64, 128, 256, 512 or 1024 keys; rows just below, at and just
     above those sizes (and rows shorter than a wavefront) against the oracle, bit for bit."""
     H, block = 2, 64
     p = binding.Params(B=1, H=H, L=Nb * block - 3, d=64, block=block, tau=0.8, r_min=0.05, r_max=0.9)
@@ -57,6 +57,22 @@ def test_rule_kernel_at_the_edges_of_its_network_sizes(Nb):
     sc = _scores(H * Nb, Nb, seed=1000 + Nb) if Nb >= 16 else np.random.default_rng(Nb).random(
         (H * Nb, Nb), dtype=np.float32)
     want, _ = oracle.mask_rule(sc, 0.8, 0.05, 0.9)
+    got = torch.empty((H, Nb, Nb), dtype=torch.uint8, device="cuda")
+    binding.asa_mask_from_scores(p, torch.from_numpy(sc).cuda(), got)
+    torch.cuda.synchronize()
+    assert np.array_equal(got.cpu().numpy().reshape(-1, Nb), want)
+
+
+@pytest.mark.parametrize("Nb", [2, 63, 64, 65, 128, 129, 193, 256, 257, 512, 513, 1023])
+@pytest.mark.parametrize("r", [0.0, 0.25, 1.0])
+def test_fixed_budget_at_the_edges_of_its_registers(Nb, r):
+    """A fixed budget is found four bits of the score at a time by counting, register by register: rows just below, at and just
+    above whole registers, with ties, zeros and NaN, against the oracle, bit for bit (r = 0: one block)."""
+    H, block = 2, 64
+    p = binding.Params(B=1, H=H, L=Nb * block - 3, d=64, block=block, r_min=r, r_max=r or 0.5 / Nb)
+    sc = _scores(H * Nb, Nb, seed=7 + Nb) if Nb >= 16 else np.random.default_rng(Nb).random((H * Nb, Nb), dtype=np.float32)
+    want, _ = oracle.mask_rule(sc, p.tau, r, p.r_max)
+    assert (want.sum(axis=1) == max(1, math.ceil(r * Nb))).all()
     got = torch.empty((H, Nb, Nb), dtype=torch.uint8, device="cuda")
     binding.asa_mask_from_scores(p, torch.from_numpy(sc).cuda(), got)
     torch.cuda.synchronize()
