@@ -104,20 +104,23 @@ __global__ __launch_bounds__(256, 3) void probe_kernel(ProbeArgs a) {
   const bf16 *qs = slab_ptr(a.q, a.tq, slab, a.H);
   const bf16 *ks = slab_ptr(a.k, a.tk, slab, a.H);
 
-  // TAB: this slab's table in LDS; positions ascend inside a block, so the samples of the last
-  // block that lie below L are a prefix
+  // TAB: this slab's table in LDS, 16 entries to a block whatever ks, so that the entries of a lane's rows are constant distances
+  // apart (with as many entries as samples the sweep spilled registers for the indexes and their masks; 48 heads of 278 blocks, d = 128,
+  // seeded mask 445 -> 391 us).  Positions ascend inside a block, so the samples of the last block that lie below L are a prefix.
   __shared__ uint8_t tab[TAB ? kMaxNb * kMaxSamples : 1];
   int n_valid_last = a.n_valid_last;
   if (TAB) {
     const uint8_t *g = a.table + (int64_t)slab * a.Nb * a.ks;
-    for (int t = tid; t < a.Nb * a.ks; t += 256) tab[t] = g[t];
+    const int u = min(tid % kMaxSamples, a.ks - 1);          // (slots beyond the last sample repeat it)
+#pragma unroll 4
+    for (int t = tid; t < a.Nb * kMaxSamples; t += 256) tab[t] = g[t / kMaxSamples * a.ks + u];
     __syncthreads();
     n_valid_last = 0;
     for (int u = 0; u < a.ks; ++u)
-      if ((a.Nb - 1) * a.block + tab[(a.Nb - 1) * a.ks + u] < a.L) ++n_valid_last;
+      if ((a.Nb - 1) * a.block + tab[(a.Nb - 1) * kMaxSamples + u] < a.L) ++n_valid_last;
   }
   auto offset_of = [&](int blk, int u) {
-    if (TAB) return (blk < a.Nb && u < a.ks) ? (int)tab[blk * a.ks + u] : 0;
+    if (TAB) return (int)tab[blk * kMaxSamples + u];      // (any value for blocks past the last one: they start at or past L)
     // (from scalar registers: an indexed read of the kernel's arguments is a load from memory, which all that follows would wait for)
     const uint32_t lo = u & 4 ? a.offs[1] : a.offs[0], hi = u & 4 ? a.offs[3] : a.offs[2];
     return (int)(((u & 8 ? hi : lo) >> (8 * (u & 3))) & 255u);
@@ -177,9 +180,8 @@ __global__ __launch_bounds__(256, 3) void probe_kernel(ProbeArgs a) {
     asm volatile("" : "+v"(dma_off0[i]));      // (else kept as the low half of a 64-bit product)
 #endif
   }
-  const int n_full_chunks = TAB ? 0 : a.n_full_chunks;
   auto fetch_any = [&](int chunk, int buf) __attribute__((always_inline)) {
-    if (chunk < n_full_chunks) {
+    if (!TAB && chunk < a.n_full_chunks) {
       const char *base = reinterpret_cast<const char *>(ks) + opaque(chunk) * a.chunk_bytes;   // wave-uniform
 #pragma unroll
       for (int i = 0; i < DMA_PER_WAVE; ++i) lds_dma16_sv(base, dma_off0[i], lds_of(i, buf));
@@ -214,7 +216,8 @@ __global__ __launch_bounds__(256, 3) void probe_kernel(ProbeArgs a) {
   // to the maximum).  finish_rule_kernel forms the numerators from the same product s * c2; the rest of
   // the rounded c2 is put right there per entry and here per chunk.
   constexpr int kNE = NT * (D / 16);              // products of a chunk
-  constexpr int kRing = 4, kDepth = 3;            // LDS operands read this many products ahead
+  // LDS operands read this many products ahead (d = 128: one more spills registers in the sweep; 12 heads, whole mask, 90.9 and 89.9 us)
+  constexpr int kRing = D == 128 ? 3 : 4, kDepth = kRing - 1;
   constexpr int kMaxSlots = kNE / 4;              // slots that form the maxima; the exponentials fill the others
   auto turn = [&](int chunk, auto buf_tag, auto mul_tag, auto vec_tag, f32x16 (&cur)[NT], f32x16 (&nxt)[NT])
       __attribute__((always_inline)) {

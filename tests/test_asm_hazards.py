@@ -159,6 +159,13 @@ def test_only_the_written_out_loads_of_a_tile_set_m0(assembly):
     assert _m0_outside_inline_code(planted) == ["s_mov_b32 m0, s2"]
 
 
+def test_mask_kernels_spill_no_vector_registers(assembly):
+    """A reload waits for the copies that the probe's sweep has in flight."""
+    spills = re.findall(r"\.name:\s+(\S+)[\s\S]*?\.vgpr_spill_count:\s+(\d+)", assembly["asa_mask.hip"])
+    assert sum("probe_kernel" in name for name, _ in spills) == 4
+    assert not [x for x in spills if x[1] != "0"]
+
+
 def _argument_loads(lines):
     """Vector loads from the kernel's arguments (s[0:1] until something else is put there)."""
     found = []
