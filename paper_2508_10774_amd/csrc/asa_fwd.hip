@@ -1382,19 +1382,37 @@ __global__ __launch_bounds__(BLK * 2 * KS, (PipeCfg<BLK, D, KS>::kWavesPerSimd))
 #pragma unroll
       for (int x = 0; x < 2 * (D / 32); ++x) tr_at[x] -= stage3;
     }
-    if constexpr (C::kSub == 1) {
-      if (first & 1) s1 = s0;
-      if (first == 1) body(std::integral_constant<int, 1>{}, s1, s0);
-    }
-    if constexpr (C::kSub <= 2) {
-      if (first == 2 || (C::kSub == 1 && first == 1)) body(std::integral_constant<int, 2>{}, s0, s1);
-      if (first != 0) body(std::integral_constant<int, 3>{}, s1, s0);
-    }
-    for (int t = -first & 3; t < n_it; t += 4) {
-      body(std::integral_constant<int, 0>{}, s0, s1);
-      body(std::integral_constant<int, 1>{}, s1, s0);
-      body(std::integral_constant<int, 2>{}, s0, s1);
-      body(std::integral_constant<int, 3>{}, s1, s0);
+    if constexpr (BLK == 128 && D == 128) {
+      // What is left over is part of a first pass through the loop: with tiles of its own in front of it the kernel spilled 42 of its
+      // 256 registers, and reloads in the loop waited for copies in flight (so and, behind it, this way, us: 9 heads of 8 blocks, 4 tiles
+      // a row, 16.7 and 14.8; 11 heads of 17, 2 tiles, 14.9 and 13.1; 1 head of 143, prefix rows, 251 and 232).  Elsewhere
+      // registers suffice, and the branches cost 1-2 % at block 64.
+      static_assert(C::kSub == 2, "no or two tiles are left over");
+      bool half = first != 0;
+      for (int left = (n_it + 3) & ~3; left > 0; left -= 4) {
+        if (!half) {
+          body(std::integral_constant<int, 0>{}, s0, s1);
+          body(std::integral_constant<int, 1>{}, s1, s0);
+        }
+        half = false;
+        body(std::integral_constant<int, 2>{}, s0, s1);
+        body(std::integral_constant<int, 3>{}, s1, s0);
+      }
+    } else {
+      if constexpr (C::kSub == 1) {
+        if (first & 1) s1 = s0;
+        if (first == 1) body(std::integral_constant<int, 1>{}, s1, s0);
+      }
+      if constexpr (C::kSub <= 2) {
+        if (first == 2 || (C::kSub == 1 && first == 1)) body(std::integral_constant<int, 2>{}, s0, s1);
+        if (first != 0) body(std::integral_constant<int, 3>{}, s1, s0);
+      }
+      for (int t = -first & 3; t < n_it; t += 4) {
+        body(std::integral_constant<int, 0>{}, s0, s1);
+        body(std::integral_constant<int, 1>{}, s1, s0);
+        body(std::integral_constant<int, 2>{}, s0, s1);
+        body(std::integral_constant<int, 3>{}, s1, s0);
+      }
     }
     // the last tile's P V (stage 3: the loop ends on a multiple of four)
     __builtin_amdgcn_s_waitcnt(0x0F70);          // stray copies must land before the LDS is given up
