@@ -45,6 +45,14 @@ struct Problem {
 
 int resolve(const asa_params *p, Problem *out);  // asa_status
 
+// Blocks in a slab's lists, as far as the parameters of the rule tell: prefix rows have all of them, the others the prefix columns
+// and the length of a fixed budget, or half of what lies between the least of the rule and a quarter of the blocks.
+inline int64_t listed_blocks(const Problem &pb) {
+  const int quarter = pb.Nb / 4 < pb.m_max ? pb.Nb / 4 : pb.m_max;
+  const int row = pb.n_prefix_blocks + (pb.m_min + (quarter > pb.m_min ? quarter : pb.m_min)) / 2;
+  return (int64_t)pb.n_prefix_blocks * pb.Nb + (int64_t)(pb.Nb - pb.n_prefix_blocks) * (row < pb.Nb ? row : pb.Nb);
+}
+
 // Lists with always-kept prefix blocks: would a prefix row, which is as long as the sequence, end a launch late?  From 1.6 times
 // what each of `resident` workgroups has to do on average (the other rows have the length of a fixed budget, or are taken
 // to lie between the least of the rule and a quarter of the blocks).

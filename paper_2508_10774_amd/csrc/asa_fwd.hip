@@ -2274,20 +2274,20 @@ static bool small_shape_pipe(const Problem &pb, bool dense, bool pooled) {
     fits |= (total + resident - 1) / resident * resident - total <= total / 20 || (total > 2 * resident && total <= 3 * resident);
   return fits && forced_fwd_kernel() != 1;
 }
-// Do two groups of wavefronts share a row (fwd_pipe_kernel)?  Where both halves of every row start at once; where one row
-// can end the launch late: prefix rows (prefix_rows_last), and uneven rows
-// where all of them start at once.  One group and two, us, mask included; d 64: 16 heads of 3 510 tokens, uneven, block 128 50
-// and 45, block 64 51 and 47; with 100 text tokens 77 and 64, 82 and 59; 3 heads of 17 776 tokens, text, block 64, 297 and
-// 193; without text 139 and 143; forward alone, 1 head of 2 266 tokens, 37 and 21; d 128, block 64: 4 heads of
-// 3 510 tokens 40 and 34, 12 slabs of 4 332, text, with backward 343 and 335; 16 heads of 3 510 tokens 56 and 66, fixed budget 75
-// and 86.
+// Do two groups of wavefronts share a row (fwd_pipe_kernel)?  Where both halves of every row start at once, and where prefix rows,
+// as long as the sequence, end the launch late: from 2.4 times what each resident group has to do on average, a row's start
+// and end counted as a block.  A full chip holds half as many rows then and is 0.71-0.9x as fast: of 377 calls with text
+// beyond the first line 160 lie above the second, 1.01-1.77x with two groups; of the others 146 lose by them and 59 gain.  (From 1.6
+// times on with the prefix columns counted half, and for uneven rows without a prefix, whose lengths the host cannot know: down to
+// 0.71x, the latter 0.95x on average of 274 calls.)  Forward alone, one group and two, us: d 64: 1 head of 2 266 tokens, block
+// 64, a quarter of the tiles, 12.1 and 8.8; 3 heads of 17 776, text, block 64, 245 and 143; 24 heads of 4 332, text, block 128, 81 and 89;
+// d 128: 12 slabs of 4 332, text, block 64, 87 and 80, below the line.
 static bool pipe_in_two(const Problem &pb, bool dense, int pooled_blocks) {
   const int resident = pb.block == 64 && pb.d == 64 ? 1024 : 512;      // groups on the chip
-  const int64_t total = (int64_t)pb.n_slabs * pb.Nb;
-  if (2 * total <= resident) return true;
-  if (dense) return false;
-  if (pb.n_prefix_blocks > 0) return prefix_rows_last(pb, resident, pooled_blocks);
-  return pb.m_min != pb.m_max && pooled_blocks == 0 && total <= resident;
+  if (2 * (int64_t)pb.n_slabs * pb.Nb <= resident) return true;
+  if (dense || pb.n_prefix_blocks == 0) return false;
+  const int64_t rows = pb.Nb * (int64_t)(pooled_blocks + 1);           // what a slab's rows have besides the blocks of their lists
+  return 5 * (int64_t)(pb.Nb + pooled_blocks + 1) * resident > 12 * pb.n_slabs * (listed_blocks(pb) + rows);
 }
 
 template <int BLK, int D>

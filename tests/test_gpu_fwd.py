@@ -370,3 +370,24 @@ def test_one_and_two_groups_of_wavefronts_per_row(block, d, many, tail):
                 assert np.array_equal(np.isneginf(got), empty)
                 assert np.abs(got[~empty] - want_lse[~empty]).max() <= 1e-3
     assert not torch.equal(out[0][0].view(torch.int16), out[1][0][:, :3].view(torch.int16))   # (two kernels ran)
+
+
+@picks_its_kernel
+@pytest.mark.parametrize("block,d,heads,Nb,text,r", [
+    (128, 64, 60, 5, 0, (0.1, 0.5)), (64, 64, 110, 6, 0, (0.0, 1.0)), (64, 128, 60, 5, 0, (0.1, 0.5)),        # uneven rows, not all at once
+    (64, 128, 93, 12, 130, (0.0, 1.0)), (128, 64, 100, 7, 20, (0.0, 1.0)), (64, 64, 40, 18, 140, (0.5, 0.5))])  # short prefix rows
+def test_a_full_chip_keeps_one_group_of_wavefronts_per_row(block, d, heads, Nb, text, r):
+    """What the parameters of the rule say of the rows (uneven, with a prefix) does not split rows where the chip is full without:
+    the same lists with parameters that never do give the same bits (two groups would round differently)."""
+    L = Nb * block - 9
+    q, k, v = (util.dev_bf16(synth.make_iid((1, heads, L, d), block + d, s)) for s in range(3))
+    mask = synth.random_block_mask(Nb, 0.4, seed=3, slabs=heads).reshape(heads, Nb, Nb)
+    first = -(-text // block)
+    mask[:, :first] = 1
+    mask[:, :, :first] = 1
+    out = []
+    for more in (dict(r_min=r[0], r_max=r[1], n_prefix_dense=text), dict(r_min=0.5, r_max=0.5)):
+        p = binding.Params(B=1, H=heads, L=L, d=d, block=block, **more)
+        print(f"case block={block} d={d} heads={heads} Nb={Nb} {more}", flush=True)
+        out.append(util.run_fwd(p, q, k, v, util.lists_from_mask(p, mask, with_csc=False)))
+    assert torch.equal(out[0][0].view(torch.int16), out[1][0].view(torch.int16)) and torch.equal(out[0][1], out[1][1])
