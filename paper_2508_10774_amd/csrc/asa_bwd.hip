@@ -968,7 +968,7 @@ __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dkv_
 // The rows and columns of always-kept prefix blocks are as long as the sequence, and a workgroup takes one alone: those of dQ
 // start right behind those of dK / dV (`lead` of each XCD's share) and not behind all of dK / dV.  Same bits; us: block 64, 17 776 tokens of
 // which 226 are text, d 64: 1 head 313 -> 244, 3 heads 330 -> 309, d 128: 3 heads 495 -> 442; 4 heads of 4 276 85 -> 68; block 128 /
-// d 128, 3 heads of 12 780, 300 text, 346 -> 295.  Where such a row is not the last to end (prefix_rows_last) it costs 1 %. (Also where
+// d 128, 3 heads of 12 780, 300 text, 346 -> 295.  (prefix_rows_last: where. Also where
 // all workgroups start at once: without it there, 1 head 311 us.) (All of dQ between dK / dV, one by
 // one: 0.96-0.98x where there is no prefix.)
 template <int BLK, int D, bool GT>
@@ -1030,6 +1030,13 @@ static bool overlap(const Problem &pb, const void *x, const TensorView &tx, cons
 
 // workgroups of dK / dV on the chip
 static int bwd_resident(int block, int d) { return block == 64 && d == 64 ? 1024 : (block == 128 && d == 128 ? 256 : 512); }
+// Would a prefix row end the launch late?  From 1.2 times what each resident workgroup has to do on average, where such rows are a
+// fifth of all at most.  (373 calls with text: early rows 0.98-1.28x in the 248 that this takes, 1.05x on average, 1.00x in the
+// others; with more of them, long rows of both kinds share compute units, down to 0.93x.)
+static bool prefix_rows_last(const Problem &pb) {
+  if (pb.n_prefix_blocks == 0 || 5 * pb.n_prefix_blocks > pb.Nb) return false;
+  return 5 * (int64_t)pb.Nb * bwd_resident(pb.block, pb.d) > 6 * pb.n_slabs * listed_blocks(pb);
+}
 
 // dq_over_inputs: dQ is written into memory that dK / dV reads (asa.h allows it): dK / dV must have ended before
 template <int BLK, int D>
@@ -1156,7 +1163,7 @@ hipError_t launch_bwd(const Problem &pb, const void *q, const void *k, const voi
       if (e != hipSuccess) return e;
       a.order = order;
       a.order_q = order_q;
-      if (prefix_rows_last(pb, bwd_resident(pb.block, pb.d), 0))
+      if (prefix_rows_last(pb))
         a.lead = std::min((pb.n_slabs + kNumXcd - 1) / kNumXcd * pb.n_prefix_blocks, (total + kNumXcd - 1) / kNumXcd);
     }
   }

@@ -52,16 +52,6 @@ inline int64_t listed_blocks(const Problem &pb) {
   const int row = pb.n_prefix_blocks + (pb.m_min + (quarter > pb.m_min ? quarter : pb.m_min)) / 2;
   return (int64_t)pb.n_prefix_blocks * pb.Nb + (int64_t)(pb.Nb - pb.n_prefix_blocks) * (row < pb.Nb ? row : pb.Nb);
 }
-
-// Lists with always-kept prefix blocks: would a prefix row, which is as long as the sequence, end a launch late?  From 1.6 times
-// what each of `resident` workgroups has to do on average (the other rows have the length of a fixed budget, or are taken
-// to lie between the least of the rule and a quarter of the blocks).
-inline bool prefix_rows_last(const Problem &pb, int resident, int pooled_blocks) {
-  if (pb.n_prefix_blocks == 0) return false;
-  const int quarter = pb.Nb / 4 < pb.m_max ? pb.Nb / 4 : pb.m_max;
-  const int rest = (pb.m_min + (quarter > pb.m_min ? quarter : pb.m_min)) / 2 + pb.n_prefix_blocks / 2;
-  return 10 * (int64_t)(pb.Nb + pooled_blocks) * resident > 16 * (int64_t)pb.n_slabs * pb.Nb * (rest + pooled_blocks);
-}
 void set_hip_error(hipError_t e);
 
 // One-shot profiling hook (asa_set_kernel_timing): record the armed events around the dominant

@@ -84,28 +84,52 @@ def test_the_same_with_pooled_tokens():
         assert torch.equal(a[:, :2].view(torch.int16), b[:, :2].view(torch.int16)), name
 
 
-@pytest.mark.parametrize("block,d,heads,text", [
-    (64, 64, 43, 1), (64, 64, 44, 64 * NB), (64, 128, 47, 70), (128, 64, 50, 300), (128, 128, 44, 129), (128, 128, 64, 10 ** 4)])
-def test_rows_of_a_prefix_start_early(block, d, heads, text):
-    """With prefix blocks some of dQ's workgroups come before the rest of dK / dV's (more than 256 lists): every one
+def _starts_early(p):
+    """The rule for prefix rows: a fifth of the rows at most, as long as 1.2 times the work of a resident workgroup (whose other
+    rows are taken to have the prefix columns and, with the parameters used here, half of a quarter of the blocks)."""
+    resident = {(64, 64): 1024, (128, 128): 256}.get((p.block, p.d), 512)
+    prefix = -(-p.n_prefix_dense // p.block)
+    listed = prefix * p.Nb + (p.Nb - prefix) * min(p.Nb, prefix + (1 + max(1, p.Nb // 4)) // 2)
+    return 0 < 5 * prefix <= p.Nb and 5 * p.Nb * resident > 6 * p.B * p.H * listed
+
+
+@pytest.mark.parametrize("pooled", [False, True])
+@pytest.mark.parametrize("block,d,heads,text,early", [
+    (64, 64, 17, 1, True), (64, 64, 20, 3 * 64, True), (64, 64, 20, 3 * 64 + 1, False), (64, 128, 19, 70, True), (128, 64, 18, 300, True),
+    (128, 128, 17, 129, True), (128, 128, 38, 129, True), (128, 128, 39, 129, False), (128, 64, 18, 10 ** 4, False)])
+def test_rows_of_a_prefix_start_early(block, d, heads, text, early, pooled):
+    """With few prefix blocks some of dQ's workgroups come before the rest of dK / dV's (more than 256 lists): every one
     runs once, whatever the number of prefix blocks, so the gradients are those of the two launches that dQ over Q takes."""
-    L = (NB - 1) * block + TAIL
-    print(f"case block={block} d={d} heads={heads} text={text}", flush=True)
+    Nb, n = 16, 32
+    L = (Nb - 1) * block + TAIL
+    print(f"case block={block} d={d} heads={heads} text={text} pooled={pooled}", flush=True)
     q, k, v, g = (util.dev_bf16(synth.make_iid((1, heads, L, d), block + d, s)) for s in range(4))
     p = binding.Params(B=1, H=heads, L=L, d=d, block=block, n_prefix_dense=min(text, L))
-    mask = synth.random_block_mask(NB, 0.3, seed=text, slabs=heads).reshape(heads, NB, NB)
+    assert heads * Nb > 256 and _starts_early(p) == early
+    mask = synth.random_block_mask(Nb, 0.3, seed=text, slabs=heads).reshape(heads, Nb, Nb)
     first = -(-p.n_prefix_dense // block)
     mask[:, :first] = 1
     mask[:, :, :first] = 1
     bufs = util.lists_from_mask(p, mask)
     lists = [bufs[x] for x in ("row_ptr", "col_idx", "col_ptr", "row_idx")]
-    o, lse, o_lo = util.run_fwd(p, q, k, v, bufs, with_lo=True)
-    ws = binding.alloc_workspace(binding.asa_bwd_workspace_bytes(p))
+    if pooled:
+        G = binding.asa_global_token_count(p, n)
+        kg, vg = (torch.zeros(1, heads, G, d, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        ws = binding.alloc_workspace(max(binding.asa_fwd_g_workspace_bytes(p, n), binding.asa_bwd_g_workspace_bytes(p, n)))
+        o, o_lo, lse = torch.empty_like(q), torch.empty_like(q), torch.empty((heads, L), dtype=torch.float32, device="cuda")
+        binding.asa_global_tokens(p, n, k, v, kg, vg)
+        binding.asa_attn_fwd_g(p, n, q, k, v, kg, vg, *lists[:2], o, lse, ws, o_lo=o_lo)
+    else:
+        o, lse, o_lo = util.run_fwd(p, q, k, v, bufs, with_lo=True)
+        ws = binding.alloc_workspace(binding.asa_bwd_workspace_bytes(p))
     out = []
     for over in (False, True):
         qq = q.clone()
         dq, dk, dv = qq if over else torch.full_like(q, float("nan")), torch.full_like(k, float("nan")), torch.full_like(v, float("nan"))
-        binding.asa_attn_bwd(p, qq, k, v, o, g, lse, *lists, dq, dk, dv, ws, o_lo=o_lo)
+        if pooled:
+            binding.asa_attn_bwd_g(p, n, qq, k, v, kg, vg, o, g, lse, *lists, dq, dk, dv, ws, o_lo=o_lo)
+        else:
+            binding.asa_attn_bwd(p, qq, k, v, o, g, lse, *lists, dq, dk, dv, ws, o_lo=o_lo)
         out.append([x.view(torch.int16) for x in (dq, dk, dv)])
     for a, b, name in zip(*out, ("dQ", "dK", "dV")):
         assert torch.equal(a, b), name
