@@ -146,20 +146,35 @@ def test_fwd_forcing_the_ping_pong_kernel_where_there_is_none_changes_nothing(L,
 
 
 @picks_its_kernel
-def test_fwd_each_slab_goes_to_the_kernel_that_suits_its_lists():
-    """Block 128 / d 128 without a lower retention clamp: both kernels are launched and each takes
-    the (batch, head) slabs whose rows are long / short for it.  Head 0 keeps 32 of 40 blocks per
-    row (ping-pong kernel), head 1 keeps 6 (lock-step kernel), head 2 sits just below the
-    switch-over (17 per row), head 3 just above (18); every row must come from exactly one."""
-    L, H = 128 * 40 - 9, 4
-    p = binding.Params(B=1, H=H, L=L, d=128, block=128)
-    qb, kb, vb = _case(1, H, L, 128, 128, seed=77)
-    mask = np.zeros((H, p.Nb, p.Nb), np.uint8)
+@pytest.mark.parametrize("heads,r", [(4, None), (6, None), (10, 0.5)])
+def test_fwd_each_slab_goes_to_the_kernel_that_suits_its_lists(heads, r):
+    """Block 128 / d 128 with lists: a kernel for long and one for short rows are launched, and each takes the (batch, head) slabs
+    that are long / short for it.  Head 0 keeps 32 of 40 blocks per row, head 1 keeps 6, head 2 sits just below the
+    switch-over (17 per row), head 3 just above (18), then from the start again; every row must come from exactly one.
+    160 query blocks: ping-pong and pipelined; 240: ping-pong and lock-step; 400 with a fixed budget: wide and lock-step."""
+    L, base_heads = 128 * 40 - 9, 4
+    base = _case(1, base_heads, L, 128, 128, seed=77)
+    at = np.arange(heads) % base_heads
+    p = binding.Params(B=1, H=heads, L=L, d=128, block=128, **({} if r is None else dict(r_min=r, r_max=r)))
+    mask = np.zeros((base_heads, p.Nb, p.Nb), np.uint8)
     rng = np.random.default_rng(7)
     for h, m in enumerate((32, 6, 17, 18)):
         for i in range(p.Nb):
             mask[h, i, rng.choice(p.Nb, size=m, replace=False)] = 1
-    _check_fwd(p, qb, kb, vb, mask)
+    bufs = util.lists_from_mask(p, mask[at], with_csc=False)
+    o = torch.full((1, heads, L, 128), float("nan"), dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((heads, L), float("nan"), dtype=torch.float32, device="cuda")
+    ws = binding.alloc_workspace(binding.asa_fwd_workspace_bytes(p))
+    binding.asa_attn_fwd(p, *(util.dev_bf16(x[:, at]) for x in base), bufs["row_ptr"], bufs["col_idx"], o, lse, ws)
+    torch.cuda.synchronize()
+    qf, kf, vf = (synth.bf16_bits_to_f32(x) for x in base)
+    for h in range(heads):
+        if h < base_heads:
+            want, want_lse = oracle.attn_fwd(qf[0, h], kf[0, h], vf[0, h], mask[h], 128)
+            util.assert_close_bf16(util.host_f32(o)[0, h], want, f"O[{h}]")
+            assert np.abs(lse[h].cpu().numpy() - want_lse).max() <= util.LSE_ABS
+        else:
+            assert torch.equal(o[0, h].view(torch.int16), o[0, h % base_heads].view(torch.int16)) and torch.equal(lse[h], lse[h % base_heads])
 
 
 def test_fwd_tiny_workload_with_oracle_mask():

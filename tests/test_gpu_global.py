@@ -134,6 +134,31 @@ def test_fwd_global_tokens_on_both_sides_of_the_kernel_choice(block, H, Nb, list
     assert same == {1: not ping_pong, 2: ping_pong}
 
 
+@pytest.mark.parametrize("block,d,many", [(64, 64, 110), (64, 128, 60), (128, 64, 60)])
+@pytest.mark.parametrize("tail", [1, 31, 33, 64])
+def test_fwd_global_tokens_with_one_and_two_groups_of_wavefronts_per_row(block, d, many, tail):
+    """Few rows: two groups of wavefronts share a row of the pipelined kernel; more than half of what the chip holds: one.
+    Lists of 0 .. 5 blocks (a row without any sees the pooled tokens only) before one or two pooled blocks, the last of
+    either part-empty."""
+    Nb, n = 5, 4 if block == 64 else 9
+    L = (Nb - 1) * block + tail
+    base = [synth.make_iid((1, 3, L, d), block + d, s) for s in range(3)]
+    rng = np.random.default_rng(tail)
+    mask = np.stack([(rng.random((Nb, Nb)).argsort(axis=1) < (np.arange(Nb)[:, None] + h) % 6) for h in range(3)]).astype(np.uint8)
+    qf, kf, vf = (synth.bf16_bits_to_f32(x) for x in base)
+    want = [og.attn_fwd_g(qf[0, h], kf[0, h], vf[0, h], mask[h], block, n) for h in range(3)]
+    for heads in (3, many):
+        print(f"case block={block} d={d} tail={tail} heads={heads}", flush=True)
+        at = np.arange(heads) % 3
+        p = binding.Params(B=1, H=heads, L=L, d=d, block=block)
+        bufs = util.lists_from_mask(p, mask[at], with_csc=False)
+        o, lse, _, _, _ = _run_fwd_g(p, n, *(util.dev_bf16(x[:, at]) for x in base), bufs)
+        for copy in range(3):
+            for h in (copy, heads - 3 + copy):
+                util.assert_close_bf16(util.host_f32(o[:, h])[0], want[at[h]][0], f"O[{h}]")
+                assert np.abs(lse[h].cpu().numpy() - want[at[h]][1]).max() <= util.LSE_ABS
+
+
 def test_fwd_global_tokens_dense_lists_and_residual():
     p = binding.Params(B=1, H=1, L=640, d=128, block=128)
     n = 32

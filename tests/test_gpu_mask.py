@@ -258,10 +258,11 @@ def test_build_mask_ragged_and_sampled(grid, n_text, d, block, ks, offs_seed):
 
 @pytest.mark.parametrize("Nb,tail,d,block,ks", [
     (1, 5, 64, 64, 16), (3, 64, 128, 64, 16), (4, 1, 128, 64, 16), (5, 64, 64, 64, 7), (8, 33, 128, 128, 16),
-    (9, 128, 64, 128, 16), (13, 2, 128, 128, 5), (16, 64, 64, 64, 16), (17, 100, 128, 128, 16), (25, 64, 64, 64, 1)])
+    (9, 128, 64, 128, 16), (13, 2, 128, 128, 5), (16, 64, 64, 64, 16), (17, 100, 128, 128, 16), (25, 64, 64, 64, 1),
+    (45, 33, 64, 64, 16), (46, 128, 128, 128, 16), (61, 7, 128, 64, 9), (77, 100, 64, 128, 16), (77, 64, 128, 64, 16)])
 def test_importance_map_at_the_edges_of_its_chunks(Nb, tail, d, block, ks):
-    """The probe takes the key blocks in chunks of four and in two ranges: ranges without a chunk, of one chunk, of
-    an odd and an even number of them, a last chunk that is part empty and a last block of `tail` tokens."""
+    """The probe takes the key blocks in chunks of four, and each of its workgroups a share of the chunks, the even or the odd ones of
+    a half: shares without a chunk and of one to five, a last chunk that is part empty and a last block of `tail` tokens."""
     L = (Nb - 1) * block + tail
     rng = np.random.default_rng(Nb)
     qb, kb = (synth.f32_to_bf16_bits(rng.standard_normal((1, 2, L, d), dtype=np.float32) * s) for s in (1.0, 2.0))

@@ -32,6 +32,8 @@ def test_offset_table_is_bit_exact(H, L, block, ks, seed):
     (2, 1024, 64, 64, 16, 0.9),
     (2, 1000, 128, 128, 16, 0.8),     # ragged last block: 104 tokens, some samples fall past L
     (1, 333, 128, 64, 7, 0.95),       # fewer than 16 samples, last block 13 tokens
+    (2, 77 * 64 - 30, 128, 64, 16, 0.9),   # shares of five chunks, a last one of one block
+    (1, 61 * 128 - 1, 64, 128, 5, 0.9),    # of four chunks, few samples
 ])
 def test_seeded_mask_matches_the_oracle(H, L, d, block, ks, tau):
     print(f"case H={H} L={L} d={d} block={block} k={ks} tau={tau}", flush=True)
