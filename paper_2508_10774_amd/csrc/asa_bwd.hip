@@ -139,9 +139,10 @@ struct BwdCfg {
 // there is one workgroup barrier per tile.  A wavefront issues one instruction every ~5 cycles, so
 // the number of instructions matters as much as the MFMAs: four LDS stages with the loop unrolled
 // by four make every LDS address a register plus an immediate; -Delta is the initial value of the
-// dP accumulator; at d = 128 the copies take their addresses from RunningTileCopy (dK / dV at block 128 / d 128 231 -> 210
-// instructions per tile; whole backward at block 64 / d 128, 8 heads of 17 776 tokens, 990 -> 970 us, block 128 / d 128,
-// 12 heads of 32 760, 4.90 -> 4.86 ms).  Operands two at a time, with one wait for both, change nothing.
+// dP accumulator; at d = 128 the copies take their addresses from RunningTileCopy, all but those of dQ at block 128 or with pooled
+// tokens (dK / dV at block 128 / d 128 231 -> 210 instructions per tile; whole backward at block 64 / d 128, 8 heads of
+// 17 776 tokens, 990 -> 970 us; block 128 / d 128, 12 heads of 32 760, no change beyond the noise of 0.5 %).  Operands two at a time,
+// with one wait for both, change nothing.
 // Registers: dK / dV at d = 128 (and dQ at block 64 / d 128) run one wavefront per SIMD with the
 // gradients in accumulation registers (the instruction is written out for that: the compiler would
 // move S and P there as well, at a vector instruction per register and tile), the others two.

@@ -2252,21 +2252,20 @@ static hipError_t launch_ping_pong(const FwdArgs &a, int grid, hipStream_t st) {
 // The rules of the shapes other than block 128 / d 128 (see launch_fwd_t for what they rest on).  Without lists the size of
 // a block means nothing: 256 rows share the tiles of the wide kernel.
 static bool small_shape_wide(const Problem &pb, bool dense, bool pooled) {
-  if (pb.block != 64 || !dense || pooled) return false;
+  if (!dense || pooled) return false;
   if (forced_fwd_kernel() != 0) return forced_fwd_kernel() == 4;
   const int wide = pb.n_slabs * ((pb.L + 255) / 256), rounds = (wide + 255) / 256;
   const bool filled = pb.d == 128 ? 4 * wide >= 3 * 256 * rounds : 16 * wide >= 15 * 256 * rounds;
   return filled && pb.L >= (pb.d == 128 ? 4000 : 8000);
 }
-static bool small_shape_ping_pong(const Problem &pb, bool dense, bool pooled) {
-  if (!pooled || pb.d != 64) return false;
+// (with pooled tokens, d 64)
+static bool small_shape_ping_pong(const Problem &pb, bool dense) {
   const int total = pb.n_slabs * pb.Nb, tiles = dense ? pb.Nb : pb.Nb / 8, forced = forced_fwd_kernel();
   const bool few_and_long = total <= (pb.block == 128 ? 256 : 512) && tiles >= (pb.block == 128 ? 16 : 24);
   return forced == 2 || ((forced == 0 || forced == 4) && few_and_long);
 }
-static bool small_shape_pipe(const Problem &pb, bool dense, bool pooled) {
-  if (small_shape_wide(pb, dense, pooled)) return false;
-  if (pooled) return !small_shape_ping_pong(pb, dense, pooled);
+// (of what the wide kernel has left, without pooled tokens)
+static bool small_shape_pipe(const Problem &pb, bool dense) {
   const bool small_tile = pb.block == 64 && pb.d == 64;
   const int resident = small_tile ? 1024 : 512, total = pb.n_slabs * pb.Nb;      // pipelined workgroups on the chip
   bool fits = total <= resident || (!small_tile && !dense);
@@ -2363,8 +2362,6 @@ static hipError_t launch_fwd_t(const FwdArgs &a, const Problem &pb, hipStream_t 
   const bool even_rows = dense || (pb.m_min == pb.m_max && !prefix);
   const bool long_rows = prefix && (int64_t)a.Nb * 512 * 2 > (int64_t)total * pb.m_min * 3;
   constexpr bool kPingPongShape = BLK == 128 && D == 128, kSmallTile = BLK == 64 && D == 64;
-  const bool has_wide = kPingPongShape || (BLK == 64 && dense && !pooled);
-  const int forced = forced_fwd_kernel() == 4 && !has_wide ? 0 : forced_fwd_kernel();
   FwdArgs b = a;
   b.select = 0;
   if constexpr (!kPingPongShape) {
@@ -2376,14 +2373,14 @@ static hipError_t launch_fwd_t(const FwdArgs &a, const Problem &pb, hipStream_t 
     }
     if (pooled) {
       if constexpr (D == 64)
-        if (small_shape_ping_pong(pb, dense, pooled)) return launch_ping_pong<BLK, D, true>(b, grid, st);
+        if (small_shape_ping_pong(pb, dense)) return launch_ping_pong<BLK, D, true>(b, grid, st);
       return pipe_in_two(pb, dense, a.Nbg) ? launch_pipe<BLK, D, true, 2>(b, grid, st) : launch_pipe<BLK, D, true, 1>(b, grid, st);
     }
-    if (small_shape_pipe(pb, dense, pooled))
+    if (small_shape_pipe(pb, dense))
       return pipe_in_two(pb, dense, 0) ? launch_pipe<BLK, D, false, 2>(b, grid, st) : launch_pipe<BLK, D, false, 1>(b, grid, st);
   } else {
     // Rounds of ping-pong workgroups (one per compute unit); a round of the wide kernel takes as long as two of them.
-    const int rounds = (total + 255) / 256;
+    const int rounds = (total + 255) / 256, forced = forced_fwd_kernel();
     constexpr int kMinTiles = 18;
     if (pooled) {
       const bool pays = a.Nb <= 8 ? rounds > 1 : rounds > 3 || (rounds == 2 && even_rows);
