@@ -102,6 +102,7 @@ size_t asa_bwd_workspace_bytes(const asa_params *p);
  *   p_imp   [B*H, Nb, Nb] fp32 importance map, or NULL
  * The workspace (asa_mask_workspace_bytes) is always needed: it holds the probe's per-row
  * block maxima and, when p_imp is NULL, the importance map.
+ * P_imp and the mask of a slab are the same bits whatever other slabs are in the call.
  */
 int asa_build_mask(const asa_params *p, const void *q, const void *k, uint8_t *mask,
                    int32_t *row_ptr, int32_t *col_idx, int32_t *col_ptr, int32_t *row_idx,
@@ -147,6 +148,10 @@ int asa_csr_from_mask(const asa_params *p, const uint8_t *mask, int32_t *row_ptr
  *      more than the 8 significant bits of o there.
  * lse  [B*H, L] fp32, natural logarithm; a row with an empty list gets O = 0, LSE = -inf
  * bf16 products accumulate in fp32; probabilities are rounded to bf16 before P V.
+ * Runs of a call repeat bit for bit.  Which kernel a call takes depends on its size (B, H, L) and
+ * on the rule's parameters, and kernels add in different orders: the last bits of o and lse of a
+ * slab may differ between calls that hold different numbers of slabs.  (The gradients of
+ * asa_attn_bwd do not, for the same o and lse.)
  * row_ptr = col_idx = NULL selects the dense specialisation (every key block, no index
  * lists read): the dense attention of the first two sampling steps (Sec. 4.3) and the
  * in-house dense baseline of the kernel-speedup ratio (Table 2); exactly one of them NULL is

@@ -70,10 +70,10 @@ __device__ __forceinline__ int probe_swz(int row) {
 
 // Bound: the vector ALU.  An entry costs an exponential (8 cycles of 64 lanes), a multiply-add, an addition and half a
 // maximum (10), 576 cycles per wavefront and chunk, beside 512 (d = 128) or 256 matrix cycles; with what a chunk costs
-// as a whole the vector ALU is busy 88 % of the cycles at d = 64 (48 heads, Nb = 278) and 68 % at d = 128 (12 heads,
+// as a whole the vector ALU is busy 87 % of the cycles at d = 64 (48 heads, Nb = 278) and 70 % at d = 128 (12 heads,
 // Nb = 256).  So the products of the next chunk stand between the vector instructions of this one, and one wavefront
 // takes whole chunks (against 8 wavefronts that share chunks of twice the size and run products and vector work one behind the
-// other: 75 -> 68 us at d = 128, 252 -> 225 us at d = 64).  Three wavefronts per SIMD: two (256 registers), with chunks of
+// other: 75 -> 66 us at d = 128, 252 -> 220 us at d = 64).  Three wavefronts per SIMD: two (256 registers), with chunks of
 // 4 or of 8 key blocks, are 3 % slower for the whole mask.
 // TAB: the sample positions differ from block to block and come from a table (seeded random
 // sampling) instead of one offset vector for all blocks.
