@@ -36,7 +36,7 @@ def pytest_generate_tests(metafunc):
 @pytest.fixture(autouse=True)
 def kernel_choice(request):
     """Every other test of this module runs four times: with the library's own choice of forward kernel
-    (at the small sizes here the pipelined one, lock-step at block 128 / d 128), with the lock-step kernel,
+    (at the small sizes here the pipelined one), with the lock-step kernel,
     which production calls reach at larger sizes, with the ping-pong kernel, which block 128 / d 128 has, and
     with the wide kernel, which that shape has and block 64 without lists (where a shape has not got it, its own
     choice runs again)."""
@@ -175,6 +175,31 @@ def test_fwd_each_slab_goes_to_the_kernel_that_suits_its_lists(heads, r):
             assert np.abs(lse[h].cpu().numpy() - want_lse).max() <= util.LSE_ABS
         else:
             assert torch.equal(o[0, h].view(torch.int16), o[0, h % base_heads].view(torch.int16)) and torch.equal(lse[h], lse[h % base_heads])
+
+
+@picks_its_kernel
+@pytest.mark.parametrize("r", [0.5, 0.1, None])
+def test_few_rows_of_any_length_whatever_the_rule_says(r):
+    """Up to 192 query blocks of block 128 / d 128 the parameters of the rule choose one kernel for all rows: ping-pong from a fixed
+    budget of 18 blocks on, pipelined below, both without one.  Lists that do not come from the rule are served all the
+    same: rows of 0, 1, 2, 17, 18 and all 39 blocks, side by side."""
+    L, H = 128 * 39 - 31, 4
+    p = binding.Params(B=1, H=H, L=L, d=128, block=128, **({} if r is None else dict(r_min=r, r_max=r)))
+    qb, kb, vb = _case(1, H, L, 128, 128, seed=78)
+    rng = np.random.default_rng(8)
+    mask = np.zeros((H, p.Nb, p.Nb), np.uint8)
+    for h in range(H):
+        for i in range(p.Nb):
+            mask[h, i, rng.choice(p.Nb, size=(0, 1, 2, 17, 18, p.Nb)[(i + h) % 6], replace=False)] = 1
+    bufs = util.lists_from_mask(p, mask, with_csc=False)
+    o, lse = util.run_fwd(p, *(util.dev_bf16(x) for x in (qb, kb, vb)), bufs)
+    qf, kf, vf = (synth.bf16_bits_to_f32(x) for x in (qb, kb, vb))
+    for h in range(H):
+        want, want_lse = oracle.attn_fwd(qf[0, h], kf[0, h], vf[0, h], mask[h], 128)
+        util.assert_close_bf16(util.host_f32(o)[0, h], want, f"O[{h}]")
+        got, empty = lse[h].cpu().numpy(), np.isneginf(want_lse)
+        assert np.array_equal(np.isneginf(got), empty) and empty.any()
+        assert np.abs(got[~empty] - want_lse[~empty]).max() <= util.LSE_ABS
 
 
 def test_fwd_tiny_workload_with_oracle_mask():
