@@ -646,13 +646,9 @@ __device__ __forceinline__ void dkv_walk(const BwdArgs &a, int workgroup, uint32
     constexpr int part = decltype(part_tag)::value;
     constexpr bool new_block = decltype(new_block_tag)::value;
     if constexpr (part == 0) {
-      if constexpr (new_block) {
-        q0 = __builtin_amdgcn_readfirstlane(entry_v) * BLK;
-        base_st = reinterpret_cast<const char *>(stat_s) + (uint32_t)q0 * 4u;
-      } else {
-        q0 += C::kST;
-        base_st += C::kST * 4;
-      }
+      q0 = new_block ? __builtin_amdgcn_readfirstlane(entry_v) * BLK : q0 + C::kST;
+      if constexpr (!kRun || new_block) base_st = reinterpret_cast<const char *>(stat_s) + (int64_t)q0 * 4;
+      else base_st += C::kST * 4;
     } else if constexpr (part == 1 && kRun) {
       if constexpr (new_block) run_q.block(q0);
       else run_q.step();
@@ -976,11 +972,16 @@ template <int BLK, int D, bool GT>
 __global__ __launch_bounds__(BLK * 2, (BwdCfg<BLK, D>::kWavesPerSimd)) void dkv_dq_kernel(BwdArgs a) {
   extern __shared__ __align__(1024) unsigned char smem[];
   __shared__ int list[kMaxNb];
-  // in an XCD's share: the first `lead` of dK / dV, the first `lead` of dQ, the rest of dK / dV, the rest of dQ
-  const int share = gridDim.x / (2 * kNumXcd), turn = blockIdx.x / kNumXcd;
-  const bool dkv = turn < a.lead || (turn >= 2 * a.lead && turn < share + a.lead);
-  const int at = turn < a.lead ? turn : (turn < 2 * a.lead || turn < share + a.lead ? turn - a.lead : turn - share);
-  const int workgroup = at * kNumXcd + blockIdx.x % kNumXcd;
+  const int first_dq = gridDim.x / 2;          // (a multiple of the number of XCDs)
+  bool dkv = (int)blockIdx.x < first_dq;
+  int workgroup = dkv ? (int)blockIdx.x : (int)blockIdx.x - first_dq;
+  if (a.lead > 0) {
+    // in an XCD's share: the first `lead` of dK / dV, the first `lead` of dQ, the rest of dK / dV, the rest of dQ
+    const int share = first_dq / kNumXcd, turn = blockIdx.x / kNumXcd;
+    dkv = turn < a.lead || (turn >= 2 * a.lead && turn < share + a.lead);
+    const int at = turn < a.lead ? turn : (turn < 2 * a.lead || turn < share + a.lead ? turn - a.lead : turn - share);
+    workgroup = at * kNumXcd + blockIdx.x % kNumXcd;
+  }
   if (dkv) dkv_walk<BLK, D>(a, workgroup, ASA_LDS_ADDR_OF(smem), list);
   else dq_walk<BLK, D, GT, false>(a, workgroup, ASA_LDS_ADDR_OF(smem), list);
 }
