@@ -8,6 +8,9 @@ forwards from each such instruction, over branches too:
   a vector instruction that writes an operand of a written-out MFMA: 2 wait states before it
   anything but an MFMA that touches its result:                      19 after it (the longest MFMA)
   a vector instruction that writes the scalar base of a load:        5 before it
+
+The same listings show what else a kernel must not do: write M0 between the loads of a tile, spill vector registers, read its
+arguments through vector memory.
 """
 
 import os
